@@ -1,15 +1,20 @@
 """Builds the HIP shared library in-tree for gfx950 (cross-compiles without a GPU)."""
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libsim355.so")
-SOURCES = [os.path.join(HERE, "csrc", "sim.hip")]
-HEADERS = [os.path.join(HERE, "csrc", f) for f in ("model.hpp", "contact_gen.hpp", "step_kernel.hpp")] + [
-    os.path.join(os.path.dirname(HERE), "include", "sim.h")]
+SOURCES = [os.path.join(HERE, "csrc", f) for f in (
+    "step_warm_pairs.hip", "step_pairs.hip", "step_plain.hip", "step_warm.hip", "step_newton_warm.hip", "step_newton.hip",
+    "sim.hip")]
+HEADERS = [os.path.join(HERE, "csrc", f) for f in (
+    "model.hpp", "contact_gen.hpp", "step_kernel.hpp", "step_variants.hpp", "step_variants_impl.hpp", "regroup.hpp",
+    "builtin_robots.hpp")] + [os.path.join(os.path.dirname(HERE), "include", "sim.h")]
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed fp32 VALU forms are kept off on this target
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
@@ -27,10 +32,20 @@ def build(force=True, verbose=False, extra=()):
     if not force and not is_stale():
         return LIB_PATH
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + HIPCC_FLAGS + list(extra) + ["-o", LIB_PATH] + SOURCES
-    if verbose:
-        print(" ".join(cmd))
-    subprocess.run(cmd, check=True)
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, os.path.basename(src) + ".o") for src in SOURCES]
+
+        def compile_one(src, obj):
+            cmd = [hipcc] + HIPCC_FLAGS + list(extra) + ["-c", "-o", obj, src]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            subprocess.run(cmd, check=True)
+
+        # one hipcc per source, side by side (the longest first)
+        with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as pool:
+            for done in [pool.submit(compile_one, s, o) for s, o in zip(SOURCES, objs)]:
+                done.result()
+        subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-o", LIB_PATH] + objs, check=True)
     return LIB_PATH
 
 

@@ -14,6 +14,7 @@
 #include "contact_gen.hpp"
 #include "model.hpp"
 #include "step_kernel.hpp"
+#include "step_variants.hpp"
 #include "regroup.hpp"
 #include "builtin_robots.hpp"
 
@@ -299,6 +300,20 @@ static bool newton_fits(const Model& m, int E) {
   return E <= 8 && m.S * E <= kThreads - joint_threads && 2 * m.B * E <= kThreads;
 }
 
+// the compiled form of the step kernel that suits a launch
+static const void* step_variant(const Model& m, int E) {
+  const bool few = m.max_joint_sides <= 4, warm = m.warm > 0.0f;
+  const int threads = threads_for(m, E);
+  if (m.solver == 1) return warm ? step_variant_of<0, 1, 1>(E, threads, few) : step_variant_of<0, 0, 1>(E, threads, few);
+  if (pairs_of(m)) return warm ? step_variant_of<1, 1, 0>(E, threads, few) : step_variant_of<1, 0, 0>(E, threads, few);
+  return warm ? step_variant_of<0, 1, 0>(E, threads, few) : step_variant_of<0, 0, 0>(E, threads, few);
+}
+
+// Envs per workgroup.  A step is a chain of dependent instructions and barriers whose length hardly
+// depends on how many envs share the workgroup, and one workgroup fills a compute unit; so: one round
+// of workgroups whenever the batch allows it (rounded up: 1500 humanoids on the heightfield take
+// 115 us as 188 workgroups of 8 and 192 us as 375 of 4), in a compiled form (as 300 of 5, which is
+// both two rounds and the general form, they take 230 us).
 static int default_envs_per_block(const Model& m, int N) {
   // bodies need a thread each, joints two (one per side) plus a wavefront left for contacts
   int lim = kThreads / m.B;
@@ -308,18 +323,28 @@ static int default_envs_per_block(const Model& m, int N) {
     if (lim > 8) lim = 8;
     while (lim > 1 && !newton_fits(m, lim)) --lim;
   }
-  int want = N / 256;  // keep at least one workgroup per compute unit when N allows
-  if (want < 1) want = 1;
-  int E = want < lim ? want : lim;
-  // a workgroup holds whole interaction groups
-  const int G = m.group > 1 ? m.group : 1;
-  if (E < G) E = G;
-  E -= E % G;
-  // and the workgroup's LDS arrays have to fit
-  while (E > G && (size_t)plan_for(m, E).total * sizeof(float) > 160 * 1024) E -= G;
-  // the collision variants are compiled for 16 and 8 envs per workgroup (any other number runs the
-  // general form, which is much slower): 8 rather than an odd number in between
-  if (pairs_of(m) && E > 8 && E < 16 && 8 % G == 0) E = 8;
+  const int G = m.group > 1 ? m.group : 1;   // a workgroup holds whole interaction groups
+  int want = (N + 255) / 256;
+  // Four envs share a workgroup's phases at no cost (64 to 1024 humanoids on the heightfield: 97 to
+  // 101 us as workgroups of 4, 118 to 123 us as workgroups of 1), and fewer workgroups make a slow
+  // one among them less likely; a handful of workgroups is quicker still with two (16: 92 against 95 us).
+  const int least = N > 128 ? 4 : 2;
+  if (want < least) want = least;
+  auto usable = [&](int E) { return E <= lim && E % G == 0 && (size_t)plan_for(m, E).total * sizeof(float) <= 160 * 1024; };
+  int E = 0;
+  const bool pairs = pairs_of(m) != 0, warm = m.warm > 0.0f, newton = m.solver == 1;
+  if (m.max_joint_sides <= 4 && !(pairs && warm && want < 8))
+    for (int c = 1; c <= 16; ++c)
+      if (step_compiled_envs(c, pairs, warm, newton) && usable(c)) {
+        E = c;
+        if (c >= want) break;
+      }
+  if (!E) {
+    // no compiled form for this group size or family, or a body with many joints: the general form
+    E = want < lim ? want : lim;
+    E = E < G ? G : E - E % G;
+    while (E > G && !usable(E)) E -= G;
+  }
   return E;
 }
 
@@ -487,34 +512,12 @@ static int launch_step(sim* s, const float* actions, float h, int substeps, int 
   if (lds_bytes > 160 * 1024) return fail(SIM_ERR_ARG, "envs_per_block %d needs %zu bytes of LDS (limit 160 KiB)", s->E, lds_bytes);
   int grid = (s->N + s->E - 1) / s->E;
   const int threads = threads_for(m, s->E);
-  auto launch = [&](auto kern) -> int {
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds_bytes));
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds_bytes, st, a);
-    return SIM_OK;
-  };
-  const bool few = m.max_joint_sides <= 4;
   if (m.solver == 1 && !newton_fits(m, s->E))
     return fail(SIM_ERR_ARG, "this robot does not fit the Newton solver's workgroup (a contact thread per slot)");
-  int lrc = (m.solver == 1 && m.warm > 0.0f) ? ((s->E == 8 && few) ? launch(&step_kernel<8, 4, 0, kThreads, 1, 1>)
-                             : few ? launch(&step_kernel<0, 4, 0, kThreads, 1, 1>) : launch(&step_kernel<0, kMaxBodyJoints, 0, kThreads, 1, 1>))
-            : m.solver == 1 ? ((s->E == 8 && few) ? launch(&step_kernel<8, 4, 0, kThreads, 0, 1>)
-                             : few ? launch(&step_kernel<0, 4, 0, kThreads, 0, 1>) : launch(&step_kernel<0, kMaxBodyJoints, 0, kThreads, 0, 1>))
-            : (m.warm > 0.0f && pairs) ? ((s->E == 16 && few) ? launch(&step_kernel<16, 4, 1, kThreads, 1>)
-                             : (s->E == 8 && few) ? launch(&step_kernel<8, 4, 1, kThreads, 1>)
-                             : few ? launch(&step_kernel<0, 4, 1, kThreads, 1>) : launch(&step_kernel<0, kMaxBodyJoints, 1, kThreads, 1>))
-            : m.warm > 0.0f ? ((s->E == 16 && few) ? launch(&step_kernel<16, 4, 0, kThreads, 1>)
-                             : few ? launch(&step_kernel<0, 4, 0, kThreads, 1>) : launch(&step_kernel<0, kMaxBodyJoints, 0, kThreads, 1>))
-            : pairs ? ((s->E == 16 && few) ? launch(&step_kernel<16, 4, 1>)
-                     : (s->E == 8 && few) ? launch(&step_kernel<8, 4, 1>)
-                     : few ? launch(&step_kernel<0, 4, 1>) : launch(&step_kernel<0, kMaxBodyJoints, 1>))
-            : threads == kThreadsWide ? launch(&step_kernel<16, 4, 0, kThreadsWide>)
-            : (s->E == 8 && few) ? launch(&step_kernel<8, 4>)
-            : (s->E == 4 && few) ? launch(&step_kernel<4, 4>)
-            : (s->E == 2 && few) ? launch(&step_kernel<2, 4>)
-            : (s->E == 1 && few) ? launch(&step_kernel<1, 4>)
-            : few ? launch(&step_kernel<0, 4>) : launch(&step_kernel<0, kMaxBodyJoints>);
-  if (lrc) return lrc;
+  const void* kern = step_variant(m, s->E);
+  HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
+  void* kargs[] = {&a};
+  HIP_TRY(hipLaunchKernel(kern, dim3(grid), dim3(threads), kargs, lds_bytes, st));
   HIP_TRY(hipGetLastError());
   if (a.recs) s->recs_valid = 1;
   if (a.pair_recs) s->pair_grid = grid;
