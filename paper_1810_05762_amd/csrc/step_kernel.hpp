@@ -1385,16 +1385,19 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       }
     }
     TMARK(16);
-    // The per-body average is split over several threads when the workgroup has room: thread (e, b)
-    // takes the linear half of body b's velocity, thread (e, B + b) the angular half; in the wide
-    // workgroup three threads take two components each (a wavefront issues one instruction every
-    // five to six cycles however many others share its SIMD, so short threads beat a long one).
-    // (the wide workgroup always has room for three threads per body: 3 * 16 bodies * 16 envs)
-    constexpr bool g_three = NT >= 768 && EC == 16;
-    const bool g_split = g_three || 2 * B * E <= kThreads;
-    const int g_half = g_three ? (idx < B ? 0 : (idx < 2 * B ? 1 : 2)) : ((g_split && idx >= B) ? 1 : 0);
-    const int g_b = idx - g_half * B;
-    const bool g_on = env_ok && g_b < B && idx < (g_three ? 3 * B : (g_split ? 2 * B : B));
+    // The per-body average is split over several threads when the workgroup has room: thread
+    // (e, p * B + b) takes part p of the six velocity components of body b.  A wavefront issues one
+    // instruction every five to six cycles however many others share its SIMD, so short threads beat
+    // a long one, as long as no SIMD gets more than a few of them.  The number of parts is the
+    // largest that always fits (kMaxBodies bodies); the general form has two or one.
+    constexpr int kParts = EC == 0 ? 2 : (6 * kMaxBodies * EC <= NT ? 6 : (3 * kMaxBodies * EC <= NT ? 3 : 2));
+    constexpr int kPartC = 6 / kParts;   // components of a part
+    const bool g_split = (EC > 0 && kParts * kMaxBodies * EC <= NT) || kParts * B * E <= kThreads;
+    int g_part = 0;
+#pragma unroll
+    for (int k = 1; k < kParts; ++k) g_part += (g_split && idx >= k * B) ? 1 : 0;
+    const int g_b = idx - g_part * B;
+    const bool g_on = env_ok && g_b < B;
     const int g_ref = g_b * E + e;
     // capsule-capsule contacts of body g_b: where their (weighted) copies will be (up to kPairList
     // of them; a body with more walks the queue in every sweep), and the sum of their weights
@@ -1744,11 +1747,9 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       }
     };
     auto gather = [&]() {
-      if constexpr (g_three) {
-        gather_part(std::integral_constant<int, 2>{}, 2 * g_half);   // two components per thread
-      } else {
-        gather_part(std::integral_constant<int, 3>{}, 3 * g_half);   // linear or angular half
-        if (!g_split) gather_part(std::integral_constant<int, 3>{}, 3);
+      gather_part(std::integral_constant<int, kPartC>{}, kPartC * g_part);
+      if constexpr (kParts == 2) {
+        if (!g_split) gather_part(std::integral_constant<int, kPartC>{}, kPartC);   // one thread per body
       }
     };
     // Warm start: sweep -1 relaxes nothing; every block applies the impulses it starts from (the
@@ -1839,24 +1840,24 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       };
       // every body: the plain sum of its blocks' contributions (in static order), on top of the
       // velocities the solve started from when `with_base`
-      // (two threads per body, linear and angular half: the host only picks launch shapes where
-      //  2 B E threads exist; all reads are issued before the first use)
+      // (split like the average of a sweep: the host only picks launch shapes where 2 B E threads
+      //  exist; all reads are issued before the first use)
       auto gather_sum = [&](bool with_base, float* dst) {
         if (!g_on) return;
-        const int ho = 3 * g_half * E;
-        float val[NJ + 3][3], base[3];
+        const int ho = kPartC * g_part * E;
+        float val[NJ + 3][kPartC], base[kPartC];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) base[c] = with_base ? Lvel[(g_b * kVS + c) * E + e + ho] : 0.0f;
+        for (int c = 0; c < kPartC; ++c) base[c] = with_base ? Lvel[(g_b * kVS + c) * E + e + ho] : 0.0f;
 #pragma unroll
         for (int k = 0; k < NJ; ++k)
 #pragma unroll
-          for (int c = 0; c < 3; ++c) val[k][c] = Loutj[gat_off[k] + ho + c * E];
+          for (int c = 0; c < kPartC; ++c) val[k][c] = Loutj[gat_off[k] + ho + c * E];
 #pragma unroll
         for (int k = 0; k < 3; ++k)
 #pragma unroll
-          for (int c = 0; c < 3; ++c) val[NJ + k][c] = Loutc[gat_slot[k] + ho + c * E];
+          for (int c = 0; c < kPartC; ++c) val[NJ + k][c] = Loutc[gat_slot[k] + ho + c * E];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
+        for (int c = 0; c < kPartC; ++c) {
           float acc = 0.0f;
 #pragma unroll
           for (int k = 0; k < NJ + 3; ++k) acc += gat_w[k] * val[k][c];
