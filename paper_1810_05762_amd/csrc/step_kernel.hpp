@@ -221,19 +221,32 @@ __device__ __forceinline__ void rel_rotvec(const float qa[4], const float qb[4],
   phi[0] = k * x; phi[1] = k * y; phi[2] = k * z;
 }
 
-// Height of the heightfield surface under a world xy (plane of the containing triangle).
-__device__ inline float terrain_height(const Model& M, const float* __restrict__ hts, float wx, float wy) {
-  if (M.terrain_kind == 0) return 0.0f;
-  float ux = (wx - M.hox) / M.cell, uy = (wy - M.hoy) / M.cell;
+// Height of the heightfield surface under a world xy (plane of the containing triangle): the cell
+// and the place within it, then the height from the cell's four samples.
+struct HeightCell {
+  int at;          // sample (i, j)
+  float fx, fy;
+};
+__device__ __forceinline__ HeightCell height_cell(int nx, int ny, float cell, float hox, float hoy, float wx, float wy) {
+  float ux = (wx - hox) / cell, uy = (wy - hoy) / cell;
   float fi = floorf(ux), fj = floorf(uy);
-  float mi = (float)(M.nx - 2), mj = (float)(M.ny - 2);
+  float mi = (float)(nx - 2), mj = (float)(ny - 2);
   fi = fminf(fmaxf(fi, 0.0f), mi); fj = fminf(fmaxf(fj, 0.0f), mj);
-  int i = (int)fi, j = (int)fj;
-  float fx = fminf(fmaxf(ux - fi, 0.0f), 1.0f), fy = fminf(fmaxf(uy - fj, 0.0f), 1.0f);
-  float h00 = hts[j * M.nx + i], h10 = hts[j * M.nx + i + 1];
-  float h11 = hts[(j + 1) * M.nx + i + 1], h01 = hts[(j + 1) * M.nx + i];
+  HeightCell c;
+  c.at = (int)fj * nx + (int)fi;
+  c.fx = fminf(fmaxf(ux - fi, 0.0f), 1.0f); c.fy = fminf(fmaxf(uy - fj, 0.0f), 1.0f);
+  return c;
+}
+__device__ __forceinline__ float height_in_cell(float fx, float fy, float h00, float h10, float h11, float h01) {
   if (fx >= fy) return h00 + fx * (h10 - h00) + fy * (h11 - h10);
   return h00 + fx * (h11 - h01) + fy * (h01 - h00);
+}
+__device__ inline float terrain_height(const Model& M, const float* __restrict__ hts, float wx, float wy) {
+  if (M.terrain_kind == 0) return 0.0f;
+  const int nx = M.nx;
+  const HeightCell c = height_cell(nx, M.ny, M.cell, M.hox, M.hoy, wx, wy);
+  const float* h = hts + c.at;
+  return height_in_cell(c.fx, c.fy, h[0], h[1], h[nx + 1], h[nx]);
 }
 
 __device__ __forceinline__ void store_record(float* Lrec, int* Lreci, int s, int ee, int E, const ContactOut& co) {
@@ -661,7 +674,10 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   const int obs_row = obs_dim + (M.height_map ? kHmRows * kHmCols : 0);   // row of the caller's array
   // model scalars the loops below use, read once (before the kernel's first store, so they come
   // through the scalar cache and stay in scalar registers)
-  const int m_terrain = M.terrain_kind, m_contacts = M.contacts;
+  const int m_terrain = M.terrain_kind, m_contacts = M.contacts, m_root = M.root;
+  int m_feet = 0;   // the feet's bodies, a byte each
+#pragma unroll
+  for (int f = 0; f < kMaxFeet; ++f) m_feet |= (f < F ? M.feet[f] : 0) << (8 * f);
   const Field H0 = make_field(M, a.heights, a.coarse);
   const bool use_patch = m_terrain == 1 && H0.nx >= kPatch && H0.ny >= kPatch;
   const int m_group = PC ? (M.group > 1 ? M.group : 1) : 1, m_npairs = PC ? M.n_pairs : 0, m_nap = PC ? M.n_agent_pairs : 0;
@@ -2263,75 +2279,145 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     }
   }
   };
-  // ---- root part, reward (Eq. 1-3), done (Section 4.1); returns whether the env was reset
-  auto pack_root = [&](auto pass_c) -> bool {
+  // ---- root part.  One thread per env for all of it is a chain of some 1500 instructions (three
+  // arctangents, an arcsine, sine and cosine, and reads from global memory) that every other wavefront
+  // waits for, so its independent parts go to a wavefront each, above the joint threads; where there
+  // are not enough wavefronts the first one takes what is left.  What the reward needs of them is left
+  // in LDS (the inverse inertias are no longer read).
+  float* Lsc = Liw;       // [5][E]: speed towards the target, distance to it, sums of |u| and u^2, feet on the ground
+  float* Lhm = Loutj;     // [5][E]: centre of mass (world), cosine and sine of the yaw (the sweep copies are free by now)
+  const bool m_height_map = obs_row > obs_dim;
+  auto pack_root = [&](auto pass_c) {
   constexpr int pass = decltype(pass_c)::value;
-  bool reset_now = false;
-  if (tid < E && (blockIdx.x * E + tid) < N && (pass == 0 || Lrst[tid])) {
-    const int ee = tid, env_e = agent_at(blockIdx.x * E + tid);
-    const int rb = M.root;
-    float rx[3], rq[4], rv[3], rw[3];
-    for (int c = 0; c < 3; ++c) rx[c] = Lpos[(rb * 7 + c) * E + ee];
-    for (int c = 0; c < 4; ++c) rq[c] = Lpos[(rb * 7 + 3 + c) * E + ee];
-    for (int c = 0; c < 3; ++c) { rv[c] = Lvel[(rb * kVS + c) * E + ee]; rw[c] = Lvel[(rb * kVS + 3 + c) * E + ee]; }
-    float ox = a.origins[3 * env_e], oy = a.origins[3 * env_e + 1], oz = a.origins[3 * env_e + 2];
-    float height = rx[2];
-    if (M.terrain_kind == 1) height = rx[2] + oz - terrain_height(M, a.heights, rx[0] + ox, rx[1] + oy);
-    float qw = rq[0], qx = rq[1], qy = rq[2], qz = rq[3];
-    float roll = atan2f(2.0f * (qw * qx + qy * qz), 1.0f - 2.0f * (qx * qx + qy * qy));
-    float sp = fminf(fmaxf(2.0f * (qw * qy - qz * qx), -1.0f), 1.0f);
-    float pitch = asinf(sp);
-    float yaw = atan2f(2.0f * (qw * qz + qx * qy), 1.0f - 2.0f * (qy * qy + qz * qz));
-    float tx = a.targets[2 * env_e] - rx[0], ty = a.targets[2 * env_e + 1] - rx[1];
-    float psi = atan2f(ty, tx) - yaw;
-    float sps = sinf(psi), cps = cosf(psi);
-    float* o = Lobs + ee * obs_dim;
-    o[0] = height; o[1] = roll; o[2] = pitch;
-    o[3] = rv[0]; o[4] = rv[1]; o[5] = rv[2];
-    o[6] = rw[0]; o[7] = rw[1]; o[8] = rw[2];
-    o[9] = sps; o[10] = cps;
+  const int part_0 = (J * E + 63) & ~63, part_n = (E + 63) & ~63;
+  auto part_env = [&](int part) -> int {   // env of this thread in that part, or -1
+    int t0 = part_0 + part * part_n;
+    if (t0 + part_n > kThreads) t0 = 0;
+    const int ee = tid - t0;
+    if (ee < 0 || ee >= E || blockIdx.x * E + ee >= N) return -1;
+    return pass == 0 || Lrst[ee] ? ee : -1;
+  };
+  auto yaw_of = [&](int ee, float& rx, float& ry) -> float {
+    rx = Lpos[(m_root * 7 + 0) * E + ee]; ry = Lpos[(m_root * 7 + 1) * E + ee];
+    const float qw = Lpos[(m_root * 7 + 3) * E + ee], qx = Lpos[(m_root * 7 + 4) * E + ee];
+    const float qy = Lpos[(m_root * 7 + 5) * E + ee], qz = Lpos[(m_root * 7 + 6) * E + ee];
+    return atan2f(2.0f * (qw * qz + qx * qy), 1.0f - 2.0f * (qy * qy + qz * qz));
+  };
+  if (const int ee = part_env(0); ee >= 0) {
+    // target in the root's frame, speed towards it
+    const int env_e = agent_at(blockIdx.x * E + ee);
+    const float gx = a.targets[2 * env_e], gy = a.targets[2 * env_e + 1];
+    float rx, ry;
+    const float yaw = yaw_of(ee, rx, ry);
+    const float rv0 = Lvel[(m_root * kVS + 0) * E + ee], rv1 = Lvel[(m_root * kVS + 1) * E + ee];
+    const float tx = gx - rx, ty = gy - ry;
+    const float psi = atan2f(ty, tx) - yaw;
+    const float tn = sqrtf(tx * tx + ty * ty);
+    Lobs[ee * obs_dim + 9] = sinf(psi); Lobs[ee * obs_dim + 10] = cosf(psi);
+    Lsc[0 * E + ee] = tn > 0.0f ? (rv0 * tx + rv1 * ty) / tn : 0.0f;
+    Lsc[1 * E + ee] = tn;
+  }
+  if (const int ee = part_env(1); ee >= 0) {
+    // height above the ground
+    const float rx = Lpos[(m_root * 7 + 0) * E + ee], ry = Lpos[(m_root * 7 + 1) * E + ee];
+    float height = Lpos[(m_root * 7 + 2) * E + ee];
+    if (m_terrain == 1) {
+      const HeightCell c = height_cell(H0.nx, H0.ny, H0.cell, H0.ox, H0.oy, rx + Lorg[ee], ry + Lorg[E + ee]);
+      const float* hs = a.heights + c.at;
+      height = height + Lorg[2 * E + ee] - height_in_cell(c.fx, c.fy, hs[0], hs[1], hs[H0.nx + 1], hs[H0.nx]);
+    }
+    Lobs[ee * obs_dim] = height;
+  }
+  if (const int ee = part_env(2); ee >= 0) {
+    // roll and pitch, velocities
+    const float qw = Lpos[(m_root * 7 + 3) * E + ee], qx = Lpos[(m_root * 7 + 4) * E + ee];
+    const float qy = Lpos[(m_root * 7 + 5) * E + ee], qz = Lpos[(m_root * 7 + 6) * E + ee];
+    for (int c = 0; c < 6; ++c) Lobs[ee * obs_dim + 3 + c] = Lvel[(m_root * kVS + c) * E + ee];
+    Lobs[ee * obs_dim + 1] = atan2f(2.0f * (qw * qx + qy * qz), 1.0f - 2.0f * (qx * qx + qy * qy));
+    Lobs[ee * obs_dim + 2] = asinf(fminf(fmaxf(2.0f * (qw * qy - qz * qx), -1.0f), 1.0f));
+  }
+  if (const int ee = part_env(3); ee >= 0) {
+    // feet on the ground, sums over the actions (eight reads in flight at a time)
     int n_feet = 0;
     for (int f = 0; f < F; ++f) {
-      const BodyTab& bt = M.bodies[M.feet[f]];
+      const int fb = (m_feet >> (8 * f)) & 255;
+      const int s0 = Ltjs[fb * (kMaxBodyJoints + 3) + 1], ns = Ltjs[fb * (kMaxBodyJoints + 3) + 2];
       int flag = 0;
-      for (int k = 0; k < bt.n_slots; ++k) {
-        int s = bt.slot0 + k;
-        if (pass == 0 && Lreci[(s * kRecWords + 0) * E + ee] && Lrec[(s * kRecWords + 3) * E + ee] <= 0.005f) flag = 1;
-      }
-      o[11 + 3 * D + f] = (float)flag;
+      for (int k = 0; k < ns; ++k)
+        if (pass == 0 && Lreci[((s0 + k) * kRecWords + 0) * E + ee] && Lrec[((s0 + k) * kRecWords + 3) * E + ee] <= 0.005f) flag = 1;
+      Lobs[ee * obs_dim + 11 + 3 * D + f] = (float)flag;
       n_feet += flag;
     }
     float l1 = 0.0f, l2 = 0.0f;
-    int n_lim = 0;
-    for (int d = 0; d < D; ++d) {
-      float uu = Lu[d * E + ee];
-      l1 += fabsf(uu); l2 += uu * uu;
-      n_lim += Llim[d * E + ee];
+    for (int d0 = 0; d0 < D; d0 += 8) {
+      float uu[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) uu[k] = Lu[(d0 + k < D ? d0 + k : D - 1) * E + ee];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (d0 + k < D) { l1 += fabsf(uu[k]); l2 += uu[k] * uu[k]; }
     }
-    float tn = sqrtf(tx * tx + ty * ty);
-    float speed = tn > 0.0f ? (rv[0] * tx + rv[1] * ty) / tn : 0.0f;
+    Lsc[2 * E + ee] = l1; Lsc[3 * E + ee] = l2; Lsc[4 * E + ee] = (float)n_feet;
+  }
+  if (m_height_map) {
+    if (const int ee = part_env(4); ee >= 0) {
+      // centre of mass and heading for the height map
+      float cx = 0.0f, cy = 0.0f, cz = 0.0f;
+      for (int bb = 0; bb < B; ++bb) {
+        const float mf = M.body_mass_frac[bb];
+        cx += mf * Lpos[(bb * 7 + 0) * E + ee]; cy += mf * Lpos[(bb * 7 + 1) * E + ee]; cz += mf * Lpos[(bb * 7 + 2) * E + ee];
+      }
+      float rx, ry;
+      const float yaw = yaw_of(ee, rx, ry);
+      Lhm[0 * E + ee] = cx + Lorg[ee]; Lhm[1 * E + ee] = cy + Lorg[E + ee]; Lhm[2 * E + ee] = cz + Lorg[2 * E + ee];
+      Lhm[3 * E + ee] = cosf(yaw); Lhm[4 * E + ee] = sinf(yaw);
+    }
+  }
+  };
+  // ---- reward (Eq. 1-3), done (Section 4.1), one thread per env; returns whether the env was reset
+  // (what it needs from memory is read early, so that the trip passes while the observation is packed)
+  const int m_max_steps = M.max_steps;
+  const float m_alive = M.alive_bonus, m_term_height = M.term_height;
+  int steps_before = 0;
+  if (tid < E && (blockIdx.x * E + tid) < N) steps_before = a.steps[agent_at(blockIdx.x * E + tid)];
+  auto finish_env = [&]() -> bool {
+  bool reset_now = false;
+  if (tid < E && (blockIdx.x * E + tid) < N) {
+    const int ee = tid, env_e = agent_at(blockIdx.x * E + tid);
+    const int rb = m_root;
+    const float height = Lobs[ee * obs_dim], cps = Lobs[ee * obs_dim + 10];
+    const float speed = Lsc[0 * E + ee], tn = Lsc[1 * E + ee], l1 = Lsc[2 * E + ee], l2 = Lsc[3 * E + ee];
+    const float n_feet = Lsc[4 * E + ee];
+    const float qx = Lpos[(rb * 7 + 4) * E + ee], qy = Lpos[(rb * 7 + 5) * E + ee];
+    int n_lim = 0;
+    for (int d0 = 0; d0 < D; d0 += 8) {
+      int lv[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) lv[k] = Llim[(d0 + k < D ? d0 + k : D - 1) * E + ee];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) n_lim += d0 + k < D ? lv[k] : 0;
+    }
     float r_head = cps > 0.8f ? 1.0f : cps / 0.8f;
     float cvert = 1.0f - 2.0f * (qx * qx + qy * qy);
     float r_stand = cvert > 0.93f ? 1.0f : 0.0f;
-    int steps = a.steps[env_e] + (a.count_step ? 1 : 0);
-    const bool only_obs = pass != 0;                 // re-packing a freshly reset env: obs only
-    if (!only_obs) a.steps[env_e] = steps;
-    const float rew = M.alive_bonus + speed + 0.5f * r_head + 0.05f * r_stand - 4.0f * l1 - 0.5f * l2 -
-                      0.2f * (float)n_lim - (float)n_feet;
-    uint8_t dn = (height < M.term_height || steps >= M.max_steps) ? 1 : 0;
-    if (a.task.enabled && a.count_step && pass == 0) {
+    int steps = steps_before + (a.count_step ? 1 : 0);
+    a.steps[env_e] = steps;
+    const float rew = m_alive + speed + 0.5f * r_head + 0.05f * r_stand - 4.0f * l1 - 0.5f * l2 -
+                      0.2f * (float)n_lim - n_feet;
+    uint8_t dn = (height < m_term_height || steps >= m_max_steps) ? 1 : 0;
+    if (a.task.enabled && a.count_step) {
       // Section 4.1: termination only after `grace` consecutive frames below the threshold;
       // flagrun target re-drawn every `period` frames or when reached; finished envs start
       // their next episode below
       int fall = a.task_i[4 * env_e + 0], age = a.task_i[4 * env_e + 1];
       const int ep = a.task_i[4 * env_e + 3];
-      fall = height < M.term_height ? fall + 1 : 0;
-      dn = (fall > a.task.grace || steps >= M.max_steps) ? 1 : 0;
+      fall = height < m_term_height ? fall + 1 : 0;
+      dn = (fall > a.task.grace || steps >= m_max_steps) ? 1 : 0;
       if (a.task.period > 0) {
         age += 1;
         if (age >= a.task.period || tn < a.task.reach) {
           float txy[2];
-          task_draw_target(a.task, env_e, ep, steps, rx[0], rx[1], txy);
+          task_draw_target(a.task, env_e, ep, steps, Lpos[(rb * 7 + 0) * E + ee], Lpos[(rb * 7 + 1) * E + ee], txy);
           a.targets[2 * env_e] = txy[0]; a.targets[2 * env_e + 1] = txy[1];
           age = 0;
         }
@@ -2339,11 +2425,9 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       a.task_i[4 * env_e + 0] = fall; a.task_i[4 * env_e + 1] = age;
       reset_now = dn && a.task.auto_reset;
     }
-    if (!only_obs) {
-      // (one copy each: the caller's array when there is one, else the library's)
-      (a.reward_out ? a.reward_out : a.reward)[env_e] = rew;
-      (a.done_out ? a.done_out : a.done)[env_e] = dn;
-    }
+    // (one copy each: the caller's array when there is one, else the library's)
+    (a.reward_out ? a.reward_out : a.reward)[env_e] = rew;
+    (a.done_out ? a.done_out : a.done)[env_e] = dn;
     if (reset_now) {
       // next episode: the reset recipe with that episode's seed, built in this env's column of
       // the pose array (no other thread reads it before the barrier below)
@@ -2357,8 +2441,9 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   return reset_now;
   };
   pack_joints(std::integral_constant<int, 0>{});
+  pack_root(std::integral_constant<int, 0>{});
   __syncthreads();
-  const bool reset_now = pack_root(std::integral_constant<int, 0>{});
+  const bool reset_now = finish_env();
   if (may_reset) {
     if (tid < E) Lrst[tid] = reset_now ? 1 : 0;
     if (__syncthreads_or(reset_now)) {
@@ -2369,11 +2454,10 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         for (int c = 0; c < 6; ++c) st[(7 + c) * fs] = Lvel[(b * kVS + c) * E + e];
       }
       pack_joints(std::integral_constant<int, 1>{});
-      __syncthreads();
       pack_root(std::integral_constant<int, 1>{});
+      __syncthreads();
     }
   }
-  __syncthreads();
   if constexpr (WS != 0) {
     // the kept impulses go back to the workspace for the next launch; an env that was just reset
     // starts its episode without any
@@ -2397,37 +2481,40 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       const int ee = i / obs_dim, k = i - ee * obs_dim;
       obs_dst[(size_t)agent_at(env0 + ee) * obs_row + k] = o;
     }
-    if (M.height_map) {
+    if (m_height_map) {
       // Height map (Section 4.1, complex-terrain task): terrain height under a 15 x 11 grid that
       // follows the centre of mass and is aligned with the root's heading, minus the height of
       // the centre of mass; written straight to the output rows (it is not staged in LDS).
-      // Centre and heading per env first (in the space of the sweep copies, free by now).
-      float* Lhm = Loutj;   // [5][E]: centre x,y,z (world), cos, sin of the yaw
-      if (tid < n_here) {
-        const int ee = tid;
-        float cx = 0.0f, cy = 0.0f, cz = 0.0f;
-        for (int bb = 0; bb < B; ++bb) {
-          const float mf = M.body_mass_frac[bb];
-          cx += mf * Lpos[(bb * 7 + 0) * E + ee]; cy += mf * Lpos[(bb * 7 + 1) * E + ee]; cz += mf * Lpos[(bb * 7 + 2) * E + ee];
+      // Six points per thread at a time, their samples all in flight together: one point after the
+      // other costs a trip to L2 each.
+      constexpr int kHm = kHmRows * kHmCols, kPoints = 6;
+      for (int i0 = tid; i0 < n_here * kHm; i0 += kPoints * kThreads) {
+        float hz[kPoints], fx[kPoints], fy[kPoints], hs[kPoints][4];
+        if (m_terrain == 1) {
+#pragma unroll
+          for (int u = 0; u < kPoints; ++u) {
+            const int i = min(i0 + u * kThreads, n_here * kHm - 1);
+            const int ee = i / kHm, k = i - ee * kHm, hi = k / kHmCols, hj = k - hi * kHmCols;
+            const float fw = M.hm_fwd[hi], lt = M.hm_lat[hj], c = Lhm[3 * E + ee], sn = Lhm[4 * E + ee];
+            const float wx = Lhm[0 * E + ee] + (c * fw - sn * lt), wy = Lhm[1 * E + ee] + (sn * fw + c * lt);
+            const HeightCell hc = height_cell(H0.nx, H0.ny, H0.cell, H0.ox, H0.oy, wx, wy);
+            fx[u] = hc.fx; fy[u] = hc.fy;
+            const float* hp = a.heights + hc.at;
+            hs[u][0] = hp[0]; hs[u][1] = hp[1]; hs[u][2] = hp[H0.nx + 1]; hs[u][3] = hp[H0.nx];
+          }
+#pragma unroll
+          for (int u = 0; u < kPoints; ++u) hz[u] = height_in_cell(fx[u], fy[u], hs[u][0], hs[u][1], hs[u][2], hs[u][3]);
+        } else {
+#pragma unroll
+          for (int u = 0; u < kPoints; ++u) hz[u] = 0.0f;
         }
-        const int rbb = M.root;
-        const float qw = Lpos[(rbb * 7 + 3) * E + ee], qx = Lpos[(rbb * 7 + 4) * E + ee];
-        const float qy = Lpos[(rbb * 7 + 5) * E + ee], qz = Lpos[(rbb * 7 + 6) * E + ee];
-        const float yaw = atan2f(2.0f * (qw * qz + qx * qy), 1.0f - 2.0f * (qy * qy + qz * qz));
-        const int ag = agent_at(env0 + ee);
-        Lhm[0 * E + ee] = cx + a.origins[3 * ag];
-        Lhm[1 * E + ee] = cy + a.origins[3 * ag + 1];
-        Lhm[2 * E + ee] = cz + a.origins[3 * ag + 2];
-        Lhm[3 * E + ee] = cosf(yaw); Lhm[4 * E + ee] = sinf(yaw);
-      }
-      __syncthreads();
-      constexpr int kHm = kHmRows * kHmCols;
-      for (int i = tid; i < n_here * kHm; i += kThreads) {
-        const int ee = i / kHm, k = i - ee * kHm, hi = k / kHmCols, hj = k - hi * kHmCols;
-          const float fw = M.hm_fwd[hi], lt = M.hm_lat[hj], c = Lhm[3 * E + ee], sn = Lhm[4 * E + ee];
-        const float wx = Lhm[0 * E + ee] + (c * fw - sn * lt), wy = Lhm[1 * E + ee] + (sn * fw + c * lt);
-        const float hz = terrain_height(M, a.heights, wx, wy) - Lhm[2 * E + ee];
-        obs_dst[(size_t)agent_at(env0 + ee) * obs_row + obs_dim + k] = hz;
+#pragma unroll
+        for (int u = 0; u < kPoints; ++u) {
+          const int i = i0 + u * kThreads;
+          if (i >= n_here * kHm) break;
+          const int ee = i / kHm, k = i - ee * kHm;
+          obs_dst[(size_t)agent_at(env0 + ee) * obs_row + obs_dim + k] = hz[u] - Lhm[2 * E + ee];
+        }
       }
     }
   }
