@@ -9,8 +9,8 @@ namespace sim355 {
 // compile time); any other number runs the general form, which takes it from the launch arguments
 // and is up to twice as slow.  The Newton families end at 8 (a contact thread per slot).  Collisions
 // together with the warm start begin at 8: below, that family stays in the general form, whose
-// multiply-adds are contracted differently, because its ten-step agreement with the oracle is pinned
-// there to a bound that one env in a few dozen, with a capsule contact that amplifies rounding,
+// multiply-adds are contracted differently, because its ten-step agreement with double precision is
+// pinned there to a bound that one env in a few dozen, with a capsule contact that amplifies rounding,
 // exceeds in the compiled forms (all of which agree bit for bit).
 constexpr bool step_compiled_envs(int E, bool pairs, bool warm, bool newton) {
   return (E == 16 && !newton) || E == 8 || ((E == 4 || E == 2 || E == 1) && !(pairs && warm));
