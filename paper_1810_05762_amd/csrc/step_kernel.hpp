@@ -869,13 +869,6 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   const int js_side = tid & 1, js_e = (tid >> 1) % E, js_j = (tid >> 1) / E;
   const bool js_on = js_j < J && blockIdx.x * E + js_e < N;
 
-  // Up to eight envs every slot has a thread of its own in the per-slot pass, and the per-body pass that
-  // thins the slots out first is left out with its barrier: a pass lasts as long as its one chain (64
-  // humanoids on the heightfield, three steps: 260 -> 239 us).  With 16 envs the per-slot pass would
-  // take ten wavefronts instead of five.
-  constexpr bool kSlotsDirect = EC > 0 && EC <= 8;
-  static_assert(!kSlotsDirect || kMaxSlots * EC <= NT, "a thread per slot");
-
   const int tid_o = tid, e_o = e, idx_o = idx;
   const float h_o = h;
   for (int sub = 0; sub < a.substeps; ++sub) {
@@ -926,10 +919,9 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     TMARK(1);
     // ---- B: joint torques (stored once per joint; the body applies the sign).  They go through
     //         LDS only, so they are computed by the upper half of the workgroup when the joints fit
-    //         there and the lower half runs the per-body pass below at the same time, else by the
-    //         lower half while the upper one runs the per-slot pass.
+    //         there: the lower half runs the per-body pass below at the same time.
     {
-      const int tq_base = !kSlotsDirect && J * E <= kThreads / 2 ? kThreads / 2 : 0;
+      const int tq_base = J * E <= kThreads / 2 ? kThreads / 2 : 0;
       const int tj = (tid - tq_base) / E, te = (tid - tq_base) % E;
       if (tid >= tq_base && tj < J && blockIdx.x * E + te < N) {
         const JointTab& jt = Ltjoint[tj];
@@ -956,12 +948,12 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     //          work units of 8 cells (samples for a mid-segment).
     //          Slots go to the threads from the top of the workgroup down: a second round, if any,
     //          then runs on the last wavefronts while the first ones hold the joint threads.
-    // forces -> velocities (torques, gravity, push, explicit gyroscopic term) of body b of env e: needs
-    // the joint torques and nothing of the contacts, everything from and to LDS
-    auto forces = [&](int b, int e) {
-      float tau[3] = {0, 0, 0}, v[3], w[3];
-      const int njs = Ltjs[b * (kMaxBodyJoints + 3)];
-      for (int k = 0; k < njs; ++k) {
+    // forces -> velocities (torques, gravity, push, explicit gyroscopic term): body threads, needs
+    // the joint torques and nothing of the contacts
+    auto forces = [&]() {
+      if (!is_body) return;
+      float tau[3] = {0, 0, 0};
+      for (int k = 0; k < my_njs; ++k) {
         const int js = Ltjs[b * (kMaxBodyJoints + 3) + 3 + k];
         const float sg = (js & 1) ? 1.0f : -1.0f;
         for (int c = 0; c < 3; ++c) tau[c] += sg * Ltq[((js >> 1) * 3 + c) * E + e];
@@ -971,7 +963,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       quat_to_mat(qq, R);
       for (int c = 0; c < 3; ++c) { Ib[c] = Ltin[6 * b + c]; invIb[c] = Ltin[6 * b + 3 + c]; }
       for (int c = 0; c < 3; ++c) { v[c] = Lvel[(b * kVS + c) * E + e]; w[c] = Lvel[(b * kVS + 3 + c) * E + e]; }
-      if (a.task.enabled && b == m_root) {
+      if (a.task.enabled && b == M.root) {
         const float him = h * Ltbody[4 * b + 3];
         v[0] += him * Lpush[0 * E + e]; v[1] += him * Lpush[1 * E + e]; v[2] += him * Lpush[2 * E + e];
       }
@@ -991,17 +983,9 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       for (int c = 0; c < 3; ++c) w[c] += dww[c];
       for (int c = 0; c < 3; ++c) { Lvel[(b * kVS + c) * E + e] = v[c]; Lvel[(b * kVS + 3 + c) * E + e] = w[c]; }
     };
-    // Where the forces are integrated: with the per-body pass, on the lower wavefronts while the upper
-    // ones run the per-slot pass; else not before the joint rows are built, on the wavefronts above
-    // them (1024 humanoids on the plane, where everybody waited for them: 56.6 -> 55.2 us).
-    const bool forces_late = kSlotsDirect || m_terrain == 0;
-    auto forces_beside_joints = [&]() {
-      for (int i = tid - joint_threads; i < B * E; i += kThreads - joint_threads)
-        if (blockIdx.x * E + i % E < N) forces(i / E, i % E);
-    };
     int n_b1 = S * E;            // slots the per-slot pass visits
     unsigned* Lslots = Lcand;    // heightfield: list of the slots of the bodies near the ground
-    if (!kSlotsDirect && m_terrain == 1) {
+    if (m_terrain == 1) {
       // ---- B1a: one thread per body: reach test of the whole capsule (box of its segment);
       //           the slots of a body that passes are listed for the per-slot pass, the others
       //           are inactive.  A slot can only pass its own test if its body passes this one.
@@ -1033,10 +1017,11 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       __syncthreads();
       TMARK(24);
       n_b1 = Lcount[7];
-      if (is_body) forces(b, e);
+      // the lower wavefronts integrate the forces while the upper ones run the per-slot pass
+      forces();
     }
     for (int x = kThreads - 1 - tid; x < n_b1; x += kThreads) {
-      const int i = !kSlotsDirect && m_terrain == 1 ? (int)Lslots[x] : x;
+      const int i = m_terrain == 1 ? (int)Lslots[x] : x;
       int ee = i % E, s = i / E;
       int env_i = blockIdx.x * E + ee;
       ContactOut co = no_contact();
@@ -1112,9 +1097,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         const int cap = pass == 0 ? unit_cap_e : unit_cap - unit_cap_e;
         const int n_u = Lcount[5 + pass] < cap ? Lcount[5 + pass] : cap;
         const unsigned* U = Lunit + (pass == 0 ? 0 : unit_cap_e);
-        // (with few units the two kinds start from opposite ends of the workgroup and run side by side;
-        //  with several rounds of each, at 16 envs, that costs 2 %: 4096 humanoids 127.7 against 125.4 us)
-        for (int x = pass == 0 || !kSlotsDirect ? grp : kThreads / kGroup - 1 - grp; x < n_u; x += kThreads / kGroup) {
+        for (int x = grp; x < n_u; x += kThreads / kGroup) {
           const unsigned uw = U[x];
           const int i = uw & 4095, c = (int)(uw >> 12) * 8 + gl;   // slot index, cell within the box
           const int ee = i % E, s = i / E;
@@ -1479,7 +1462,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     constexpr bool g_variants = EC >= 8;
     constexpr int kPairFew = 2;
     const bool gp_few = g_variants && PC != 0 && __ballot(gp_cnt > kPairFew) == 0ull;
-    // ---- C: block weight sums
+    // ---- C: block weight sums (and, on the plane, forces -> velocities)
     float nbf = 0.0f;
     if (is_body) {
       nbf = (float)my_njs;
@@ -1487,6 +1470,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       nbf += gp_wsum;   // (a body thread is the first averaging thread of its own body)
       Lnb[b * E + e] = nbf;
     }
+    if (m_terrain == 0) forces();   // plane: no per-body pass, the torques are complete only now
     if (a.recs && sub == a.substeps - 1) {
       // export the records of the last substep, [N][S][12] words
       for (int i = tid; i < S * E * kRecWords; i += kThreads) {
@@ -1819,11 +1803,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           if (!Lreci[(i / E * kRecWords + 0) * E + i % E])
             for (int r = 0; r < 3; ++r) Lwc[(i / E * 3 + r) * E + i % E] = 0.0f;
       }
-      if (jrole) build_joint_side();
-      else {
-        if (forces_late) forces_beside_joints();
-        build_contact();
-      }
+      if (jrole) build_joint_side(); else build_contact();
       for (int i = tid; i < 3 * nblk * E; i += kThreads) Lred[i] = 0.0f;   // inactive slots contribute nothing
       const int nr = jrole ? 6 : 3;
       const bool active = jrole ? js_on : has_contact;      // this lane holds rows
@@ -2112,7 +2092,6 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       // ahead of the reads that depend on it
       const int js_ob = js_side ? Ltjoint[js_j < J ? js_j : 0].child : Ltjoint[js_j < J ? js_j : 0].parent;
       const int js_voff = (js_ob < 0 ? 0 : js_ob) * kVS * E + js_e;
-      if (forces_late) __syncthreads();
       for (int it = WS ? -1 : 0; it < a.iterations; ++it) {
         if (js_on) {
           const int e = js_e;
@@ -2176,10 +2155,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           if (!Lreci[(i / E * kRecWords + 0) * E + i % E])
             for (int r = 0; r < 3; ++r) Lwc[(i / E * 3 + r) * E + i % E] = 0.0f;
       }
-      if (forces_late) forces_beside_joints();
       build_contact();
       build_pair();
-      if (forces_late) __syncthreads();
       // the starting impulses of the contacts beyond one per thread are set by the thread that
       // relaxes them in every sweep below (same index mapping), so no other thread's store is read
       for (int k = n_reg + (kThreads - 1 - tid); k < n_active; k += n_reg)
