@@ -27,11 +27,11 @@
 //   D  joint / contact threads build row constants
 //   S  (warm-start variant: sweep -1 applies the impulses kept from the last substep)
 //      `iterations` sweeps: every block relaxes its rows one after another on a
-//      private copy of its bodies taken from the shared snapshot and leaves the change; a body is
+//      private copy of its bodies taken from the shared snapshot; a body is
 //      shared out among its blocks by weight (joint 1, contact a ramp from 0 at
 //      the margin to 1 at half the margin) and acts inside block c with inverse
 //      mass scaled by W / w_c; then every body takes the weighted average of the
-//      changes of its blocks in static order (no atomics)
+//      copies of its blocks in static order (no atomics)
 //   E  damping, angular-velocity cap, position integration
 #pragma once
 #include <hip/hip_runtime.h>
@@ -125,7 +125,7 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.patch = o; o += with_patch ? E * kPatch * kPatch : 0;
   p.mip = o; o += with_patch ? E * kPatchBlocks * kPatchBlocks : 0;
   p.pq = o; o += pairs ? kPairCap * kPairWords : 0;   // sorted queue of the substep's contacts
-  p.po = o; o += pairs ? (kPairCap + 1) * 12 : 0;     // weighted velocity changes of their two bodies; the last entry stays zero
+  p.po = o; o += pairs ? (kPairCap + 1) * 12 : 0;     // weighted velocity copies of their two bodies; the last entry stays zero
   p.pnear = o; o += pairs ? (E * pairs) / 2 + 1 : 0;  // agent pairs whose bounding spheres overlap
   p.pbs = o; o += pairs ? E : 0;                      // bounding radius of every agent about its root
   p.pcount = o; o += pairs ? 4 : 0;
@@ -355,37 +355,34 @@ __device__ __forceinline__ void project_on_disc(float& l1, float& l2, float lim)
   }
 }
 
-// One sweep of a contact block on the snapshot (vv, ww) of the body velocity, which it replaces by
-// the change its rows make: normal row (impulse >= 0), then the friction pair projected on the disc
-// mu * lambda_n.  n, t1 and t2 are orthonormal, so the normal impulse's linear part does not show in
-// the tangential rows and only the angular velocity is brought up to date between the two.
+// One sweep of a contact block on its private copy (vv, ww) of the body velocity:
+// normal row (impulse >= 0), then the friction pair projected on the disc mu * lambda_n.
 __device__ __forceinline__ void relax_contact(ContactRows& c, float mu, float vv[3], float ww[3]) {
-  const float jv0 = dot(c.dir[0], vv) + dot(c.ang[0], ww);
-  const float ln = fmaxf(c.lam[0] - c.meff[0] * (jv0 + c.bias), 0.0f);
-  const float d0 = ln - c.lam[0];
-  c.lam[0] = ln;
-  float dw[3], wn[3];
-  for (int k = 0; k < 3; ++k) { dw[k] = c.Y[0][k] * d0; wn[k] = ww[k] + dw[k]; }
-  const float jv1 = dot(c.dir[1], vv) + dot(c.ang[1], wn);
-  const float jv2 = dot(c.dir[2], vv) + dot(c.ang[2], wn);
+  {
+    float jv = dot(c.dir[0], vv) + dot(c.ang[0], ww);
+    float dl = -c.meff[0] * (jv + c.bias);
+    float ln = fmaxf(c.lam[0] + dl, 0.0f);
+    dl = ln - c.lam[0];
+    c.lam[0] = ln;
+    for (int k = 0; k < 3; ++k) { vv[k] += c.ls * c.dir[0][k] * dl; ww[k] += c.Y[0][k] * dl; }
+  }
+  float jv1 = dot(c.dir[1], vv) + dot(c.ang[1], ww);
+  float jv2 = dot(c.dir[2], vv) + dot(c.ang[2], ww);
   float l1 = c.lam[1] - c.meff[1] * jv1, l2 = c.lam[2] - c.meff[2] * jv2;
   const float lim = mu * c.lam[0];
   project_on_disc(l1, l2, lim);
-  const float d1 = l1 - c.lam[1], d2 = l2 - c.lam[2];
+  float d1 = l1 - c.lam[1], d2 = l2 - c.lam[2];
   c.lam[1] = l1; c.lam[2] = l2;
-  const float s0 = c.ls * d0, s1 = c.ls * d1, s2 = c.ls * d2;
   for (int k = 0; k < 3; ++k) {
-    vv[k] = c.dir[0][k] * s0 + c.dir[1][k] * s1 + c.dir[2][k] * s2;
-    ww[k] = dw[k] + c.Y[1][k] * d1 + c.Y[2][k] * d2;
+    vv[k] += c.ls * (c.dir[1][k] * d1 + c.dir[2][k] * d2);
+    ww[k] += c.Y[1][k] * d1 + c.Y[2][k] * d2;
   }
 }
 
-// Warm start: the change the impulses the rows start from make to the body.
-__device__ __forceinline__ void contact_impulse_change(const ContactRows& c, float vv[3], float ww[3]) {
-  for (int k = 0; k < 3; ++k) {
-    vv[k] = c.ls * (c.dir[0][k] * c.lam[0] + c.dir[1][k] * c.lam[1] + c.dir[2][k] * c.lam[2]);
-    ww[k] = c.Y[0][k] * c.lam[0] + c.Y[1][k] * c.lam[1] + c.Y[2][k] * c.lam[2];
-  }
+// Warm start: the block's copy of its body after the impulses the rows start from.
+__device__ __forceinline__ void apply_contact_impulses(const ContactRows& c, float vv[3], float ww[3]) {
+  for (int r = 0; r < 3; ++r)
+    for (int k = 0; k < 3; ++k) { vv[k] += c.ls * c.dir[r][k] * c.lam[r]; ww[k] += c.Y[r][k] * c.lam[r]; }
 }
 
 // Rows of one capsule-capsule contact (Section 3.1: contacts among bodies; Section 4.1:
@@ -472,27 +469,27 @@ __device__ __forceinline__ void build_pair_side(PairSide& c, int side, const flo
   c.off = bo * kVS * E + eo;
 }
 
-// One sweep of one side of a capsule-capsule block on the snapshot (v, w) of the own body's velocity,
-// which it replaces by the change the rows make (like relax_contact, the sum of both sides).
+// One sweep of one side of a capsule-capsule block on its private copy of the own body's velocity.
 __device__ __forceinline__ void relax_pair_side(PairSide& c, float mu, float v[3], float w[3]) {
-  const float p0 = dot(c.sd[0], v) + dot(c.sa[0], w);
-  const float jv0 = p0 + lane_swap1(p0);
-  const float ln = fmaxf(c.lam[0] - c.meff[0] * (jv0 + c.bias), 0.0f);
-  const float d0 = ln - c.lam[0];
-  c.lam[0] = ln;
-  float dw[3], wn[3];
-  for (int k = 0; k < 3; ++k) { dw[k] = c.Y[0][k] * d0; wn[k] = w[k] + dw[k]; }
-  const float p1 = dot(c.sd[1], v) + dot(c.sa[1], wn), p2 = dot(c.sd[2], v) + dot(c.sa[2], wn);
+  {
+    const float part = dot(c.sd[0], v) + dot(c.sa[0], w);
+    const float jv = part + lane_swap1(part);
+    float dl = -c.meff[0] * (jv + c.bias);
+    const float ln = fmaxf(c.lam[0] + dl, 0.0f);
+    dl = ln - c.lam[0];
+    c.lam[0] = ln;
+    for (int k = 0; k < 3; ++k) { v[k] += c.ls * c.sd[0][k] * dl; w[k] += c.Y[0][k] * dl; }
+  }
+  const float p1 = dot(c.sd[1], v) + dot(c.sa[1], w), p2 = dot(c.sd[2], v) + dot(c.sa[2], w);
   const float jv1 = p1 + lane_swap1(p1), jv2 = p2 + lane_swap1(p2);
   float l1 = c.lam[1] - c.meff[1] * jv1, l2 = c.lam[2] - c.meff[2] * jv2;
   const float lim = mu * c.lam[0];
   project_on_disc(l1, l2, lim);
   const float d1 = l1 - c.lam[1], d2 = l2 - c.lam[2];
   c.lam[1] = l1; c.lam[2] = l2;
-  const float s0 = c.ls * d0, s1 = c.ls * d1, s2 = c.ls * d2;
   for (int k = 0; k < 3; ++k) {
-    v[k] = c.sd[0][k] * s0 + c.sd[1][k] * s1 + c.sd[2][k] * s2;
-    w[k] = dw[k] + c.Y[1][k] * d1 + c.Y[2][k] * d2;
+    v[k] += c.ls * (c.sd[1][k] * d1 + c.sd[2][k] * d2);
+    w[k] += c.Y[1][k] * d1 + c.Y[2][k] * d2;
   }
 }
 
@@ -719,7 +716,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   float* Ltin = lds + P.tin;                          // body table: inertia(3), inverse inertia(3)
   const JointTab* Ltjoint = reinterpret_cast<const JointTab*>(lds + P.tjoint);  // joint table
   float* Lpq = lds + P.pq;                            // capsule-capsule contacts, kPairWords each, sorted by key
-  float* Lpo = lds + P.po;                            // their changes times the block weight: A (v, w), B (v, w)
+  float* Lpo = lds + P.po;                            // their copies times the block weight: A (v, w), B (v, w)
   int* Lnear = reinterpret_cast<int*>(lds + P.pnear);
   int* Lbs = reinterpret_cast<int*>(lds + P.pbs);     // bounding radii as float bits (ordered like ints)
   int* Lpcount = reinterpret_cast<int*>(lds + P.pcount);  // contacts found, near agent pairs
@@ -1665,11 +1662,10 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         // every load is unconditional: unused entries read a valid location and enter the sum
         // with weight 0 (the copy arrays only ever hold finite numbers); all reads are issued
         // before the first use so their LDS latency is paid once
-        // The blocks leave the changes they make to their bodies, copy_k - v0, and the average is
-        // (sum of w_k change_k) / W added to v0: the changes are small next to the velocity itself, so
-        // the sum rounds at their magnitude and the velocity is rounded once per sweep.  (Copies that
-        // hold the velocities themselves cost this pass, which every wavefront of the wide workgroup
-        // takes part in, a subtraction per copy and component; a block has the linear changes anyway.)
+        // The average is taken over the copies' differences from the snapshot, (sum of w_k (copy_k -
+        // v0)) / W added to v0: the differences are small next to the velocity itself, so the sum
+        // rounds at their magnitude and the velocity is rounded once per sweep, where a weighted
+        // sum of the copies themselves would round it once per copy.
         const int ho = c0 * E;
         float v0[NC], acc[NC];
 #pragma unroll
@@ -1694,12 +1690,12 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
 #pragma unroll
           for (int k = 0; k < KJ; ++k)
 #pragma unroll
-            for (int c = 0; c < NC; ++c) acc[c] += gat_w[k] * val[k][c];
+            for (int c = 0; c < NC; ++c) acc[c] += gat_w[k] * (val[k][c] - v0[c]);
           if constexpr (HC != 0) {
 #pragma unroll
             for (int k = 0; k < 3; ++k)
 #pragma unroll
-              for (int c = 0; c < NC; ++c) acc[c] += gat_w[NJ + k] * val[KJ + k][c];
+              for (int c = 0; c < NC; ++c) acc[c] += gat_w[NJ + k] * (val[KJ + k][c] - v0[c]);
           }
         };
         constexpr int kFew = NJ > 2 ? 2 : NJ;
@@ -1721,6 +1717,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
                 if (((refs >> 16) & 0xffff) == g_ref)
                   for (int c = 0; c < NC; ++c) acc[c] += Lpo[k * 12 + 6 + c0 + c];
               }
+              for (int c = 0; c < NC; ++c) acc[c] -= gp_wsum * v0[c];   // (their copies come multiplied by the weights)
             } else {
               // the (weighted) copies of the listed contacts (the list holds the used entries first);
               // unused entries point at zeros
@@ -1742,6 +1739,9 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
               } else {
                 sum_pairs(std::integral_constant<int, kPairList>{});
               }
+              // (the listed copies come multiplied by their weights: the snapshot's share goes off in one piece)
+#pragma unroll
+              for (int c = 0; c < NC; ++c) acc[c] -= gp_wsum * v0[c];
             }
           }
         }
@@ -1750,15 +1750,13 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     };
     // one sweep of this thread's side of a capsule-capsule contact, if it has one
     // (a capsule-capsule contact starts every substep without impulses: in the warm start's
-    // sweep -1 it changes nothing)
+    // sweep -1 its copies are the bodies' velocities as they are)
     auto pair_sweep = [&](bool relax) {
       if constexpr (PC != 0) {
         if (has_pair) {
-          float vo[3] = {0.0f, 0.0f, 0.0f}, wo[3] = {0.0f, 0.0f, 0.0f};
-          if (relax) {
-            for (int c = 0; c < 3; ++c) { vo[c] = Lvel[pr.off + c * E]; wo[c] = Lvel[pr.off + (3 + c) * E]; }
-            relax_pair_side(pr, p_mu, vo, wo);
-          }
+          float vo[3], wo[3];
+          for (int c = 0; c < 3; ++c) { vo[c] = Lvel[pr.off + c * E]; wo[c] = Lvel[pr.off + (3 + c) * E]; }
+          if (relax) relax_pair_side(pr, p_mu, vo, wo);
           const int po = (2 * pk + (tid & 1)) * 6;
           for (int c = 0; c < 3; ++c) { Lpo[po + c] = pr.wk * vo[c]; Lpo[po + 3 + c] = pr.wk * wo[c]; }
         }
@@ -2087,7 +2085,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           if (jr.onesided & (1 << k)) jr.nl[k] = -l0;
         }
       }
-      // own body's velocity rows, found once (the world's side of a joint reads body 0's and changes
+      // own body's velocity rows, found once (the world's side of a joint reads body 0's and writes
       // nothing): looked up inside the loop, the body index costs every sweep an LDS round trip
       // ahead of the reads that depend on it
       const int js_ob = js_side ? Ltjoint[js_j < J ? js_j : 0].child : Ltjoint[js_j < J ? js_j : 0].parent;
@@ -2095,9 +2093,9 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       for (int it = WS ? -1 : 0; it < a.iterations; ++it) {
         if (js_on) {
           const int e = js_e;
-          // (row k alone sees and changes component k of the linear velocity, so its change needs no copy)
-          float vo[3], wo[3], w0[3], dv[3];
-          for (int c = 0; c < 3; ++c) { vo[c] = Lvel[js_voff + c * E]; wo[c] = w0[c] = Lvel[js_voff + (3 + c) * E]; }
+          const int ob = js_ob;
+          float vo[3], wo[3];
+          for (int c = 0; c < 3; ++c) { vo[c] = Lvel[js_voff + c * E]; wo[c] = Lvel[js_voff + (3 + c) * E]; }
   #pragma unroll
           for (int k = 0; k < 3; ++k) {
             float dl;
@@ -2109,7 +2107,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
               dl = jv * jr.pme[k] + jr.pnb[k];
               if constexpr (WS != 0) acc[k] += dl;
             }
-            dv[k] = jr.sv * dl;
+            vo[k] += jr.sv * dl;
             for (int c = 0; c < 3; ++c) wo[c] += jr.Y[k][c] * dl;
           }
   #pragma unroll
@@ -2127,11 +2125,11 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
             }
             for (int c = 0; c < 3; ++c) wo[c] += jr.Z[k][c] * dl;
           }
-          // (the world's side leaves zeros where nobody reads)
-          for (int c = 0; c < 3; ++c) {
-            Loutj[(js_j * kJS + js_side * 6 + c) * E + e] = dv[c];
-            Loutj[(js_j * kJS + js_side * 6 + 3 + c) * E + e] = wo[c] - w0[c];
-          }
+          if (ob >= 0)
+            for (int c = 0; c < 3; ++c) {
+              Loutj[(js_j * kJS + js_side * 6 + c) * E + e] = vo[c];
+              Loutj[(js_j * kJS + js_side * 6 + 3 + c) * E + e] = wo[c];
+            }
         }
         pair_sweep(!(WS != 0 && it < 0));
         __syncthreads();
@@ -2166,7 +2164,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           const int ee = cr.slot_e % E, sl = cr.slot_e / E;
           float vv[3], ww[3];
           for (int k = 0; k < 3; ++k) { vv[k] = Lvel[(cr.body * kVS + k) * E + ee]; ww[k] = Lvel[(cr.body * kVS + 3 + k) * E + ee]; }
-          if (WS != 0 && it < 0) contact_impulse_change(cr, vv, ww);
+          if (WS != 0 && it < 0) apply_contact_impulses(cr, vv, ww);
           else relax_contact(cr, p_mu, vv, ww);
           for (int k = 0; k < 3; ++k) { Loutc[(sl * kCS + k) * E + ee] = vv[k]; Loutc[(sl * kCS + 3 + k) * E + ee] = ww[k]; }
         }
@@ -2179,7 +2177,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           for (int r = 0; r < 3; ++r) c2.lam[r] = overflow_lam(k, r);
           float vv[3], ww[3];
           for (int r = 0; r < 3; ++r) { vv[r] = Lvel[(body * kVS + r) * E + ee]; ww[r] = Lvel[(body * kVS + 3 + r) * E + ee]; }
-          if (WS != 0 && it < 0) contact_impulse_change(c2, vv, ww);
+          if (WS != 0 && it < 0) apply_contact_impulses(c2, vv, ww);
           else relax_contact(c2, p_mu, vv, ww);
           for (int r = 0; r < 3; ++r) overflow_lam(k, r) = c2.lam[r];
           for (int r = 0; r < 3; ++r) { Loutc[(sl * kCS + r) * E + ee] = vv[r]; Loutc[(sl * kCS + 3 + r) * E + ee] = ww[r]; }
