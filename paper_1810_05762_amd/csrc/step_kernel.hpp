@@ -849,6 +849,9 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     }
   }
 
+  // phase A reads the tables that other wavefronts copied; without the heightfield's copy there is no
+  // barrier between the two
+  if (!(use_patch && a.substeps > 0)) __syncthreads();
   TMARK(0);
   // wavefronts [0, joint_threads/64) hold the joint-side threads; contact k of a workgroup goes
   // to thread kThreads-1-k as long as that thread is not in a joint wavefront (n_reg contacts)
