@@ -58,10 +58,11 @@ struct Field {
   int pi0, pj0, ps;
 };
 constexpr int kMip = 4;
+constexpr int kPatch = 28;  // samples per side of that copy (ps is this or 0)
 
 __device__ __forceinline__ float field_height(const Field& H, int i, int j) {
   unsigned di = (unsigned)(i - H.pi0), dj = (unsigned)(j - H.pj0);
-  if (di < (unsigned)H.ps && dj < (unsigned)H.ps) return H.patch[dj * H.ps + di];
+  if (di < (unsigned)H.ps && dj < (unsigned)H.ps) return H.patch[dj * kPatch + di];
   return H.h[j * H.nx + i];
 }
 
@@ -71,8 +72,8 @@ __device__ __forceinline__ void field_cell_heights(const Field& H, int i, int j,
                                                    float& h11, float& h01) {
   unsigned di = (unsigned)(i - H.pi0), dj = (unsigned)(j - H.pj0);
   if (di + 1u < (unsigned)H.ps && dj + 1u < (unsigned)H.ps) {
-    const lds_float* p = H.patch + dj * H.ps + di;
-    h00 = p[0]; h10 = p[1]; h01 = p[H.ps]; h11 = p[H.ps + 1];
+    const lds_float* p = H.patch + dj * kPatch + di;
+    h00 = p[0]; h10 = p[1]; h01 = p[kPatch]; h11 = p[kPatch + 1];
   } else {
     const float* p = H.h + j * H.nx + i;
     h00 = p[0]; h10 = p[1]; h01 = p[H.nx]; h11 = p[H.nx + 1];
@@ -85,8 +86,8 @@ __device__ __forceinline__ void field_cell_heights_clamped(const Field& H, int i
                                                            float& h11, float& h01) {
   unsigned di = (unsigned)(i - H.pi0), dj = (unsigned)(j - H.pj0);
   if (di + 1u < (unsigned)H.ps && dj + 1u < (unsigned)H.ps) {
-    const lds_float* p = H.patch + dj * H.ps + di;
-    h00 = p[0]; h10 = p[1]; h01 = p[H.ps]; h11 = p[H.ps + 1];
+    const lds_float* p = H.patch + dj * kPatch + di;
+    h00 = p[0]; h10 = p[1]; h01 = p[kPatch]; h11 = p[kPatch + 1];
   } else {
     const int ip = i + 1 < H.nx ? i + 1 : i, jp = j + 1 < H.ny ? j + 1 : j;
     h00 = H.h[j * H.nx + i]; h10 = H.h[j * H.nx + ip]; h01 = H.h[jp * H.nx + i]; h11 = H.h[jp * H.nx + ip];
@@ -108,28 +109,26 @@ __device__ __forceinline__ void tri_closest_vw(f3 P, f3 A, f3 B, f3 C, float& v,
   float g11 = dot3(ab, ab), g12 = dot3(ab, ac), g22 = dot3(ac, ac);
   float d1 = dot3(ab, ap), d2 = dot3(ac, ap);
   float d3 = d1 - g11, d4 = d2 - g12, d5 = d1 - g12, d6 = d2 - g22;
-  if (d1 <= 0.0f && d2 <= 0.0f) {
-    v = 0.0f; w = 0.0f;
-  } else if (d3 >= 0.0f && d4 <= d3) {
-    v = 1.0f; w = 0.0f;
-  } else if (d6 >= 0.0f && d5 <= d6) {
-    v = 0.0f; w = 1.0f;
-  } else {
-    float vc = d1 * d4 - d3 * d2;
-    float vb = d5 * d2 - d1 * d6;
-    float va = d3 * d6 - d5 * d4;
-    float e43 = d4 - d3, e56 = d5 - d6;
-    if (vc <= 0.0f && d1 >= 0.0f && d3 <= 0.0f) {
-      v = d1 / g11; w = 0.0f;
-    } else if (vb <= 0.0f && d2 >= 0.0f && d6 <= 0.0f) {
-      v = 0.0f; w = d2 / g22;
-    } else if (va <= 0.0f && e43 >= 0.0f && e56 >= 0.0f) {
-      w = e43 / (e43 + e56); v = 1.0f - w;
-    } else {
-      float s = (va + vb) + vc;
-      v = vb / s; w = vc / s;
-    }
-  }
+  // The regions in their order (corners A, B, C, edges AB, AC, BC, the face); the operands are selected
+  // before the two divisions, since the lanes of a wavefront are in all of the regions and would run
+  // the five divisions of a branching form one after the other.
+  const bool at_a = d1 <= 0.0f && d2 <= 0.0f;
+  const bool at_b = d3 >= 0.0f && d4 <= d3;
+  const bool at_c = d6 >= 0.0f && d5 <= d6;
+  const float vc = d1 * d4 - d3 * d2;
+  const float vb = d5 * d2 - d1 * d6;
+  const float va = d3 * d6 - d5 * d4;
+  const float e43 = d4 - d3, e56 = d5 - d6;
+  const bool on_ab = vc <= 0.0f && d1 >= 0.0f && d3 <= 0.0f;
+  const bool on_ac = vb <= 0.0f && d2 >= 0.0f && d6 <= 0.0f;
+  const bool on_bc = va <= 0.0f && e43 >= 0.0f && e56 >= 0.0f;
+  const float s = (va + vb) + vc;
+  const float v_edge = (on_ab ? d1 : vb) / (on_ab ? g11 : s);
+  const float w_edge = (on_ac ? d2 : (on_bc ? e43 : vc)) / (on_ac ? g22 : (on_bc ? e43 + e56 : s));
+  v = on_ab ? v_edge : (on_ac ? 0.0f : (on_bc ? 1.0f - w_edge : v_edge));
+  w = on_ab ? 0.0f : w_edge;
+  v = at_a ? 0.0f : (at_b ? 1.0f : (at_c ? 0.0f : v));
+  w = at_a ? 0.0f : (at_b ? 0.0f : (at_c ? 1.0f : w));
 }
 __device__ __forceinline__ f3 tri_point(f3 A, f3 B, f3 C, float v, float w) {
   f3 ab = sub3(B, A), ac = sub3(C, A);
@@ -186,12 +185,10 @@ __device__ __forceinline__ void seg_edge_st(f3 P0, f3 P1, f3 Q0, f3 Q1, float& s
     float bs = b * s;
     t = (bs + f) / e;
   }
-  if (t < 0.0f) {
-    t = 0.0f;
-    s = clamp01((0.0f - c) / a);
-  } else if (t > 1.0f) {
-    t = 1.0f;
-    s = clamp01((b - c) / a);
+  if (t < 0.0f || t > 1.0f) {   // beyond an end of the edge: closest point of the segment to that end
+    const float num = t < 0.0f ? 0.0f - c : b - c;
+    t = t < 0.0f ? 0.0f : 1.0f;
+    s = clamp01(num / a);
   }
 }
 
@@ -240,30 +237,37 @@ __device__ __forceinline__ bool pair_in_contact(f3 p0, f3 p1, f3 q0, f3 q1, cons
   return true;
 }
 
-// End points of a body's segment: env-local (p0,p1) from the state, in the same
-// operation order the selection is specified in.
-__device__ __forceinline__ void body_ends(const float x[3], const float q[4], float half_len, int axis,
-                                          f3& p0, f3& p1) {
-  float qw = q[0], qx = q[1], qy = q[2], qz = q[3];
-  f3 c;
-  if (axis == 0) {
-    float yy = qy * qy, zz = qz * qz, xy = qx * qy, wz = qw * qz, xz = qx * qz, wy = qw * qy;
-    c = f3{1.0f - 2.0f * (yy + zz), 2.0f * (xy + wz), 2.0f * (xz - wy)};
-  } else if (axis == 1) {
-    float xx = qx * qx, zz = qz * qz, xy = qx * qy, wz = qw * qz, yz = qy * qz, wx = qw * qx;
-    c = f3{2.0f * (xy - wz), 1.0f - 2.0f * (xx + zz), 2.0f * (yz + wx)};
-  } else {
-    float xx = qx * qx, yy = qy * qy, xz = qx * qz, wy = qw * qy, yz = qy * qz, wx = qw * qx;
-    c = f3{2.0f * (xz + wy), 2.0f * (yz - wx), 1.0f - 2.0f * (xx + yy)};
-  }
-  f3 a = f3{half_len * c.x, half_len * c.y, half_len * c.z};
+// Half of a body's segment: the vector from the centre to its second end.  The end points are the
+// centre minus and plus this vector, in the operation order the selection is specified in.
+__device__ __forceinline__ f3 body_half(const float q[4], float half_len, int axis) {
+  // The three axes are cyclic relabellings of one formula, so the components are selected instead of
+  // branching (bodies of all three axes share a wavefront, which would run every branch).
+  // (the components as values first: choosing between elements of an array that lives in registers would
+  // send the array to scratch memory)
+  const float qw = q[0], qx = q[1], qy = q[2], qz = q[3];
+  const float a_ = axis == 0 ? qx : (axis == 1 ? qy : qz);
+  const float b_ = axis == 0 ? qy : (axis == 1 ? qz : qx);
+  const float c_ = axis == 0 ? qz : (axis == 1 ? qx : qy);
+  const float bb = b_ * b_, cc = c_ * c_, ab = a_ * b_, wc = qw * c_, ac = a_ * c_, wb = qw * b_;
+  const float along = 1.0f - 2.0f * (bb + cc), next = 2.0f * (ab + wc), last = 2.0f * (ac - wb);
+  const f3 c = f3{axis == 0 ? along : (axis == 1 ? last : next), axis == 0 ? next : (axis == 1 ? along : last),
+                  axis == 0 ? last : (axis == 1 ? next : along)};
+  return f3{half_len * c.x, half_len * c.y, half_len * c.z};
+}
+__device__ __forceinline__ void ends_of(const float x[3], f3 a, f3& p0, f3& p1) {
   p0 = f3{x[0] - a.x, x[1] - a.y, x[2] - a.z};
   p1 = f3{x[0] + a.x, x[1] + a.y, x[2] + a.z};
+}
+// End points of a body's segment: env-local (p0,p1) from the state.
+__device__ __forceinline__ void body_ends(const float x[3], const float q[4], float half_len, int axis,
+                                          f3& p0, f3& p1) {
+  ends_of(x, body_half(q, half_len, axis), p0, p1);
 }
 
 // Everything a slot needs to be tested against the terrain.
 struct SlotGeom {
   f3 xc;          // body centre, env-local
+  f3 a;           // from the centre to the segment's second end
   f3 p0, p1;      // segment end points, env-local
   f3 P0, P1;      // the same in world coordinates (env origin added)
   f3 org;
@@ -272,14 +276,14 @@ struct SlotGeom {
   int i0, i1, j0, j1;  // cells the reach box overlaps
 };
 
-__device__ __forceinline__ SlotGeom slot_geom(float radius, float half_len, int axis, float margin,
-                                              const float x[3], const float q[4], int slot_kind,
-                                              const float origin[3]) {
+__device__ __forceinline__ SlotGeom slot_geom_from_half(float radius, float margin, const float x[3], f3 a, int slot_kind,
+                                                        const float origin[3]) {
   SlotGeom g;
   g.kind = slot_kind;
   g.r = radius;
   g.Rq = (g.r + margin) + kSelSlack;
-  body_ends(x, q, half_len, axis, g.p0, g.p1);
+  g.a = a;
+  ends_of(x, a, g.p0, g.p1);
   g.xc = f3{x[0], x[1], x[2]};
   g.org = f3{origin[0], origin[1], origin[2]};
   g.P0 = f3{g.p0.x + g.org.x, g.p0.y + g.org.y, g.p0.z + g.org.z};
@@ -287,6 +291,16 @@ __device__ __forceinline__ SlotGeom slot_geom(float radius, float half_len, int 
   g.i0 = 0; g.i1 = -1; g.j0 = 0; g.j1 = -1;
   return g;
 }
+__device__ __forceinline__ SlotGeom slot_geom(float radius, float half_len, int axis, float margin,
+                                              const float x[3], const float q[4], int slot_kind,
+                                              const float origin[3]) {
+  return slot_geom_from_half(radius, margin, x, body_half(q, half_len, axis), slot_kind, origin);
+}
+// End sphere's centre, and a point of the terrain, seen from the body's centre: the differences of
+// neighbouring coordinates are exact, so what follows rounds at the size of the body and not at that
+// of its distance from the origin.
+__device__ __forceinline__ f3 end_from_centre(const SlotGeom& g) { return g.kind == 0 ? f3{-g.a.x, -g.a.y, -g.a.z} : g.a; }
+__device__ __forceinline__ f3 from_centre(const SlotGeom& g, f3 world) { return sub3(sub3(world, g.org), g.xc); }
 
 __device__ __forceinline__ ContactOut plane_contact(const SlotGeom& g, float margin) {
   ContactOut out = no_contact();
@@ -296,7 +310,8 @@ __device__ __forceinline__ ContactOut plane_contact(const SlotGeom& g, float mar
   if (!(d < margin)) return out;
   out.active = 1; out.kind = 0; out.feat = -1; out.d = d;
   out.n = f3{0.0f, 0.0f, 1.0f};
-  out.rc = f3{p.x - g.xc.x, p.y - g.xc.y, (p.z - g.r) - g.xc.z};
+  const f3 pl = end_from_centre(g);
+  out.rc = f3{pl.x, pl.y, pl.z - g.r};
   out.w = block_weight(margin, d, 1.0f);
   return out;
 }
@@ -336,7 +351,7 @@ __device__ __forceinline__ bool slot_reach(const Field& H, SlotGeom& g, bool exa
   if (H.ps > 0 && g.i0 >= H.pi0 && g.i1 + 1 < H.pi0 + H.ps && g.j0 >= H.pj0 && g.j1 + 1 < H.pj0 + H.ps) {
     // the whole reach box lies inside the LDS copy: maximum over the blocks it touches
     // (up to 3 x 3 of them read without a loop; larger boxes take the loop)
-    const int nb = (H.ps + kMip - 1) / kMip;
+    const int nb = (kPatch + kMip - 1) / kMip;
     const int I0 = (g.i0 - H.pi0) / kMip, I1 = (g.i1 + 1 - H.pi0) / kMip;
     const int J0 = (g.j0 - H.pj0) / kMip, J1 = (g.j1 + 1 - H.pj0) / kMip;
     if (I1 - I0 <= 2 && J1 - J0 <= 2) {
@@ -362,7 +377,7 @@ __device__ __forceinline__ bool slot_reach(const Field& H, SlotGeom& g, bool exa
         float hv[36];
         int col[6], row[6];
 #pragma unroll
-        for (int d = 0; d < 6; ++d) { col[d] = bi + (d < ni ? d : ni - 1); row[d] = (bj + (d < nj ? d : nj - 1)) * H.ps; }
+        for (int d = 0; d < 6; ++d) { col[d] = bi + (d < ni ? d : ni - 1); row[d] = (bj + (d < nj ? d : nj - 1)) * kPatch; }
 #pragma unroll
         for (int dj = 0; dj < 6; ++dj)
 #pragma unroll
@@ -387,7 +402,7 @@ __device__ __forceinline__ bool underneath_contact(const Field& H, const SlotGeo
                                                    ContactOut& out) {
   const int ncx = H.nx - 1, ncy = H.ny - 1;
   f3 P = g.kind == 0 ? g.P0 : g.P1;
-  f3 pl = g.kind == 0 ? g.p0 : g.p1;
+  const f3 pl = end_from_centre(g);
   float ux = (P.x - H.ox) * H.inv_cell, uy = (P.y - H.oy) * H.inv_cell;
   float fi = floorf(ux), fj = floorf(uy);
   if (!(fi >= 0.0f && fi <= (float)(ncx - 1) && fj >= 0.0f && fj <= (float)(ncy - 1))) return false;
@@ -406,9 +421,9 @@ __device__ __forceinline__ bool underneath_contact(const Field& H, const SlotGeo
   float inv = 1.0f / sqrtf(dot3(nt, nt));
   f3 n = f3{nt.x * inv, nt.y * inv, nt.z * inv};
   out.active = 1; out.kind = 2; out.feat = 2 * (j * ncx + i) + t;
-  out.d = dot3(sub3(pl, sub3(A, g.org)), n) - g.r;  // gap measured in env-local coordinates
+  out.d = dot3(sub3(pl, from_centre(g, A)), n) - g.r;  // gap measured from the body's centre
   out.n = n;
-  out.rc = f3{(pl.x - g.r * n.x) - g.xc.x, (pl.y - g.r * n.y) - g.xc.y, (pl.z - g.r * n.z) - g.xc.z};
+  out.rc = f3{pl.x - g.r * n.x, pl.y - g.r * n.y, pl.z - g.r * n.z};
   out.w = block_weight(margin, out.d, 1.0f);
   return true;
 }
@@ -522,8 +537,8 @@ __device__ __forceinline__ int segment_candidates(const Field& H, const SegCull&
   {
     unsigned di = (unsigned)(i - H.pi0), dj = (unsigned)(j - H.pj0);
     if (di + 1u < (unsigned)H.ps && dj + 1u < (unsigned)H.ps) {
-      const lds_float* p = H.patch + dj * H.ps + di;
-      h00 = p[0]; h10 = p[1]; h01 = p[H.ps]; h11 = p[H.ps + 1];
+      const lds_float* p = H.patch + dj * kPatch + di;
+      h00 = p[0]; h10 = p[1]; h01 = p[kPatch]; h11 = p[kPatch + 1];
     } else {
       h00 = H.h[j * H.nx + i]; h10 = H.h[j * H.nx + ip]; h01 = H.h[jp * H.nx + i]; h11 = H.h[jp * H.nx + ip];
     }
@@ -574,9 +589,8 @@ __device__ __forceinline__ void segment_vertex(const Field& H, const SlotGeom& g
   }
 }
 
-// Record of the selected triangle (end sphere).  The geometry is rebuilt in
-// env-local coordinates (vertex minus env origin), where the sphere centre
-// carries no rounding from the world offset.
+// Record of the selected triangle (end sphere).  The geometry is rebuilt as seen from the body's
+// centre.
 __device__ __forceinline__ ContactOut finish_sphere(const Field& H, const SlotGeom& g, float margin, float best,
                                                     int best_id) {
   ContactOut out = no_contact();
@@ -585,15 +599,15 @@ __device__ __forceinline__ ContactOut finish_sphere(const Field& H, const SlotGe
   float d = dist - g.r;
   if (!(d < margin)) return out;
   const int ncx = H.nx - 1;
-  f3 pl = g.kind == 0 ? g.p0 : g.p1;
+  const f3 pl = end_from_centre(g);
   int t = best_id & 1, c = best_id >> 1, i = c % ncx, j = c / ncx;
   float h00, h10, h11, h01;
   field_cell_heights(H, i, j, h00, h10, h11, h01);
   const float x0 = field_x(H, i), x1 = field_x(H, i + 1), y0 = field_y(H, j), y1 = field_y(H, j + 1);
   const f3 C1 = f3{x1, y1, h11};
-  f3 A = sub3(f3{x0, y0, h00}, g.org);
-  f3 Bv = sub3(t == 0 ? f3{x1, y0, h10} : C1, g.org);
-  f3 Cv = sub3(t == 0 ? C1 : f3{x0, y1, h01}, g.org);
+  f3 A = from_centre(g, f3{x0, y0, h00});
+  f3 Bv = from_centre(g, t == 0 ? f3{x1, y0, h10} : C1);
+  f3 Cv = from_centre(g, t == 0 ? C1 : f3{x0, y1, h01});
   float v, w;
   tri_closest_vw(pl, A, Bv, Cv, v, w);
   f3 df = sub3(pl, tri_point(A, Bv, Cv, v, w));
@@ -609,12 +623,12 @@ __device__ __forceinline__ ContactOut finish_sphere(const Field& H, const SlotGe
     n = f3{df.x * inv, df.y * inv, df.z * inv};
   }
   out.active = 1; out.kind = 1; out.feat = best_id; out.d = d; out.n = n;
-  out.rc = f3{(pl.x - g.r * n.x) - g.xc.x, (pl.y - g.r * n.y) - g.xc.y, (pl.z - g.r * n.z) - g.xc.z};
+  out.rc = f3{pl.x - g.r * n.x, pl.y - g.r * n.y, pl.z - g.r * n.z};
   out.w = block_weight(margin, d, 1.0f);
   return out;
 }
 
-// Record of the selected edge (mid-segment slot), geometry in env-local coordinates.
+// Record of the selected edge (mid-segment slot), geometry as seen from the body's centre.
 __device__ __forceinline__ ContactOut finish_segment(const Field& H, const SlotGeom& g, float margin, float best,
                                                      int best_id) {
   ContactOut out = no_contact();
@@ -625,13 +639,13 @@ __device__ __forceinline__ ContactOut finish_segment(const Field& H, const SlotG
   int k = best_id % 3, vtx = best_id / 3, i = vtx % H.nx, j = vtx / H.nx;
   float h00, h10, h11, h01;
   field_cell_heights_clamped(H, i, j, h00, h10, h11, h01);
-  f3 Q0 = sub3(f3{field_x(H, i), field_y(H, j), h00}, g.org);
-  f3 Q1 = sub3(f3{field_x(H, i + (k == 1 ? 0 : 1)), field_y(H, j + (k == 0 ? 0 : 1)), k == 0 ? h10 : (k == 1 ? h01 : h11)},
-               g.org);
+  f3 Q0 = from_centre(g, f3{field_x(H, i), field_y(H, j), h00});
+  f3 Q1 = from_centre(g, f3{field_x(H, i + (k == 1 ? 0 : 1)), field_y(H, j + (k == 0 ? 0 : 1)), k == 0 ? h10 : (k == 1 ? h01 : h11)});
   float s, t;
-  seg_edge_st(g.p0, g.p1, Q0, Q1, s, t);
-  f3 d1 = sub3(g.p1, g.p0), d2 = sub3(Q1, Q0);
-  f3 cl = f3{g.p0.x + d1.x * s, g.p0.y + d1.y * s, g.p0.z + d1.z * s};
+  const f3 p0 = f3{-g.a.x, -g.a.y, -g.a.z};
+  seg_edge_st(p0, g.a, Q0, Q1, s, t);
+  f3 d1 = sub3(g.a, p0), d2 = sub3(Q1, Q0);
+  f3 cl = f3{p0.x + d1.x * s, p0.y + d1.y * s, p0.z + d1.z * s};
   f3 c2 = f3{Q0.x + d2.x * t, Q0.y + d2.y * t, Q0.z + d2.z * t};
   f3 df = sub3(cl, c2);
   dist = sqrtf(dot3(df, df));
@@ -640,7 +654,7 @@ __device__ __forceinline__ ContactOut finish_segment(const Field& H, const SlotG
   if (dist < 1e-9f) n = f3{0.0f, 0.0f, 1.0f};
   else { float inv = 1.0f / dist; n = f3{df.x * inv, df.y * inv, df.z * inv}; }
   out.active = 1; out.kind = 3; out.feat = best_id; out.d = d; out.n = n;
-  out.rc = f3{(cl.x - g.r * n.x) - g.xc.x, (cl.y - g.r * n.y) - g.xc.y, (cl.z - g.r * n.z) - g.xc.z};
+  out.rc = f3{cl.x - g.r * n.x, cl.y - g.r * n.y, cl.z - g.r * n.z};
   float se = s < 1.0f - s ? s : 1.0f - s;
   out.w = block_weight(margin, d, fminf(fmaxf((se - 0.001f) / 0.1f, 0.0f), 1.0f));
   return out;
@@ -677,5 +691,119 @@ __device__ inline ContactOut generate_contact(const Model& M, const float* __res
 }
 
 #pragma clang fp contract(fast)
+
+// The terrain search of one slot by rows of cells.  All of this is conservative (lower bounds of the
+// distance with a slack of 1 to 2 mm, since sample coordinates and the tests themselves are rounded) and
+// needs no fixed operation order.
+
+// Cells to search for a slot whose reach box overlaps the field (slot_reach), and the squared reach.
+// The surface straight below an end sphere's centre is at most `up` away, so nothing further than
+// that can be its nearest triangle, and a centre below the surface is decided by underneath_contact
+// alone: false, nothing to search.  Edges start at the samples of the box; the field's last row and
+// column of samples have no cell of their own and are added to a box that ends at them.
+__device__ __forceinline__ bool slot_search_box(const Field& H, SlotGeom& g, float& r2) {
+  if (g.kind == 2) {
+    const float reach = g.Rq + 2.0f * kSelSlack;
+    r2 = reach * reach;
+    if (g.i1 == H.nx - 2) ++g.i1;
+    if (g.j1 == H.ny - 2) ++g.j1;
+    return true;
+  }
+  const f3 P = g.kind == 0 ? g.P0 : g.P1;
+  const float ux = (P.x - H.ox) * H.inv_cell, uy = (P.y - H.oy) * H.inv_cell;
+  const float fi = floorf(ux), fj = floorf(uy);
+  float reach = g.Rq + kSelSlack;
+  r2 = reach * reach;
+  if (fi >= 0.0f && fi <= (float)(H.nx - 2) && fj >= 0.0f && fj <= (float)(H.ny - 2)) {
+    float h00, h10, h11, h01;
+    field_cell_heights(H, (int)fi, (int)fj, h00, h10, h11, h01);
+    const float fx = ux - fi, fy = uy - fj;
+    const float hz = fx >= fy ? h00 + fx * (h10 - h00) + fy * (h11 - h10) : h00 + fx * (h11 - h01) + fy * (h01 - h00);
+    const float up = P.z - hz, near = up + 2.0f * kSelSlack;
+    if (near < 0.0f) return false;
+    if (near < reach) {
+      r2 = near * near;
+      return cell_span(H, P.x - near, P.x + near, H.ox, H.nx - 1, g.i0, g.i1) &&
+             cell_span(H, P.y - near, P.y + near, H.oy, H.ny - 1, g.j0, g.j1);
+    }
+  }
+  return true;
+}
+
+// Highest corner of the cells (i .. i + NC - 1, j), of which n are wanted; a corner beyond the last row
+// or column is replaced by some other number, which can only raise a maximum.
+constexpr int kSegCells = 7, kEndCells = 4;
+template <int NC>
+__device__ __forceinline__ void row_heights(const Field& H, int i, int j, int n, float zq[NC]) {
+  float m[NC + 1];
+  const unsigned di = (unsigned)(i - H.pi0), dj = (unsigned)(j - H.pj0);
+  if (di < (unsigned)H.ps && di + (unsigned)(n < NC ? n : NC) < (unsigned)H.ps && dj + 1u < (unsigned)H.ps) {
+    // (all columns are read; those beyond n are not used and lie inside the workgroup's LDS: the
+    //  block maxima follow the copies)
+    const lds_float* p = H.patch + dj * kPatch + di;
+    float lo[NC + 1], hi[NC + 1];
+#pragma unroll
+    for (int c = 0; c <= NC; ++c) { lo[c] = p[c]; hi[c] = p[kPatch + c]; }
+#pragma unroll
+    for (int c = 0; c <= NC; ++c) m[c] = fmaxf(lo[c], hi[c]);
+  } else {
+    const int j1 = j + 1 < H.ny ? j + 1 : j;
+#pragma unroll
+    for (int c = 0; c <= NC; ++c) {
+      const int ic = i + c < H.nx ? i + c : H.nx - 1;
+      m[c] = fmaxf(H.h[j * H.nx + ic], H.h[j1 * H.nx + ic]);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c) zq[c] = fmaxf(m[c], m[c + 1]);
+}
+
+// Bit c: cell (i + c, j) may hold a triangle within reach of P (horizontal gap to the cell's square and
+// height above its highest corner).
+__device__ __forceinline__ unsigned cells_near_sphere(const Field& H, f3 P, float r2, int i, int j, int n) {
+  float zq[kEndCells];
+  row_heights<kEndCells>(H, i, j, n, zq);
+  const float hc = 0.5f * H.cell;
+  const float xc = (H.ox + ((float)i + 0.5f) * H.cell) - P.x, yc = (H.oy + ((float)j + 0.5f) * H.cell) - P.y;
+  const float gy = fmaxf(fabsf(yc) - hc, 0.0f), gy2 = gy * gy;
+  unsigned mask = 0;
+#pragma unroll
+  for (int c = kEndCells - 1; c >= 0; --c) {
+    const float gx = fmaxf(fabsf(xc + (float)c * H.cell) - hc, 0.0f), gz = fmaxf(P.z - zq[c], 0.0f);
+    mask = 2 * mask + (gx * gx + (gz * gz + gy2) <= r2 ? 1u : 0u);
+  }
+  return n < kEndCells ? mask & ((1u << n) - 1u) : mask;
+}
+
+// Bit c: an edge starting at sample (i + c, j) may be within reach of the segment's interior.  The up to
+// three edges that start there lie in the square of the cell: gap across and along the segment between
+// it and that square (in the xy plane), and height of the part of the segment that can be within
+// reach above the square's highest corner.
+__device__ __forceinline__ unsigned cells_near_segment(const Field& H, const SlotGeom& g, float r2, int i, int j, int n) {
+  float zq[kSegCells];
+  row_heights<kSegCells>(H, i, j, n, zq);
+  const float dx = g.P1.x - g.P0.x, dy = g.P1.y - g.P0.y, dz = g.P1.z - g.P0.z, L2 = dx * dx + dy * dy;
+  // direction and length in the plane; a (nearly) vertical segment is a point there
+  const bool flat = L2 > 1e-8f;
+  const float inv = flat ? __builtin_amdgcn_rsqf(L2) : 0.0f;
+  const float ux = flat ? dx * inv : 1.0f, uy = dy * inv, L = flat ? L2 * inv : 1e-4f;
+  const float half = 0.5f * H.cell * (fabsf(ux) + fabsf(uy)), mid = 0.5f * L, ha = half + mid;
+  // lowest point of the part of the segment within reach of the cell: s = clamp(along * inv + s0)
+  const float side = flat ? (half + (g.Rq + 2.0f * kSelSlack)) * inv + 1e-4f : 0.0f;
+  const float s0 = mid * inv + (dz >= 0.0f ? -side : (flat ? side : 1.0f));
+  const float xc = (H.ox + ((float)i + 0.5f) * H.cell) - g.P0.x, yc = (H.oy + ((float)j + 0.5f) * H.cell) - g.P0.y;
+  const float cross0 = ux * yc - uy * xc, along0 = (ux * xc + uy * yc) - mid;
+  const float dc = uy * H.cell, da = ux * H.cell;
+  unsigned mask = 0;
+#pragma unroll
+  for (int c = kSegCells - 1; c >= 0; --c) {
+    const float along = along0 + (float)c * da;
+    const float gc = fmaxf(fabsf(cross0 - (float)c * dc) - half, 0.0f), ga = fmaxf(fabsf(along) - ha, 0.0f);
+    const float s = __builtin_amdgcn_fmed3f(along * inv + s0, 0.0f, 1.0f);
+    const float gz = fmaxf((g.P0.z + dz * s) - zq[c], 0.0f);
+    mask = 2 * mask + (gc * gc + (ga * ga + gz * gz) <= r2 ? 1u : 0u);
+  }
+  return n < kSegCells ? mask & ((1u << n) - 1u) : mask;
+}
 
 }  // namespace sim355

@@ -46,7 +46,6 @@ namespace sim355 {
 constexpr int kThreads = 512;       // threads per workgroup every shape fits (host-side limits)
 constexpr int kThreadsWide = 768;   // the wider workgroup the big heightfield batches are run with
 constexpr int kGroup = 8;  // lanes that share the fine terrain search of one slot
-constexpr int kPatch = 28; // samples per side of the per-env heightfield copy kept in LDS
 constexpr int kPatchBlocks = (kPatch + kMip - 1) / kMip;
 
 struct StepArgs {
@@ -85,9 +84,10 @@ constexpr int kVS = 7, kCS = 7, kJS = 13;
 constexpr int kPairHitMin = 256;   // (gap, key) words a workgroup keeps at least
 
 struct LdsPlan {
-  int pos, vel, iw, nb, tq, push, outj, outc, tjs, rec, list, surv, lam, u, obs, lim, count, patch, mip, porg, org, tslot, tbody, tin, tjoint, total;
+  int pos, vel, iw, nb, tq, push, outj, outc, zero, tjs, rec, list, surv, lam, u, obs, lim, count, patch, mip, porg, org, tslot, tbody, tin, tjoint, total;
   int pq, po, pnear, pbs, pcount, pbcnt, pblist;  // capsule-capsule contacts (only with pairs != 0)
   int phit, hit_cap;                              // their (gap, key) words: offset (64-bit aligned) and capacity
+  int half, cand, cand_cap;                       // terrain search: half segments of the bodies, lists (in the copies' space)
   int wj, wc;                                     // kept impulses of joints and slots (only with warm != 0)
   int nu, nred, nsum;                             // Newton solver: body vectors, reduction entries, partial sums
 };
@@ -104,11 +104,19 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.tq = o; o += J * 3 * E;
   p.push = o; o += 3 * E;
   o += o & 1;  // the search results kept in the copy arrays are 64-bit words
-  p.outj = o; o += J * kJS * E;
-  p.outc = o; o += S * kCS * E;
+  // The sweep copies.  The terrain search, which is over before the first sweep, keeps its results there:
+  // a 64-bit minimum per slot, half the segment of every body and the lists of rows and cells.
+  const int copies = (J * kJS + S * kCS) * E, search = (2 * S + 3 * B) * E;
+  p.outj = o;
+  p.outc = o + J * kJS * E;
+  p.half = o + 2 * S * E;
+  p.cand = o + search;
+  p.cand_cap = copies - search > 32 * E ? copies - search : 32 * E;
+  o += copies > search + p.cand_cap ? copies : search + p.cand_cap;
+  p.zero = o; o += 6 * E;  // zeros in the place of a copy: what a body without that joint or contact adds up
   p.rec = o; o += S * kRecWords * E;
   p.list = o; o += S * E;
-  p.surv = o; o += S * E;
+  p.surv = o; o += S * E;   // slots near the heightfield: end spheres from the front, mid-segments from the back
   p.lam = o;   // (with the warm start these impulses live in the per-slot array below)
   o += warm ? 0 : 3 * (S * E > threads - ((2 * J * E + 63) / 64) * 64 ? S * E - (threads - ((2 * J * E + 63) / 64) * 64) : 0);
   p.u = o; o += (D > 0 ? D : 1) * E;
@@ -134,8 +142,8 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   // one 64-bit (gap, key) word per capsule-capsule contact found, for the choice of those that stay
   // when a workgroup finds more than it holds: in the space of the terrain search's candidate list
   // (idle by then) where that holds kPairHitMin words, else in a region of their own
-  p.hit_cap = ((J * kJS + S * kCS) * E - 5 * S * E - 2) / 2;
-  p.phit = p.outj + ((5 * S * E + 1) & ~1);
+  p.hit_cap = (p.cand_cap - 2) / 2;
+  p.phit = (p.cand + 1) & ~1;
   if (pairs && p.hit_cap < kPairHitMin) {
     o += o & 1;
     p.phit = o; o += 2 * kPairHitMin;
@@ -150,40 +158,52 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   return p;
 }
 
+// The arithmetic of a step is written out down to the single rounded operation: contraction is off in
+// this file and every fused multiply-add is spelled, so that the forms of the kernel give the same bits
+// whatever the compiler inlines, hoists or splits into blocks around them.  A sum of products is
+// a0 b0 + a1 b1 + a2 b2 = fma(a2, b2, fma(a0, b0, a1 b1)).
+#pragma clang fp contract(off)
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ float sum2(float a0, float b0, float a1, float b1) { return fma_(a0, b0, a1 * b1); }
+__device__ __forceinline__ float diff2(float a0, float b0, float a1, float b1) { return fma_(a0, b0, -(a1 * b1)); }
+__device__ __forceinline__ float sum3(float a0, float b0, float a1, float b1, float a2, float b2) {
+  return fma_(a2, b2, sum2(a0, b0, a1, b1));
+}
+
 __device__ __forceinline__ void quat_to_mat(const float q[4], float R[9]) {
   // R[3*r + c]: row r, column c; column c is the image of body axis c
   float w = q[0], x = q[1], y = q[2], z = q[3];
-  R[0] = 1.0f - 2.0f * (y * y + z * z); R[1] = 2.0f * (x * y - w * z); R[2] = 2.0f * (x * z + w * y);
-  R[3] = 2.0f * (x * y + w * z); R[4] = 1.0f - 2.0f * (x * x + z * z); R[5] = 2.0f * (y * z - w * x);
-  R[6] = 2.0f * (x * z - w * y); R[7] = 2.0f * (y * z + w * x); R[8] = 1.0f - 2.0f * (x * x + y * y);
+  R[0] = fma_(-2.0f, sum2(y, y, z, z), 1.0f); R[1] = 2.0f * diff2(x, y, w, z); R[2] = 2.0f * sum2(x, z, w, y);
+  R[3] = 2.0f * sum2(x, y, w, z); R[4] = fma_(-2.0f, sum2(x, x, z, z), 1.0f); R[5] = 2.0f * diff2(y, z, w, x);
+  R[6] = 2.0f * diff2(x, z, w, y); R[7] = 2.0f * sum2(y, z, w, x); R[8] = fma_(-2.0f, sum2(x, x, y, y), 1.0f);
 }
 __device__ __forceinline__ void mat_vec(const float R[9], const float a[3], float o[3]) {
-  o[0] = R[0] * a[0] + R[1] * a[1] + R[2] * a[2];
-  o[1] = R[3] * a[0] + R[4] * a[1] + R[5] * a[2];
-  o[2] = R[6] * a[0] + R[7] * a[1] + R[8] * a[2];
+  o[0] = sum3(R[0], a[0], R[1], a[1], R[2], a[2]);
+  o[1] = sum3(R[3], a[0], R[4], a[1], R[5], a[2]);
+  o[2] = sum3(R[6], a[0], R[7], a[1], R[8], a[2]);
 }
 __device__ __forceinline__ void mat_t_vec(const float R[9], const float a[3], float o[3]) {
-  o[0] = R[0] * a[0] + R[3] * a[1] + R[6] * a[2];
-  o[1] = R[1] * a[0] + R[4] * a[1] + R[7] * a[2];
-  o[2] = R[2] * a[0] + R[5] * a[1] + R[8] * a[2];
+  o[0] = sum3(R[0], a[0], R[3], a[1], R[6], a[2]);
+  o[1] = sum3(R[1], a[0], R[4], a[1], R[7], a[2]);
+  o[2] = sum3(R[2], a[0], R[5], a[1], R[8], a[2]);
 }
 // symmetric 3x3 (xx,xy,xz,yy,yz,zz) times vector
 __device__ __forceinline__ void sym_vec(const float S[6], const float a[3], float o[3]) {
-  o[0] = S[0] * a[0] + S[1] * a[1] + S[2] * a[2];
-  o[1] = S[1] * a[0] + S[3] * a[1] + S[4] * a[2];
-  o[2] = S[2] * a[0] + S[4] * a[1] + S[5] * a[2];
+  o[0] = sum3(S[0], a[0], S[1], a[1], S[2], a[2]);
+  o[1] = sum3(S[1], a[0], S[3], a[1], S[4], a[2]);
+  o[2] = sum3(S[2], a[0], S[4], a[1], S[5], a[2]);
 }
 __device__ __forceinline__ void cross(const float a[3], const float b[3], float o[3]) {
-  o[0] = a[1] * b[2] - a[2] * b[1];
-  o[1] = a[2] * b[0] - a[0] * b[2];
-  o[2] = a[0] * b[1] - a[1] * b[0];
+  o[0] = diff2(a[1], b[2], a[2], b[1]);
+  o[1] = diff2(a[2], b[0], a[0], b[2]);
+  o[2] = diff2(a[0], b[1], a[1], b[0]);
 }
 __device__ __forceinline__ float dot(const float a[3], const float b[3]) {
-  return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
+  return sum3(a[0], b[0], a[1], b[1], a[2], b[2]);
 }
 // (r x e_k) . w for the unit vector e_k, zero terms left out
 __device__ __forceinline__ float cross_unit_dot(const float r[3], int k, const float w[3]) {
-  return k == 0 ? r[2] * w[1] - r[1] * w[2] : (k == 1 ? r[0] * w[2] - r[2] * w[0] : r[1] * w[0] - r[0] * w[1]);
+  return k == 0 ? diff2(r[2], w[1], r[1], w[2]) : (k == 1 ? diff2(r[0], w[2], r[2], w[0]) : diff2(r[1], w[0], r[0], w[1]));
 }
 // r x e_k
 __device__ __forceinline__ void cross_unit(const float r[3], int k, float o[3]) {
@@ -205,17 +225,17 @@ __device__ __forceinline__ float atan2_first_quadrant(float y, float x) {
   const float t = num * __builtin_amdgcn_rcpf(den);
   const float base = big ? 1.5707963267948966f : (mid ? 0.7853981633974483f : 0.0f);
   const float z = t * t;
-  const float p = (((8.05374449538e-2f * z - 1.38776856032e-1f) * z + 1.99777106478e-1f) * z - 3.33329491539e-1f) * z * t + t;
+  const float p = fma_(fma_(fma_(fma_(8.05374449538e-2f, z, -1.38776856032e-1f), z, 1.99777106478e-1f), z, -3.33329491539e-1f) * z, t, t);
   return base + p;
 }
 
 __device__ __forceinline__ void rel_rotvec(const float qa[4], const float qb[4], float phi[3]) {
-  float w = qa[0] * qb[0] + qa[1] * qb[1] + qa[2] * qb[2] + qa[3] * qb[3];
-  float x = qa[0] * qb[1] - qa[1] * qb[0] - qa[2] * qb[3] + qa[3] * qb[2];
-  float y = qa[0] * qb[2] + qa[1] * qb[3] - qa[2] * qb[0] - qa[3] * qb[1];
-  float z = qa[0] * qb[3] - qa[1] * qb[2] + qa[2] * qb[1] - qa[3] * qb[0];
+  float w = fma_(qa[3], qb[3], sum3(qa[0], qb[0], qa[1], qb[1], qa[2], qb[2]));
+  float x = fma_(qa[3], qb[2], fma_(-qa[2], qb[3], diff2(qa[0], qb[1], qa[1], qb[0])));
+  float y = fma_(-qa[3], qb[1], fma_(-qa[2], qb[0], sum2(qa[0], qb[2], qa[1], qb[3])));
+  float z = fma_(-qa[3], qb[0], fma_(qa[2], qb[1], diff2(qa[0], qb[3], qa[1], qb[2])));
   if (w < 0.0f) { w = -w; x = -x; y = -y; z = -z; }
-  const float s2 = x * x + y * y + z * z;
+  const float s2 = sum3(x, x, y, y, z, z);
   const float inv_s = __builtin_amdgcn_rsqf(fmaxf(s2, 1e-30f)), s = s2 * inv_s;
   float k = (s < 1e-12f) ? 2.0f : 2.0f * atan2_first_quadrant(s, w) * inv_s;
   phi[0] = k * x; phi[1] = k * y; phi[2] = k * z;
@@ -238,8 +258,8 @@ __device__ __forceinline__ HeightCell height_cell(int nx, int ny, float cell, fl
   return c;
 }
 __device__ __forceinline__ float height_in_cell(float fx, float fy, float h00, float h10, float h11, float h01) {
-  if (fx >= fy) return h00 + fx * (h10 - h00) + fy * (h11 - h10);
-  return h00 + fx * (h11 - h01) + fy * (h01 - h00);
+  if (fx >= fy) return fma_(fy, h11 - h10, fma_(fx, h10 - h00, h00));
+  return fma_(fy, h01 - h00, fma_(fx, h11 - h01, h00));
 }
 
 __device__ __forceinline__ void store_record(float* Lrec, int* Lreci, int s, int ee, int E, const ContactOut& co) {
@@ -282,6 +302,14 @@ __device__ __forceinline__ float lane_swap1(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, true));
 }
 
+// maximum without the instruction that quietens a signalling NaN first, which the compiler puts before
+// every fmaxf whose operand comes from an earlier round of a loop
+__device__ __forceinline__ float max_of(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
 struct ContactRows {
   float dir[3][3];   // n, t1, t2
   float ang[3][3];   // rc x dir
@@ -305,7 +333,7 @@ struct ContactRows {
 // Row constants of one active contact slot from its LDS record (d, n, rc, weight), the
 // body's world inverse inertia, weight sum and inverse mass.
 __device__ __forceinline__ void build_contact_rows(ContactRows& c, const float* Lrec, const float* Liw,
-                                                   const float* Lnb, int s, int ee, int E, int body, float imb,
+                                                   float nb, int s, int ee, int E, int body, float imb,
                                                    float h, float beta_c, float v_depen, bool whole_body = false) {
   c.body = body;
   c.slot_e = s * E + ee;
@@ -313,7 +341,7 @@ __device__ __forceinline__ void build_contact_rows(ContactRows& c, const float* 
   float n[3], rc[3], iwb[6];
   for (int k = 0; k < 3; ++k) { n[k] = Lrec[(s * kRecWords + 4 + k) * E + ee]; rc[k] = Lrec[(s * kRecWords + 7 + k) * E + ee]; }
   for (int k = 0; k < 6; ++k) iwb[k] = Liw[(body * kVS + k) * E + ee];
-  float nbb = Lnb[body * E + ee] / Lrec[(s * kRecWords + 10) * E + ee];
+  float nbb = nb / Lrec[(s * kRecWords + 10) * E + ee];
   if (whole_body) nbb = 1.0f;   // (the Newton solver does not split the body among its blocks)
   float t1[3], t2[3];
   if (fabsf(n[0]) < 0.57735f) { t1[0] = 0.0f; t1[1] = n[2]; t1[2] = -n[1]; }
@@ -341,7 +369,7 @@ __device__ __forceinline__ void build_contact_rows(ContactRows& c, const float* 
 // scale lim / |l| comes from the hardware's reciprocal square root (1 ulp) instead of a correctly
 // rounded square root and division; the floor keeps a denormal |l|^2 from turning into infinity.
 __device__ __forceinline__ void project_on_disc(float& l1, float& l2, float lim) {
-  const float n2 = l1 * l1 + l2 * l2;
+  const float n2 = sum2(l1, l1, l2, l2);
   if (n2 > lim * lim) {
     const float sc = lim * __builtin_amdgcn_rsqf(fmaxf(n2, 1e-30f));
     l1 *= sc; l2 *= sc;
@@ -353,29 +381,28 @@ __device__ __forceinline__ void project_on_disc(float& l1, float& l2, float lim)
 __device__ __forceinline__ void relax_contact(ContactRows& c, float mu, float vv[3], float ww[3]) {
   {
     float jv = dot(c.dir[0], vv) + dot(c.ang[0], ww);
-    float dl = -c.meff[0] * (jv + c.bias);
-    float ln = fmaxf(c.lam[0] + dl, 0.0f);
-    dl = ln - c.lam[0];
+    const float ln = fmaxf(fma_(-c.meff[0], jv + c.bias, c.lam[0]), 0.0f);
+    const float dl = ln - c.lam[0];
     c.lam[0] = ln;
-    for (int k = 0; k < 3; ++k) { vv[k] += c.ls * c.dir[0][k] * dl; ww[k] += c.Y[0][k] * dl; }
+    for (int k = 0; k < 3; ++k) { vv[k] = fma_(c.ls * c.dir[0][k], dl, vv[k]); ww[k] = fma_(c.Y[0][k], dl, ww[k]); }
   }
   float jv1 = dot(c.dir[1], vv) + dot(c.ang[1], ww);
   float jv2 = dot(c.dir[2], vv) + dot(c.ang[2], ww);
-  float l1 = c.lam[1] - c.meff[1] * jv1, l2 = c.lam[2] - c.meff[2] * jv2;
+  float l1 = fma_(-c.meff[1], jv1, c.lam[1]), l2 = fma_(-c.meff[2], jv2, c.lam[2]);
   const float lim = mu * c.lam[0];
   project_on_disc(l1, l2, lim);
   float d1 = l1 - c.lam[1], d2 = l2 - c.lam[2];
   c.lam[1] = l1; c.lam[2] = l2;
   for (int k = 0; k < 3; ++k) {
-    vv[k] += c.ls * (c.dir[1][k] * d1 + c.dir[2][k] * d2);
-    ww[k] += c.Y[1][k] * d1 + c.Y[2][k] * d2;
+    vv[k] = fma_(c.ls, sum2(c.dir[1][k], d1, c.dir[2][k], d2), vv[k]);
+    ww[k] += sum2(c.Y[1][k], d1, c.Y[2][k], d2);
   }
 }
 
 // Warm start: the block's copy of its body after the impulses the rows start from.
 __device__ __forceinline__ void apply_contact_impulses(const ContactRows& c, float vv[3], float ww[3]) {
   for (int r = 0; r < 3; ++r)
-    for (int k = 0; k < 3; ++k) { vv[k] += c.ls * c.dir[r][k] * c.lam[r]; ww[k] += c.Y[r][k] * c.lam[r]; }
+    for (int k = 0; k < 3; ++k) { vv[k] = fma_(c.ls * c.dir[r][k], c.lam[r], vv[k]); ww[k] = fma_(c.Y[r][k], c.lam[r], ww[k]); }
 }
 
 // Rows of one capsule-capsule contact (Section 3.1: contacts among bodies; Section 4.1:
@@ -406,23 +433,20 @@ __device__ __forceinline__ void build_pair_side(PairSide& c, int side, const flo
   const int ra = refs & 0xffff, rb = (refs >> 16) & 0xffff;
   const int ba = ra / E, ea = ra - ba * E, bb = rb / E, eb = rb - bb * E;
   const float sp = Lpq[k * kPairWords + 2], tp = Lpq[k * kPairWords + 3], wk = Lpq[k * kPairWords + 4];
-  float xa[3], xb[3], qa[4], qb[4];
-  for (int i = 0; i < 3; ++i) {
-    xa[i] = Lpos[(ba * 7 + i) * E + ea];
-    xb[i] = Lpos[(bb * 7 + i) * E + eb] + (Lorg[i * E + eb] - Lorg[i * E + ea]);   // in A's env frame
-  }
+  // the closest points as seen from the two centres: ca, cb; df from B's to A's
+  float qa[4], qb[4];
   for (int i = 0; i < 4; ++i) { qa[i] = Lpos[(ba * 7 + 3 + i) * E + ea]; qb[i] = Lpos[(bb * 7 + 3 + i) * E + eb]; }
   const float radA = Ltbody[4 * ba], hlA = Ltbody[4 * ba + 1];
   const float radB = Ltbody[4 * bb], hlB = Ltbody[4 * bb + 1];
   const int axA = __float_as_int(Ltbody[4 * ba + 2]), axB = __float_as_int(Ltbody[4 * bb + 2]);
-  float Ra[9], Rb[9], cp[3], cq[3], df[3];
+  float Ra[9], Rb[9], ca[3], cb[3], df[3];
   quat_to_mat(qa, Ra);
   quat_to_mat(qb, Rb);
   for (int i = 0; i < 3; ++i) {
-    const float ha = Ra[3 * i + axA] * hlA, hb = Rb[3 * i + axB] * hlB;
-    cp[i] = xa[i] - ha + 2.0f * sp * ha;
-    cq[i] = xb[i] - hb + 2.0f * tp * hb;
-    df[i] = cp[i] - cq[i];
+    ca[i] = (2.0f * sp - 1.0f) * (Ra[3 * i + axA] * hlA);
+    cb[i] = (2.0f * tp - 1.0f) * (Rb[3 * i + axB] * hlB);
+    const float dx = (Lpos[(ba * 7 + i) * E + ea] - Lpos[(bb * 7 + i) * E + eb]) - (Lorg[i * E + eb] - Lorg[i * E + ea]);
+    df[i] = dx + (ca[i] - cb[i]);
   }
   const float dist = sqrtf(dot(df, df));
   float n[3] = {0.0f, 0.0f, 1.0f};
@@ -433,8 +457,8 @@ __device__ __forceinline__ void build_pair_side(PairSide& c, int side, const flo
   const float sg = side ? -1.0f : 1.0f;
   float arm[3], iwo[6];
   for (int i = 0; i < 3; ++i) {
-    const float pm = 0.5f * ((cp[i] - n[i] * radA) + (cq[i] + n[i] * radB));
-    arm[i] = pm - (side ? xb[i] : xa[i]);
+    // midway between the two surface points, seen from the own centre (the other side's closest point is df away)
+    arm[i] = fma_(0.5f, fma_(n[i], radB - radA, side ? df[i] : -df[i]), side ? cb[i] : ca[i]);
   }
   for (int i = 0; i < 6; ++i) iwo[i] = Liw[(bo * kVS + i) * E + eo];
   const float imo = Ltbody[4 * bo + 3];
@@ -467,28 +491,28 @@ __device__ __forceinline__ void relax_pair_side(PairSide& c, float mu, float v[3
   {
     const float part = dot(c.sd[0], v) + dot(c.sa[0], w);
     const float jv = part + lane_swap1(part);
-    float dl = -c.meff[0] * (jv + c.bias);
-    const float ln = fmaxf(c.lam[0] + dl, 0.0f);
-    dl = ln - c.lam[0];
+    const float ln = fmaxf(fma_(-c.meff[0], jv + c.bias, c.lam[0]), 0.0f);
+    const float dl = ln - c.lam[0];
     c.lam[0] = ln;
-    for (int k = 0; k < 3; ++k) { v[k] += c.ls * c.sd[0][k] * dl; w[k] += c.Y[0][k] * dl; }
+    for (int k = 0; k < 3; ++k) { v[k] = fma_(c.ls * c.sd[0][k], dl, v[k]); w[k] = fma_(c.Y[0][k], dl, w[k]); }
   }
   const float p1 = dot(c.sd[1], v) + dot(c.sa[1], w), p2 = dot(c.sd[2], v) + dot(c.sa[2], w);
   const float jv1 = p1 + lane_swap1(p1), jv2 = p2 + lane_swap1(p2);
-  float l1 = c.lam[1] - c.meff[1] * jv1, l2 = c.lam[2] - c.meff[2] * jv2;
+  float l1 = fma_(-c.meff[1], jv1, c.lam[1]), l2 = fma_(-c.meff[2], jv2, c.lam[2]);
   const float lim = mu * c.lam[0];
   project_on_disc(l1, l2, lim);
   const float d1 = l1 - c.lam[1], d2 = l2 - c.lam[2];
   c.lam[1] = l1; c.lam[2] = l2;
   for (int k = 0; k < 3; ++k) {
-    v[k] += c.ls * (c.sd[1][k] * d1 + c.sd[2][k] * d2);
-    w[k] += c.Y[1][k] * d1 + c.Y[2][k] * d2;
+    v[k] = fma_(c.ls, sum2(c.sd[1][k], d1, c.sd[2][k], d2), v[k]);
+    w[k] += sum2(c.Y[1][k], d1, c.Y[2][k], d2);
   }
 }
 
 // EC > 0: envs per workgroup fixed at compile time (LDS offsets become immediates);
 // EC == 0: taken from the launch arguments.  NJ: compile-time bound on the joints one body
 // belongs to (the per-body average reads NJ joint copies without branching).
+#pragma clang fp contract(fast)
 // counter-based uniform draw: one 64-bit mixing finaliser per (seed, env, index)
 __device__ inline float reset_uniform(uint64_t seed, uint64_t env, uint64_t idx) {
   uint64_t z = seed + env * 0x632BE59BD9B4E019ULL + idx * 0xD1B54A32D192ED03ULL;
@@ -632,6 +656,16 @@ __device__ __forceinline__ int wave_alloc(int n, int* counter) {
   return base + before;
 }
 
+#pragma clang fp contract(off)
+// The same address of constant memory, as one that the compiler knows nothing about: what is read
+// through it is read here, through the scalar cache.
+template <class T>
+__device__ __forceinline__ const T* reload_constant(const T* p) {
+  auto c = (const __attribute__((address_space(4))) T*)p;
+  asm volatile("" : "+s"(c));
+  return (const T*)c;
+}
+
 // PC != 0: capsule-capsule contacts (within an agent and between the agents of a group) compiled in.
 // NT: threads per workgroup.
 // NS != 0: the rows are solved by the non-smooth Newton / conjugate-residual solver instead of
@@ -661,13 +695,9 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   const bool is_body = idx < B && env_ok;
   const bool is_joint = idx < J && env_ok;
   const int obs_dim = 11 + 3 * D + F;                                      // staged in LDS
-  const int obs_row = obs_dim + (M.height_map ? kHmRows * kHmCols : 0);   // row of the caller's array
   // model scalars the loops below use, read once (before the kernel's first store, so they come
   // through the scalar cache and stay in scalar registers)
-  const int m_terrain = M.terrain_kind, m_contacts = M.contacts, m_root = M.root;
-  int m_feet = 0;   // the feet's bodies, a byte each
-#pragma unroll
-  for (int f = 0; f < kMaxFeet; ++f) m_feet |= (f < F ? M.feet[f] : 0) << (8 * f);
+  const int m_terrain = M.terrain_kind, m_contacts = M.contacts;
   const Field H0 = make_field(M, a.heights, a.coarse);
   const bool use_patch = m_terrain == 1 && H0.nx >= kPatch && H0.ny >= kPatch;
   const int m_group = PC ? (M.group > 1 ? M.group : 1) : 1, m_npairs = PC ? M.n_pairs : 0, m_nap = PC ? M.n_agent_pairs : 0;
@@ -685,15 +715,18 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   int* Lsurv = reinterpret_cast<int*>(lds + P.surv);
   float* Llam = lds + P.lam;                         // impulses of the contacts beyond one per thread
   // fine search: per slot (index s * E + env) the minimum of (squared distance, feature id) packed in 64 bits,
-  // then the list of candidate edges; both live in the space of the copies the sweeps use
+  // half of every body's segment, and four lists (rows of cells and single cells, each for the end
+  // spheres and for the mid-segments); all of it lives in the space of the copies the sweeps use
   unsigned long long* Lbest64 = reinterpret_cast<unsigned long long*>(lds + P.outj);
-  float* Lgeo = lds + P.outj + 2 * S * E;           // per slot: reach, and R L, 1/L^2 of a segment
-  unsigned* Lcand = reinterpret_cast<unsigned*>(lds + P.outj) + 5 * S * E;
-  const int cand_cap = (J * kJS + S * kCS) * E - 5 * S * E;
-  // work units of the fine search (8 cells of one queued slot each): end spheres in the first
-  // third of the list, mid-segments in the rest.  The space holds the observations at the end.
-  unsigned* Lunit = reinterpret_cast<unsigned*>(lds + P.obs);
-  const int unit_cap = (11 + 3 * D + F) * E, unit_cap_e = unit_cap / 3;
+  float* Lhalf = lds + P.half;                       // [B][3][E]: from the centre to the segment's second end
+  unsigned* Lcell_e = reinterpret_cast<unsigned*>(lds + P.cand);
+  const int cap32 = P.cand_cap / 32, cell_e_cap = 6 * cap32, cell_m_cap = 10 * cap32, row_e_cap = 6 * cap32, row_m_cap = 10 * cap32;
+  unsigned* Lcell_m = Lcell_e + cell_e_cap;
+  unsigned* Lrow_e = Lcell_m + cell_m_cap;
+  unsigned* Lrow_m = Lrow_e + row_e_cap;
+  // candidate pairs of the capsule-capsule search, in the space the observations are staged in at the end
+  unsigned* Lpair = reinterpret_cast<unsigned*>(lds + P.obs);
+  const int pair_cap = (11 + 3 * D + F) * E;
   float* Ltq = lds + P.tq;                           // joint torques, [J][3][E]
   float* Lpush = lds + P.push;                       // external force on the root body, [3][E]
   float* Lu = lds + P.u;
@@ -710,7 +743,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   const JointTab* Ltjoint = reinterpret_cast<const JointTab*>(lds + P.tjoint);  // joint table
   float* Lpq = lds + P.pq;                            // capsule-capsule contacts, kPairWords each, sorted by key
   float* Lpo = lds + P.po;                            // their copies times the block weight: A (v, w), B (v, w)
-  int* Lnear = reinterpret_cast<int*>(lds + P.pnear);
+  int* Lmeet = reinterpret_cast<int*>(lds + P.pnear);
   int* Lbs = reinterpret_cast<int*>(lds + P.pbs);     // bounding radii as float bits (ordered like ints)
   int* Lpcount = reinterpret_cast<int*>(lds + P.pcount);  // contacts found, near agent pairs
   int* Lpbcnt = reinterpret_cast<int*>(lds + P.pbcnt);
@@ -774,7 +807,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     if (a.task.enabled && a.count_step && env_t_ok) { a.push[3 * env_t] = fx; a.push[3 * env_t + 1] = fy; a.push[3 * env_t + 2] = 0.0f; }
   }
   for (int i = tid; i < M.table_words; i += kThreads) reinterpret_cast<int*>(lds + P.tjs)[i] = M.table_image[i];
-  for (int i = tid; i < (J * kJS + S * kCS) * E; i += kThreads) Loutj[i] = 0.0f;  // copies may be read (weight 0) before they are written
+  for (int i = tid; i < 6 * E; i += kThreads) lds[P.zero + i] = 0.0f;
+  if (tid < 8) Lcount[tid] = 0;
   if constexpr (WS != 0) {
     for (int i = tid; i < J * 6 * E; i += kThreads) {
       const int env_i = blockIdx.x * E + i % E;
@@ -849,9 +883,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     }
   }
 
-  // phase A reads the tables that other wavefronts copied; without the heightfield's copy there is no
-  // barrier between the two
-  if (!(use_patch && a.substeps > 0)) __syncthreads();
+  // phase A reads what other wavefronts copied (tables, counters, block maxima)
+  __syncthreads();
   TMARK(0);
   // wavefronts [0, joint_threads/64) hold the joint-side threads; contact k of a workgroup goes
   // to thread kThreads-1-k as long as that thread is not in a joint wavefront (n_reg contacts)
@@ -861,6 +894,23 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   // joint-side role: lanes 2p and 2p+1 are the parent and the child side of pair p = (joint, env)
   const int js_side = tid & 1, js_e = (tid >> 1) % E, js_j = (tid >> 1) / E;
   const bool js_on = js_j < J && blockIdx.x * E + js_e < N;
+
+  // the heightfield with the env's copy of it
+  auto field_of = [&](int ee) -> Field {
+    Field H = H0;
+    if (use_patch) {
+      H.patch = (const lds_float*)(Lpatch + ee * (kPatch * kPatch)); H.mip = (const lds_float*)(Lmip + ee * (kPatchBlocks * kPatchBlocks));
+      H.pi0 = Lporg[2 * ee]; H.pj0 = Lporg[2 * ee + 1]; H.ps = kPatch;
+    }
+    return H;
+  };
+  // geometry of one slot, from what phase A left in LDS
+  auto listed_geom = [&](int bb, int ee, int kind) -> SlotGeom {
+    const float bx[3] = {Lpos[(bb * 7 + 0) * E + ee], Lpos[(bb * 7 + 1) * E + ee], Lpos[(bb * 7 + 2) * E + ee]};
+    const float bo[3] = {Lorg[ee], Lorg[E + ee], Lorg[2 * E + ee]};
+    const float* lh = Lhalf + bb * 3 * E + ee;
+    return slot_geom_from_half(Ltbody[4 * bb], p_margin, bx, f3{lh[0], lh[E], lh[2 * E]}, kind, bo);
+  };
 
   const int tid_o = tid, e_o = e, idx_o = idx;
   const float h_o = h;
@@ -883,7 +933,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     }
     const int b = idx;
     // ---- A: publish pose and world inverse inertia
-    if (tid == 0) { Lcount[0] = 0; Lcount[1] = 0; Lcount[2] = 0; Lcount[3] = 0; Lcount[4] = 0; Lcount[5] = 0; Lcount[6] = 0; Lcount[7] = 0; }
+    if (tid == 0) Lcount[0] = 0;
     if constexpr (PC != 0) {
       if (tid < 4) Lpcount[tid] = 0;
       if (tid < E) Lbs[tid] = 0;
@@ -899,22 +949,23 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       quat_to_mat(q, R);
       for (int c = 0; c < 3; ++c) invIb[c] = Ltin[6 * b + 3 + c];
       float iw[6];
-      iw[0] = R[0] * R[0] * invIb[0] + R[1] * R[1] * invIb[1] + R[2] * R[2] * invIb[2];
-      iw[1] = R[0] * R[3] * invIb[0] + R[1] * R[4] * invIb[1] + R[2] * R[5] * invIb[2];
-      iw[2] = R[0] * R[6] * invIb[0] + R[1] * R[7] * invIb[1] + R[2] * R[8] * invIb[2];
-      iw[3] = R[3] * R[3] * invIb[0] + R[4] * R[4] * invIb[1] + R[5] * R[5] * invIb[2];
-      iw[4] = R[3] * R[6] * invIb[0] + R[4] * R[7] * invIb[1] + R[5] * R[8] * invIb[2];
-      iw[5] = R[6] * R[6] * invIb[0] + R[7] * R[7] * invIb[1] + R[8] * R[8] * invIb[2];
+      iw[0] = sum3(R[0] * R[0], invIb[0], R[1] * R[1], invIb[1], R[2] * R[2], invIb[2]);
+      iw[1] = sum3(R[0] * R[3], invIb[0], R[1] * R[4], invIb[1], R[2] * R[5], invIb[2]);
+      iw[2] = sum3(R[0] * R[6], invIb[0], R[1] * R[7], invIb[1], R[2] * R[8], invIb[2]);
+      iw[3] = sum3(R[3] * R[3], invIb[0], R[4] * R[4], invIb[1], R[5] * R[5], invIb[2]);
+      iw[4] = sum3(R[3] * R[6], invIb[0], R[4] * R[7], invIb[1], R[5] * R[8], invIb[2]);
+      iw[5] = sum3(R[6] * R[6], invIb[0], R[7] * R[7], invIb[1], R[8] * R[8], invIb[2]);
       for (int c = 0; c < 6; ++c) Liw[(b * kVS + c) * E + e] = iw[c];
+      if (m_terrain == 1) {
+        const f3 a = body_half(q, Ltbody[4 * b + 1], __float_as_int(Ltbody[4 * b + 2]));
+        Lhalf[(b * 3 + 0) * E + e] = a.x; Lhalf[(b * 3 + 1) * E + e] = a.y; Lhalf[(b * 3 + 2) * E + e] = a.z;
+      }
     }
     __syncthreads();
 
     TMARK(1);
-    // ---- B: joint torques (stored once per joint; the body applies the sign).  They go through
-    //         LDS only, so they are computed by the upper half of the workgroup when the joints fit
-    //         there: the lower half runs the per-body pass below at the same time.
-    {
-      const int tq_base = J * E <= kThreads / 2 ? kThreads / 2 : 0;
+    // ---- B: joint torques (stored once per joint; the body applies the sign) by the threads from tq_base on
+    auto torques = [&](int tq_base) {
       const int tj = (tid - tq_base) / E, te = (tid - tq_base) % E;
       if (tid >= tq_base && tj < J && blockIdx.x * E + te < N) {
         const JointTab& jt = Ltjoint[tj];
@@ -929,38 +980,34 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           float ak[3];
           mat_vec(Ra, jt.axes[k], ak);
           float t = jt.gear[k] * Lu[jt.act[k] * E + te];
-          tq[0] += t * ak[0]; tq[1] += t * ak[1]; tq[2] += t * ak[2];
+          for (int c = 0; c < 3; ++c) tq[c] = fma_(t, ak[c], tq[c]);
         }
         for (int c = 0; c < 3; ++c) Ltq[(tj * 3 + c) * E + te] = tq[c];
       }
-    }
-    // ---- B1: every slot: plane contact, or reach test against the heightfield copy.  A slot
-    //          that may touch the heightfield (block maxima, then the exact maximum over its box)
-    //          is queued (end spheres from the front of the queue, mid-segments from the back), its
-    //          world-space geometry is left in its still unused record, and its box is cut into
-    //          work units of 8 cells (samples for a mid-segment).
-    //          Slots go to the threads from the top of the workgroup down: a second round, if any,
-    //          then runs on the last wavefronts while the first ones hold the joint threads.
-    // forces -> velocities (torques, gravity, push, explicit gyroscopic term): body threads, needs
-    // the joint torques and nothing of the contacts
-    auto forces = [&]() {
-      if (!is_body) return;
+    };
+    // forces -> velocities (torques, gravity, push, explicit gyroscopic term): needs the joint torques and
+    // nothing of the contacts.  Threads from t0 up; entry i is body i / E of env i % E.
+    auto forces = [&](int t0) {
+     for (int i = tid - t0; i >= 0 && i < B * E; i += kThreads - t0) {
+      const int e = i % E, b = i / E;
+      if (blockIdx.x * E + e >= N) continue;
       float tau[3] = {0, 0, 0};
-      for (int k = 0; k < my_njs; ++k) {
+      const int njs = Ltjs[b * (kMaxBodyJoints + 3)];
+      for (int k = 0; k < njs; ++k) {
         const int js = Ltjs[b * (kMaxBodyJoints + 3) + 3 + k];
         const float sg = (js & 1) ? 1.0f : -1.0f;
-        for (int c = 0; c < 3; ++c) tau[c] += sg * Ltq[((js >> 1) * 3 + c) * E + e];
+        for (int c = 0; c < 3; ++c) tau[c] = fma_(sg, Ltq[((js >> 1) * 3 + c) * E + e], tau[c]);
       }
-      float R[9], qq[4], Ib[3], invIb[3];
+      float R[9], qq[4], Ib[3], invIb[3], v[3], w[3];
       for (int c = 0; c < 4; ++c) qq[c] = Lpos[(b * 7 + 3 + c) * E + e];
       quat_to_mat(qq, R);
       for (int c = 0; c < 3; ++c) { Ib[c] = Ltin[6 * b + c]; invIb[c] = Ltin[6 * b + 3 + c]; }
       for (int c = 0; c < 3; ++c) { v[c] = Lvel[(b * kVS + c) * E + e]; w[c] = Lvel[(b * kVS + 3 + c) * E + e]; }
       if (a.task.enabled && b == M.root) {
         const float him = h * Ltbody[4 * b + 3];
-        v[0] += him * Lpush[0 * E + e]; v[1] += him * Lpush[1 * E + e]; v[2] += him * Lpush[2 * E + e];
+        for (int c = 0; c < 3; ++c) v[c] = fma_(him, Lpush[c * E + e], v[c]);
       }
-      v[0] += h * g0; v[1] += h * g1; v[2] += h * g2;
+      v[0] = fma_(h, g0, v[0]); v[1] = fma_(h, g1, v[1]); v[2] = fma_(h, g2, v[2]);
       float wb[3], tb[3];
       mat_t_vec(R, w, wb);
       mat_t_vec(R, tau, tb);
@@ -975,248 +1022,213 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       mat_vec(R, dwb, dww);
       for (int c = 0; c < 3; ++c) w[c] += dww[c];
       for (int c = 0; c < 3; ++c) { Lvel[(b * kVS + c) * E + e] = v[c]; Lvel[(b * kVS + 3 + c) * E + e] = w[c]; }
+     }
     };
-    int n_b1 = S * E;            // slots the per-slot pass visits
-    unsigned* Lslots = Lcand;    // heightfield: list of the slots of the bodies near the ground
-    if (m_terrain == 1) {
-      // ---- B1a: one thread per body: reach test of the whole capsule (box of its segment);
-      //           the slots of a body that passes are listed for the per-slot pass, the others
-      //           are inactive.  A slot can only pass its own test if its body passes this one.
-      for (int i = tid; i < B * E; i += kThreads) {
-        const int ee = i % E, bb = i / E;
-        const int env_i = blockIdx.x * E + ee;
-        const int s0 = Ltjs[bb * (kMaxBodyJoints + 3) + 1], ns = Ltjs[bb * (kMaxBodyJoints + 3) + 2];
-        bool near = false;
-        if (env_i < N && m_contacts) {
-          float bx[3], bq[4], bo[3];
-          for (int c = 0; c < 3; ++c) bx[c] = Lpos[(bb * 7 + c) * E + ee];
-          for (int c = 0; c < 4; ++c) bq[c] = Lpos[(bb * 7 + 3 + c) * E + ee];
-          for (int c = 0; c < 3; ++c) bo[c] = Lorg[c * E + ee];
-          SlotGeom g = slot_geom(Ltbody[4 * bb], Ltbody[4 * bb + 1], __float_as_int(Ltbody[4 * bb + 2]), p_margin, bx, bq,
-                                 2, bo);
-          Field H = H0;
-          if (use_patch) { H.patch = (const lds_float*)(Lpatch + ee * (kPatch * kPatch)); H.mip = (const lds_float*)(Lmip + ee * (kPatchBlocks * kPatchBlocks)); H.pi0 = Lporg[2 * ee]; H.pj0 = Lporg[2 * ee + 1]; H.ps = kPatch; }
-          near = slot_reach(H, g, false);
-        }
-        const int pos = wave_alloc<2>(near ? ns : 0, &Lcount[7]);
-        for (int k = 0; k < ns; ++k) {
-          if (near) Lslots[pos + k] = (unsigned)((s0 + k) * E + ee);
-          else {
-            Lreci[((s0 + k) * kRecWords + 0) * E + ee] = 0;
-            Lrec[((s0 + k) * kRecWords + 10) * E + ee] = 0.0f;
-          }
-        }
-      }
-      __syncthreads();
-      TMARK(24);
-      n_b1 = Lcount[7];
-      // the lower wavefronts integrate the forces while the upper ones run the per-slot pass
-      forces();
-    }
-    for (int x = kThreads - 1 - tid; x < n_b1; x += kThreads) {
-      const int i = m_terrain == 1 ? (int)Lslots[x] : x;
-      int ee = i % E, s = i / E;
-      int env_i = blockIdx.x * E + ee;
-      ContactOut co = no_contact();
-      int nu_e = 0, nu_m = 0, qi = 0;
-      if (env_i < N && m_contacts) {
-        const SlotTab sl{Ltslot[2 * s], Ltslot[2 * s + 1]};
-        float bx[3], bq[4], bo[3];
-        for (int c = 0; c < 3; ++c) bx[c] = Lpos[(sl.body * 7 + c) * E + ee];
-        for (int c = 0; c < 4; ++c) bq[c] = Lpos[(sl.body * 7 + 3 + c) * E + ee];
-        for (int c = 0; c < 3; ++c) bo[c] = Lorg[c * E + ee];
-        SlotGeom g = slot_geom(Ltbody[4 * sl.body], Ltbody[4 * sl.body + 1], __float_as_int(Ltbody[4 * sl.body + 2]),
-                               p_margin, bx, bq, sl.kind, bo);
-        if (m_terrain == 0) {
-          co = plane_contact(g, p_margin);
-        } else {
-          Field H = H0;
-          if (use_patch) { H.patch = (const lds_float*)(Lpatch + ee * (kPatch * kPatch)); H.mip = (const lds_float*)(Lmip + ee * (kPatchBlocks * kPatchBlocks)); H.pi0 = Lporg[2 * ee]; H.pj0 = Lporg[2 * ee + 1]; H.ps = kPatch; }
-          if (slot_reach(H, g)) {
-            const bool mid = sl.kind == 2;
-            qi = mid ? S * E - 1 - atomicAdd(&Lcount[2], 1) : atomicAdd(&Lcount[1], 1);
-            Lsurv[qi] = i;
-            Lbest64[i] = ~0ull;
-            const int ni = g.i1 - g.i0 + (mid ? 2 : 1), nj = g.j1 - g.j0 + (mid ? 2 : 1);
-            const bool fits = ni <= 15 && nj <= 15 && g.i0 < 4096 && g.j0 < 4096;  // packed box below
-            const f3 Pa = sl.kind == 1 ? g.P1 : g.P0;
-            Lrec[(s * kRecWords + 1) * E + ee] = Pa.x; Lrec[(s * kRecWords + 2) * E + ee] = Pa.y;
-            Lrec[(s * kRecWords + 3) * E + ee] = Pa.z;
-            Lreci[(s * kRecWords + 7) * E + ee] = g.i0 | (g.j0 << 12) | (ni << 24) | (nj << 28);
-            Lreci[(s * kRecWords + 8) * E + ee] = fits ? 0 : 1;   // 1: search this slot the slow way
-            Lgeo[3 * i] = g.Rq;
-            if (mid) {
-              Lrec[(s * kRecWords + 4) * E + ee] = g.P1.x; Lrec[(s * kRecWords + 5) * E + ee] = g.P1.y;
-              Lrec[(s * kRecWords + 6) * E + ee] = g.P1.z;
-              float RL, inv_L2;
-              seg_cull_consts(g, RL, inv_L2);
-              Lgeo[3 * i + 1] = RL; Lgeo[3 * i + 2] = inv_L2;
-            }
-            if (!fits) Lcount[4] = 1;
-            else if (mid) nu_m = (ni * nj + 7) >> 3;
-            else nu_e = (ni * nj + 7) >> 3;
-          }
-        }
-      }
-      if (m_terrain == 1) {
-        // list space for the units of the whole wavefront, one atomic per kind
-        const int ue = wave_alloc<5>(nu_e, &Lcount[5]), um = wave_alloc<5>(nu_m, &Lcount[6]);
-        const int nu = nu_e + nu_m, u0 = nu_e ? ue : um, cap = nu_e ? unit_cap_e : unit_cap - unit_cap_e;
-        unsigned* U = Lunit + (nu_e ? 0 : unit_cap_e);
-        for (int u = 0; u < nu; ++u)
-          if (u0 + u < cap) U[u0 + u] = (unsigned)i | ((unsigned)u << 12);
-        if (nu > 0 && u0 + nu > cap) { Lreci[(s * kRecWords + 8) * E + ee] = 1; Lcount[4] = 1; }
-      }
-      if (co.active) {
-        store_record(Lrec, Lreci, s, ee, E, co);
-        Llist[atomicAdd(&Lcount[0], 1)] = i;
-      } else {
-        Lreci[(s * kRecWords + 0) * E + ee] = 0;      // the other words of an inactive record are not read
-        Lrec[(s * kRecWords + 10) * E + ee] = 0.0f;
-      }
-    }
-    TMARK(2);
-    if (m_terrain == 1) {
-      __syncthreads();
-      TMARK(25);
-      // ---- B2: fine search in two stages.  Stage 1: kGroup lanes per work unit, one cell per
-      //          lane: a cheap reach test decides which triangles (end sphere) or edges
-      //          (mid-segment) of the cell become candidates.  Stage 2: one candidate per thread:
-      //          exact distance, minimum of (d2, id) per slot with a 64-bit LDS atomic.
-      const int grp = tid / kGroup, gl = tid % kGroup;
-      Field H = H0;
-      const int n_end = Lcount[1], n_mid = Lcount[2];
-      for (int pass = 0; pass < 2; ++pass) {
-        const int cap = pass == 0 ? unit_cap_e : unit_cap - unit_cap_e;
-        const int n_u = Lcount[5 + pass] < cap ? Lcount[5 + pass] : cap;
-        const unsigned* U = Lunit + (pass == 0 ? 0 : unit_cap_e);
-        for (int x = grp; x < n_u; x += kThreads / kGroup) {
-          const unsigned uw = U[x];
-          const int i = uw & 4095, c = (int)(uw >> 12) * 8 + gl;   // slot index, cell within the box
-          const int ee = i % E, s = i / E;
-          const unsigned box = (unsigned)Lreci[(s * kRecWords + 7) * E + ee];
-          const int i0 = box & 4095, j0 = (box >> 12) & 4095, ni = (box >> 24) & 15, nj = box >> 28;
-          // c / ni for small non-negative integers: the quotient of (c + 0.5) / ni is at least
-          // 0.5 / 15 away from an integer, far more than the error of the reciprocal
-          const int dj = (int)(((float)c + 0.5f) * __builtin_amdgcn_rcpf((float)ni)), di = c - dj * ni;
-          if (use_patch) { H.patch = (const lds_float*)(Lpatch + ee * (kPatch * kPatch)); H.mip = (const lds_float*)(Lmip + ee * (kPatchBlocks * kPatchBlocks)); H.pi0 = Lporg[2 * ee]; H.pj0 = Lporg[2 * ee + 1]; H.ps = kPatch; }
-          const f3 Pa = f3{Lrec[(s * kRecWords + 1) * E + ee], Lrec[(s * kRecWords + 2) * E + ee], Lrec[(s * kRecWords + 3) * E + ee]};
-          const float Rq = Lgeo[3 * i];
-          int mask = 0;
-          if (pass == 0) {
-            if (c < ni * nj && sphere_cell_reach(H, Pa, Rq + kSelSlack, i0 + di, j0 + dj)) mask = 3;
-          } else {
-            const f3 Pb = f3{Lrec[(s * kRecWords + 4) * E + ee], Lrec[(s * kRecWords + 5) * E + ee], Lrec[(s * kRecWords + 6) * E + ee]};
-            const SegCull sc = seg_cull_from(Pa, Pb, Rq, Lgeo[3 * i + 1], Lgeo[3 * i + 2], i0 + ni - 2, j0 + nj - 2);
-            if (c < ni * nj) mask = segment_candidates(H, sc, i0 + di, j0 + dj);
-          }
-          int pos = wave_alloc<2>(__popc(mask), &Lcount[3]);
-          const unsigned cw = (unsigned)i | ((unsigned)di << 14) | ((unsigned)dj << 18) | ((unsigned)pass << 22);
-#pragma unroll
-          for (int k = 0; k < 3; ++k)
-            if ((mask >> k) & 1) {
-              if (pos < cand_cap) Lcand[pos] = cw | ((unsigned)k << 12);
-              ++pos;
-            }
-          if (mask != 0 && pos > cand_cap) {
-            // candidate list full: the slot is searched again by the fallback below
-            Lreci[(s * kRecWords + 8) * E + ee] = 1;
-            Lcount[4] = 1;
-          }
-        }
-        TMARK(10 + pass);
-      }
-      __syncthreads();
-      {
-        const int n_c = Lcount[3] < cand_cap ? Lcount[3] : cand_cap;
-        for (int t = tid; t < n_c; t += kThreads) {
-          const unsigned cw = Lcand[t];
-          const int i = cw & 4095, k = (cw >> 12) & 3, di = (cw >> 14) & 15, dj = (cw >> 18) & 15;
-          const int ee = i % E, s = i / E;
-          const unsigned box = (unsigned)Lreci[(s * kRecWords + 7) * E + ee];
-          const int ci = (int)(box & 4095) + di, cj = (int)((box >> 12) & 4095) + dj;
-          if (use_patch) { H.patch = (const lds_float*)(Lpatch + ee * (kPatch * kPatch)); H.mip = (const lds_float*)(Lmip + ee * (kPatchBlocks * kPatchBlocks)); H.pi0 = Lporg[2 * ee]; H.pj0 = Lporg[2 * ee + 1]; H.ps = kPatch; }
-          const f3 Pa = f3{Lrec[(s * kRecWords + 1) * E + ee], Lrec[(s * kRecWords + 2) * E + ee], Lrec[(s * kRecWords + 3) * E + ee]};
-          float d2;
-          if (((cw >> 22) & 1) == 0) {
-            if (sphere_tri_d2(H, Pa, ci, cj, k, d2)) atomicMin(&Lbest64[i], pack_best(d2, 2 * (cj * (H.nx - 1) + ci) + k));
-          } else {
-            const f3 Pb = f3{Lrec[(s * kRecWords + 4) * E + ee], Lrec[(s * kRecWords + 5) * E + ee], Lrec[(s * kRecWords + 6) * E + ee]};
-            if (segment_edge_d2(H, Pa, Pb, ci, cj, k, d2)) atomicMin(&Lbest64[i], pack_best(d2, 3 * (cj * H.nx + ci) + k));
-          }
-        }
-        __syncthreads();
-        TMARK(13);
-        if (Lcount[4]) {
-          // rare: a box too large for the packed indices, or a full list: those slots are searched
-          // directly, kGroup lanes per slot
-          for (int sv = grp; sv < n_end + n_mid; sv += kThreads / kGroup) {
-            const int qi = sv < n_end ? sv : S * E - 1 - (sv - n_end);
-            const int i = Lsurv[qi];
-            const int ee = i % E, s = i / E;
-            if (!Lreci[(s * kRecWords + 8) * E + ee]) continue;
-            const SlotTab sl{Ltslot[2 * s], Ltslot[2 * s + 1]};
-            float bx[3], bq[4], bo[3];
-            for (int c = 0; c < 3; ++c) bx[c] = Lpos[(sl.body * 7 + c) * E + ee];
-            for (int c = 0; c < 4; ++c) bq[c] = Lpos[(sl.body * 7 + 3 + c) * E + ee];
-            for (int c = 0; c < 3; ++c) bo[c] = Lorg[c * E + ee];
-            SlotGeom g = slot_geom(Ltbody[4 * sl.body], Ltbody[4 * sl.body + 1], __float_as_int(Ltbody[4 * sl.body + 2]),
-                                   p_margin, bx, bq, sl.kind, bo);
-            if (use_patch) { H.patch = (const lds_float*)(Lpatch + ee * (kPatch * kPatch)); H.mip = (const lds_float*)(Lmip + ee * (kPatchBlocks * kPatchBlocks)); H.pi0 = Lporg[2 * ee]; H.pj0 = Lporg[2 * ee + 1]; H.ps = kPatch; }
-            slot_range(H, g);
-            float best = INFINITY;
-            int best_id = -1;
-            if (sl.kind < 2) {
-              const f3 Pc = sl.kind == 0 ? g.P0 : g.P1;
-              const int ni = g.i1 - g.i0 + 1, nc = ni * (g.j1 - g.j0 + 1);
-              for (int c = gl; c < nc; c += kGroup) sphere_cell(H, Pc, g.Rq, g.i0 + c % ni, g.j0 + c / ni, best, best_id);
-            } else {
-              const int ni = g.i1 - g.i0 + 2, nc = ni * (g.j1 - g.j0 + 2);
-              const SegCull sc = seg_cull(g);
-              for (int c = gl; c < nc; c += kGroup) segment_vertex(H, g, sc, g.i0 + c % ni, g.j0 + c / ni, best, best_id);
-            }
-            if (best_id >= 0) atomicMin(&Lbest64[i], pack_best(best, best_id));
-          }
-          __syncthreads();
-        }
-      }
-#ifdef SIM_PHASE_TIMING
-      if (tid == 0 && blockIdx.x == 7) { a.dbg[14] += Lcount[5] + Lcount[6]; a.dbg[15] += Lcount[3]; }
-#endif
-      // ---- B3: one thread per queued slot turns the selected feature into a contact record
-      //          (end spheres on the lower half of the workgroup, mid-segments on the upper half,
-      //          so that a wavefront follows one path)
-      for (int sv = tid < kThreads / 2 ? tid : tid - kThreads / 2; sv < (tid < kThreads / 2 ? n_end : n_mid); sv += kThreads / 2) {
-        const int qi = tid < kThreads / 2 ? sv : S * E - 1 - sv;
-        const int i = Lsurv[qi];
+    if (m_terrain == 0) {
+      // plane: the torques from the lower end of the workgroup, every slot's contact from the upper one
+      torques(0);
+      for (int i = kThreads - 1 - tid; i < S * E; i += kThreads) {
         const int ee = i % E, s = i / E;
-        const SlotTab sl{Ltslot[2 * s], Ltslot[2 * s + 1]};
-        float bx[3], bq[4], bo[3];
-        for (int c = 0; c < 3; ++c) bx[c] = Lpos[(sl.body * 7 + c) * E + ee];
-        for (int c = 0; c < 4; ++c) bq[c] = Lpos[(sl.body * 7 + 3 + c) * E + ee];
-        for (int c = 0; c < 3; ++c) bo[c] = Lorg[c * E + ee];
-        SlotGeom g = slot_geom(Ltbody[4 * sl.body], Ltbody[4 * sl.body + 1], __float_as_int(Ltbody[4 * sl.body + 2]),
-                               p_margin, bx, bq, sl.kind, bo);
-        if (use_patch) { H.patch = (const lds_float*)(Lpatch + ee * (kPatch * kPatch)); H.mip = (const lds_float*)(Lmip + ee * (kPatchBlocks * kPatchBlocks)); H.pi0 = Lporg[2 * ee]; H.pj0 = Lporg[2 * ee + 1]; H.ps = kPatch; }
         ContactOut co = no_contact();
-        const unsigned long long bw = Lbest64[i];
-        const float bestd = __uint_as_float((unsigned)(bw >> 32));
-        const int besti = (int)(unsigned)bw;
-        if (sl.kind < 2) {
-          // a centre underneath the surface overrides the nearest-triangle search
-          if (!underneath_contact(H, g, p_margin, co)) co = finish_sphere(H, g, p_margin, bestd, besti);
-        } else {
-          co = finish_segment(H, g, p_margin, bestd, besti);
+        if (blockIdx.x * E + ee < N && m_contacts) {
+          const SlotTab sl{Ltslot[2 * s], Ltslot[2 * s + 1]};
+          float bx[3], bq[4], bo[3];
+          for (int c = 0; c < 3; ++c) bx[c] = Lpos[(sl.body * 7 + c) * E + ee];
+          for (int c = 0; c < 4; ++c) bq[c] = Lpos[(sl.body * 7 + 3 + c) * E + ee];
+          for (int c = 0; c < 3; ++c) bo[c] = Lorg[c * E + ee];
+          const SlotGeom g = slot_geom(Ltbody[4 * sl.body], Ltbody[4 * sl.body + 1], __float_as_int(Ltbody[4 * sl.body + 2]),
+                                       p_margin, bx, bq, sl.kind, bo);
+          co = plane_contact(g, p_margin);
         }
         if (co.active) {
           store_record(Lrec, Lreci, s, ee, E, co);
           Llist[atomicAdd(&Lcount[0], 1)] = i;
+        } else {
+          Lreci[(s * kRecWords + 0) * E + ee] = 0;      // the other words of an inactive record are not read
+          Lrec[(s * kRecWords + 10) * E + ee] = 0.0f;
+        }
+      }
+      TMARK(2);
+    } else {
+      // ---- B1: one thread per slot (end spheres, then mid-segments in wavefronts of their own): reach
+      //          box against the block maxima of the heightfield copy.  A slot that may touch the field is
+      //          queued (end spheres from the front of the queue, mid-segments from the back) and the rows
+      //          of its box are listed; an end sphere's box is first cut down to what can be nearer than
+      //          the ground straight below its centre.  Box and reach stay in the slot's unused record.
+      {
+        const int t_mid = (2 * B * E + 63) & ~63;
+        for (int t = tid; t < t_mid + B * E; t += kThreads) {
+          const bool mid = t >= t_mid;
+          if (!mid && t >= 2 * B * E) continue;
+          const int r = mid ? t - t_mid : t, ee = r % E, bk = r / E, bb = mid ? bk : bk >> 1;
+          const int s0 = Ltjs[bb * (kMaxBodyJoints + 3) + 1], ns = Ltjs[bb * (kMaxBodyJoints + 3) + 2];
+          // a capsule's slots are its two ends and its interior, a sphere has the second end's alone
+          const int kind = mid ? 2 : bk & 1;
+          bool on = mid ? ns == 3 : ns > 1 || kind == 1;
+          const int s = s0 + (ns == 1 ? 0 : kind), i = s * E + ee;
+          int n_rows = 0;
+          if (on) {
+            Lreci[(s * kRecWords + 0) * E + ee] = 0;      // the other words of an inactive record are not read
+            Lrec[(s * kRecWords + 10) * E + ee] = 0.0f;
+            on = false;
+            if (blockIdx.x * E + ee < N && m_contacts) {
+              const Field H = field_of(ee);
+              SlotGeom g = listed_geom(bb, ee, kind);
+              if (slot_reach(H, g, false)) {
+                on = true;
+                float r2;
+                const bool search = slot_search_box(H, g, r2);
+                const int ni = g.i1 - g.i0 + 1, nj = g.j1 - g.j0 + 1;
+                const bool fits = ni >= 1 && ni <= 15 && nj >= 1 && nj <= 15 && g.i0 < 4096 && g.j0 < 4096;
+                Lreci[(s * kRecWords + 1) * E + ee] = g.i0 | (g.j0 << 12) | (ni << 24) | (nj << 28);
+                Lrec[(s * kRecWords + 2) * E + ee] = r2;
+                Lreci[(s * kRecWords + 8) * E + ee] = search && !fits ? 1 : 0;   // 1: search this slot the slow way
+                if (search && !fits) Lcount[4] = 1;
+                n_rows = search && fits ? nj : 0;
+                Lbest64[i] = ~0ull;
+              }
+            }
+          }
+          if (on) Lsurv[mid ? S * E - 1 - atomicAdd(&Lcount[2], 1) : atomicAdd(&Lcount[1], 1)] = i;
+          const int cap = mid ? row_m_cap : row_e_cap, r0 = wave_alloc<4>(n_rows, &Lcount[mid ? 6 : 5]);
+          unsigned* U = mid ? Lrow_m : Lrow_e;
+          if (r0 + n_rows <= cap) {
+            for (int k = 0; k < n_rows; ++k) U[r0 + k] = (unsigned)i | ((unsigned)k << 20);
+          } else {
+            for (int k = r0; k < cap; ++k) U[k] = (unsigned)i | (15u << 20);   // (a row past every box)
+            Lreci[(s * kRecWords + 8) * E + ee] = 1;
+            Lcount[4] = 1;
+          }
+        }
+      }
+      torques(kThreads - ((J * E + 63) & ~63));   // (beside the slots; 2 J E threads fit below)
+      TMARK(2);
+      __syncthreads();
+      TMARK(24);
+      // ---- B2: fine search in two stages.  Stage 1: one row of a box per thread: which of its cells can
+      //          hold a triangle within reach of the end sphere, or an edge within reach of the segment
+      //          (conservative tests, from the corner heights).  Those are listed.  Stage 2: one triangle /
+      //          edge of a listed cell per thread: exact distance, minimum of (d2, id) per slot with a
+      //          64-bit LDS atomic.
+      const int n_end = Lcount[1], n_mid = Lcount[2];
+      {
+        const int n_re = Lcount[5] < row_e_cap ? Lcount[5] : row_e_cap, n_rm = Lcount[6] < row_m_cap ? Lcount[6] : row_m_cap;
+        const int t_mid = (n_re + 63) & ~63;
+        for (int t = tid; t < t_mid + n_rm; t += kThreads) {
+          const bool mid = t >= t_mid;
+          if (!mid && t >= n_re) continue;
+          const unsigned uw = mid ? Lrow_m[t - t_mid] : Lrow_e[t];
+          const int i = uw & 4095, row = (int)(uw >> 20), ee = i % E, s = i / E, bb = Ltslot[2 * s];
+          const unsigned box = (unsigned)Lreci[(s * kRecWords + 1) * E + ee];
+          const float r2 = Lrec[(s * kRecWords + 2) * E + ee];
+          const int i0 = box & 4095, j0 = (box >> 12) & 4095, ni = (box >> 24) & 15, nj = box >> 28;
+          const Field H = field_of(ee);
+          const SlotGeom g = listed_geom(bb, ee, mid ? 2 : Ltslot[2 * s + 1]);
+          if (row >= nj) continue;
+          const int cells = mid ? kSegCells : kEndCells;
+          for (int col = 0; col < ni; col += cells) {
+            unsigned m = mid ? cells_near_segment(H, g, r2, i0 + col, j0 + row, ni - col)
+                             : cells_near_sphere(H, g.kind == 0 ? g.P0 : g.P1, r2, i0 + col, j0 + row, ni - col);
+            int pos = wave_alloc<3>(__popc(m), &Lcount[mid ? 7 : 3]);
+            const int cap = mid ? cell_m_cap : cell_e_cap;
+            unsigned* C = mid ? Lcell_m : Lcell_e;
+            unsigned cw = (unsigned)i | ((unsigned)row << 20) | ((unsigned)col << 16);
+            if (m && pos + __popc(m) > cap) {
+              // list full: the slot is searched again by the fallback below
+              for (; pos < cap; ++pos) C[pos] = cw;
+              Lreci[(s * kRecWords + 8) * E + ee] = 1;
+              Lcount[4] = 1;
+              m = 0;
+            }
+            for (; m; m &= m - 1) C[pos++] = cw + ((unsigned)(__ffs(m) - 1) << 16);
+          }
+        }
+      }
+      TMARK(10);
+      __syncthreads();
+      TMARK(25);
+      {
+        const int t_end = 2 * (Lcount[3] < cell_e_cap ? Lcount[3] : cell_e_cap), t_mid = (t_end + 63) & ~63;
+        const int t_all = t_mid + 3 * (Lcount[7] < cell_m_cap ? Lcount[7] : cell_m_cap);
+        for (int t = tid; t < t_all; t += kThreads) {
+          const bool mid = t >= t_mid;
+          if (!mid && t >= t_end) continue;
+          const int c = mid ? (t - t_mid) / 3 : t >> 1, k = mid ? (t - t_mid) - 3 * c : t & 1;
+          const unsigned cw = mid ? Lcell_m[c] : Lcell_e[c];
+          const int i = cw & 4095, ee = i % E, s = i / E, bb = Ltslot[2 * s];
+          const unsigned box = (unsigned)Lreci[(s * kRecWords + 1) * E + ee];
+          const int ci = (int)(box & 4095) + (int)((cw >> 16) & 15), cj = (int)((box >> 12) & 4095) + (int)((cw >> 20) & 15);
+          const Field H = field_of(ee);
+          const SlotGeom g = listed_geom(bb, ee, mid ? 2 : Ltslot[2 * s + 1]);
+          float d2;
+          if (!mid) {
+            if (sphere_tri_d2(H, g.kind == 0 ? g.P0 : g.P1, ci, cj, k, d2))
+              atomicMin(&Lbest64[i], pack_best(d2, 2 * (cj * (H.nx - 1) + ci) + k));
+          } else if ((k == 1 || ci < H.nx - 1) && (k == 0 || cj < H.ny - 1)) {   // (the last row and column have no cell of their own)
+            if (segment_edge_d2(H, g.P0, g.P1, ci, cj, k, d2)) atomicMin(&Lbest64[i], pack_best(d2, 3 * (cj * H.nx + ci) + k));
+          }
         }
       }
       __syncthreads();
-      TMARK(12);
-      // the search results shared the space of the contact copies: leave finite numbers behind
-      for (int i = tid; i < 5 * S * E; i += kThreads) Loutj[i] = 0.0f;
+      TMARK(13);
+      if (Lcount[4]) {
+        // rare: a box too large for the packed indices, or a full list: those slots are searched
+        // directly, kGroup lanes per slot
+        const int grp = tid / kGroup, gl = tid % kGroup;
+        for (int sv = grp; sv < n_end + n_mid; sv += kThreads / kGroup) {
+          const int i = Lsurv[sv < n_end ? sv : S * E - 1 - (sv - n_end)];
+          const int ee = i % E, s = i / E;
+          if (!Lreci[(s * kRecWords + 8) * E + ee]) continue;
+          const Field H = field_of(ee);
+          SlotGeom g = listed_geom(Ltslot[2 * s], ee, Ltslot[2 * s + 1]);
+          slot_range(H, g);
+          float best = INFINITY;
+          int best_id = -1;
+          if (g.kind < 2) {
+            const f3 Pc = g.kind == 0 ? g.P0 : g.P1;
+            const int ni = g.i1 - g.i0 + 1, nc = ni * (g.j1 - g.j0 + 1);
+            for (int c = gl; c < nc; c += kGroup) sphere_cell(H, Pc, g.Rq, g.i0 + c % ni, g.j0 + c / ni, best, best_id);
+          } else {
+            const int ni = g.i1 - g.i0 + 2, nc = ni * (g.j1 - g.j0 + 2);
+            const SegCull sc = seg_cull(g);
+            for (int c = gl; c < nc; c += kGroup) segment_vertex(H, g, sc, g.i0 + c % ni, g.j0 + c / ni, best, best_id);
+          }
+          if (best_id >= 0) atomicMin(&Lbest64[i], pack_best(best, best_id));
+        }
+        __syncthreads();
+      }
+#ifdef SIM_PHASE_TIMING
+      if (tid == 0 && blockIdx.x == 7) { a.dbg[14] += Lcount[5]; a.dbg[20] += Lcount[6]; a.dbg[15] += Lcount[3]; a.dbg[11] += Lcount[7]; a.dbg[21] += n_end; a.dbg[22] += n_mid; }
+#endif
+      // ---- B3: one thread per queued slot turns the selected feature into a contact record (end spheres,
+      //          then mid-segments in wavefronts of their own, so that a wavefront follows one path), from
+      //          the lower end of the workgroup up, while the forces are integrated from its upper end down
+      {
+        const int t_mid = (n_end + 63) & ~63;
+          for (int x = tid; x < t_mid + n_mid; x += kThreads) {
+            const bool mids = x >= t_mid;
+            if (!mids && x >= n_end) continue;
+            const int i = Lsurv[mids ? S * E - 1 - (x - t_mid) : x], ee = i % E, s = i / E;
+            const SlotGeom g = listed_geom(Ltslot[2 * s], ee, Ltslot[2 * s + 1]);
+            const Field H = field_of(ee);
+            ContactOut co = no_contact();
+            const unsigned long long bw = Lbest64[i];
+            const float bestd = __uint_as_float((unsigned)(bw >> 32));
+            const int besti = (int)(unsigned)bw;
+            if (!mids) {
+              // a centre underneath the surface overrides the nearest-triangle search
+              if (!underneath_contact(H, g, p_margin, co)) co = finish_sphere(H, g, p_margin, bestd, besti);
+            } else {
+              co = finish_segment(H, g, p_margin, bestd, besti);
+            }
+            if (co.active) {
+              store_record(Lrec, Lreci, s, ee, E, co);
+              Llist[atomicAdd(&Lcount[0], 1)] = i;
+            }
+          }
+        TMARK(12);
+        forces(kThreads - ((B * E + 63) & ~63));
+      }
     }
     __syncthreads();
     TMARK(3);
@@ -1255,7 +1267,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
               near = dd <= rr * rr;
             }
             const int pos = wave_alloc<1>(near ? 1 : 0, &Lpcount[1]);
-            if (near) Lnear[pos] = ea | (eb << 16);
+            if (near) Lmeet[pos] = ea | (eb << 16);
           }
           __syncthreads();
         }
@@ -1263,7 +1275,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         // Every hit also leaves (gap, key) as one 64-bit word whose unsigned order is that of the
         // pair: when a workgroup finds more than it can hold, the kPairCap contacts with the smallest
         // gap stay (ties: smaller key), whichever wavefront found what first.  Where they live:
-        // see make_plan (cleared again below, since the sweeps' copies share the space).
+        // see make_plan.
         unsigned long long* Lhit = reinterpret_cast<unsigned long long*>(lds + P.phit);
         const int hit_cap = P.hit_cap;
         // the segment-segment test of one candidate pair from the poses of phase A
@@ -1308,7 +1320,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         // Stage 1: bounding spheres of the two capsules only; what passes is listed as a packed word
         // (env and body of A, env and body of B: also the sort key of a hit).  The list lives where
         // the observations are staged at the end of the step.
-        unsigned* Lc2 = Lunit;
+        unsigned* Lc2 = Lpair;
         auto cull_pair = [&](int ea, int ba, int eb, int bb, bool valid) {
           bool pass = false;
           if (valid) {
@@ -1322,7 +1334,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           }
           const int pos = wave_alloc<1>(pass ? 1 : 0, &Lpcount[2]);
           if (pass) {
-            if (pos < unit_cap) Lc2[pos] = ((unsigned)ea << 20) | ((unsigned)eb << 8) | (unsigned)(ba << 4) | (unsigned)bb;
+            if (pos < pair_cap) Lc2[pos] = ((unsigned)ea << 20) | ((unsigned)eb << 8) | (unsigned)(ba << 4) | (unsigned)bb;
             else Lpcount[3] = 1;   // list full: everything is tested the slow way below
           }
         };
@@ -1334,7 +1346,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         const int n_near = m_group > 1 ? Lpcount[1] : 0;
         for (int nn = tid >> 8; nn < n_near; nn += kThreads >> 8) {
           const int cb = tid & 255, ba = cb >> 4, bb = cb & 15;
-          const int pr = Lnear[nn];
+          const int pr = Lmeet[nn];
           cull_pair(pr & 0xffff, ba, pr >> 16, bb, ba < B && bb < B);
         }
         __syncthreads();
@@ -1351,7 +1363,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
               test_pair(e, M.pair_a[pp], e, M.pair_b[pp], ((unsigned)e << 20) | ((unsigned)e << 8) | (unsigned)(M.pair_a[pp] << 4) | (unsigned)M.pair_b[pp], env_ok);
           for (int nn = tid >> 8; nn < n_near; nn += kThreads >> 8) {
             const int cb = tid & 255, ba = cb >> 4, bb = cb & 15;
-            const int pr = Lnear[nn], ea = pr & 0xffff, eb = pr >> 16;
+            const int pr = Lmeet[nn], ea = pr & 0xffff, eb = pr >> 16;
             test_pair(ea, ba, eb, bb, ((unsigned)ea << 20) | ((unsigned)eb << 8) | (unsigned)(ba << 4) | (unsigned)bb, ba < B && bb < B);
           }
         }
@@ -1376,7 +1388,6 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           }
           __syncthreads();
         }
-        for (int i = tid; i < 2 * n_hit; i += kThreads) reinterpret_cast<float*>(Lhit)[i] = 0.0f;   // finite numbers for the sweeps' copies
         if (tid < n_pc) {
           const unsigned key = __float_as_uint(Ltmp[tid * kPairWords]);
           int rank = 0;
@@ -1455,15 +1466,29 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     constexpr bool g_variants = EC >= 8;
     constexpr int kPairFew = 2;
     const bool gp_few = g_variants && PC != 0 && __ballot(gp_cnt > kPairFew) == 0ull;
-    // ---- C: block weight sums (and, on the plane, forces -> velocities)
-    float nbf = 0.0f;
-    if (is_body) {
-      nbf = (float)my_njs;
-      for (int k = 0; k < my_nslots; ++k) nbf += Lrec[((my_slot0 + k) * kRecWords + 10) * E + e];
-      nbf += gp_wsum;   // (a body thread is the first averaging thread of its own body)
-      Lnb[b * E + e] = nbf;
+    // ---- C: a body's sum of block weights.  With capsule-capsule contacts the body threads work it out for
+    //         everybody (and, on the plane, others integrate the forces); without, the lanes that need it
+    //         add up the body's three slots themselves, which saves a phase and its barrier.
+    if constexpr (PC != 0) {
+      if (is_body) {
+        float nbf = (float)my_njs;
+        for (int k = 0; k < my_nslots; ++k) nbf += Lrec[((my_slot0 + k) * kRecWords + 10) * E + e];
+        Lnb[b * E + e] = nbf + gp_wsum;   // (a body thread is the first averaging thread of its own body)
+      }
+      if (m_terrain == 0) forces(kThreads - ((B * E + 63) & ~63));   // plane: the torques are complete only now
     }
-    if (m_terrain == 0) forces();   // plane: no per-body pass, the torques are complete only now
+    auto weight_sum = [&](int bb, int ee) -> float {
+      if constexpr (PC != 0) return Lnb[bb * E + ee];
+      const int* tb = Ltjs + bb * (kMaxBodyJoints + 3);
+      const int slot0 = tb[1], nslots = tb[2];
+      float wk[3], nbf = (float)tb[0];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) wk[k] = Lrec[((slot0 + (k < nslots ? k : 0)) * kRecWords + 10) * E + ee];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) nbf += k < nslots ? wk[k] : 0.0f;
+      return nbf;
+    };
+    if (tid > 0 && tid < 8) Lcount[tid] = 0;   // for the next substep's search
     if (a.recs && sub == a.substeps - 1) {
       // export the records of the last substep, [N][S][12] words
       for (int i = tid; i < S * E * kRecWords; i += kThreads) {
@@ -1488,8 +1513,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           o[6] = __float_as_int(Lpq[tid * kPairWords + 5]); o[7] = __float_as_int(Lpq[tid * kPairWords + 4]);
         }
       }
+      __syncthreads();
     }
-    __syncthreads();
 
     TMARK(4);
     // ---- D: row constants
@@ -1511,23 +1536,23 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       for (int c = 0; c < 3; ++c) xo[c] = Lpos[(bo * 7 + c) * E + e];
       for (int c = 0; c < 4; ++c) qo[c] = Lpos[(bo * 7 + 3 + c) * E + e];
       for (int c = 0; c < 6; ++c) iwo[c] = Liw[(bo * kVS + c) * E + e];
-      float no = NS ? 1.0f : Lnb[bo * E + e], imo = Ltbody[4 * bo + 3];   // (Newton: no mass splitting)
+      float no = NS ? 1.0f : weight_sum(bo, e), imo = Ltbody[4 * bo + 3];   // (Newton: no mass splitting)
       if (ghost) {
         for (int c = 0; c < 3; ++c) xo[c] = 0.0f;
         qo[0] = 1.0f; qo[1] = qo[2] = qo[3] = 0.0f;
         for (int c = 0; c < 6; ++c) iwo[c] = 0.0f;
         no = 0.0f; imo = 0.0f;
       }
-      // anchors: own one here, the other side's through the lane swap
-      float Ro[9], lo[3], t0[3], pw[3], C[3], r[3];
+      // The other side's centre and anchor come through the lane swap.  The separation of the anchors
+      // and the lever arm are put together from differences of centres and of arms, which round at
+      // the size of a body and not at that of its distance from the origin.
+      float Ro[9], lo[3], t0[3], C[3], r[3];
       quat_to_mat(qo, Ro);
       for (int c = 0; c < 3; ++c) lo[c] = js_side ? jt.lb[c] : jt.la[c];
       mat_vec(Ro, lo, t0);
       for (int c = 0; c < 3; ++c) {
-        pw[c] = xo[c] + t0[c];
-        const float po = lane_swap1(pw[c]);
-        C[c] = sg * (pw[c] - po);                        // child anchor minus parent anchor
-        r[c] = 0.5f * (pw[c] + po) - xo[c];              // impulses act at the midpoint
+        C[c] = sg * ((xo[c] - lane_swap1(xo[c])) + (t0[c] - lane_swap1(t0[c])));   // child anchor minus parent anchor
+        r[c] = fma_(-0.5f * sg, C[c], t0[c]);            // impulses act at the midpoint
       }
       // the world's side of a joint adds nothing to J v (whatever velocity its lane reads)
       const float sgl = ghost ? 0.0f : sg;
@@ -1588,7 +1613,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       if (n_active > 0) {
         const int i = Llist[li < n_active ? li : n_active - 1];
         const int ee = i % E, sl = i / E, body = Ltslot[2 * sl];
-        build_contact_rows(cr, Lrec, Liw, Lnb, sl, ee, E, body, Ltbody[4 * body + 3], h, p_beta_c, p_vdepen, NS != 0);
+        build_contact_rows(cr, Lrec, Liw, NS ? 1.0f : weight_sum(body, ee), sl, ee, E, body, Ltbody[4 * body + 3], h, p_beta_c, p_vdepen, NS != 0);
         if constexpr (WS != 0)
           for (int r = 0; r < 3; ++r) cr.lam[r] = p_warm * Lwc[(sl * 3 + r) * E + ee];
       } else {
@@ -1615,29 +1640,31 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     };
 
     TMARK(5);
-    // The copies a body averages: NJ joint sides (unused entries point at joint 0's copy with
-    // weight 0) and its three contact slots (weight 0 when inactive).
+    // The copies a body averages: NJ joint sides and its three contact slots.  Entries that are not in use
+    // point at zeros and have weight 0 (the copies share their space with the terrain search, so only
+    // those that a block writes in every sweep are read).
     float g_inb = 0.0f;
     int gat_off[NJ], gat_slot[3];
     float gat_w[NJ + 3];
     {
       const int* tb = Ltjs + (g_on ? g_b : 0) * (kMaxBodyJoints + 3);
       const int g_njs = tb[0], g_slot0 = tb[1], g_nslots = tb[2];
-      const float g_nbf = g_on ? Lnb[g_b * E + e] : 0.0f;
+      const float g_nbf = g_on && NS == 0 ? weight_sum(g_b, e) : 0.0f;
       g_inb = g_nbf > 0.0f ? 1.0f / g_nbf : 0.0f;
 #pragma unroll
       for (int k = 0; k < NJ; ++k) {
         const bool used = g_on && k < g_njs;
         int js = used ? tb[3 + k] : 0;
-        gat_off[k] = ((js >> 1) * kJS + (js & 1) * 6) * E + e;
+        gat_off[k] = (used ? P.outj + ((js >> 1) * kJS + (js & 1) * 6) * E : P.zero) + e;
         gat_w[k] = used ? 1.0f : 0.0f;
       }
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         const bool used = g_on && k < g_nslots;
-        gat_slot[k] = (g_slot0 + (used ? k : 0)) * kCS * E + e;
-        gat_w[NJ + k] = used ? Lrec[((g_slot0 + k) * kRecWords + 10) * E + e] : 0.0f;
-        if constexpr (NS != 0) gat_w[NJ + k] = (used && Lreci[((g_slot0 + k) * kRecWords + 0) * E + e]) ? 1.0f : 0.0f;
+        float wk = used ? Lrec[((g_slot0 + k) * kRecWords + 10) * E + e] : 0.0f;
+        if constexpr (NS != 0) wk = wk > 0.0f ? 1.0f : 0.0f;
+        gat_w[NJ + k] = wk;
+        gat_slot[k] = (wk != 0.0f ? P.outc + (g_slot0 + k) * kCS * E : P.zero) + e;
       }
     }
     // no body of this wavefront has more than two joint sides: its averages read two joint copies
@@ -1655,8 +1682,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     auto gather_part = [&](auto nc_tag, int c0) {
       constexpr int NC = decltype(nc_tag)::value;
       if (g_on && g_inb > 0.0f) {
-        // every load is unconditional: unused entries read a valid location and enter the sum
-        // with weight 0 (the copy arrays only ever hold finite numbers); all reads are issued
+        // every load is unconditional: unused entries read zeros and enter the sum
+        // with weight 0; all reads are issued
         // before the first use so their LDS latency is paid once
         // The average is taken over the copies' differences from the snapshot, (sum of w_k (copy_k -
         // v0)) / W added to v0: the differences are small next to the velocity itself, so the sum
@@ -1673,12 +1700,12 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
 #pragma unroll
           for (int k = 0; k < KJ; ++k)
 #pragma unroll
-            for (int c = 0; c < NC; ++c) val[k][c] = Loutj[gat_off[k] + ho + c * E];
+            for (int c = 0; c < NC; ++c) val[k][c] = lds[gat_off[k] + ho + c * E];
           if constexpr (HC != 0) {
 #pragma unroll
             for (int k = 0; k < 3; ++k)
 #pragma unroll
-              for (int c = 0; c < NC; ++c) val[KJ + k][c] = Loutc[gat_slot[k] + ho + c * E];
+              for (int c = 0; c < NC; ++c) val[KJ + k][c] = lds[gat_slot[k] + ho + c * E];
           }
           __builtin_amdgcn_sched_group_barrier(0x100, NC == 3 ? (KJ + 1 + 3 * HC) * 2 : KJ + 1 + 3 * HC, 0);  // the DS reads first
 #pragma unroll
@@ -1686,12 +1713,12 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
 #pragma unroll
           for (int k = 0; k < KJ; ++k)
 #pragma unroll
-            for (int c = 0; c < NC; ++c) acc[c] += gat_w[k] * (val[k][c] - v0[c]);
+            for (int c = 0; c < NC; ++c) acc[c] = fma_(gat_w[k], val[k][c] - v0[c], acc[c]);
           if constexpr (HC != 0) {
 #pragma unroll
             for (int k = 0; k < 3; ++k)
 #pragma unroll
-              for (int c = 0; c < NC; ++c) acc[c] += gat_w[NJ + k] * (val[KJ + k][c] - v0[c]);
+              for (int c = 0; c < NC; ++c) acc[c] = fma_(gat_w[NJ + k], val[KJ + k][c] - v0[c], acc[c]);
           }
         };
         constexpr int kFew = NJ > 2 ? 2 : NJ;
@@ -1713,7 +1740,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
                 if (((refs >> 16) & 0xffff) == g_ref)
                   for (int c = 0; c < NC; ++c) acc[c] += Lpo[k * 12 + 6 + c0 + c];
               }
-              for (int c = 0; c < NC; ++c) acc[c] -= gp_wsum * v0[c];   // (their copies come multiplied by the weights)
+              for (int c = 0; c < NC; ++c) acc[c] = fma_(-gp_wsum, v0[c], acc[c]);   // (their copies come multiplied by the weights)
             } else {
               // the (weighted) copies of the listed contacts (the list holds the used entries first);
               // unused entries point at zeros
@@ -1737,11 +1764,11 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
               }
               // (the listed copies come multiplied by their weights: the snapshot's share goes off in one piece)
 #pragma unroll
-              for (int c = 0; c < NC; ++c) acc[c] -= gp_wsum * v0[c];
+              for (int c = 0; c < NC; ++c) acc[c] = fma_(-gp_wsum, v0[c], acc[c]);
             }
           }
         }
-        for (int c = 0; c < NC; ++c) Lvel[(g_b * kVS + c) * E + e + ho] = v0[c] + acc[c] * g_inb;
+        for (int c = 0; c < NC; ++c) Lvel[(g_b * kVS + c) * E + e + ho] = fma_(acc[c], g_inb, v0[c]);
       }
     };
     // one sweep of this thread's side of a capsule-capsule contact, if it has one
@@ -1768,6 +1795,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     // kept ones times the share) to its copies, and the average of the copies hands every body
     // the plain sum of them, as a sweep does with the increments.
     if constexpr (NS != 0) {
+#pragma clang fp contract(fast)
       // ---- S (Newton): the paper's solver (Section 3.1), a non-smooth Newton method whose every
       // iteration is solved by a fixed number of preconditioned conjugate-residual iterations.
       // Unknowns: the impulses lambda of all rows; u = v* + M^-1 J^T lambda; residual s = J u + bias.
@@ -1797,6 +1825,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           if (!Lreci[(i / E * kRecWords + 0) * E + i % E])
             for (int r = 0; r < 3; ++r) Lwc[(i / E * 3 + r) * E + i % E] = 0.0f;
       }
+      if (m_terrain == 0 && !jrole) forces(joint_threads);   // (the first gather is behind a barrier)
       if (jrole) build_joint_side(); else build_contact();
       for (int i = tid; i < 3 * nblk * E; i += kThreads) Lred[i] = 0.0f;   // inactive slots contribute nothing
       const int nr = jrole ? 6 : 3;
@@ -1863,11 +1892,11 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
 #pragma unroll
         for (int k = 0; k < NJ; ++k)
 #pragma unroll
-          for (int c = 0; c < kPartC; ++c) val[k][c] = Loutj[gat_off[k] + ho + c * E];
+          for (int c = 0; c < kPartC; ++c) val[k][c] = lds[gat_off[k] + ho + c * E];
 #pragma unroll
         for (int k = 0; k < 3; ++k)
 #pragma unroll
-          for (int c = 0; c < kPartC; ++c) val[NJ + k][c] = Loutc[gat_slot[k] + ho + c * E];
+          for (int c = 0; c < kPartC; ++c) val[NJ + k][c] = lds[gat_slot[k] + ho + c * E];
 #pragma unroll
         for (int c = 0; c < kPartC; ++c) {
           float acc = 0.0f;
@@ -2064,6 +2093,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     if (joint_wave) {
       build_joint_side();
       build_pair();
+      if (PC == 0 && m_terrain == 0) __syncthreads();   // (the velocities, which the other wavefronts integrate meanwhile)
       TMARK(17);
       float acc[3] = {0.0f, 0.0f, 0.0f};   // impulses of the positional rows so far (kept for the next substep)
       if constexpr (WS != 0) {
@@ -2098,13 +2128,13 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
             if (WS != 0 && it < 0) {
               dl = acc[k];
             } else {
-              const float part = jr.sg * vo[k] + cross_unit_dot(jr.sr, k, wo);
+              const float part = fma_(jr.sg, vo[k], cross_unit_dot(jr.sr, k, wo));
               const float jv = part + lane_swap1(part);
-              dl = jv * jr.pme[k] + jr.pnb[k];
+              dl = fma_(jv, jr.pme[k], jr.pnb[k]);
               if constexpr (WS != 0) acc[k] += dl;
             }
-            vo[k] += jr.sv * dl;
-            for (int c = 0; c < 3; ++c) wo[c] += jr.Y[k][c] * dl;
+            vo[k] = fma_(jr.sv, dl, vo[k]);
+            for (int c = 0; c < 3; ++c) wo[c] = fma_(jr.Y[k][c], dl, wo[c]);
           }
   #pragma unroll
           for (int k = 0; k < 3; ++k) {
@@ -2115,11 +2145,11 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
               const float part = dot(jr.sax[k], wo);
               const float jv = part + lane_swap1(part);
               // a limit row's impulse stays >= 0: max(lam + dl, 0) - lam = max(dl, -lam)
-              dl = fmaxf(jv * jr.ame[k] + jr.anb[k], jr.nl[k]);
+              dl = max_of(fma_(jv, jr.ame[k], jr.anb[k]), jr.nl[k]);
               jr.nl[k] -= dl;
               if constexpr (WS != 0) jr.lam[k] += dl;
             }
-            for (int c = 0; c < 3; ++c) wo[c] += jr.Z[k][c] * dl;
+            for (int c = 0; c < 3; ++c) wo[c] = fma_(jr.Z[k][c], dl, wo[c]);
           }
           if (ob >= 0)
             for (int c = 0; c < 3; ++c) {
@@ -2149,8 +2179,13 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           if (!Lreci[(i / E * kRecWords + 0) * E + i % E])
             for (int r = 0; r < 3; ++r) Lwc[(i / E * 3 + r) * E + i % E] = 0.0f;
       }
+      if (PC == 0 && m_terrain == 0) {
+        // plane: the torques are complete only now; the forces are integrated beside the joint rows
+        forces(joint_threads);
+      }
       build_contact();
       build_pair();
+      if (PC == 0 && m_terrain == 0) __syncthreads();
       // the starting impulses of the contacts beyond one per thread are set by the thread that
       // relaxes them in every sweep below (same index mapping), so no other thread's store is read
       for (int k = n_reg + (kThreads - 1 - tid); k < n_active; k += n_reg)
@@ -2169,7 +2204,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           const int i = Llist[k];
           const int ee = i % E, sl = i / E, body = Ltslot[2 * sl];
           ContactRows c2;
-          build_contact_rows(c2, Lrec, Liw, Lnb, sl, ee, E, body, Ltbody[4 * body + 3], h, p_beta_c, p_vdepen);
+          build_contact_rows(c2, Lrec, Liw, weight_sum(body, ee), sl, ee, E, body, Ltbody[4 * body + 3], h, p_beta_c, p_vdepen);
           for (int r = 0; r < 3; ++r) c2.lam[r] = overflow_lam(k, r);
           float vv[3], ww[3];
           for (int r = 0; r < 3; ++r) { vv[r] = Lvel[(body * kVS + r) * E + ee]; ww[r] = Lvel[(body * kVS + 3 + r) * E + ee]; }
@@ -2199,26 +2234,44 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       for (int c = 0; c < 4; ++c) q[c] = Lpos[(b * 7 + 3 + c) * E + e];
       // the solved velocities were left in LDS by the threads that averaged them
       for (int c = 0; c < 3; ++c) { v[c] = Lvel[(b * kVS + c) * E + e]; w[c] = Lvel[(b * kVS + 3 + c) * E + e]; }
-      float dl = __builtin_amdgcn_rcpf(1.0f + h * p_clin), da = __builtin_amdgcn_rcpf(1.0f + h * p_cang);
+      float dl = __builtin_amdgcn_rcpf(fma_(h, p_clin, 1.0f)), da = __builtin_amdgcn_rcpf(fma_(h, p_cang, 1.0f));
       for (int c = 0; c < 3; ++c) { v[c] *= dl; w[c] *= da; }
       const float w2 = dot(w, w);
       if (w2 > p_wmax * p_wmax) { float sc = p_wmax * __builtin_amdgcn_rsqf(w2); for (int c = 0; c < 3; ++c) w[c] *= sc; }
-      for (int c = 0; c < 3; ++c) x[c] += h * v[c];
+      for (int c = 0; c < 3; ++c) x[c] = fma_(h, v[c], x[c]);
       float dq[4];
-      dq[0] = -w[0] * q[1] - w[1] * q[2] - w[2] * q[3];
-      dq[1] = w[0] * q[0] + w[1] * q[3] - w[2] * q[2];
-      dq[2] = -w[0] * q[3] + w[1] * q[0] + w[2] * q[1];
-      dq[3] = w[0] * q[2] - w[1] * q[1] + w[2] * q[0];
+      dq[0] = fma_(-w[2], q[3], diff2(-w[0], q[1], w[1], q[2]));
+      dq[1] = fma_(-w[2], q[2], sum2(w[0], q[0], w[1], q[3]));
+      dq[2] = fma_(w[2], q[1], sum2(-w[0], q[3], w[1], q[0]));
+      dq[3] = fma_(w[2], q[0], diff2(w[0], q[2], w[1], q[1]));
       float hh = 0.5f * h;
-      for (int c = 0; c < 4; ++c) q[c] += hh * dq[c];
-      float inv = __builtin_amdgcn_rsqf(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
+      for (int c = 0; c < 4; ++c) q[c] = fma_(hh, dq[c], q[c]);
+      float inv = __builtin_amdgcn_rsqf(fma_(q[3], q[3], sum3(q[0], q[0], q[1], q[1], q[2], q[2])));
       for (int c = 0; c < 4; ++c) q[c] *= inv;
     }
-    __syncthreads();  // the next substep overwrites pose, counters and lists read above
+    // Phase A of the next substep follows without a barrier: since the last sweep's barrier a body's pose
+    // and velocity are touched by its own thread alone.  (Without a sweep there was none.)
+    if (a.iterations <= 0) __syncthreads();
     TMARK(7);
   }
 
   // ---- store state, publish final pose/velocity for packing
+  // What the end of the step needs of the launch arguments and of the model is read again here (two trips
+  // through the scalar cache) instead of being kept in scalar registers through all substeps.
+  {
+  const StepArgs& a = *reload_constant(reinterpret_cast<const StepArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr()));
+  const Model& M = *reload_constant(a.M);
+  const Field H0 = make_field(M, a.heights, a.coarse);
+  const int N = a.N, m_root = M.root, m_terrain = M.terrain_kind;
+  const int obs_row = obs_dim + (M.height_map ? kHmRows * kHmCols : 0);   // row of the caller's array
+  int m_feet = 0;   // the feet's bodies, a byte each
+#pragma unroll
+  for (int f = 0; f < kMaxFeet; ++f) m_feet |= (f < F ? M.feet[f] : 0) << (8 * f);
+  auto agent_at = [&](int place) -> int {
+    if constexpr (PC != 0) { if (a.place_env && place < N) return a.place_env[place]; }
+    return place;
+  };
+  const int agent = agent_at(env);
   __syncthreads();
   TMARK(8);
   if (is_body) {
@@ -2244,6 +2297,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   const bool may_reset = a.task.enabled && a.task.auto_reset && a.count_step;
   // ---- observation vector (Table 2 "Ours"), per joint part
   auto pack_joints = [&](auto pass_c) {
+#pragma clang fp contract(fast)
   constexpr int pass = decltype(pass_c)::value;
   if (is_joint && (pass == 0 || Lrst[e])) {
     const JointTab& jt = Ltjoint[idx];
@@ -2282,6 +2336,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   float* Lhm = Loutj;     // [5][E]: centre of mass (world), cosine and sine of the yaw (the sweep copies are free by now)
   const bool m_height_map = obs_row > obs_dim;
   auto pack_root = [&](auto pass_c) {
+#pragma clang fp contract(fast)
   constexpr int pass = decltype(pass_c)::value;
   const int part_0 = (J * E + 63) & ~63, part_n = (E + 63) & ~63;
   auto part_env = [&](int part) -> int {   // env of this thread in that part, or -1
@@ -2375,6 +2430,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   int steps_before = 0;
   if (tid < E && (blockIdx.x * E + tid) < N) steps_before = a.steps[agent_at(blockIdx.x * E + tid)];
   auto finish_env = [&]() -> bool {
+#pragma clang fp contract(fast)
   bool reset_now = false;
   if (tid < E && (blockIdx.x * E + tid) < N) {
     const int ee = tid, env_e = agent_at(blockIdx.x * E + tid);
@@ -2512,7 +2568,9 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       }
     }
   }
+  }
   TMARK(9);
 }
+#pragma clang fp contract(fast)
 
 }  // namespace sim355
