@@ -130,6 +130,7 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.tbody = o; o += 4 * B;
   p.tin = o; o += 6 * B;
   p.tjoint = o; o += J * (int)(sizeof(JointTab) / 4);
+  if (with_patch) o = (o + 3) & ~3;   // (written four samples at a time)
   p.patch = o; o += with_patch ? E * kPatch * kPatch : 0;
   p.mip = o; o += with_patch ? E * kPatchBlocks * kPatchBlocks : 0;
   p.pq = o; o += pairs ? kPairCap * kPairWords : 0;   // sorted queue of the substep's contacts
@@ -757,9 +758,20 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   const float h = a.h;
 
   // ---- load: body state into registers, clipped actions into LDS
+  // The heightfield samples around an env's root body are copied by a share of the threads of its own
+  // (the whole robot stays within them during one step; anything outside falls back to global memory).
+  // What decides where the copy starts is asked for before everything else, so that two trips to
+  // memory, not three, lie between the launch and the copy.
+  const bool copy_field = use_patch && a.substeps > 0;   // (a launch without substeps never searches the terrain)
+  const int tpe = kThreads / E, pe = tid / tpe, pl = tid - pe * tpe;
+  float root_wx = 0.0f, root_wy = 0.0f;
+  if (copy_field && pe < E && blockIdx.x * E + pe < N) {
+    const int ag = agent_at(blockIdx.x * E + pe);
+    const float* st = a.state + (size_t)M.root * N + ag;
+    root_wx = st[0] + a.origins[3 * ag]; root_wy = st[(size_t)B * N] + a.origins[3 * ag + 1];
+  }
   float x[3] = {0, 0, 0}, q[4] = {1, 0, 0, 0}, v[3] = {0, 0, 0}, w[3] = {0, 0, 0};
   int my_slot0 = 0, my_nslots = 0, my_njs = 0;
-  float root_ox = 0.0f, root_oy = 0.0f;
   const int b = idx;
   if (is_body) {
     const float* st = a.state + (size_t)b * N + agent;
@@ -770,7 +782,30 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     w[0] = st[10 * fs]; w[1] = st[11 * fs]; w[2] = st[12 * fs];
     const BodyTab& bt = M.bodies[b];
     my_slot0 = bt.slot0; my_nslots = bt.n_slots; my_njs = bt.n_joint_sides;
-    if (b == M.root) { root_ox = a.origins[3 * agent]; root_oy = a.origins[3 * agent + 1]; }   // for the heightfield copy
+  }
+  if (copy_field && pe < E) {
+    // four samples at a time (a row of the copy is seven of them; rows start at any sample), all of a
+    // thread's reads in flight together
+    constexpr int kQuads = kPatch * kPatch / 4, kShare = EC > 0 ? kThreads / EC : 64, kInFlight = (kQuads + kShare - 1) / kShare;
+    typedef float quad __attribute__((ext_vector_type(4), aligned(4)));
+    typedef float quad16 __attribute__((ext_vector_type(4)));
+    float ci = floorf((root_wx - M.hox) * M.inv_cell), cj = floorf((root_wy - M.hoy) * M.inv_cell);
+    ci = fminf(fmaxf(ci - (float)(kPatch / 2), 0.0f), (float)(M.nx - kPatch));
+    cj = fminf(fmaxf(cj - (float)(kPatch / 2), 0.0f), (float)(M.ny - kPatch));
+    const int i0 = (int)ci, j0 = (int)cj;
+    if (pl == 0) { Lporg[2 * pe] = i0; Lporg[2 * pe + 1] = j0; }
+    const float* h0 = a.heights + j0 * H0.nx + i0;
+    for (int k0 = pl; k0 < kQuads; k0 += kInFlight * tpe) {
+      quad hv[kInFlight];
+#pragma unroll
+      for (int k = 0; k < kInFlight; ++k) {
+        const int i = k0 + k * tpe < kQuads ? k0 + k * tpe : k0, row = i / (kPatch / 4), c4 = i - row * (kPatch / 4);
+        hv[k] = *reinterpret_cast<const quad*>(h0 + row * H0.nx + 4 * c4);
+      }
+#pragma unroll
+      for (int k = 0; k < kInFlight; ++k)
+        if (k0 + k * tpe < kQuads) *reinterpret_cast<quad16*>(Lpatch + pe * (kPatch * kPatch) + 4 * (k0 + k * tpe)) = hv[k];
+    }
   }
   // uniform parameters and this thread's joint, read once
   const float g0 = M.g[0], g1 = M.g[1], g2 = M.g[2];
@@ -822,45 +857,11 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   if constexpr (PC != 0) {
     if (tid < 12) Lpo[kPairCap * 12 + tid] = 0.0f;   // the entry unused list slots point at
   }
-  // contact records start cleared (a step with zero substeps packs "no contact")
-  for (int i = tid; i < S * E; i += kThreads) {
-    Lreci[(i / E * kRecWords + 0) * E + i % E] = 0;
-    Lreci[(i / E * kRecWords + 1) * E + i % E] = -1;
-    Lreci[(i / E * kRecWords + 2) * E + i % E] = -1;
-    for (int c = 3; c < kRecWords; ++c) Lrec[(i / E * kRecWords + c) * E + i % E] = 0.0f;
-  }
+  // a step without substeps packs "no contact" (otherwise the contact phase clears what it does not set)
+  if (a.substeps == 0)
+    for (int i = tid; i < S * E; i += kThreads) Lreci[(i / E * kRecWords + 0) * E + i % E] = 0;
 
-  // per-env copy of the heightfield samples around the root body (the whole robot stays
-  // within it during one step; anything outside falls back to global memory)
-  if (use_patch && a.substeps > 0) {   // (a launch without substeps never searches the terrain)
-    // where the copy starts: from the root body's position, which its body thread has just loaded
-    if (is_body && b == M.root) {
-      const float rx = x[0] + root_ox, ry = x[1] + root_oy;
-      float ci = floorf((rx - M.hox) * M.inv_cell), cj = floorf((ry - M.hoy) * M.inv_cell);
-      ci = fminf(fmaxf(ci - (float)(kPatch / 2), 0.0f), (float)(M.nx - kPatch));
-      cj = fminf(fmaxf(cj - (float)(kPatch / 2), 0.0f), (float)(M.ny - kPatch));
-      Lporg[2 * e] = (int)ci; Lporg[2 * e + 1] = (int)cj;
-    }
-    if (tid < E && blockIdx.x * E + tid >= N) { Lporg[2 * tid] = 0; Lporg[2 * tid + 1] = 0; }
-    __syncthreads();
-    // many samples per thread in flight at a time (the reads come from L2, one at a time each
-    // would cost its full latency): the wide workgroup fetches the copies of 16 envs in one round
-    constexpr int kInFlight = NT >= 768 ? 17 : 13;
-    for (int i0 = tid; i0 < E * kPatch * kPatch; i0 += kInFlight * kThreads) {
-      float hv[kInFlight];
-#pragma unroll
-      for (int k = 0; k < kInFlight; ++k) {
-        const int i = i0 + k * kThreads;
-        hv[k] = 0.0f;
-        if (i < E * kPatch * kPatch) {
-          int ee = i / (kPatch * kPatch), r = i - ee * (kPatch * kPatch), pj = r / kPatch, pi = r - pj * kPatch;
-          hv[k] = a.heights[(Lporg[2 * ee + 1] + pj) * H0.nx + Lporg[2 * ee] + pi];
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < kInFlight; ++k)
-        if (i0 + k * kThreads < E * kPatch * kPatch) Lpatch[i0 + k * kThreads] = hv[k];
-    }
+  if (copy_field) {
     __syncthreads();
     for (int i = tid; i < E * kPatchBlocks * kPatchBlocks; i += kThreads) {
       int ee = i / (kPatchBlocks * kPatchBlocks), r = i - ee * (kPatchBlocks * kPatchBlocks);
@@ -1497,6 +1498,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         if (env_i < N) {
           int word = Lreci[(s * kRecWords + wd) * E + ee];
           if (!Lreci[(s * kRecWords + 0) * E + ee]) word = (wd == 1 || wd == 2) ? -1 : 0;   // inactive: canonical record
+          if (wd == kRecWords - 1) word = 0;   // (not in use)
           a.recs[((size_t)agent_at(env_i) * S + s) * kRecWords + wd] = word;
         }
       }
