@@ -70,6 +70,9 @@ struct Model {
   int32_t n_pairs, group, n_agent_pairs;
   uint8_t pair_a[kMaxPairs], pair_b[kMaxPairs];
   uint8_t agent_pair_a[kMaxAgentPairs], agent_pair_b[kMaxAgentPairs];
+  // Order in which a reset places the joints' children: all of one level at once, parents' levels first
+  // (one joint after another where a body is the child of several).
+  int32_t n_levels, joint_level[kMaxJoints];
   BodyTab bodies[kMaxBodies];
   JointTab joints[kMaxJoints];
   SlotTab slots[kMaxSlots];

@@ -151,6 +151,9 @@ static int build_model(const sim_desc_t* d, int num_envs, Model* m) {
   }
   m->S = S;
   int D = 0;
+  std::vector<int> joint_of(m->B, -1);   // the joint a body is the child of
+  bool tree = true;
+  m->n_levels = 0;
   std::vector<char> placed(m->B, 0);
   placed[0] = 1;
   for (int j = 0; j < m->J; ++j) {
@@ -159,6 +162,8 @@ static int build_model(const sim_desc_t* d, int num_envs, Model* m) {
       return fail(SIM_ERR_ARG, "joint %d: parent/child out of range", j);
     if (s.parent >= 0 && !placed[s.parent]) return fail(SIM_ERR_ARG, "joint %d: joints must be listed parents-first from body 0", j);
     placed[s.child] = 1;
+    if (joint_of[s.child] >= 0) tree = false;
+    joint_of[s.child] = j;
     JointTab& t = m->joints[j];
     t.parent = s.parent; t.child = s.child;
     for (int c = 0; c < 3; ++c) {
@@ -188,6 +193,14 @@ static int build_model(const sim_desc_t* d, int num_envs, Model* m) {
       if (bt.n_joint_sides >= kMaxBodyJoints) return fail(SIM_ERR_ARG, "body %d belongs to more than %d joints", body, kMaxBodyJoints);
       bt.joint_sides[bt.n_joint_sides++] = 2 * j + side;
     }
+  }
+  // a reset places a level of joints at a time (where the joints are no tree listed from its root: one by one, in order)
+  for (int j = 0; j < m->J && tree; ++j)
+    if (d->joints[j].parent >= 0 && joint_of[d->joints[j].parent] > j) tree = false;
+  for (int j = 0; j < m->J; ++j) {
+    const int up = d->joints[j].parent >= 0 ? joint_of[d->joints[j].parent] : -1;
+    m->joint_level[j] = !tree ? j : (up >= 0 ? m->joint_level[up] + 1 : 0);
+    if (m->joint_level[j] >= m->n_levels) m->n_levels = m->joint_level[j] + 1;
   }
   m->D = D;
   for (int b = 0; b < m->B; ++b)
@@ -421,36 +434,6 @@ __global__ void gen_contacts_kernel(const Model* Mp, const float* __restrict__ h
   r[10] = __float_as_int(c.w); r[11] = 0;
 }
 
-// Seeded reset of one env by one thread: the poses are built in local arrays, then stored.
-struct LocalPoses {
-  float x[kMaxBodies][3], q[kMaxBodies][4], v[kMaxBodies][3], w[kMaxBodies][3];
-  __device__ float& X(int b, int c) { return x[b][c]; }
-  __device__ float& Q(int b, int c) { return q[b][c]; }
-  __device__ float& V(int b, int c) { return v[b][c]; }
-  __device__ float& W(int b, int c) { return w[b][c]; }
-};
-__device__ void reset_one_env(const Model& M, float* __restrict__ state, int32_t* __restrict__ steps, int env,
-                              uint64_t seed, int N) {
-  LocalPoses P;
-  reset_pose(M, env, seed, P);
-  const size_t fs = (size_t)M.B * N;
-  for (int b = 0; b < M.B; ++b) {
-    float* st = state + (size_t)b * N + env;
-    for (int c = 0; c < 3; ++c) st[c * fs] = P.x[b][c];
-    for (int c = 0; c < 4; ++c) st[(3 + c) * fs] = P.q[b][c];
-    for (int c = 0; c < 3; ++c) { st[(7 + c) * fs] = P.v[b][c]; st[(10 + c) * fs] = P.w[b][c]; }
-  }
-  steps[env] = 0;
-}
-
-__global__ void reset_kernel(const Model* Mp, float* __restrict__ state, int32_t* __restrict__ steps,
-                             const uint8_t* __restrict__ mask, uint64_t seed, int N) {
-  int env = blockIdx.x * blockDim.x + threadIdx.x;
-  if (env >= N) return;
-  if (mask && !mask[env]) return;
-  reset_one_env(*Mp, state, steps, env, seed, N);
-}
-
 // Warm start: what is kept from step to step ([rows][N], rows = 6 per joint or 3 per slot) is
 // dropped for the envs of the mask (NULL: all).
 __global__ void clear_kept_kernel(float* __restrict__ lam, const uint8_t* __restrict__ mask, int rows, int N) {
@@ -485,9 +468,13 @@ __global__ void task_init_kernel(const Model* Mp, const float* __restrict__ stat
 }
 
 // ---------------------------------------------------------------- launches
+struct ResetCall {
+  const uint8_t* mask;
+  uint64_t seed;
+};
 static int launch_step(sim* s, const float* actions, float h, int substeps, int iterations, int count_step,
                        hipStream_t st, float* obs_out = nullptr, float* reward_out = nullptr,
-                       uint8_t* done_out = nullptr) {
+                       uint8_t* done_out = nullptr, const ResetCall* reset = nullptr) {
   const Model& m = s->host_model;
   StepArgs a;
   a.M = reinterpret_cast<const Model*>(s->ws + s->lay.model);
@@ -505,6 +492,7 @@ static int launch_step(sim* s, const float* actions, float h, int substeps, int 
   a.N = s->N; a.E = s->E; a.substeps = substeps; a.iterations = iterations; a.count_step = count_step;
   a.h = h;
   a.obs_out = obs_out; a.reward_out = reward_out; a.done_out = done_out;
+  a.reset = reset != nullptr; a.reset_mask = reset ? reset->mask : nullptr; a.reset_seed = reset ? reset->seed : 0;
   a.task = s->task;
   a.task_i = reinterpret_cast<int32_t*>(s->ws + s->lay.task_i);
   a.push = reinterpret_cast<float*>(s->ws + s->lay.push);
@@ -751,15 +739,11 @@ extern "C" int sim_get_kept_impulses(sim_t* s, float* joint_rows_dev, float* slo
 extern "C" int sim_reset(sim_t* s, const uint8_t* env_mask_dev, uint64_t seed, void* stream) {
   if (!s) return fail(SIM_ERR_ARG, "sim is NULL");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(reset_kernel, dim3(blocks_for(s->N, 64)), dim3(64), 0, st,
-                     reinterpret_cast<const Model*>(s->ws + s->lay.model),
-                     reinterpret_cast<float*>(s->ws + s->lay.state),
-                     reinterpret_cast<int32_t*>(s->ws + s->lay.steps), env_mask_dev, seed, s->N);
-  HIP_TRY(hipGetLastError());
   int rc = clear_kept(s, env_mask_dev, st);
   if (rc) return rc;
   s->recs_valid = 0;
-  return launch_step(s, nullptr, 1.0f, 0, 0, 0, st);
+  const ResetCall reset{env_mask_dev, seed};
+  return launch_step(s, nullptr, 1.0f, 0, 0, 0, st, nullptr, nullptr, nullptr, &reset);
 }
 
 // One env-step is one launch of the fused kernel (with the task logic's auto-reset, the envs

@@ -75,6 +75,9 @@ struct StepArgs {
   int32_t* pair_recs;    // [grid][kPairCap][8] capsule-capsule contacts of the last substep, or null
   int32_t* pair_count;   // [grid] their number per workgroup
   int32_t* pair_dropped; // [1] contacts dropped because a workgroup found more than kPairCap
+  const uint8_t* reset_mask; // sim_reset (a launch without substeps): which envs (null: all), the seed, and whether
+  uint64_t reset_seed;
+  int reset;
   const int32_t* place_env;  // [N] agent standing at every place of the launch, or null: agent = place
 };
 
@@ -547,68 +550,67 @@ __device__ inline void task_draw_target(const TaskParams& t, int env, int episod
 // through the joint list; the top of the tree gets one uniform linear velocity and no spin, a
 // child turns with its parent plus its hinge rates and moves so that the two anchor points of its
 // joint share one velocity (the world as a parent stands still).
-// `P` holds the state while it is built: P.X(b, c), P.Q(b, c), P.V(b, c), P.W(b, c) are
-// references to component c of position, quaternion, linear and angular velocity of body b (local
-// arrays for the stand-alone reset kernels, the env's columns of the pose and velocity arrays in
-// LDS for the reset at the end of a step).
-template <class Poses>
-__device__ inline void reset_pose(const Model& M, int env, uint64_t seed, Poses& P) {
+// Built by a thread per body and joint: a joint's draws depend on nothing else, its child's pose on the
+// parent's, so the joints are placed level by level (Model::joint_level).
+struct ResetDraw {
+  float dq[4], rate[3];   // rotation of the child in the parent's frame, hinge rates
+};
+__device__ __forceinline__ void reset_draw_joint(const Model& M, int j, int env, uint64_t seed, ResetDraw& d) {
   const float a = M.reset_noise;
-  float off[3], vel[3];
-  for (int c = 0; c < 3; ++c) {
-    off[c] = a * (2.0f * reset_uniform(seed, env, c) - 1.0f);
-    vel[c] = a * (2.0f * reset_uniform(seed, env, 3 + c) - 1.0f);
+  const JointTab& jt = M.joints[j];
+  float phi[3] = {0, 0, 0};
+  for (int k = 0; k < 3; ++k) {
+    d.rate[k] = 0.0f;
+    if (jt.mode[k] != 1) continue;
+    float th = a * (2.0f * reset_uniform(seed, env, 8 + 3 * j + k) - 1.0f);
+    th = fminf(fmaxf(th, jt.lo[k]), jt.hi[k]);
+    for (int c = 0; c < 3; ++c) phi[c] += th * jt.axes[k][c];
+    d.rate[k] = a * (2.0f * reset_uniform(seed, env, 256 + 3 * j + k) - 1.0f);
   }
-  for (int b = 0; b < M.B; ++b) {
-    for (int c = 0; c < 3; ++c) P.X(b, c) = M.bodies[b].rest_pos[c] + off[c];
-    P.Q(b, 0) = 1.0f; P.Q(b, 1) = 0.0f; P.Q(b, 2) = 0.0f; P.Q(b, 3) = 0.0f;
-    for (int c = 0; c < 3; ++c) { P.V(b, c) = vel[c]; P.W(b, c) = 0.0f; }
+  const float ang = sqrtf(dot(phi, phi));
+  if (ang < 1e-12f) { d.dq[0] = 1.0f; d.dq[1] = 0.5f * phi[0]; d.dq[2] = 0.5f * phi[1]; d.dq[3] = 0.5f * phi[2]; }
+  else { const float sn = sinf(0.5f * ang) / ang; d.dq[0] = cosf(0.5f * ang); d.dq[1] = sn * phi[0]; d.dq[2] = sn * phi[1]; d.dq[3] = sn * phi[2]; }
+}
+// the child of one joint, from its parent (poses and velocities in LDS)
+struct LdsPoses {
+  float* Lpos; float* Lvel; int E, ee;
+  __device__ float& X(int b, int c) { return Lpos[(b * 7 + c) * E + ee]; }
+  __device__ float& Q(int b, int c) { return Lpos[(b * 7 + 3 + c) * E + ee]; }
+  __device__ float& V(int b, int c) { return Lvel[(b * kVS + c) * E + ee]; }
+  __device__ float& W(int b, int c) { return Lvel[(b * kVS + 3 + c) * E + ee]; }
+};
+__device__ __forceinline__ void reset_place_joint(const JointTab& jt, const ResetDraw& d, LdsPoses P) {
+  float qa[4] = {1, 0, 0, 0}, xa[3] = {0, 0, 0}, va[3] = {0, 0, 0}, wa[3] = {0, 0, 0};
+  if (jt.parent >= 0) {
+    for (int c = 0; c < 4; ++c) qa[c] = P.Q(jt.parent, c);
+    for (int c = 0; c < 3; ++c) { xa[c] = P.X(jt.parent, c); va[c] = P.V(jt.parent, c); wa[c] = P.W(jt.parent, c); }
   }
-  for (int j = 0; j < M.J; ++j) {
-    const JointTab& jt = M.joints[j];
-    float phi[3] = {0, 0, 0};
-    for (int k = 0; k < 3; ++k) {
-      if (jt.mode[k] != 1) continue;
-      float th = a * (2.0f * reset_uniform(seed, env, 8 + 3 * j + k) - 1.0f);
-      th = fminf(fmaxf(th, jt.lo[k]), jt.hi[k]);
-      for (int c = 0; c < 3; ++c) phi[c] += th * jt.axes[k][c];
-    }
-    float ang = sqrtf(dot(phi, phi));
-    float dq[4];
-    if (ang < 1e-12f) { dq[0] = 1.0f; dq[1] = 0.5f * phi[0]; dq[2] = 0.5f * phi[1]; dq[3] = 0.5f * phi[2]; }
-    else { float s = sinf(0.5f * ang) / ang; dq[0] = cosf(0.5f * ang); dq[1] = s * phi[0]; dq[2] = s * phi[1]; dq[3] = s * phi[2]; }
-    float qa[4] = {1, 0, 0, 0}, xa[3] = {0, 0, 0}, va[3] = {0, 0, 0}, wa[3] = {0, 0, 0};
-    if (jt.parent >= 0) {
-      for (int c = 0; c < 4; ++c) qa[c] = P.Q(jt.parent, c);
-      for (int c = 0; c < 3; ++c) { xa[c] = P.X(jt.parent, c); va[c] = P.V(jt.parent, c); wa[c] = P.W(jt.parent, c); }
-    }
-    float qb[4];
-    qb[0] = qa[0] * dq[0] - qa[1] * dq[1] - qa[2] * dq[2] - qa[3] * dq[3];
-    qb[1] = qa[0] * dq[1] + qa[1] * dq[0] + qa[2] * dq[3] - qa[3] * dq[2];
-    qb[2] = qa[0] * dq[2] - qa[1] * dq[3] + qa[2] * dq[0] + qa[3] * dq[1];
-    qb[3] = qa[0] * dq[3] + qa[1] * dq[2] - qa[2] * dq[1] + qa[3] * dq[0];
-    float inv = 1.0f / sqrtf(qb[0] * qb[0] + qb[1] * qb[1] + qb[2] * qb[2] + qb[3] * qb[3]);
-    for (int c = 0; c < 4; ++c) qb[c] *= inv;
-    float Ra[9], Rb[9], t0[3], t1[3];
-    quat_to_mat(qa, Ra);
-    quat_to_mat(qb, Rb);
-    mat_vec(Ra, jt.la, t0);
-    mat_vec(Rb, jt.lb, t1);
-    for (int c = 0; c < 4; ++c) P.Q(jt.child, c) = qb[c];
-    for (int c = 0; c < 3; ++c) P.X(jt.child, c) = xa[c] + t0[c] - t1[c];
-    float wb[3] = {wa[0], wa[1], wa[2]};
-    for (int k = 0; k < 3; ++k) {
-      if (jt.mode[k] != 1) continue;
-      const float rate = a * (2.0f * reset_uniform(seed, env, 256 + 3 * j + k) - 1.0f);
-      float ak[3];
-      mat_vec(Ra, jt.axes[k], ak);
-      for (int c = 0; c < 3; ++c) wb[c] += rate * ak[c];
-    }
-    float ca[3], cb[3];
-    cross(wa, t0, ca);
-    cross(wb, t1, cb);
-    for (int c = 0; c < 3; ++c) { P.W(jt.child, c) = wb[c]; P.V(jt.child, c) = va[c] + ca[c] - cb[c]; }
+  const float* dq = d.dq;
+  float qb[4];
+  qb[0] = qa[0] * dq[0] - qa[1] * dq[1] - qa[2] * dq[2] - qa[3] * dq[3];
+  qb[1] = qa[0] * dq[1] + qa[1] * dq[0] + qa[2] * dq[3] - qa[3] * dq[2];
+  qb[2] = qa[0] * dq[2] - qa[1] * dq[3] + qa[2] * dq[0] + qa[3] * dq[1];
+  qb[3] = qa[0] * dq[3] + qa[1] * dq[2] - qa[2] * dq[1] + qa[3] * dq[0];
+  const float inv = 1.0f / sqrtf(qb[0] * qb[0] + qb[1] * qb[1] + qb[2] * qb[2] + qb[3] * qb[3]);
+  for (int c = 0; c < 4; ++c) qb[c] *= inv;
+  float Ra[9], Rb[9], t0[3], t1[3];
+  quat_to_mat(qa, Ra);
+  quat_to_mat(qb, Rb);
+  mat_vec(Ra, jt.la, t0);
+  mat_vec(Rb, jt.lb, t1);
+  for (int c = 0; c < 4; ++c) P.Q(jt.child, c) = qb[c];
+  for (int c = 0; c < 3; ++c) P.X(jt.child, c) = xa[c] + t0[c] - t1[c];
+  float wb[3] = {wa[0], wa[1], wa[2]};
+  for (int k = 0; k < 3; ++k) {
+    if (jt.mode[k] != 1) continue;
+    float ak[3];
+    mat_vec(Ra, jt.axes[k], ak);
+    for (int c = 0; c < 3; ++c) wb[c] += d.rate[k] * ak[c];
   }
+  float ca[3], cb[3];
+  cross(wa, t0, ca);
+  cross(wb, t1, cb);
+  for (int c = 0; c < 3; ++c) { P.W(jt.child, c) = wb[c]; P.V(jt.child, c) = va[c] + ca[c] - cb[c]; }
 }
 // Start of an episode for the task logic (Section 4.1): counters cleared, first push time and
 // (flagrun) first target drawn around the root.
@@ -619,15 +621,6 @@ __device__ inline void task_begin_episode(const TaskParams& t, int32_t* __restri
   task_i[4 * env + 3] = episode;
   if (t.period > 0) task_draw_target(t, env, episode, 0, rx, ry, targets + 2 * env);
 }
-// the env's column of the pose array in LDS ([body][7][E]) as the place reset_pose builds in
-struct LdsPoses {
-  float* Lpos; float* Lvel; int E, ee;
-  __device__ float& X(int b, int c) { return Lpos[(b * 7 + c) * E + ee]; }
-  __device__ float& Q(int b, int c) { return Lpos[(b * 7 + 3 + c) * E + ee]; }
-  __device__ float& V(int b, int c) { return Lvel[(b * kVS + c) * E + ee]; }
-  __device__ float& W(int b, int c) { return Lvel[(b * kVS + 3 + c) * E + ee]; }
-};
-
 // (squared distance, feature id) as one 64-bit word whose unsigned order is the lexicographic
 // order of the pair (squared distances are non-negative, ids non-negative)
 __device__ __forceinline__ unsigned long long pack_best(float d2, int id) {
@@ -2295,13 +2288,17 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   // env whose episode ends in pass 0 is put back to a fresh initial state right here, and pass 1
   // packs the observation of that state for it (no action, no contact), so the caller gets the
   // finished step's reward and done flag next to the first observation of the next episode.
-  int* Lrst = reinterpret_cast<int*>(Lpush);   // [E]: env was reset in pass 0 (the pushes are no longer read)
+  // sim_reset is a launch without substeps that goes straight to the reset and packs every env in pass 1.
+  // (Two copies of the packing: as a loop over the passes the addresses of both are computed ahead of it,
+  // 1.3 us of a step of 16 ants.)
+  int* Lrst = reinterpret_cast<int*>(Lpush);   // [E]: env is reset (the pushes are no longer read)
   const bool may_reset = a.task.enabled && a.task.auto_reset && a.count_step;
+  const bool only_reset = a.substeps == 0 && a.reset;
   // ---- observation vector (Table 2 "Ours"), per joint part
   auto pack_joints = [&](auto pass_c) {
 #pragma clang fp contract(fast)
   constexpr int pass = decltype(pass_c)::value;
-  if (is_joint && (pass == 0 || Lrst[e])) {
+  if (is_joint && (pass == 0 || only_reset || Lrst[e])) {
     const JointTab& jt = Ltjoint[idx];
     const int pa = jt.parent, pb = jt.child;
     float qa[4] = {1, 0, 0, 0}, wa[3] = {0, 0, 0}, qb[4], wb[3];
@@ -2346,7 +2343,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     if (t0 + part_n > kThreads) t0 = 0;
     const int ee = tid - t0;
     if (ee < 0 || ee >= E || blockIdx.x * E + ee >= N) return -1;
-    return pass == 0 || Lrst[ee] ? ee : -1;
+    return pass == 0 || only_reset || Lrst[ee] ? ee : -1;
   };
   auto yaw_of = [&](int ee, float& rx, float& ry) -> float {
     rx = Lpos[(m_root * 7 + 0) * E + ee]; ry = Lpos[(m_root * 7 + 1) * E + ee];
@@ -2430,7 +2427,9 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   const int m_max_steps = M.max_steps;
   const float m_alive = M.alive_bonus, m_term_height = M.term_height;
   int steps_before = 0;
-  if (tid < E && (blockIdx.x * E + tid) < N) steps_before = a.steps[agent_at(blockIdx.x * E + tid)];
+  if (tid < E && (blockIdx.x * E + tid) < N) {
+    steps_before = a.steps[agent_at(blockIdx.x * E + tid)];
+  }
   auto finish_env = [&]() -> bool {
 #pragma clang fp contract(fast)
   bool reset_now = false;
@@ -2480,35 +2479,77 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     // (one copy each: the caller's array when there is one, else the library's)
     (a.reward_out ? a.reward_out : a.reward)[env_e] = rew;
     (a.done_out ? a.done_out : a.done)[env_e] = dn;
-    if (reset_now) {
-      // next episode: the reset recipe with that episode's seed, built in this env's column of
-      // the pose array (no other thread reads it before the barrier below)
-      const int episode = a.task_i[4 * env_e + 3] + 1;
-      LdsPoses poses{Lpos, Lvel, E, ee};
-      reset_pose(M, env_e, a.task.seed + (uint64_t)episode * kEpisodeStride, poses);
-      a.steps[env_e] = 0;
-      task_begin_episode(a.task, a.task_i, a.targets, env_e, episode, Lpos[(rb * 7 + 0) * E + ee], Lpos[(rb * 7 + 1) * E + ee]);
-    }
   }
   return reset_now;
   };
-  pack_joints(std::integral_constant<int, 0>{});
-  pack_root(std::integral_constant<int, 0>{});
-  __syncthreads();
-  const bool reset_now = finish_env();
-  if (may_reset) {
-    if (tid < E) Lrst[tid] = reset_now ? 1 : 0;
-    if (__syncthreads_or(reset_now)) {
-      if (is_body && Lrst[e]) {
-        float* st = a.state + (size_t)b * N + agent;
-        const size_t fs = (size_t)B * N;
-        for (int c = 0; c < 7; ++c) st[c * fs] = Lpos[(b * 7 + c) * E + e];
-        for (int c = 0; c < 6; ++c) st[(7 + c) * fs] = Lvel[(b * kVS + c) * E + e];
+  // The marked envs start from the reset recipe (after a barrier behind Lrst; nothing of the sweeps'
+  // copies is needed any more).
+  auto reset_envs = [&](const StepArgs& a, const Model& M) {
+#pragma clang fp contract(fast)
+    const bool fresh = env_ok && Lrst[e];
+    auto seed_of = [&](int ag) -> uint64_t {
+      return only_reset ? a.reset_seed : a.task.seed + (uint64_t)(a.task_i[4 * ag + 3] + 1) * kEpisodeStride;
+    };
+    ResetDraw d;
+    int level = -1;
+    if (fresh && idx < B) {
+      const uint64_t seed = seed_of(agent);
+      const float noise = M.reset_noise;
+      for (int c = 0; c < 3; ++c) {
+        const float off = noise * (2.0f * reset_uniform(seed, agent, c) - 1.0f);
+        const float vel = noise * (2.0f * reset_uniform(seed, agent, 3 + c) - 1.0f);
+        Lpos[(idx * 7 + c) * E + e] = M.bodies[idx].rest_pos[c] + off;
+        Lvel[(idx * kVS + c) * E + e] = vel; Lvel[(idx * kVS + 3 + c) * E + e] = 0.0f;
       }
-      pack_joints(std::integral_constant<int, 1>{});
-      pack_root(std::integral_constant<int, 1>{});
+      for (int c = 0; c < 4; ++c) Lpos[(idx * 7 + 3 + c) * E + e] = c == 0 ? 1.0f : 0.0f;
+    }
+    if (fresh && idx < J) { reset_draw_joint(M, idx, agent, seed_of(agent), d); level = M.joint_level[idx]; }
+    __syncthreads();
+    for (int l = 0; l < M.n_levels; ++l) {
+      if (level == l) reset_place_joint(Ltjoint[idx], d, LdsPoses{Lpos, Lvel, E, e});
       __syncthreads();
     }
+    if (is_body && fresh) {
+      float* st = a.state + (size_t)b * N + agent;
+      const size_t fs = (size_t)B * N;
+      for (int c = 0; c < 7; ++c) st[c * fs] = Lpos[(b * 7 + c) * E + e];
+      for (int c = 0; c < 6; ++c) st[(7 + c) * fs] = Lvel[(b * kVS + c) * E + e];
+    }
+    if (!only_reset && tid < E && (blockIdx.x * E + tid) < N && Lrst[tid]) {
+      const int ag = agent_at(blockIdx.x * E + tid);
+      a.steps[ag] = 0;
+      task_begin_episode(a.task, a.task_i, a.targets, ag, a.task_i[4 * ag + 3] + 1, Lpos[(m_root * 7 + 0) * E + tid], Lpos[(m_root * 7 + 1) * E + tid]);
+    }
+    __syncthreads();
+  };
+  bool resetting = only_reset;
+  if (!resetting) {
+    pack_joints(std::integral_constant<int, 0>{});
+    pack_root(std::integral_constant<int, 0>{});
+    __syncthreads();
+    const bool reset_now = finish_env();
+    if (may_reset) {
+      if (tid < E) Lrst[tid] = reset_now ? 1 : 0;
+      resetting = __syncthreads_or(reset_now);
+    }
+  }
+  if (__builtin_expect(resetting, false)) {
+    const StepArgs& a = *reload_constant(reinterpret_cast<const StepArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr()));
+    const Model& M = *reload_constant(a.M);   // (nothing of this is fetched ahead of the branch)
+    if (only_reset) {
+      if (tid < E && (blockIdx.x * E + tid) < N) {
+        const int ag = agent_at(blockIdx.x * E + tid);
+        const bool fresh = !a.reset_mask || a.reset_mask[ag];
+        Lrst[tid] = fresh ? 1 : 0;
+        if (fresh) steps_before = 0;
+      }
+      __syncthreads();
+    }
+    reset_envs(a, M);
+    pack_joints(std::integral_constant<int, 1>{});
+    pack_root(std::integral_constant<int, 1>{});
+    __syncthreads();
+    if (only_reset) finish_env();
   }
   if constexpr (WS != 0) {
     // the kept impulses go back to the workspace for the next launch; an env that was just reset
