@@ -103,7 +103,7 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.pos = o; o += B * 7 * E;
   p.vel = o; o += B * kVS * E;
   p.iw = o; o += B * kVS * E;
-  p.nb = o; o += B * E;
+  p.nb = o; o += pairs ? B * E : 0;
   p.tq = o; o += J * 3 * E;
   p.push = o; o += 3 * E;
   o += o & 1;  // the search results kept in the copy arrays are 64-bit words
@@ -116,7 +116,6 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.cand = o + search;
   p.cand_cap = copies - search > 32 * E ? copies - search : 32 * E;
   o += copies > search + p.cand_cap ? copies : search + p.cand_cap;
-  p.zero = o; o += 6 * E;  // zeros in the place of a copy: what a body without that joint or contact adds up
   p.rec = o; o += S * kRecWords * E;
   p.list = o; o += S * E;
   p.surv = o; o += S * E;   // slots near the heightfield: end spheres from the front, mid-segments from the back
@@ -124,7 +123,11 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   o += warm ? 0 : 3 * (S * E > threads - ((2 * J * E + 63) / 64) * 64 ? S * E - (threads - ((2 * J * E + 63) / 64) * 64) : 0);
   p.u = o; o += (D > 0 ? D : 1) * E;
   p.obs = o; o += (11 + 3 * D + F) * E;
+  p.zero = p.obs;   // (six of them are zeros until the observation is packed)
   p.lim = o; o += (D > 0 ? D : 1) * E;
+  if (with_patch) o = (o + 3) & ~3;   // (written four samples at a time)
+  p.patch = o; o += with_patch ? E * kPatch * kPatch : 0;
+  p.mip = o; o += with_patch ? E * kPatchBlocks * kPatchBlocks : 0;
   p.count = o; o += 8;
   p.porg = o; o += 2 * E;
   p.org = o; o += 3 * E;
@@ -133,9 +136,6 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.tbody = o; o += 4 * B;
   p.tin = o; o += 6 * B;
   p.tjoint = o; o += J * (int)(sizeof(JointTab) / 4);
-  if (with_patch) o = (o + 3) & ~3;   // (written four samples at a time)
-  p.patch = o; o += with_patch ? E * kPatch * kPatch : 0;
-  p.mip = o; o += with_patch ? E * kPatchBlocks * kPatchBlocks : 0;
   p.pq = o; o += pairs ? kPairCap * kPairWords : 0;   // sorted queue of the substep's contacts
   p.po = o; o += pairs ? (kPairCap + 1) * 12 : 0;     // weighted velocity copies of their two bodies; the last entry stays zero
   p.pnear = o; o += pairs ? (E * pairs) / 2 + 1 : 0;  // agent pairs whose bounding spheres overlap
@@ -312,6 +312,24 @@ __device__ __forceinline__ float max_of(float a, float b) {
   float r;
   asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
+}
+
+// Sum over the 64 lanes of a wavefront, the same in all of them (a fixed tree of DPP moves: pairs, fours,
+// eights and sixteens within a row, then across the rows into the last lane).
+template <int kCtrl, int kRows>
+__device__ __forceinline__ float dpp_add(float x) {
+  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, kRows, 0xF, false));
+}
+__device__ __forceinline__ void wave_sum3(float& a, float& b, float& c) {
+  a = dpp_add<0x111, 0xF>(a); b = dpp_add<0x111, 0xF>(b); c = dpp_add<0x111, 0xF>(c);   // row_shr:1
+  a = dpp_add<0x112, 0xF>(a); b = dpp_add<0x112, 0xF>(b); c = dpp_add<0x112, 0xF>(c);   // row_shr:2
+  a = dpp_add<0x114, 0xF>(a); b = dpp_add<0x114, 0xF>(b); c = dpp_add<0x114, 0xF>(c);   // row_shr:4
+  a = dpp_add<0x118, 0xF>(a); b = dpp_add<0x118, 0xF>(b); c = dpp_add<0x118, 0xF>(c);   // row_shr:8
+  a = dpp_add<0x142, 0xA>(a); b = dpp_add<0x142, 0xA>(b); c = dpp_add<0x142, 0xA>(c);   // row_bcast:15
+  a = dpp_add<0x143, 0xC>(a); b = dpp_add<0x143, 0xC>(b); c = dpp_add<0x143, 0xC>(c);   // row_bcast:31
+  a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), 63));
+  b = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(b), 63));
+  c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c), 63));
 }
 
 struct ContactRows {
@@ -1519,7 +1537,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     // wavefronts concerned builds rows, the idle ones from a clamped index: a value assigned on
     // every path is not carried from one substep into the next in registers, as a conditionally
     // assigned one is.
-    auto build_joint_side = [&]() {
+    auto build_joint_side = [&](int js_j, int js_e, int js_side) {
      {
       const JointTab& jt = Ltjoint[js_j < J ? js_j : J - 1];
       const int e = js_e;
@@ -1651,6 +1669,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         const bool used = g_on && k < g_njs;
         int js = used ? tb[3 + k] : 0;
         gat_off[k] = (used ? P.outj + ((js >> 1) * kJS + (js & 1) * 6) * E : P.zero) + e;
+        gat_w[k] = used ? 1.0f : 0.0f;
         gat_w[k] = used ? 1.0f : 0.0f;
       }
 #pragma unroll
@@ -1789,7 +1808,251 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     // Warm start: sweep -1 relaxes nothing; every block applies the impulses it starts from (the
     // kept ones times the share) to its copies, and the average of the copies hands every body
     // the plain sum of them, as a sweep does with the increments.
-    if constexpr (NS != 0) {
+    const bool env_per_wave = NS != 0 && 2 * J + S <= 64;
+    if (NS != 0 && env_per_wave) {
+      // ---- S (Newton), where the rows of an env fit one wavefront: the solve of the block below with a
+      // wavefront for every env.  Lane l < 2 J is side l & 1 of joint l >> 1, the lanes above hold the
+      // contact slots.  Blocks and bodies still meet in LDS, but a wavefront's LDS instructions stay in
+      // their order, so nothing waits at a barrier, and the dot products are sums over the lanes: an inner
+      // iteration is one wavefront's chain instead of four phases of the whole workgroup.
+      // Bound by that chain (LDS round trips and the sums' lane crossings).  1024 humanoids on the
+      // heightfield, 3 Newton x 8 inner iterations x 4 substeps: 184 us with the block below, 135 us here
+      // An env of more rows keeps the block below: two wavefronts per env would need barriers again.
+      if constexpr (NS != 0) {
+      if (m_terrain == 0) { forces(0); __syncthreads(); }
+      const int we = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+      if (we < E && blockIdx.x * E + we < N) {
+        float* LU = lds + P.nu;        // [B][kVS][E]: M^-1 J^T x (plus v* when asked for)
+        const float p_reg = M.newton_reg;
+        const int n_kry = M.krylov;
+        constexpr float kFrictionEps = 1e-3f;   // m/s
+        const bool jrole = lane < 2 * J;
+        const int w_j = jrole ? lane >> 1 : 0, w_side = lane & 1;
+        const int w_s = !jrole && lane - 2 * J < S ? lane - 2 * J : 0;
+        const bool has = !jrole && lane - 2 * J < S && Lreci[(w_s * kRecWords + 0) * E + we] != 0;
+        // The row constants of either role in one array, so that the two roles share registers:
+        //   joint side: K[0..2] lever arm, K[3] linear response, K[4] sign, K[5..13] angular response of
+        //               the positional rows, K[14..22] the three axes, K[23..31] their angular response;
+        //   contact:    K[0..8] directions n, t1, t2, K[9..17] lever x direction, K[18..26] angular
+        //               response, K[27] linear response.
+        float K[32], Dg[6], bs[6], lam[6];
+        int ones = 0, uppers = 0, ob = -1;
+        for (int k = 0; k < 32; ++k) K[k] = 0.0f;
+        for (int k = 0; k < 6; ++k) Dg[k] = bs[k] = lam[k] = 0.0f;
+        if (jrole) {
+          build_joint_side(w_j, we, w_side);
+          for (int k = 0; k < 3; ++k) {
+            K[k] = jr.sr[k];
+            for (int c = 0; c < 3; ++c) { K[5 + 3 * k + c] = jr.Y[k][c]; K[14 + 3 * k + c] = jr.sax[k][c]; K[23 + 3 * k + c] = jr.Z[k][c]; }
+            Dg[k] = jr.pD[k]; bs[k] = jr.pb[k]; Dg[3 + k] = jr.aD[k]; bs[3 + k] = jr.ab[k];
+          }
+          K[3] = jr.sv; K[4] = jr.sg;
+          ones = jr.onesided; uppers = jr.upper;
+          ob = w_side ? Ltjoint[w_j].child : Ltjoint[w_j].parent;
+          if constexpr (WS != 0) {
+            // Warm start: the first iterate is the share of what the rows ended the last substep with
+            // (a limit row only if it stands for the same limit as then).
+            for (int k = 0; k < 3; ++k) lam[k] = p_warm * Lwj[(w_j * 6 + k) * E + we];
+            for (int k = 0; k < 3; ++k) {
+              const float kept = Lwj[(w_j * 6 + 3 + k) * E + we];
+              float l0 = p_warm * kept;
+              if ((ones >> k) & 1) {
+                const bool was_upper = __float_as_int(kept) < 0, is_upper = (uppers >> k) & 1;
+                l0 = was_upper == is_upper ? fabsf(l0) : 0.0f;
+              }
+              lam[3 + k] = l0;
+            }
+          }
+        } else if (has) {
+          ob = Ltslot[2 * w_s];
+          build_contact_rows(cr, Lrec, Liw, 1.0f, w_s, we, E, ob, Ltbody[4 * ob + 3], h, p_beta_c, p_vdepen, true);
+          for (int r = 0; r < 3; ++r) {
+            for (int c = 0; c < 3; ++c) { K[3 * r + c] = cr.dir[r][c]; K[9 + 3 * r + c] = cr.ang[r][c]; K[18 + 3 * r + c] = cr.Y[r][c]; }
+            Dg[r] = cr.D[r];
+            if constexpr (WS != 0) lam[r] = p_warm * Lwc[(w_s * 3 + r) * E + we];   // (a slot that was not active then holds zero)
+          }
+          bs[0] = cr.bias; K[27] = cr.ls;
+        }
+        const bool active = jrole || has, counts = has || (jrole && w_side == 0);   // (a joint's rows are counted once)
+        const int nr = jrole ? 6 : 3, vo = (ob < 0 ? 0 : ob) * kVS * E + we;
+        float* out = jrole ? Loutj + (w_j * kJS + w_side * 6) * E + we : Loutc + w_s * kCS * E + we;
+        // gathering lanes: three per body, two velocity components each
+        const int g_b = lane / 3, g_c = 2 * (lane - 3 * g_b);
+        const bool g_on = g_b < B;
+        int g_src[NJ + 3];
+        {
+          const int* tb = Ltjs + (g_on ? g_b : 0) * (kMaxBodyJoints + 3);
+          const int n_js = tb[0], slot0 = tb[1], n_slots = tb[2];
+#pragma unroll
+          for (int k = 0; k < NJ; ++k) {
+            const int js = k < n_js ? tb[3 + k] : 0;
+            g_src[k] = (g_on && k < n_js ? P.outj + ((js >> 1) * kJS + (js & 1) * 6) * E : P.zero) + g_c * E + we;
+          }
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const bool used = g_on && k < n_slots && Lreci[((slot0 + (k < n_slots ? k : 0)) * kRecWords + 0) * E + we] != 0;
+            g_src[NJ + k] = (used ? P.outc + (slot0 + k) * kCS * E : P.zero) + g_c * E + we;
+          }
+        }
+        // stores of this wavefront's lanes before, loads after
+        auto in_order = [&]() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier(); };
+        auto scatter = [&](const float* xv) {
+          float dv[3], dw[3];
+          if (jrole) {
+            for (int c = 0; c < 3; ++c) {
+              dv[c] = K[3] * xv[c];
+              dw[c] = sum3(K[5 + c], xv[0], K[8 + c], xv[1], K[11 + c], xv[2]);
+              dw[c] = fma_(K[23 + c], xv[3], dw[c]); dw[c] = fma_(K[26 + c], xv[4], dw[c]); dw[c] = fma_(K[29 + c], xv[5], dw[c]);
+            }
+          } else {
+            for (int c = 0; c < 3; ++c) {
+              dv[c] = K[27] * sum3(K[c], xv[0], K[3 + c], xv[1], K[6 + c], xv[2]);
+              dw[c] = sum3(K[18 + c], xv[0], K[21 + c], xv[1], K[24 + c], xv[2]);
+            }
+          }
+          if (ob >= 0)
+            for (int c = 0; c < 3; ++c) { out[c * E] = dv[c]; out[(3 + c) * E] = dw[c]; }
+          in_order();
+        };
+        // every body: the plain sum of its blocks' contributions (in static order), on top of the
+        // velocities the solve started from when `with_base`
+        auto gather_sum = [&](bool with_base, float* dst) {
+          if (g_on) {
+            float val[NJ + 3][2], acc[2];
+#pragma unroll
+            for (int k = 0; k < NJ + 3; ++k) { val[k][0] = lds[g_src[k]]; val[k][1] = lds[g_src[k] + E]; }
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+              acc[c] = val[0][c];
+#pragma unroll
+              for (int k = 1; k < NJ + 3; ++k) acc[c] += val[k][c];
+              const int o = (g_b * kVS + g_c + c) * E + we;
+              dst[o] = with_base ? Lvel[o] + acc[c] : acc[c];
+            }
+          }
+          in_order();
+        };
+        auto rows_of = [&](const float* src, float* y) {
+          float uv[3], uw[3];
+          for (int c = 0; c < 3; ++c) { uv[c] = src[vo + c * E]; uw[c] = src[vo + (3 + c) * E]; }
+          float pj[6], pc[3];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            pj[k] = fma_(K[4], uv[k], cross_unit_dot(K, k, uw));
+            pj[3 + k] = sum3(K[14 + 3 * k], uw[0], K[15 + 3 * k], uw[1], K[16 + 3 * k], uw[2]);
+            pc[k] = dot(K + 3 * k, uv) + dot(K + 9 + 3 * k, uw);
+          }
+#pragma unroll
+          for (int k = 0; k < 6; ++k) {
+            const float both = pj[k] + lane_swap1(pj[k]);
+            y[k] = jrole ? both : (k < 3 ? pc[k] : 0.0f);
+          }
+          in_order();
+        };
+        for (int it = 0; it < a.iterations; ++it) {
+          float sres[6], known[6], cp[6], ipd[6], tmp[6];
+          int on = 0;
+          // residual of the current iterate
+          scatter(lam);
+          gather_sum(true, LU);
+          rows_of(LU, sres);
+          for (int k = 0; k < 6; ++k) { sres[k] += bs[k]; known[k] = 0.0f; cp[k] = 0.0f; }
+          // the branch every row is on
+          if (jrole) {
+            on = 7;
+            for (int k = 0; k < 3; ++k) {
+              const bool one = (ones >> k) & 1;
+              const bool s_branch = !one || (Dg[3 + k] > 0.0f && lam[3 + k] - sres[3 + k] / Dg[3 + k] > 0.0f);
+              if (s_branch) on |= 8 << k; else known[3 + k] = -lam[3 + k];
+            }
+          } else {
+            if (Dg[0] > 0.0f && lam[0] - sres[0] / Dg[0] > 0.0f) on |= 1; else known[0] = -lam[0];
+            const float rad = p_mu * lam[0];
+            if (rad > 0.0f) {
+              on |= 6;
+              cp[1] = cp[2] = sqrtf(sum3(sres[1], sres[1], sres[2], sres[2], kFrictionEps, kFrictionEps)) / rad;
+            } else { known[1] = -lam[1]; known[2] = -lam[2]; }
+          }
+          // (ipd: inverse of the preconditioner's diagonal on the rows of the "s" branch, 0 elsewhere)
+          for (int k = 0; k < 6; ++k) {
+            const float pdk = fma_(Dg[k], 1.0f + p_reg, cp[k]);
+            if (!(pdk > 0.0f) || k >= nr || !active) on &= ~(1 << k);
+            ipd[k] = ((on >> k) & 1) ? 1.0f / pdk : 0.0f;
+          }
+          // right-hand side of the rows on the "s" branch: -s - c lambda - A known
+          scatter(known);
+          gather_sum(false, LU);
+          rows_of(LU, tmp);
+          float x[6], z[6], pv[6], q[6], az[6], damp[6];
+          for (int k = 0; k < 6; ++k) {
+            const float rhs = ((on >> k) & 1) ? fma_(-cp[k], lam[k], -sres[k]) - tmp[k] : 0.0f;
+            x[k] = 0.0f; z[k] = rhs * ipd[k]; pv[k] = z[k];
+            damp[k] = fma_(p_reg, Dg[k], cp[k]);
+          }
+          // (A + reg D + c) z on the rows of the "s" branch
+          auto apply_hat = [&](const float* xv, float* y) {
+            scatter(xv);
+            gather_sum(false, LU);
+            rows_of(LU, y);
+            for (int k = 0; k < 6; ++k) y[k] = ((on >> k) & 1) ? fma_(damp[k], xv[k], y[k]) : 0.0f;
+          };
+          // z.Az, Az.Az / pd, Az.q / pd over the rows of the env
+          auto products = [&](float& ta, float& tb, float& tc) {
+            ta = tb = tc = 0.0f;
+            for (int k = 0; k < 6; ++k) {
+              const float ap = az[k] * ipd[k];
+              ta = fma_(z[k], az[k], ta); tb = fma_(az[k], ap, tb); tc = fma_(ap, q[k], tc);
+            }
+            if (!counts) { ta = 0.0f; tb = 0.0f; tc = 0.0f; }
+            wave_sum3(ta, tb, tc);
+          };
+          apply_hat(z, az);
+          for (int k = 0; k < 6; ++k) q[k] = az[k];
+          float gamma, den, unused;
+          products(gamma, den, unused);
+          const float gamma0 = gamma;
+          for (int kk = 0; kk < n_kry; ++kk) {
+            if (!(den > 0.0f) || !(gamma > 1e-12f * gamma0)) break;
+            const float alpha = gamma / den;
+            for (int k = 0; k < 6; ++k) { x[k] = fma_(alpha, pv[k], x[k]); z[k] = fma_(-alpha * q[k], ipd[k], z[k]); }   // (all zero off the "s" branch)
+            if (kk == n_kry - 1) break;       // (the last iteration's operator product would not be used)
+            apply_hat(z, az);
+            float ta, tb, tc;
+            products(ta, tb, tc);
+            const float beta = ta / gamma;
+            for (int k = 0; k < 6; ++k) { pv[k] = fma_(beta, pv[k], z[k]); q[k] = fma_(beta, q[k], az[k]); }
+            den = fma_(beta * beta, den, fma_(2.0f * beta, tc, tb));     // q . q / pd of the new q
+            gamma = ta;
+          }
+          // update, then back into the feasible set
+          for (int k = 0; k < 6; ++k) lam[k] += ((on >> k) & 1) ? x[k] : known[k];
+          if (jrole) {
+            for (int k = 0; k < 3; ++k) if ((ones >> k) & 1) lam[3 + k] = fmaxf(lam[3 + k], 0.0f);
+          } else {
+            lam[0] = fmaxf(lam[0], 0.0f);
+            const float rad = p_mu * lam[0], nrm = sqrtf(sum2(lam[1], lam[1], lam[2], lam[2]));
+            if (nrm > rad) { const float sc = nrm > 0.0f ? rad / nrm : 0.0f; lam[1] *= sc; lam[2] *= sc; }
+          }
+        }
+        // the solved velocities: v* + M^-1 J^T lambda
+        scatter(lam);
+        gather_sum(true, Lvel);
+        if constexpr (WS != 0) {
+          // kept for the next substep (both lanes of a joint hold the same impulses)
+          if (jrole) {
+            if (w_side == 0) {
+              for (int k = 0; k < 3; ++k) Lwj[(w_j * 6 + k) * E + we] = lam[k];
+              for (int k = 0; k < 3; ++k)
+                Lwj[(w_j * 6 + 3 + k) * E + we] = ((ones & uppers) >> k) & 1 ? -lam[3 + k] : lam[3 + k];
+            }
+          } else if (lane - 2 * J < S) {
+            for (int r = 0; r < 3; ++r) Lwc[(w_s * 3 + r) * E + we] = has ? lam[r] : 0.0f;   // (an inactive slot hands nothing on)
+          }
+        }
+      }
+      __syncthreads();
+      }
+    } else if constexpr (NS != 0) {
 #pragma clang fp contract(fast)
       // ---- S (Newton): the paper's solver (Section 3.1), a non-smooth Newton method whose every
       // iteration is solved by a fixed number of preconditioned conjugate-residual iterations.
@@ -1821,7 +2084,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
             for (int r = 0; r < 3; ++r) Lwc[(i / E * 3 + r) * E + i % E] = 0.0f;
       }
       if (m_terrain == 0 && !jrole) forces(joint_threads);   // (the first gather is behind a barrier)
-      if (jrole) build_joint_side(); else build_contact();
+      if (jrole) build_joint_side(js_j, js_e, js_side); else build_contact();
       for (int i = tid; i < 3 * nblk * E; i += kThreads) Lred[i] = 0.0f;   // inactive slots contribute nothing
       const int nr = jrole ? 6 : 3;
       const bool active = jrole ? js_on : has_contact;      // this lane holds rows
@@ -2086,7 +2349,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       }
     } else
     if (joint_wave) {
-      build_joint_side();
+      build_joint_side(js_j, js_e, js_side);
       build_pair();
       if (PC == 0 && m_terrain == 0) __syncthreads();   // (the velocities, which the other wavefronts integrate meanwhile)
       TMARK(17);
