@@ -924,6 +924,23 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     return slot_geom_from_half(Ltbody[4 * bb], p_margin, bx, f3{lh[0], lh[E], lh[2 * E]}, kind, bo);
   };
 
+  // Capsule-capsule candidates of this thread, the same in every substep: its first four body pairs within its
+  // agent (a byte each) and its agent pair.  Read from the model's tables in global memory inside the
+  // substep, each of them was a trip to the cache that the whole workgroup waited for.
+  const int pair_stride = kThreads / E;
+  unsigned my_pairs = 0;
+  int my_meet = 0;
+  if constexpr (PC != 0) {
+    if (idx < pair_stride)
+      for (int k = 0; k < 4; ++k)
+        if (idx + k * pair_stride < m_npairs)
+          my_pairs |= (unsigned)(M.pair_a[idx + k * pair_stride] << 4 | M.pair_b[idx + k * pair_stride]) << (8 * k);
+    const int t = kThreads - 1 - tid;
+    if (m_group > 1 && t < (E / m_group) * m_nap) {
+      const int gi = t / m_nap, pi = t - gi * m_nap;
+      my_meet = (gi * m_group + M.agent_pair_a[pi]) | ((gi * m_group + M.agent_pair_b[pi]) << 16);
+    }
+  }
   const int tid_o = tid, e_o = e, idx_o = idx;
   const float h_o = h;
   for (int sub = 0; sub < a.substeps; ++sub) {
@@ -1036,9 +1053,21 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       for (int c = 0; c < 3; ++c) { Lvel[(b * kVS + c) * E + e] = v[c]; Lvel[(b * kVS + 3 + c) * E + e] = w[c]; }
      }
     };
+    // bounding radius of every agent about its root, for the pairs of agents below
+    auto agent_radius = [&](int t0) {
+      for (int i = tid - t0; i >= 0 && i < B * E; i += kThreads - t0) {
+        const int e = i % E, b = i / E;
+        if (blockIdx.x * E + e >= N) continue;
+        float dx[3];
+        for (int c = 0; c < 3; ++c) dx[c] = Lpos[(b * 7 + c) * E + e] - Lpos[(M.root * 7 + c) * E + e];
+        const float rad = __builtin_amdgcn_sqrtf(dot(dx, dx)) * 1.000001f + Ltbody[4 * b + 1] + Ltbody[4 * b];
+        atomicMax(&Lbs[e], __float_as_int(rad));
+      }
+    };
     if (m_terrain == 0) {
       // plane: the torques from the lower end of the workgroup, every slot's contact from the upper one
       torques(0);
+      if (PC != 0 && m_group > 1) agent_radius(0);
       for (int i = kThreads - 1 - tid; i < S * E; i += kThreads) {
         const int ee = i % E, s = i / E;
         ContactOut co = no_contact();
@@ -1240,6 +1269,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           }
         TMARK(12);
         forces(kThreads - ((B * E + 63) & ~63));
+        if (PC != 0 && m_group > 1) agent_radius(kThreads - ((B * E + 63) & ~63));
       }
     }
     __syncthreads();
@@ -1255,19 +1285,38 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     //         wavefront found what first.
     int n_pc = 0;
     if constexpr (PC != 0) {
-      if (m_contacts && (m_npairs > 0 || m_group > 1)) {
+      const bool search = m_contacts && (m_npairs > 0 || m_group > 1);
+      // (plane: the torques are complete by now, and most of the workgroup has no candidate in stage 2)
+      auto plane_forces = [&]() {
+        if (m_terrain == 0) forces(kThreads - ((B * E + 63) & ~63));
+      };
+      if (!search) plane_forces();
+      if (search) {
+        // Bounding spheres of the bodies for stage 1: centre relative to the group's first origin, radius
+        // (enlarged by what the centre's two roundings can be off), one 16-byte word each, env after env
+        // with an odd stride, so that a candidate costs two reads from LDS instead of sixteen and neighbouring
+        // lanes fall on different banks.  They lie where the terrain search was and the sweep copies will be.
+        float4* const Lsph = reinterpret_cast<float4*>(lds + ((P.outj + 3) & ~3));
+        const int sph_e = B | 1;
+        for (int i = tid; i < B * E; i += kThreads) {
+          const int e = i % E, b = i / E, e0 = e - e % m_group;
+          float4 w;
+          w.x = Lpos[(b * 7 + 0) * E + e] + (Lorg[0 * E + e] - Lorg[0 * E + e0]);
+          w.y = Lpos[(b * 7 + 1) * E + e] + (Lorg[1 * E + e] - Lorg[1 * E + e0]);
+          w.z = Lpos[(b * 7 + 2) * E + e] + (Lorg[2 * E + e] - Lorg[2 * E + e0]);
+          w.w = fma_(0x1p-22f, fabsf(w.x) + fabsf(w.y) + fabsf(w.z), (Ltbody[4 * b] + Ltbody[4 * b + 1]) + 0.5f * p_margin + 1e-3f);
+          Lsph[e * sph_e + b] = w;
+        }
+        // agents of one group whose bounding spheres overlap, from the upper end of the workgroup
         if (m_group > 1) {
-          if (is_body) {
-            float dx[3];
-            for (int c = 0; c < 3; ++c) dx[c] = Lpos[(b * 7 + c) * E + e] - Lpos[(M.root * 7 + c) * E + e];
-            const float rad = sqrtf(dot(dx, dx)) + Ltbody[4 * b + 1] + Ltbody[4 * b];
-            atomicMax(&Lbs[e], __float_as_int(rad));
-          }
-          __syncthreads();
           const int n_ap = (E / m_group) * m_nap;
-          for (int t = tid; t < n_ap; t += kThreads) {
-            const int gi = t / m_nap, pi = t - gi * m_nap;
-            const int ea = gi * m_group + M.agent_pair_a[pi], eb = gi * m_group + M.agent_pair_b[pi];
+          for (int t = kThreads - 1 - tid; t < n_ap; t += kThreads) {
+            int pr = my_meet;
+            if (t >= kThreads) {   // (more pairs than threads)
+              const int gi = t / m_nap, pi = t - gi * m_nap;
+              pr = (gi * m_group + M.agent_pair_a[pi]) | ((gi * m_group + M.agent_pair_b[pi]) << 16);
+            }
+            const int ea = pr & 0xffff, eb = pr >> 16;
             bool near = false;
             if (blockIdx.x * E + eb < N) {   // (ea < eb)
               float dd = 0.0f;
@@ -1279,9 +1328,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
               near = dd <= rr * rr;
             }
             const int pos = wave_alloc<1>(near ? 1 : 0, &Lpcount[1]);
-            if (near) Lmeet[pos] = ea | (eb << 16);
+            if (near) Lmeet[pos] = pr;
           }
-          __syncthreads();
         }
         float* Ltmp = Lpo;   // unsorted queue; the copies are not in use yet
         // Every hit also leaves (gap, key) as one 64-bit word whose unsigned order is that of the
@@ -1333,36 +1381,72 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         // (env and body of A, env and body of B: also the sort key of a hit).  The list lives where
         // the observations are staged at the end of the step.
         unsigned* Lc2 = Lpair;
-        auto cull_pair = [&](int ea, int ba, int eb, int bb, bool valid) {
-          bool pass = false;
-          if (valid) {
-            float dd = 0.0f;
-            for (int c = 0; c < 3; ++c) {
-              const float dc = (Lpos[(bb * 7 + c) * E + eb] + (Lorg[c * E + eb] - Lorg[c * E + ea])) - Lpos[(ba * 7 + c) * E + ea];
-              dd += dc * dc;
-            }
-            const float reach = (Ltbody[4 * ba] + Ltbody[4 * ba + 1]) + (Ltbody[4 * bb] + Ltbody[4 * bb + 1]) + p_margin + 2e-3f;
-            pass = dd <= reach * reach;
-          }
-          const int pos = wave_alloc<1>(pass ? 1 : 0, &Lpcount[2]);
-          if (pass) {
-            if (pos < pair_cap) Lc2[pos] = ((unsigned)ea << 20) | ((unsigned)eb << 8) | (unsigned)(ba << 4) | (unsigned)bb;
+        auto near_pair = [&](int ea, int ba, int eb, int bb) -> bool {
+          const float4 sa = Lsph[ea * sph_e + ba], sb = Lsph[eb * sph_e + bb];
+          const float dx = sb.x - sa.x, dy = sb.y - sa.y, dz = sb.z - sa.z, reach = sa.w + sb.w;
+          return sum3(dx, dx, dy, dy, dz, dz) <= reach * reach;
+        };
+        auto pair_key = [&](int ea, int ba, int eb, int bb) -> unsigned {
+          return ((unsigned)ea << 20) | ((unsigned)eb << 8) | (unsigned)(ba << 4) | (unsigned)bb;
+        };
+        // Four candidates of a thread at a time: their reads from LDS are in flight together and they take
+        // their places in the list with one atomic add per wavefront.  One after the other, with sixteen
+        // reads each, they were bound by those reads: 9500 cycles per substep for 16 humanoids in groups of
+        // four, 5800 so (1000 humanoids in groups of 16: 151 to 142 us a step with the changes around it).
+        constexpr int kCull = 4;
+        auto list_pairs = [&](const bool* pass, const unsigned* key) {
+          int n = 0;
+#pragma unroll
+          for (int k = 0; k < kCull; ++k) n += pass[k] ? 1 : 0;
+          int pos = wave_alloc<3>(n, &Lpcount[2]);
+#pragma unroll
+          for (int k = 0; k < kCull; ++k) {
+            if (!pass[k]) continue;
+            if (pos < pair_cap) Lc2[pos] = key[k];
             else Lpcount[3] = 1;   // list full: everything is tested the slow way below
+            ++pos;
           }
         };
+        __syncthreads();
         // the listed pairs of every agent: thread (idx, e) takes pairs idx, idx + stride, ...
-        const int pair_stride = kThreads / E;
         if (idx < pair_stride)
-          for (int pp = idx; pp < m_npairs; pp += pair_stride) cull_pair(e, M.pair_a[pp], e, M.pair_b[pp], env_ok);
+          for (int p0 = idx; p0 < m_npairs; p0 += kCull * pair_stride) {
+            bool pass[kCull];
+            unsigned key[kCull];
+#pragma unroll
+            for (int k = 0; k < kCull; ++k) {
+              const int pp = p0 + k * pair_stride;
+              const bool valid = env_ok && pp < m_npairs;
+              int ab = (my_pairs >> (8 * k)) & 255u;
+              if (p0 != idx) ab = valid ? (M.pair_a[pp] << 4 | M.pair_b[pp]) : 0;   // (more than four per thread)
+              pass[k] = near_pair(e, ab >> 4, e, ab & 15) && valid;
+              key[k] = pair_key(e, ab >> 4, e, ab & 15);
+            }
+            list_pairs(pass, key);
+          }
         // agents of one group: 256 lanes per near agent pair, lane = (body of A) * 16 + (body of B)
-        const int n_near = m_group > 1 ? Lpcount[1] : 0;
-        for (int nn = tid >> 8; nn < n_near; nn += kThreads >> 8) {
+        int n_near = 0;
+        if (m_group > 1) {
+          n_near = Lpcount[1];
           const int cb = tid & 255, ba = cb >> 4, bb = cb & 15;
-          const int pr = Lmeet[nn];
-          cull_pair(pr & 0xffff, ba, pr >> 16, bb, ba < B && bb < B);
+          const bool valid = ba < B && bb < B;
+          const int sa = ba < B ? ba : 0, sb = bb < B ? bb : 0;
+          for (int n0 = tid >> 8; n0 < n_near; n0 += kCull * (kThreads >> 8)) {
+            bool pass[kCull];
+            unsigned key[kCull];
+#pragma unroll
+            for (int k = 0; k < kCull; ++k) {
+              const int nn = n0 + k * (kThreads >> 8);
+              const int pr = Lmeet[nn < n_near ? nn : n0];
+              pass[k] = near_pair(pr & 0xffff, sa, pr >> 16, sb) && valid && nn < n_near;
+              key[k] = pair_key(pr & 0xffff, sa, pr >> 16, sb);
+            }
+            list_pairs(pass, key);
+          }
         }
         __syncthreads();
         // Stage 2: the segment-segment test, one listed candidate per lane
+        plane_forces();
         if (!Lpcount[3]) {
           const int n_c2 = Lpcount[2];
           for (int c = tid; c < n_c2; c += kThreads) {
@@ -1372,11 +1456,11 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         } else {
           if (idx < pair_stride)
             for (int pp = idx; pp < m_npairs; pp += pair_stride)
-              test_pair(e, M.pair_a[pp], e, M.pair_b[pp], ((unsigned)e << 20) | ((unsigned)e << 8) | (unsigned)(M.pair_a[pp] << 4) | (unsigned)M.pair_b[pp], env_ok);
+              test_pair(e, M.pair_a[pp], e, M.pair_b[pp], pair_key(e, M.pair_a[pp], e, M.pair_b[pp]), env_ok);
           for (int nn = tid >> 8; nn < n_near; nn += kThreads >> 8) {
             const int cb = tid & 255, ba = cb >> 4, bb = cb & 15;
             const int pr = Lmeet[nn], ea = pr & 0xffff, eb = pr >> 16;
-            test_pair(ea, ba, eb, bb, ((unsigned)ea << 20) | ((unsigned)eb << 8) | (unsigned)(ba << 4) | (unsigned)bb, ba < B && bb < B);
+            test_pair(ea, ba, eb, bb, pair_key(ea, ba, eb, bb), ba < B && bb < B);
           }
         }
         __syncthreads();
@@ -1401,21 +1485,27 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           __syncthreads();
         }
         if (tid < n_pc) {
+          // (eight keys in flight at a time: one after the other the loop waits for LDS n_pc times)
           const unsigned key = __float_as_uint(Ltmp[tid * kPairWords]);
           int rank = 0;
-          for (int k = 0; k < n_pc; ++k) rank += __float_as_uint(Ltmp[k * kPairWords]) < key ? 1 : 0;
+          static_assert(kPairCap % 8 == 0, "");
+          for (int k0 = 0; k0 < n_pc; k0 += 8) {
+            unsigned other[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) other[k] = __float_as_uint(Ltmp[(k0 + k) * kPairWords]);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) rank += (int)(k0 + k < n_pc) & (int)(other[k] < key);
+          }
           for (int wd = 0; wd < kPairWords; ++wd) Lpq[rank * kPairWords + wd] = Ltmp[tid * kPairWords + wd];
+          // every contact enters the lists of its two bodies (the order in which they arrive does not
+          // matter: the averaging threads sort their list)
+          const int refs = __float_as_int(Ltmp[tid * kPairWords + 1]);
+          const int ra = refs & 0xffff, rb = (refs >> 16) & 0xffff;
+          const int slot_a = atomicAdd(&Lpbcnt[ra], 1), slot_b = atomicAdd(&Lpbcnt[rb], 1);
+          if (slot_a < 6) Lpblist[ra * 6 + slot_a] = (uint8_t)(2 * rank);
+          if (slot_b < 6) Lpblist[rb * 6 + slot_b] = (uint8_t)(2 * rank + 1);
         }
         if (tid == 0 && n_raw > kPairCap) atomicAdd(a.pair_dropped, n_raw - kPairCap);
-        __syncthreads();
-        // every contact enters the lists of its two bodies (the order in which they arrive does not
-        // matter: the averaging threads sort their list)
-        if (tid < 2 * n_pc) {
-          const int refs = __float_as_int(Lpq[(tid >> 1) * kPairWords + 1]);
-          const int ref = (tid & 1) ? (refs >> 16) & 0xffff : refs & 0xffff;
-          const int slot = atomicAdd(&Lpbcnt[ref], 1);
-          if (slot < 6) Lpblist[ref * 6 + slot] = (uint8_t)tid;   // 2 * (queue index) + side
-        }
         __syncthreads();
       }
     }
@@ -1479,7 +1569,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     constexpr int kPairFew = 2;
     const bool gp_few = g_variants && PC != 0 && __ballot(gp_cnt > kPairFew) == 0ull;
     // ---- C: a body's sum of block weights.  With capsule-capsule contacts the body threads work it out for
-    //         everybody (and, on the plane, others integrate the forces); without, the lanes that need it
+    //         everybody; without, the lanes that need it
     //         add up the body's three slots themselves, which saves a phase and its barrier.
     if constexpr (PC != 0) {
       if (is_body) {
@@ -1487,7 +1577,6 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         for (int k = 0; k < my_nslots; ++k) nbf += Lrec[((my_slot0 + k) * kRecWords + 10) * E + e];
         Lnb[b * E + e] = nbf + gp_wsum;   // (a body thread is the first averaging thread of its own body)
       }
-      if (m_terrain == 0) forces(kThreads - ((B * E + 63) & ~63));   // plane: the torques are complete only now
     }
     auto weight_sum = [&](int bb, int ee) -> float {
       if constexpr (PC != 0) return Lnb[bb * E + ee];
