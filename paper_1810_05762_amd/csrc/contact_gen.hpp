@@ -66,12 +66,20 @@ __device__ __forceinline__ float field_height(const Field& H, int i, int j) {
   return H.h[j * H.nx + i];
 }
 
+// Does the copy hold the samples (di, dj) .. (di + 1, dj + 1), counted from its first one?  The unsigned
+// difference of a sample in front of the copy is huge, so it is compared as it is: one added to it
+// would wrap to zero and pass.
+__device__ __forceinline__ bool cell_in_copy(const Field& H, unsigned di, unsigned dj) {
+  const unsigned last = H.ps > 0 ? (unsigned)H.ps - 1u : 0u;
+  return di < last && dj < last;
+}
+
 // Heights of the four corners of cell (i,j) with a single inside-the-copy test, so the four
 // reads are issued together.
 __device__ __forceinline__ void field_cell_heights(const Field& H, int i, int j, float& h00, float& h10,
                                                    float& h11, float& h01) {
   unsigned di = (unsigned)(i - H.pi0), dj = (unsigned)(j - H.pj0);
-  if (di + 1u < (unsigned)H.ps && dj + 1u < (unsigned)H.ps) {
+  if (cell_in_copy(H, di, dj)) {
     const lds_float* p = H.patch + dj * kPatch + di;
     h00 = p[0]; h10 = p[1]; h01 = p[kPatch]; h11 = p[kPatch + 1];
   } else {
@@ -85,7 +93,7 @@ __device__ __forceinline__ void field_cell_heights(const Field& H, int i, int j,
 __device__ __forceinline__ void field_cell_heights_clamped(const Field& H, int i, int j, float& h00, float& h10,
                                                            float& h11, float& h01) {
   unsigned di = (unsigned)(i - H.pi0), dj = (unsigned)(j - H.pj0);
-  if (di + 1u < (unsigned)H.ps && dj + 1u < (unsigned)H.ps) {
+  if (cell_in_copy(H, di, dj)) {
     const lds_float* p = H.patch + dj * kPatch + di;
     h00 = p[0]; h10 = p[1]; h01 = p[kPatch]; h11 = p[kPatch + 1];
   } else {
@@ -536,7 +544,7 @@ __device__ __forceinline__ int segment_candidates(const Field& H, const SegCull&
   float h00, h10, h11, h01;
   {
     unsigned di = (unsigned)(i - H.pi0), dj = (unsigned)(j - H.pj0);
-    if (di + 1u < (unsigned)H.ps && dj + 1u < (unsigned)H.ps) {
+    if (cell_in_copy(H, di, dj)) {
       const lds_float* p = H.patch + dj * kPatch + di;
       h00 = p[0]; h10 = p[1]; h01 = p[kPatch]; h11 = p[kPatch + 1];
     } else {
@@ -737,7 +745,7 @@ template <int NC>
 __device__ __forceinline__ void row_heights(const Field& H, int i, int j, int n, float zq[NC]) {
   float m[NC + 1];
   const unsigned di = (unsigned)(i - H.pi0), dj = (unsigned)(j - H.pj0);
-  if (di < (unsigned)H.ps && di + (unsigned)(n < NC ? n : NC) < (unsigned)H.ps && dj + 1u < (unsigned)H.ps) {
+  if (cell_in_copy(H, di, dj) && di + (unsigned)(n < NC ? n : NC) < (unsigned)H.ps) {
     // (all columns are read; those beyond n are not used and lie inside the workgroup's LDS: the
     //  block maxima follow the copies)
     const lds_float* p = H.patch + dj * kPatch + di;
