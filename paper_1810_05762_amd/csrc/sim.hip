@@ -355,7 +355,7 @@ static int default_envs_per_block(const Model& m, int N) {
   }
   auto usable = [&](int E) {
     return E <= lim && E % G == 0 && (E <= most || (G == 1 && E * m.n_pairs <= kPairCap)) &&
-           (size_t)plan_for(m, E).total * sizeof(float) <= 160 * 1024;
+           plan_for(m, E).total <= kLdsWords;
   };
   int E = 0;
   if (m.max_joint_sides <= 4)
@@ -510,7 +510,7 @@ static int launch_step(sim* s, const float* actions, float h, int substeps, int 
 #endif
   LdsPlan P = plan_for(m, s->E);
   size_t lds_bytes = (size_t)P.total * sizeof(float);
-  if (lds_bytes > 160 * 1024) return fail(SIM_ERR_ARG, "envs_per_block %d needs %zu bytes of LDS (limit 160 KiB)", s->E, lds_bytes);
+  if (P.total > kLdsWords) return fail(SIM_ERR_ARG, "envs_per_block %d needs %zu bytes of LDS (limit %d)", s->E, lds_bytes, kLdsWords * 4);
   int grid = (s->N + s->E - 1) / s->E;
   const int threads = threads_for(m, s->E);
   if (m.solver == 1 && !newton_fits(m, s->E))
@@ -704,7 +704,7 @@ extern "C" int sim_set_envs_per_block(sim_t* s, int E) {
   if (m.solver == 1 && !newton_fits(m, E))
     return fail(SIM_ERR_ARG, "envs_per_block %d: the Newton solver needs a contact thread per slot (at most 8 envs per workgroup)", E);
   LdsPlan P = plan_for(m, E);
-  if ((size_t)P.total * 4 > 160 * 1024) return fail(SIM_ERR_ARG, "envs_per_block %d exceeds LDS", E);
+  if (P.total > kLdsWords) return fail(SIM_ERR_ARG, "envs_per_block %d exceeds LDS", E);
   s->E = E;
   return SIM_OK;
 }

@@ -85,6 +85,9 @@ struct StepArgs {
 // counts, so that neighbouring items start in different LDS banks when E is 16.
 constexpr int kVS = 7, kCS = 7, kJS = 13;
 constexpr int kPairHitMin = 256;   // (gap, key) words a workgroup keeps at least
+// Words of LDS a workgroup can ask for: 160 KiB without the 256 bytes that the compiler takes for the barrier
+// that also says whether an env was reset.
+constexpr int kLdsWords = (160 * 1024 - 256) / 4;
 
 struct LdsPlan {
   int pos, vel, iw, nb, tq, push, outj, outc, zero, tjs, rec, list, surv, lam, u, obs, lim, count, patch, mip, porg, org, tslot, tbody, tin, tjoint, total;
