@@ -303,8 +303,8 @@ static int threads_for(const Model& m, int E) {
   return (E == 16 && m.max_joint_sides <= 4 && !pairs_of(m) && !(m.warm > 0.0f) && m.solver == 0) ? kThreadsWide : kThreads;
 }
 static LdsPlan plan_for(const Model& m, int E) {
-  const int with_patch = (m.terrain_kind == 1 && m.nx >= kPatch && m.ny >= kPatch) ? 1 : 0;
-  return make_plan(m.B, m.J, m.S, m.D, m.F, E, with_patch, pairs_of(m), threads_for(m, E), m.warm > 0.0f ? 1 : 0, m.solver);
+  const int field = m.terrain_kind != 1 ? 0 : (m.nx >= kPatch && m.ny >= kPatch ? 2 : 1);
+  return make_plan(m.B, m.J, m.S, m.D, m.F, E, field, pairs_of(m), threads_for(m, E), m.warm > 0.0f ? 1 : 0, m.solver);
 }
 // The Newton solver keeps every row's vectors in registers, one contact per thread: every slot of
 // every env of the workgroup needs a contact thread of its own next to the joint wavefronts.

@@ -93,16 +93,18 @@ struct LdsPlan {
   int pos, vel, iw, nb, tq, push, outj, outc, zero, tjs, rec, list, surv, lam, u, obs, lim, count, patch, mip, porg, org, tslot, tbody, tin, tjoint, total;
   int pq, po, pnear, pbs, pcount, pbcnt, pblist;  // capsule-capsule contacts (only with pairs != 0)
   int phit, hit_cap;                              // their (gap, key) words: offset (64-bit aligned) and capacity
-  int half, cand, cand_cap;                       // terrain search: half segments of the bodies, lists (in the copies' space)
+  int half, cand, cand_cap;                       // terrain search: half segments of the bodies, lists
   int wj, wc;                                     // kept impulses of joints and slots (only with warm != 0)
   int nu, nred, nsum;                             // Newton solver: body vectors, reduction entries, partial sums
 };
 
+// field: 0 = plane, 1 = heightfield, 2 = heightfield of which every env keeps a copy
 // pairs: 0 = no capsule-capsule contacts, else the interaction group size (1 = self-collision only)
-__host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, int E, int with_patch, int pairs = 0,
+__host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, int E, int field, int pairs = 0,
                                              int threads = kThreads, int warm = 0, int newton = 0) {
   LdsPlan p;
   int o = 0;
+  const bool with_patch = field == 2;
   p.pos = o; o += B * 7 * E;
   p.vel = o; o += B * kVS * E;
   p.iw = o; o += B * kVS * E;
@@ -111,14 +113,23 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.push = o; o += 3 * E;
   o += o & 1;  // the search results kept in the copy arrays are 64-bit words
   // The sweep copies.  The terrain search, which is over before the first sweep, keeps its results there:
-  // a 64-bit minimum per slot, half the segment of every body and the lists of rows and cells.
-  const int copies = (J * kJS + S * kCS) * E, search = (2 * S + 3 * B) * E;
+  // a 64-bit minimum per slot and half the segment of every body (together never more than the copies,
+  // since every body has a slot), and behind them the lists of rows and cells, for which 32 words per env are
+  // enough.  So does the search for capsule-capsule contacts its spheres (one 16-byte word per body, an
+  // odd number of them per env).  A robot with few joints has less room than that behind its results: up to
+  // 16 envs the copies' space is then made larger, which LDS always has room for.  With more of them (which only
+  // a caller asks for) nothing is reserved that the ground does not need, and the lists take what is left at
+  // the end: full lists only cost time (the direct search), and no form is refused for them.
+  const bool many = E > 16;
+  const int copies = (J * kJS + S * kCS) * E, search = many && !field ? 0 : (2 * S + 3 * B) * E;
+  const int spheres = pairs ? 4 * (B | 1) * E + 3 : 0;
   p.outj = o;
   p.outc = o + J * kJS * E;
   p.half = o + 2 * S * E;
   p.cand = o + search;
-  p.cand_cap = copies - search > 32 * E ? copies - search : 32 * E;
+  p.cand_cap = copies - search > 32 * E ? copies - search : (many ? copies - search : 32 * E);
   o += copies > search + p.cand_cap ? copies : search + p.cand_cap;
+  o += many && spheres > copies ? spheres - copies : 0;
   p.rec = o; o += S * kRecWords * E;
   p.list = o; o += S * E;
   p.surv = o; o += S * E;   // slots near the heightfield: end spheres from the front, mid-segments from the back
@@ -141,7 +152,7 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.tjoint = o; o += J * (int)(sizeof(JointTab) / 4);
   p.pq = o; o += pairs ? kPairCap * kPairWords : 0;   // sorted queue of the substep's contacts
   p.po = o; o += pairs ? (kPairCap + 1) * 12 : 0;     // weighted velocity copies of their two bodies; the last entry stays zero
-  p.pnear = o; o += pairs ? (E * pairs) / 2 + 1 : 0;  // agent pairs whose bounding spheres overlap
+  p.pnear = o; o += pairs ? E * (pairs - 1) / 2 : 0;  // agent pairs whose bounding spheres overlap: at most all of them
   p.pbs = o; o += pairs ? E : 0;                      // bounding radius of every agent about its root
   p.pcount = o; o += pairs ? 4 : 0;
   p.pbcnt = o; o += pairs ? B * E : 0;                  // per body: how many of them touch it
@@ -161,6 +172,13 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.nu = o; o += newton ? B * kVS * E : 0;
   p.nred = o; o += newton ? 3 * (J + S) * E : 0;
   p.nsum = o; o += newton ? 3 * 8 * E : 0;
+  if (many && (field || pairs) && p.cand_cap < 32 * E) {
+    const int room = kLdsWords - o, cap = room < 32 * E ? room : 32 * E;
+    if (cap > p.cand_cap) {
+      p.cand = o; p.cand_cap = cap; o += cap;
+      if ((cap - 2) / 2 > p.hit_cap) { p.phit = (p.cand + 1) & ~1; p.hit_cap = (cap - 2) / 2; }
+    }
+  }
   p.total = o;
   return p;
 }
@@ -716,7 +734,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   const Field H0 = make_field(M, a.heights, a.coarse);
   const bool use_patch = m_terrain == 1 && H0.nx >= kPatch && H0.ny >= kPatch;
   const int m_group = PC ? (M.group > 1 ? M.group : 1) : 1, m_npairs = PC ? M.n_pairs : 0, m_nap = PC ? M.n_agent_pairs : 0;
-  const LdsPlan P = make_plan(B, J, S, D, F, E, use_patch ? 1 : 0, PC ? m_group : 0, NT, WS, NS);
+  const LdsPlan P = make_plan(B, J, S, D, F, E, use_patch ? 2 : (m_terrain == 1 ? 1 : 0), PC ? m_group : 0, NT, WS, NS);
   float* Lpos = lds + P.pos;
   float* Lvel = lds + P.vel;
   float* Liw = lds + P.iw;
