@@ -60,12 +60,6 @@ struct Field {
 constexpr int kMip = 4;
 constexpr int kPatch = 28;  // samples per side of that copy (ps is this or 0)
 
-__device__ __forceinline__ float field_height(const Field& H, int i, int j) {
-  unsigned di = (unsigned)(i - H.pi0), dj = (unsigned)(j - H.pj0);
-  if (di < (unsigned)H.ps && dj < (unsigned)H.ps) return H.patch[dj * kPatch + di];
-  return H.h[j * H.nx + i];
-}
-
 // Does the copy hold the samples (di, dj) .. (di + 1, dj + 1), counted from its first one?  The unsigned
 // difference of a sample in front of the copy is huge, so it is compared as it is: one added to it
 // would wrap to zero and pass.
@@ -104,11 +98,6 @@ __device__ __forceinline__ void field_cell_heights_clamped(const Field& H, int i
 // world x / y of sample column i / row j
 __device__ __forceinline__ float field_x(const Field& H, int i) { float fx = (float)i * H.cell; return H.ox + fx; }
 __device__ __forceinline__ float field_y(const Field& H, int j) { float fy = (float)j * H.cell; return H.oy + fy; }
-
-__device__ __forceinline__ f3 field_vertex(const Field& H, int i, int j) {
-  float fx = (float)i * H.cell, fy = (float)j * H.cell;
-  return f3{H.ox + fx, H.oy + fy, field_height(H, i, j)};
-}
 
 // Barycentric coordinates (v,w) of the point of triangle A,B,C closest to P,
 // found from the projections of P on the two edge directions at each corner.
@@ -341,7 +330,7 @@ __device__ __forceinline__ bool slot_range(const Field& H, SlotGeom& g) {
 
 // Cells overlapped by the reach box; false when the slot cannot touch the field
 // (box outside the field, or higher than every sample of the coarse blocks under it).
-__device__ __forceinline__ bool slot_reach(const Field& H, SlotGeom& g, bool exact = true) {
+__device__ __forceinline__ bool slot_reach(const Field& H, SlotGeom& g) {
   const int ncx = H.nx - 1, ncy = H.ny - 1;
   float xl, xh, yl, yh, zl;
   if (g.kind < 2) {
@@ -363,37 +352,17 @@ __device__ __forceinline__ bool slot_reach(const Field& H, SlotGeom& g, bool exa
     const int I0 = (g.i0 - H.pi0) / kMip, I1 = (g.i1 + 1 - H.pi0) / kMip;
     const int J0 = (g.j0 - H.pj0) / kMip, J1 = (g.j1 + 1 - H.pj0) / kMip;
     if (I1 - I0 <= 2 && J1 - J0 <= 2) {
-      {
-        float m[9];
+      float m[9];
 #pragma unroll
-        for (int dj = 0; dj < 3; ++dj)
+      for (int dj = 0; dj < 3; ++dj)
 #pragma unroll
-          for (int di = 0; di < 3; ++di) {
-            int I = I0 + di < I1 ? I0 + di : I1, J = J0 + dj < J1 ? J0 + dj : J1;
-            m[dj * 3 + di] = H.mip[J * nb + I];
-          }
-        __builtin_amdgcn_sched_group_barrier(0x100, 9, 0);  // the nine reads first, one wait
+        for (int di = 0; di < 3; ++di) {
+          int I = I0 + di < I1 ? I0 + di : I1, J = J0 + dj < J1 ? J0 + dj : J1;
+          m[dj * 3 + di] = H.mip[J * nb + I];
+        }
+      __builtin_amdgcn_sched_group_barrier(0x100, 9, 0);  // the nine reads first, one wait
 #pragma unroll
-        for (int k = 0; k < 9; ++k) hmax = fmaxf(hmax, m[k]);
-      }
-      // block maxima say "maybe": take the exact maximum over the samples of the box when it
-      // is at most 6 x 6 (all 36 reads are issued together, indices clamped into the box)
-      const int ni = g.i1 - g.i0 + 2, nj = g.j1 - g.j0 + 2;
-      if (exact && !(zcut > hmax) && ni <= 6 && nj <= 6) {
-        const int bi = g.i0 - H.pi0, bj = g.j0 - H.pj0;
-        hmax = -INFINITY;
-        float hv[36];
-        int col[6], row[6];
-#pragma unroll
-        for (int d = 0; d < 6; ++d) { col[d] = bi + (d < ni ? d : ni - 1); row[d] = (bj + (d < nj ? d : nj - 1)) * kPatch; }
-#pragma unroll
-        for (int dj = 0; dj < 6; ++dj)
-#pragma unroll
-          for (int di = 0; di < 6; ++di) hv[dj * 6 + di] = H.patch[row[dj] + col[di]];
-        __builtin_amdgcn_sched_group_barrier(0x100, 36, 0);  // all reads before the first use
-#pragma unroll
-        for (int k = 0; k < 36; ++k) hmax = fmaxf(hmax, hv[k]);
-      }
+      for (int k = 0; k < 9; ++k) hmax = fmaxf(hmax, m[k]);
     } else {
       for (int J = J0; J <= J1; ++J)
         for (int I = I0; I <= I1; ++I) hmax = fmaxf(hmax, H.mip[J * nb + I]);
@@ -498,28 +467,17 @@ struct SegCull {
   float zcut;                           // lower end minus the reach
   int i1, j1;                           // last cell of the box in x and y
 };
-__device__ __forceinline__ SegCull seg_cull_from(f3 P0, f3 P1, float Rq, float RL, float inv_L2, int i1, int j1) {
-  SegCull c;
-  c.P0 = P0;
-  c.dx = P1.x - P0.x; c.dy = P1.y - P0.y; c.dz = P1.z - P0.z;
-  c.L2 = c.dx * c.dx + c.dy * c.dy;
-  c.R = Rq + kSelSlack;
-  c.RL = RL; c.inv_L2 = inv_L2;
-  c.zcut = (P0.z < P1.z ? P0.z : P1.z) - Rq;
-  c.i1 = i1; c.j1 = j1;
-  return c;
-}
-// the two per-slot constants worth keeping: R L and 1 / L^2
-__device__ __forceinline__ void seg_cull_consts(const SlotGeom& g, float& RL, float& inv_L2) {
-  const float dx = g.P1.x - g.P0.x, dy = g.P1.y - g.P0.y;
-  const float L2 = dx * dx + dy * dy;
-  RL = (g.Rq + kSelSlack) * sqrtf(L2);
-  inv_L2 = L2 > 1e-8f ? 1.0f / L2 : 0.0f;
-}
 __device__ __forceinline__ SegCull seg_cull(const SlotGeom& g) {
-  float RL, inv_L2;
-  seg_cull_consts(g, RL, inv_L2);
-  return seg_cull_from(g.P0, g.P1, g.Rq, RL, inv_L2, g.i1, g.j1);
+  SegCull c;
+  c.P0 = g.P0;
+  c.dx = g.P1.x - g.P0.x; c.dy = g.P1.y - g.P0.y; c.dz = g.P1.z - g.P0.z;
+  c.L2 = c.dx * c.dx + c.dy * c.dy;
+  c.R = g.Rq + kSelSlack;
+  c.RL = c.R * sqrtf(c.L2);
+  c.inv_L2 = c.L2 > 1e-8f ? 1.0f / c.L2 : 0.0f;
+  c.zcut = (g.P0.z < g.P1.z ? g.P0.z : g.P1.z) - g.Rq;
+  c.i1 = g.i1; c.j1 = g.j1;
+  return c;
 }
 
 // Cheap part of the mid-segment search at sample (i,j): bit k of the result is set when edge k
@@ -539,18 +497,8 @@ __device__ __forceinline__ int segment_candidates(const Field& H, const SegCull&
   const float lim = sc.RL + 1e-3f * (fabsf(sc.dx) + fabsf(sc.dy));
   if (cmin > lim || cmax < -lim) return 0;
   if (amax < -lim || amin > sc.L2 + lim) return 0;
-  // corner heights; neighbours beyond the last sample are clamped (their edges are excluded below)
-  const int ip = i + 1 < H.nx ? i + 1 : i, jp = j + 1 < H.ny ? j + 1 : j;
   float h00, h10, h11, h01;
-  {
-    unsigned di = (unsigned)(i - H.pi0), dj = (unsigned)(j - H.pj0);
-    if (cell_in_copy(H, di, dj)) {
-      const lds_float* p = H.patch + dj * kPatch + di;
-      h00 = p[0]; h10 = p[1]; h01 = p[kPatch]; h11 = p[kPatch + 1];
-    } else {
-      h00 = H.h[j * H.nx + i]; h10 = H.h[j * H.nx + ip]; h01 = H.h[jp * H.nx + i]; h11 = H.h[jp * H.nx + ip];
-    }
-  }
+  field_cell_heights_clamped(H, i, j, h00, h10, h11, h01);   // (edges beyond the last sample are excluded below)
   const float zq = fmaxf(fmaxf(h00, h10), fmaxf(h01, h11));
   if (sc.zcut > zq) return 0;  // the whole square is out of reach below the capsule
   if (sc.inv_L2 > 0.0f) {

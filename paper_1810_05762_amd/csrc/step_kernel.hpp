@@ -1136,7 +1136,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
             if (blockIdx.x * E + ee < N && m_contacts) {
               const Field H = field_of(ee);
               SlotGeom g = listed_geom(bb, ee, kind);
-              if (slot_reach(H, g, false)) {
+              if (slot_reach(H, g)) {
                 on = true;
                 float r2;
                 const bool search = slot_search_box(H, g, r2);
@@ -1779,7 +1779,6 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         const bool used = g_on && k < g_njs;
         int js = used ? tb[3 + k] : 0;
         gat_off[k] = (used ? P.outj + ((js >> 1) * kJS + (js & 1) * 6) * E : P.zero) + e;
-        gat_w[k] = used ? 1.0f : 0.0f;
         gat_w[k] = used ? 1.0f : 0.0f;
       }
 #pragma unroll
