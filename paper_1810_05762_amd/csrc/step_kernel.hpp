@@ -137,7 +137,7 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   o += warm ? 0 : 3 * (S * E > threads - ((2 * J * E + 63) / 64) * 64 ? S * E - (threads - ((2 * J * E + 63) / 64) * 64) : 0);
   p.u = o; o += (D > 0 ? D : 1) * E;
   p.obs = o; o += (11 + 3 * D + F) * E;
-  p.zero = p.obs;   // (six of them are zeros until the observation is packed)
+  p.zero = p.obs;   // (the first six rows are zeros until the observation is packed; with capsule pairs: small numbers, see Lpair)
   p.lim = o; o += (D > 0 ? D : 1) * E;
   if (with_patch) o = (o + 3) & ~3;   // (written four samples at a time)
   p.patch = o; o += with_patch ? E * kPatch * kPatch : 0;
@@ -183,10 +183,12 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   return p;
 }
 
-// The arithmetic of a step is written out down to the single rounded operation: contraction is off in
-// this file and every fused multiply-add is spelled, so that the forms of the kernel give the same bits
-// whatever the compiler inlines, hoists or splits into blocks around them.  A sum of products is
-// a0 b0 + a1 b1 + a2 b2 = fma(a2, b2, fma(a0, b0, a1 b1)).
+// The arithmetic of the substeps is written out down to the single rounded operation: contraction is off
+// and every fused multiply-add is spelled, so that the forms of the kernel give the same bits whatever the
+// compiler inlines, hoists or splits into blocks around them.  A sum of products is
+// a0 b0 + a1 b1 + a2 b2 = fma(a2, b2, fma(a0, b0, a1 b1)).  Left to the compiler are the Newton solve by the whole
+// workgroup (robots with more rows than a wavefront has lanes) and what follows the substeps: the
+// observation, the reward and the poses of a reset.
 #pragma clang fp contract(off)
 __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ float sum2(float a0, float b0, float a1, float b1) { return fma_(a0, b0, a1 * b1); }
@@ -757,7 +759,10 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   unsigned* Lcell_m = Lcell_e + cell_e_cap;
   unsigned* Lrow_e = Lcell_m + cell_m_cap;
   unsigned* Lrow_m = Lrow_e + row_e_cap;
-  // candidate pairs of the capsule-capsule search, in the space the observations are staged in at the end
+  // Candidate pairs of the capsule-capsule search, in the space the observations are staged in at the end.  The
+  // average of the copies reads its unused entries there, with weight 0: a packed pair, read as a float, is
+  // finite (the env in its top twelve bits would have to reach 2040 to make the exponent of an infinity).
+  static_assert(((kThreadsWide - 1) << 20 | 0xfffff) < 0x7f800000, "a packed pair is no finite float");
   unsigned* Lpair = reinterpret_cast<unsigned*>(lds + P.obs);
   const int pair_cap = (11 + 3 * D + F) * E;
   float* Ltq = lds + P.tq;                           // joint torques, [J][3][E]
@@ -1764,8 +1769,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
 
     TMARK(5);
     // The copies a body averages: NJ joint sides and its three contact slots.  Entries that are not in use
-    // point at zeros and have weight 0 (the copies share their space with the terrain search, so only
-    // those that a block writes in every sweep are read).
+    // point at finite numbers (P.zero) and have weight 0 (the copies share their space with the terrain search,
+    // so only those that a block writes in every sweep are read).
     float g_inb = 0.0f;
     int gat_off[NJ], gat_slot[3];
     float gat_w[NJ + 3];
@@ -1805,9 +1810,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     auto gather_part = [&](auto nc_tag, int c0) {
       constexpr int NC = decltype(nc_tag)::value;
       if (g_on && g_inb > 0.0f) {
-        // every load is unconditional: unused entries read zeros and enter the sum
-        // with weight 0; all reads are issued
-        // before the first use so their LDS latency is paid once
+        // every load is unconditional: unused entries read P.zero and enter the sum with weight 0; all
+        // reads are issued before the first use so their LDS latency is paid once
         // The average is taken over the copies' differences from the snapshot, (sum of w_k (copy_k -
         // v0)) / W added to v0: the differences are small next to the velocity itself, so the sum
         // rounds at their magnitude and the velocity is rounded once per sweep, where a weighted
