@@ -325,8 +325,8 @@ static const void* step_variant(const Model& m, int E) {
 // Envs per workgroup.  A step is a chain of dependent instructions and barriers whose length hardly
 // depends on how many envs share the workgroup, and one workgroup fills a compute unit; so: one round
 // of workgroups whenever the batch allows it (rounded up: 1500 humanoids on the heightfield take
-// 106 us as 188 workgroups of 8 and 176 us as 375 of 4), in a compiled form (as 300 of 5, which is
-// both two rounds and the general form, they take 227 us).
+// 90 us as 188 workgroups of 8 and 152 us as 375 of 4), in a compiled form (as 300 of 5, which is
+// both two rounds and the general form, they take 194 us).
 static int default_envs_per_block(const Model& m, int N) {
   // bodies need a thread each, joints two (one per side) plus a wavefront left for contacts
   int lim = kThreads / m.B;
@@ -339,15 +339,15 @@ static int default_envs_per_block(const Model& m, int N) {
   const int G = m.group > 1 ? m.group : 1;   // a workgroup holds whole interaction groups
   const bool pairs = pairs_of(m) != 0, newton = m.solver == 1;
   int want = (N + 255) / 256;
-  // Four envs share a workgroup's phases at no cost (64 to 1024 humanoids on the heightfield: 88 to
-  // 93 us as workgroups of 4, 64 to 256 103 to 111 us as workgroups of 1), and fewer workgroups make a slow
-  // one among them less likely; a handful of workgroups is quicker still with two (16: 84 against 87 us).
+  // A workgroup's envs share its phases (16 to 512 humanoids on the heightfield: 71 to 73 us as workgroups of 2, 76
+  // to 78 us of 4, 74 to 82 us of 1), and fewer workgroups make a slow one among them less likely: two up to 128
+  // envs, four beyond.  (The line was drawn where four cost nothing; up to 512 envs two are 5 us quicker now.)
   const int least = N > 128 ? 4 : 2;
   if (want < least) want = least;
   // With capsule-capsule collisions a workgroup's envs share a queue of kPairCap contacts, and what
   // does not fit is left out of the step.  There the envs that fill 256 workgroups (rounded down) are
   // the most that share one, unless their own pairs cannot fill it: contacts come before time (300
-  // humanoids: 219 us as workgroups of 1, 123 us of 2; 1500: 239 us of 4, 142 us of 8).
+  // humanoids: 188 us as workgroups of 1, 104 us of 2; 1500: 214 us of 4, 129 us of 8).
   int most = 16;
   if (pairs) {
     most = N / 256 > 1 ? N / 256 : 1;

@@ -20,11 +20,15 @@
 //
 // Per substep (Section 3.1 of the paper: maximal coordinates, torque control,
 // speculative unilateral contacts, isotropic Coulomb friction, restitution 0):
-//   A  body threads publish pose and world inverse inertia
-//   B  contact generation per slot; joint threads turn actions into torques
-//   C  body threads count their blocks, integrate gravity/torque/gyroscopic term
-//   P  (collision variant) capsule-capsule contacts within an agent and within a group
-//   D  joint / contact threads build row constants
+//   A  body threads publish pose, world inverse inertia and half segment
+//   B  contact generation per slot; joint threads turn actions into torques.  On the heightfield the
+//      search by rows of cells, with the gravity / torque / gyroscopic term integrated beside the records
+//   P  (collision variant) capsule-capsule contacts within an agent and within a group; on the plane
+//      the forces are integrated beside them
+//   C  (collision variant) body threads sum up the weights of their blocks; without capsule pairs the
+//      lanes that need such a sum form it themselves
+//   D  joint / contact threads build row constants; on the plane without capsule pairs the contact
+//      wavefronts integrate the forces beside the joint rows
 //   S  (warm-start variant: sweep -1 applies the impulses kept from the last substep)
 //      `iterations` sweeps: every block relaxes its rows one after another on a
 //      private copy of its bodies taken from the shared snapshot; a body is

@@ -7,14 +7,11 @@ namespace sim355 {
 
 // Envs per workgroup that have a form of their own (index arithmetic and LDS offsets fixed at
 // compile time); any other number runs the general form, which takes it from the launch arguments
-// and is up to twice as slow.  The Newton families end at 8 (a contact thread per slot).  One env
-// per workgroup is the library's own choice only with collisions (room in the contact queue) and
-// where two do not fit; elsewhere a caller asks for it.  The 512-thread forms of a family give the
-// same bits.  Where collisions and the warm start come together the general form contracts other
-// multiply-adds and agrees with double precision no better (3840 colliding humanoids, ten steps:
-// 0.34 % beyond 1e-3, compiled forms 0.26 %, the same formulas in plain fp32 20.7 %), so size and
-// speed alone decide: 40 self-colliding humanoids take 170 us in it and 134 us in the form for one
-// env, 1000 as workgroups of 2 322 us and 253 us.
+// and is a quarter to a third slower (300 self-colliding humanoids with the warm start: 150 us as
+// workgroups of 3, 120 us of 4, 116 us of 2).  The Newton families end at 8 (a contact thread per slot).
+// One env per workgroup is the library's own choice only with collisions (room in the contact queue)
+// and where two do not fit; elsewhere a caller asks for it.  All forms of a family give the same bits
+// (robots that the whole workgroup solves with Newton's method aside), so size and speed alone decide.
 constexpr bool step_compiled_envs(int E, bool newton) {
   return (E == 16 && !newton) || E == 8 || E == 4 || E == 2 || E == 1;
 }

@@ -142,6 +142,28 @@ def test_narrow_forms_of_a_family_give_the_same_bits(family):
         assert all(np.array_equal(a, b) for a, b in zip(o, outs[0]))
 
 
+@pytest.mark.parametrize("family", FAMILIES)
+def test_general_and_wide_forms_give_the_bits_of_the_narrow_ones(family):
+    """Three envs per workgroup run the form that takes their number from the launch arguments, 16 plain ones the
+    768-thread form: the arithmetic of all of them is spelled out to the single operation."""
+    import paper_1810_05762_amd as P
+    n = 35
+    sc, cfg = _scene(family, n)
+    dt, sub, its = float(np.float32(cfg["dt"])), cfg["substeps"], 3 if "newton" in family else cfg["iterations"]
+    outs = []
+    for epb in (2, 3) + ((16,) if family == "plain" else ()):
+        sim = P.Sim(sc)
+        sim.set_envs_per_block(epb)
+        assert sim.launch_info()["threads_per_block"] == (768 if epb == 16 else 512)
+        sim.reset(cfg["seed"])
+        for s in range(45):
+            sim.step(scenes.actions_for_step(cfg["seed"], s, n, sc.robot.n_dofs), dt, sub, its)
+        outs.append([sim.get_state().cpu().numpy()] + [x.cpu().numpy() for x in sim.get_obs()])
+        sim.check(); sim.close()
+    for o in outs[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(o, outs[0]))
+
+
 @pytest.mark.parametrize("family,n,group,expect", [
     ("plain", 1, 1, 2), ("plain", 128, 1, 2), ("plain", 129, 1, 4), ("plain", 1024, 1, 4), ("plain", 1025, 1, 8),
     ("plain", 2049, 1, 16), ("plain", 5000, 1, 16), ("newton", 1025, 1, 8), ("newton", 5000, 1, 8),
