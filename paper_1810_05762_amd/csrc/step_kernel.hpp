@@ -1423,14 +1423,19 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         // their places in the list with one atomic add per wavefront.  One after the other, with sixteen
         // reads each, they were bound by those reads: 9500 cycles per substep for 16 humanoids in groups of
         // four, 5800 so (1000 humanoids in groups of 16: 151 to 142 us a step with the changes around it).
-        constexpr int kCull = 4;
-        auto list_pairs = [&](const bool* pass, const unsigned* key) {
+        // Where an agent has at least as many threads as a robot can have pairs (up to four envs per
+        // workgroup), a thread has one of its own at most, and the reads of three that are not there were in
+        // its way: 512 self-colliding humanoids on the plane, 4 x 8 sweeps, 53.8 to 52.5 us a step, on the
+        // heightfield 62.9 to 61.0 us, 512 chains of 16 links on the plane 51.2 to 50.2 us.
+        constexpr int kCull = 4, kOwn = EC > 0 && kThreads / (EC > 0 ? EC : 1) >= kMaxPairs ? 1 : kCull;
+        auto list_pairs = [&](auto count, const bool* pass, const unsigned* key) {
+          constexpr int NC = decltype(count)::value;
           int n = 0;
 #pragma unroll
-          for (int k = 0; k < kCull; ++k) n += pass[k] ? 1 : 0;
-          int pos = wave_alloc<3>(n, &Lpcount[2]);
+          for (int k = 0; k < NC; ++k) n += pass[k] ? 1 : 0;
+          int pos = wave_alloc<NC == 1 ? 1 : 3>(n, &Lpcount[2]);
 #pragma unroll
-          for (int k = 0; k < kCull; ++k) {
+          for (int k = 0; k < NC; ++k) {
             if (!pass[k]) continue;
             if (pos < pair_cap) Lc2[pos] = key[k];
             else Lpcount[3] = 1;   // list full: everything is tested the slow way below
@@ -1440,11 +1445,11 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         __syncthreads();
         // the listed pairs of every agent: thread (idx, e) takes pairs idx, idx + stride, ...
         if (idx < pair_stride)
-          for (int p0 = idx; p0 < m_npairs; p0 += kCull * pair_stride) {
-            bool pass[kCull];
-            unsigned key[kCull];
+          for (int p0 = idx; p0 < m_npairs; p0 += kOwn * pair_stride) {
+            bool pass[kOwn];
+            unsigned key[kOwn];
 #pragma unroll
-            for (int k = 0; k < kCull; ++k) {
+            for (int k = 0; k < kOwn; ++k) {
               const int pp = p0 + k * pair_stride;
               const bool valid = env_ok && pp < m_npairs;
               int ab = (my_pairs >> (8 * k)) & 255u;
@@ -1452,7 +1457,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
               pass[k] = near_pair(e, ab >> 4, e, ab & 15) && valid;
               key[k] = pair_key(e, ab >> 4, e, ab & 15);
             }
-            list_pairs(pass, key);
+            list_pairs(std::integral_constant<int, kOwn>{}, pass, key);
           }
         // agents of one group: 256 lanes per near agent pair, lane = (body of A) * 16 + (body of B)
         int n_near = 0;
@@ -1471,7 +1476,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
               pass[k] = near_pair(pr & 0xffff, sa, pr >> 16, sb) && valid && nn < n_near;
               key[k] = pair_key(pr & 0xffff, sa, pr >> 16, sb);
             }
-            list_pairs(pass, key);
+            list_pairs(std::integral_constant<int, kCull>{}, pass, key);
           }
         }
         __syncthreads();

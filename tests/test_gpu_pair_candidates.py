@@ -25,7 +25,7 @@ def _scene(bodies, group, n, spread, seed):
 
 
 @pytest.mark.parametrize("bodies,group,epb,n", [(14, 1, 32, 64), (14, 1, 5, 12), (16, 1, 1, 4), (16, 1, 16, 48), (4, 16, 128, 256), (1, 16, 256, 256),
-                                                (16, 16, 16, 48), (13, 4, 4, 20), (3, 3, 12, 30), (2, 8, 8, 40)])
+                                                (16, 1, 2, 6), (16, 1, 4, 12), (16, 2, 2, 6), (16, 4, 4, 8), (16, 16, 16, 48), (13, 4, 4, 20), (3, 3, 12, 30), (2, 8, 8, 40)])
 def test_candidates_of_every_split_equal_the_oracles_contacts(bodies, group, epb, n):
     """The set of contacts after one substep is the oracle's, in workgroups that hold them all."""
     import paper_1810_05762_amd as P
