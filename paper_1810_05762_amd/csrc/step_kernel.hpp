@@ -595,8 +595,19 @@ __device__ inline void task_draw_target(const TaskParams& t, int env, int episod
 // through the joint list; the top of the tree gets one uniform linear velocity and no spin, a
 // child turns with its parent plus its hinge rates and moves so that the two anchor points of its
 // joint share one velocity (the world as a parent stands still).
-// Built by a thread per body and joint: a joint's draws depend on nothing else, its child's pose on the
-// parent's, so the joints are placed level by level (Model::joint_level).
+// In the step kernel by a thread per body and joint: a joint's draws depend on nothing else, its child's pose
+// on the parent's, so the joints are placed level by level (Model::joint_level).  In reset_kernel (sim_reset of
+// many envs) by one thread per env, in the joints' order.
+template <class Poses>
+__device__ __forceinline__ void reset_place_body(const Model& M, int b, int env, uint64_t seed, Poses P) {
+  const float noise = M.reset_noise;
+  for (int c = 0; c < 3; ++c) {
+    P.X(b, c) = fma_(noise, 2.0f * reset_uniform(seed, env, c) - 1.0f, M.bodies[b].rest_pos[c]);
+    P.V(b, c) = noise * (2.0f * reset_uniform(seed, env, 3 + c) - 1.0f);
+    P.W(b, c) = 0.0f;
+  }
+  for (int c = 0; c < 4; ++c) P.Q(b, c) = c == 0 ? 1.0f : 0.0f;
+}
 struct ResetDraw {
   float dq[4], rate[3];   // rotation of the child in the parent's frame, hinge rates
 };
@@ -616,7 +627,7 @@ __device__ __forceinline__ void reset_draw_joint(const Model& M, int j, int env,
   if (ang < 1e-12f) { d.dq[0] = 1.0f; d.dq[1] = 0.5f * phi[0]; d.dq[2] = 0.5f * phi[1]; d.dq[3] = 0.5f * phi[2]; }
   else { const float sn = sinf(0.5f * ang) / ang; d.dq[0] = cosf(0.5f * ang); d.dq[1] = sn * phi[0]; d.dq[2] = sn * phi[1]; d.dq[3] = sn * phi[2]; }
 }
-// the child of one joint, from its parent (poses and velocities in LDS)
+// where the poses and velocities are built: in LDS, or in the state itself (its column of one env)
 struct LdsPoses {
   float* Lpos; float* Lvel; int E, ee;
   __device__ float& X(int b, int c) { return Lpos[(b * 7 + c) * E + ee]; }
@@ -624,7 +635,16 @@ struct LdsPoses {
   __device__ float& V(int b, int c) { return Lvel[(b * kVS + c) * E + ee]; }
   __device__ float& W(int b, int c) { return Lvel[(b * kVS + 3 + c) * E + ee]; }
 };
-__device__ __forceinline__ void reset_place_joint(const JointTab& jt, const ResetDraw& d, LdsPoses P) {
+struct StatePoses {
+  float* st; size_t body, field;   // floats from one body, from one component to the next
+  __device__ float& X(int b, int c) { return st[c * field + b * body]; }
+  __device__ float& Q(int b, int c) { return st[(3 + c) * field + b * body]; }
+  __device__ float& V(int b, int c) { return st[(7 + c) * field + b * body]; }
+  __device__ float& W(int b, int c) { return st[(10 + c) * field + b * body]; }
+};
+// the child of one joint, from its parent
+template <class Poses>
+__device__ __forceinline__ void reset_place_joint(const JointTab& jt, const ResetDraw& d, Poses P) {
   float qa[4] = {1, 0, 0, 0}, xa[3] = {0, 0, 0}, va[3] = {0, 0, 0}, wa[3] = {0, 0, 0};
   if (jt.parent >= 0) {
     for (int c = 0; c < 4; ++c) qa[c] = P.Q(jt.parent, c);
@@ -2877,17 +2897,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     };
     ResetDraw d;
     int level = -1;
-    if (fresh && idx < B) {
-      const uint64_t seed = seed_of(agent);
-      const float noise = M.reset_noise;
-      for (int c = 0; c < 3; ++c) {
-        const float off = noise * (2.0f * reset_uniform(seed, agent, c) - 1.0f);
-        const float vel = noise * (2.0f * reset_uniform(seed, agent, 3 + c) - 1.0f);
-        Lpos[(idx * 7 + c) * E + e] = M.bodies[idx].rest_pos[c] + off;
-        Lvel[(idx * kVS + c) * E + e] = vel; Lvel[(idx * kVS + 3 + c) * E + e] = 0.0f;
-      }
-      for (int c = 0; c < 4; ++c) Lpos[(idx * 7 + 3 + c) * E + e] = c == 0 ? 1.0f : 0.0f;
-    }
+    if (fresh && idx < B) reset_place_body(M, idx, agent, seed_of(agent), LdsPoses{Lpos, Lvel, E, e});
     if (fresh && idx < J) { reset_draw_joint(M, idx, agent, seed_of(agent), d); level = M.joint_level[idx]; }
     __syncthreads();
     for (int l = 0; l < M.n_levels; ++l) {

@@ -45,3 +45,36 @@ def test_reset_of_every_kind_of_tree_matches_the_oracle(name, epb):
     ref.set_state(after.astype(np.float64)); ref.set_step_count(0)
     np.testing.assert_allclose(sim.get_obs()[0].cpu().numpy()[mask == 1], ref.get_obs()[0][mask == 1], atol=1e-4)
     sim.check(); sim.close()
+
+
+@pytest.mark.parametrize("share", [0.0, 0.8])
+@pytest.mark.parametrize("name", ["chain14", "loop", "star", "single", "humanoid"])
+def test_reset_of_many_workgroups_gives_the_bits_of_one_launch(name, share):
+    """More than six rounds of workgroups (1536) are reset by a kernel of their own ahead of the step kernel's
+    launch, fewer inside it: the same state, observation, reward, done flag, step counter and kept impulses."""
+    import paper_1810_05762_amd as P
+    n = 1537
+    rob = _robots()[name]
+    rob.term_height = -1e9
+    sc = scenes.make_scene(rob, scenes.make_plane(), n, params=scenes.SimParams(warm_start=share, max_episode_steps=4))
+    mask = np.zeros(n, np.uint8); mask[[0, 5, 64, n - 1]] = 1
+    ref = oracle.OracleSim(sc)
+    ref.reset(7)
+    outs = []
+    for epb in (1, 2, 5):
+        sim, got = P.Sim(sc), []
+        sim.set_envs_per_block(epb)
+        sim.reset(7)
+        got += [sim.get_state().cpu().numpy()] + [x.cpu().numpy() for x in sim.get_obs()]
+        np.testing.assert_allclose(got[0], ref.get_state(), atol=4e-6)
+        for s in range(3):
+            sim.step(scenes.actions_for_step(3, s, n, max(rob.n_dofs, 1))[:, :rob.n_dofs], 1.0 / 60.0, 2, 4)
+        sim.reset(8, mask)
+        got += [sim.get_state().cpu().numpy()] + [x.cpu().numpy() for x in sim.get_obs()]
+        sim.step(None, 1.0 / 60.0, 2, 4)          # the fourth step of the envs that were not reset: their episode is over
+        got += [sim.get_state().cpu().numpy()] + [x.cpu().numpy() for x in sim.get_obs()]
+        assert np.array_equal(got[-1] != 0, mask == 0)
+        sim.check(); sim.close()
+        outs.append(got)
+    for o in outs[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(o, outs[0]))
