@@ -1624,8 +1624,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     constexpr int kPairFew = 2;
     const bool gp_few = g_variants && PC != 0 && __ballot(gp_cnt > kPairFew) == 0ull;
     // ---- C: a body's sum of block weights.  With capsule-capsule contacts the body threads work it out for
-    //         everybody; without, the lanes that need it
-    //         add up the body's three slots themselves, which saves a phase and its barrier.
+    //         everybody; without, the lanes that need it add up the body's three slots themselves, which
+    //         saves a phase and its barrier.
     if constexpr (PC != 0) {
       if (is_body) {
         float nbf = (float)my_njs;
