@@ -347,7 +347,7 @@ static int default_envs_per_block(const Model& m, int N) {
   // With capsule-capsule collisions a workgroup's envs share a queue of kPairCap contacts, and what
   // does not fit is left out of the step.  There the envs that fill 256 workgroups (rounded down) are
   // the most that share one, unless their own pairs cannot fill it: contacts come before time (300
-  // humanoids: 188 us as workgroups of 1, 104 us of 2; 1500: 214 us of 4, 129 us of 8).
+  // humanoids: 187 us as workgroups of 1, 102 us of 2; 1500: 211 us of 4, 128 us of 8).
   int most = 16;
   if (pairs) {
     most = N / 256 > 1 ? N / 256 : 1;
