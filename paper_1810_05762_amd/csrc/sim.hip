@@ -304,7 +304,8 @@ static int threads_for(const Model& m, int E) {
 }
 static LdsPlan plan_for(const Model& m, int E) {
   const int field = m.terrain_kind != 1 ? 0 : (m.nx >= kPatch && m.ny >= kPatch ? 2 : 1);
-  return make_plan(m.B, m.J, m.S, m.D, m.F, E, field, pairs_of(m), threads_for(m, E), m.warm > 0.0f ? 1 : 0, m.solver);
+  return make_plan(m.B, m.J, m.S, m.D, m.F, E, field, pairs_of(m), threads_for(m, E), m.warm > 0.0f ? 1 : 0, m.solver,
+                   joint_lanes(E, m.max_joint_sides <= 4, pairs_of(m) != 0, m.solver == 1));
 }
 // The Newton solver keeps every row's vectors in registers, one contact per thread: every slot of
 // every env of the workgroup needs a contact thread of its own next to the joint wavefronts.

@@ -8,8 +8,9 @@
 // consecutive global addresses of the [field][body][env] state arrays.
 // Roles (a thread can hold several):
 //   body thread  (e, b): owns pose and velocity of one body in registers,
-//   joint-side threads  : two neighbouring lanes own the six rows of one joint, one lane per
-//                         body (parent, child); a row's J v is the sum of the two lanes' parts,
+//   joint threads       : two neighbouring lanes own the six rows of one joint, one lane per
+//                         body (parent, child); a row's J v is the sum of the two lanes' parts
+//                         (four lanes in small workgroups, one where collisions share a large one),
 //   contact thread      : owns the three rows of one active contact slot (constants in
 //                         registers); a workgroup's contacts beyond one per thread are
 //                         rebuilt from their LDS record every sweep,
@@ -30,12 +31,13 @@
 //   D  joint / contact threads build row constants; on the plane without capsule pairs the contact
 //      wavefronts integrate the forces beside the joint rows
 //   S  (warm-start variant: sweep -1 applies the impulses kept from the last substep)
-//      `iterations` sweeps: every block relaxes its rows one after another on a
+//      `iterations` sweeps: every block relaxes its rows one after another, as on a
 //      private copy of its bodies taken from the shared snapshot; a body is
 //      shared out among its blocks by weight (joint 1, contact a ramp from 0 at
 //      the margin to 1 at half the margin) and acts inside block c with inverse
 //      mass scaled by W / w_c; then every body takes the weighted average of the
-//      copies of its blocks in static order (no atomics)
+//      copies, which is the plain sum of what the blocks' impulses change in its
+//      velocity, in static order (no atomics)
 //   E  damping, angular-velocity cap, position integration
 #pragma once
 #include <hip/hip_runtime.h>
@@ -87,7 +89,8 @@ struct StepArgs {
 
 // Rows (E consecutive floats) per item of the velocity, inverse-inertia and copy arrays.  Odd
 // counts, so that neighbouring items start in different LDS banks when E is 16.
-constexpr int kVS = 7, kCS = 7, kJS = 13;
+// The two sides of a joint lie an odd number of rows apart as well: neighbouring lanes store to both at once.
+constexpr int kVS = 7, kCS = 7, kJS = 13, kSide = 7;
 constexpr int kPairHitMin = 256;   // (gap, key) words a workgroup keeps at least
 // Words of LDS a workgroup can ask for: 160 KiB without the 256 bytes that the compiler takes for the barrier
 // that also says whether an env was reset.
@@ -104,8 +107,9 @@ struct LdsPlan {
 
 // field: 0 = plane, 1 = heightfield, 2 = heightfield of which every env keeps a copy
 // pairs: 0 = no capsule-capsule contacts, else the interaction group size (1 = self-collision only)
+// lanes: lanes that relax one joint (1, 2 or 4)
 __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, int E, int field, int pairs = 0,
-                                             int threads = kThreads, int warm = 0, int newton = 0) {
+                                             int threads = kThreads, int warm = 0, int newton = 0, int lanes = 2) {
   LdsPlan p;
   int o = 0;
   const bool with_patch = field == 2;
@@ -138,10 +142,11 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.list = o; o += S * E;
   p.surv = o; o += S * E;   // slots near the heightfield: end spheres from the front, mid-segments from the back
   p.lam = o;   // (with the warm start these impulses live in the per-slot array below)
-  o += warm ? 0 : 3 * (S * E > threads - ((2 * J * E + 63) / 64) * 64 ? S * E - (threads - ((2 * J * E + 63) / 64) * 64) : 0);
+  const int contact_threads = threads - ((lanes * J * E + 63) / 64) * 64;
+  o += warm ? 0 : 3 * (S * E > contact_threads ? S * E - contact_threads : 0);
   p.u = o; o += (D > 0 ? D : 1) * E;
   p.obs = o; o += (11 + 3 * D + F) * E;
-  p.zero = p.obs;   // (the first six rows are zeros until the observation is packed; with capsule pairs: small numbers, see Lpair)
+  p.zero = p.obs;   // (the first six rows are zeros while the sweeps run)
   p.lim = o; o += (D > 0 ? D : 1) * E;
   if (with_patch) o = (o + 3) & ~3;   // (written four samples at a time)
   p.patch = o; o += with_patch ? E * kPatch * kPatch : 0;
@@ -309,17 +314,24 @@ __device__ __forceinline__ void store_record(float* Lrec, int* Lreci, int s, int
 
 // Rows of one joint as seen from ONE of its two bodies (a joint is relaxed by a pair of
 // neighbouring lanes, one per side; a row's J v is the sum of the two lanes' parts, exchanged
-// with a DPP lane swap, and each lane then updates its own body's copy).  sg = -1 for the
-// parent side, +1 for the child side; all signs are folded into the stored vectors.
+// with a DPP lane swap, and each lane then leaves its own body's change of velocity).  sg = -1 for
+// the parent side, +1 for the child side; all signs are folded into the stored vectors.
+// The rows of a block are relaxed one after another, each on the velocities the ones before it left.
+// All six J v are taken from the snapshot at once, and what an earlier row of the block adds to a later
+// row's is its impulse times an entry of J M^-1 J^T (both bodies scaled by W / w), known since the set-up:
+// the sequence is then a triangular one over impulses instead of a trip through both velocities per row.
 struct SideRows {
   float sr[3];             // sg * lever arm from the own centre to the shared impulse point
-  float sv;                // sg * n_o / m_o: own linear response per unit impulse
+  float sv;                // sg / m_o: own linear response per unit impulse
   float sg;
   float Y[3][3];           // own angular response per unit impulse of positional row k
   float pme[3], pnb[3];    // -m_eff and -m_eff * bias of the positional rows (world x, y, z)
   float sax[3][3];         // sg * joint axis k (sign of an upper limit folded in)
   float Z[3][3];           // own angular response per unit impulse of angular row k
   float ame[3], anb[3];
+  float pp[3];             // -m_eff (J M^-1 J^T) of rows (1, 0), (2, 0), (2, 1)
+  float ap[3][3];          //                     of angular row k and positional row c
+  float aa[3];             //                     of angular rows (1, 0), (2, 0), (2, 1)
   float nl[3];             // lower bound of the next increment of angular row k: minus the impulse so
                            // far for a limit row (impulse >= 0), -infinity for a locked axis
   float lam[3];            // impulses of the angular rows so far (only the warm start keeps them)
@@ -331,6 +343,35 @@ struct SideRows {
 // value of the neighbouring lane (lane ^ 1), one DPP move
 __device__ __forceinline__ float lane_swap1(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, true));
+}
+
+// value of another lane of the same four: lane i takes that of lane (kCtrl >> 2 i) & 3
+template <int kCtrl>
+__device__ __forceinline__ float quad_move(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xF, 0xF, true));
+}
+
+// All six rows of a joint in one lane: what SideRows holds of both sides ([0] parent, [1] child; signs folded in).
+struct JointRows {
+  float sr[2][3], sv[2], Y[2][3][3], sax[2][3][3], Z[2][3][3];
+  float pme[3], pnb[3], ame[3], anb[3], pp[3], ap[3][3], aa[3], nl[3], lam[3];
+  int onesided, upper;
+};
+
+// The three rows of one lane of four (see the sweeps): positional or angular ones of one side of a joint.
+struct QuadRows {
+  float K[3][3], kv;       // J on the side's angular velocity; on its linear velocity (angular rows: 0)
+  float me[3], nb[3];      // -m_eff, -m_eff * bias
+  float t1[3], t2[3];      // -m_eff (J M^-1 J^T) among positional, among angular rows (0 in the other kind's lanes)
+  float ap[3][3];          //                     of angular with positional rows (positional: 0)
+  float nl[3], lam[3];     // lower bound of the next increments; impulses so far (warm start)
+  float R[3][3], sv;       // the side's angular response, its linear one
+};
+
+// lane_swap1 through the LDS crossbar (no memory is touched): twice the latency of a DPP move for a wavefront that has
+// its SIMD to itself, but a DPP move holds up the SIMD's other wavefronts
+__device__ __forceinline__ float lane_swap1_crossbar(float x) {
+  return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0x041F /* lane ^ 1 */));
 }
 
 // maximum without the instruction that quietens a signalling NaN first, which the compiler puts before
@@ -361,10 +402,12 @@ __device__ __forceinline__ void wave_sum3(float& a, float& b, float& c) {
 
 struct ContactRows {
   float dir[3][3];   // n, t1, t2
+  float rc[3];       // lever arm
   float ang[3][3];   // rc x dir
   float Y[3][3];     // angular response
-  float ls;          // linear response n_b / m
+  float ls;          // linear response 1 / m
   float meff[3], bias, lam[3];
+  float tn[2];       // -m_eff (J M^-1 J^T) of the tangent rows and the normal row, see SideRows
   float D[3];        // (Newton solver) diagonal of J M^-1 J^T
   int slot_e;        // slot * E + e
   int body;
@@ -399,15 +442,15 @@ __device__ __forceinline__ void build_contact_rows(ContactRows& c, const float* 
   for (int k = 0; k < 3; ++k) t1[k] *= inv;
   cross(n, t1, t2);
   for (int k = 0; k < 3; ++k) { c.dir[0][k] = n[k]; c.dir[1][k] = t1[k]; c.dir[2][k] = t2[k]; }
-  c.ls = nbb * imb;
+  for (int k = 0; k < 3; ++k) c.rc[k] = rc[k];
+  c.ls = imb;
   for (int r = 0; r < 3; ++r) {
-    float y[3];
     cross(rc, c.dir[r], c.ang[r]);
-    sym_vec(iwb, c.ang[r], y);
-    float keff = nbb * (imb + dot(c.ang[r], y));
+    sym_vec(iwb, c.ang[r], c.Y[r]);
+    float keff = nbb * (imb + dot(c.ang[r], c.Y[r]));
     c.meff[r] = keff > 0.0f ? 1.0f / keff : 0.0f;
     c.D[r] = keff;
-    for (int k = 0; k < 3; ++k) c.Y[r][k] = nbb * y[k];
+    if (r > 0) c.tn[r - 1] = -c.meff[r] * (nbb * dot(c.ang[r], c.Y[0]));   // (n and t are orthogonal: no linear part)
     c.lam[r] = 0.0f;
   }
   c.bias = d >= 0.0f ? d / h : fmaxf(beta_c * d / h, -v_depen);
@@ -419,39 +462,34 @@ __device__ __forceinline__ void build_contact_rows(ContactRows& c, const float* 
 // rounded square root and division; the floor keeps a denormal |l|^2 from turning into infinity.
 __device__ __forceinline__ void project_on_disc(float& l1, float& l2, float lim) {
   const float n2 = sum2(l1, l1, l2, l2);
-  if (n2 > lim * lim) {
-    const float sc = lim * __builtin_amdgcn_rsqf(fmaxf(n2, 1e-30f));
-    l1 *= sc; l2 *= sc;
-  }
+  const float on_disc = lim * __builtin_amdgcn_rsqf(fmaxf(n2, 1e-30f));
+  const float sc = n2 > lim * lim ? on_disc : 1.0f;
+  l1 *= sc; l2 *= sc;
 }
 
-// One sweep of a contact block on its private copy (vv, ww) of the body velocity:
-// normal row (impulse >= 0), then the friction pair projected on the disc mu * lambda_n.
-__device__ __forceinline__ void relax_contact(ContactRows& c, float mu, float vv[3], float ww[3]) {
-  {
-    float jv = dot(c.dir[0], vv) + dot(c.ang[0], ww);
-    const float ln = fmaxf(fma_(-c.meff[0], jv + c.bias, c.lam[0]), 0.0f);
-    const float dl = ln - c.lam[0];
-    c.lam[0] = ln;
-    for (int k = 0; k < 3; ++k) { vv[k] = fma_(c.ls * c.dir[0][k], dl, vv[k]); ww[k] = fma_(c.Y[0][k], dl, ww[k]); }
-  }
-  float jv1 = dot(c.dir[1], vv) + dot(c.ang[1], ww);
-  float jv2 = dot(c.dir[2], vv) + dot(c.ang[2], ww);
-  float l1 = fma_(-c.meff[1], jv1, c.lam[1]), l2 = fma_(-c.meff[2], jv2, c.lam[2]);
-  const float lim = mu * c.lam[0];
-  project_on_disc(l1, l2, lim);
-  float d1 = l1 - c.lam[1], d2 = l2 - c.lam[2];
-  c.lam[1] = l1; c.lam[2] = l2;
+// What the impulses d of a contact's rows change in its body's velocity.
+__device__ __forceinline__ void contact_response(const ContactRows& c, const float d[3], float vv[3], float ww[3]) {
   for (int k = 0; k < 3; ++k) {
-    vv[k] = fma_(c.ls, sum2(c.dir[1][k], d1, c.dir[2][k], d2), vv[k]);
-    ww[k] += sum2(c.Y[1][k], d1, c.Y[2][k], d2);
+    vv[k] = c.ls * sum3(c.dir[0][k], d[0], c.dir[1][k], d[1], c.dir[2][k], d[2]);
+    ww[k] = sum3(c.Y[0][k], d[0], c.Y[1][k], d[1], c.Y[2][k], d[2]);
   }
 }
 
-// Warm start: the block's copy of its body after the impulses the rows start from.
-__device__ __forceinline__ void apply_contact_impulses(const ContactRows& c, float vv[3], float ww[3]) {
-  for (int r = 0; r < 3; ++r)
-    for (int k = 0; k < 3; ++k) { vv[k] = fma_(c.ls * c.dir[r][k], c.lam[r], vv[k]); ww[k] = fma_(c.Y[r][k], c.lam[r], ww[k]); }
+// One sweep of a contact block from the snapshot (vv, ww) of the body velocity, which the change it makes
+// replaces: normal row (impulse >= 0), then the friction pair projected on the disc mu * lambda_n.
+__device__ __forceinline__ void relax_contact(ContactRows& c, float mu, float vv[3], float ww[3]) {
+  // velocity of the contact point
+  const float u[3] = {fma_(ww[1], c.rc[2], fma_(-ww[2], c.rc[1], vv[0])), fma_(ww[2], c.rc[0], fma_(-ww[0], c.rc[2], vv[1])),
+                      fma_(ww[0], c.rc[1], fma_(-ww[1], c.rc[0], vv[2]))};
+  const float b1 = fma_(-c.meff[1], dot(c.dir[1], u), c.lam[1]), b2 = fma_(-c.meff[2], dot(c.dir[2], u), c.lam[2]);
+  const float ln = fmaxf(fma_(-c.meff[0], dot(c.dir[0], u) + c.bias, c.lam[0]), 0.0f);
+  float d[3];
+  d[0] = ln - c.lam[0];
+  float l1 = fma_(c.tn[0], d[0], b1), l2 = fma_(c.tn[1], d[0], b2);
+  project_on_disc(l1, l2, mu * ln);
+  d[1] = l1 - c.lam[1]; d[2] = l2 - c.lam[2];
+  c.lam[0] = ln; c.lam[1] = l1; c.lam[2] = l2;
+  contact_response(c, d, vv, ww);
 }
 
 // Rows of one capsule-capsule contact (Section 3.1: contacts among bodies; Section 4.1:
@@ -459,15 +497,15 @@ __device__ __forceinline__ void apply_contact_impulses(const ContactRows& c, flo
 // body A (+J) and body B (-J), one contact point for both (midway between the closest surface
 // points, so the pair of opposite impulses carries no net torque).  Like a joint, a contact is
 // relaxed by two neighbouring lanes, one per body; a row's J v is the sum of the two lanes'
-// parts, both lanes compute the same impulse and each updates its own body's copy.  All signs
-// (+1 for A, -1 for B) are folded into the stored vectors.
+// parts, both lanes compute the same impulse and each leaves its own body's change of velocity.  All
+// signs (+1 for A, -1 for B) are folded into the stored vectors.
 struct PairSide {
   float sd[3][3];    // sg * (n, t1, t2); n points from B to A
   float sa[3][3];    // sg * (lever arm x direction)
   float Y[3][3];     // own angular response per unit impulse
   float ls;          // own linear response per unit impulse along sd
   float meff[3], bias, lam[3];
-  float wk;          // the block's weight: copies are published multiplied by it
+  float tn[2];       // -m_eff (J M^-1 J^T) of the tangent rows and the normal row, see SideRows
   int off;           // own body's velocity rows in LDS: body * kVS * E + env
 };
 
@@ -519,42 +557,38 @@ __device__ __forceinline__ void build_pair_side(PairSide& c, int side, const flo
   for (int i = 0; i < 3; ++i) t1[i] *= inv;
   cross(n, t1, t2);
   for (int i = 0; i < 3; ++i) { c.sd[0][i] = sg * n[i]; c.sd[1][i] = sg * t1[i]; c.sd[2][i] = sg * t2[i]; }
-  c.ls = nbo * imo;
+  c.ls = imo;
   for (int r = 0; r < 3; ++r) {
-    float y[3];
     cross(arm, c.sd[r], c.sa[r]);
-    sym_vec(iwo, c.sa[r], y);
-    const float kp = nbo * (imo + dot(c.sa[r], y));
+    sym_vec(iwo, c.sa[r], c.Y[r]);
+    const float kp = nbo * (imo + dot(c.sa[r], c.Y[r]));
     const float keff = kp + lane_swap1(kp);
     c.meff[r] = keff > 0.0f ? 1.0f / keff : 0.0f;
-    for (int i = 0; i < 3; ++i) c.Y[r][i] = nbo * y[i];
+    if (r > 0) {
+      const float kt = nbo * dot(c.sa[r], c.Y[0]);
+      c.tn[r - 1] = -c.meff[r] * (kt + lane_swap1(kt));
+    }
     c.lam[r] = 0.0f;
   }
   c.bias = d >= 0.0f ? d / h : fmaxf(beta_c * d / h, -v_depen);
-  c.wk = wk;
   c.off = bo * kVS * E + eo;
 }
 
-// One sweep of one side of a capsule-capsule block on its private copy of the own body's velocity.
+// One sweep of one side of a capsule-capsule block from the snapshot (v, w) of the own body's velocity, which
+// the change it makes replaces.
 __device__ __forceinline__ void relax_pair_side(PairSide& c, float mu, float v[3], float w[3]) {
-  {
-    const float part = dot(c.sd[0], v) + dot(c.sa[0], w);
-    const float jv = part + lane_swap1(part);
-    const float ln = fmaxf(fma_(-c.meff[0], jv + c.bias, c.lam[0]), 0.0f);
-    const float dl = ln - c.lam[0];
-    c.lam[0] = ln;
-    for (int k = 0; k < 3; ++k) { v[k] = fma_(c.ls * c.sd[0][k], dl, v[k]); w[k] = fma_(c.Y[0][k], dl, w[k]); }
-  }
-  const float p1 = dot(c.sd[1], v) + dot(c.sa[1], w), p2 = dot(c.sd[2], v) + dot(c.sa[2], w);
-  const float jv1 = p1 + lane_swap1(p1), jv2 = p2 + lane_swap1(p2);
-  float l1 = fma_(-c.meff[1], jv1, c.lam[1]), l2 = fma_(-c.meff[2], jv2, c.lam[2]);
-  const float lim = mu * c.lam[0];
-  project_on_disc(l1, l2, lim);
+  const float p0 = dot(c.sd[0], v) + dot(c.sa[0], w), p1 = dot(c.sd[1], v) + dot(c.sa[1], w), p2 = dot(c.sd[2], v) + dot(c.sa[2], w);
+  const float jv0 = p0 + lane_swap1(p0), jv1 = p1 + lane_swap1(p1), jv2 = p2 + lane_swap1(p2);
+  const float b1 = fma_(-c.meff[1], jv1, c.lam[1]), b2 = fma_(-c.meff[2], jv2, c.lam[2]);
+  const float ln = fmaxf(fma_(-c.meff[0], jv0 + c.bias, c.lam[0]), 0.0f);
+  const float d0 = ln - c.lam[0];
+  float l1 = fma_(c.tn[0], d0, b1), l2 = fma_(c.tn[1], d0, b2);
+  project_on_disc(l1, l2, mu * ln);
   const float d1 = l1 - c.lam[1], d2 = l2 - c.lam[2];
-  c.lam[1] = l1; c.lam[2] = l2;
+  c.lam[0] = ln; c.lam[1] = l1; c.lam[2] = l2;
   for (int k = 0; k < 3; ++k) {
-    v[k] = fma_(c.ls, sum2(c.sd[1][k], d1, c.sd[2][k], d2), v[k]);
-    w[k] += sum2(c.Y[1][k], d1, c.Y[2][k], d2);
+    v[k] = c.ls * sum3(c.sd[0][k], d0, c.sd[1][k], d1, c.sd[2][k], d2);
+    w[k] = sum3(c.Y[0][k], d0, c.Y[1][k], d1, c.Y[2][k], d2);
   }
 }
 
@@ -729,7 +763,8 @@ __device__ __forceinline__ const T* reload_constant(const T* p) {
 // NT: threads per workgroup.
 // NS != 0: the rows are solved by the non-smooth Newton / conjugate-residual solver instead of
 // the Jacobi sweeps (at most 8 envs per workgroup, every slot has a contact thread of its own).
-template <int EC, int NJ, int PC = 0, int NT = kThreads, int WS = 0, int NS = 0>
+// JL: lanes that relax one joint: one, two (one per side) or four (one per side and kind of row).
+template <int EC, int NJ, int PC = 0, int NT = kThreads, int WS = 0, int NS = 0, int JL = 2>
 __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   constexpr int kThreads = NT;   // (shadows the namespace-scope default inside the kernel)
 #ifdef SIM_PHASE_TIMING
@@ -760,7 +795,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   const Field H0 = make_field(M, a.heights, a.coarse);
   const bool use_patch = m_terrain == 1 && H0.nx >= kPatch && H0.ny >= kPatch;
   const int m_group = PC ? (M.group > 1 ? M.group : 1) : 1, m_npairs = PC ? M.n_pairs : 0, m_nap = PC ? M.n_agent_pairs : 0;
-  const LdsPlan P = make_plan(B, J, S, D, F, E, use_patch ? 2 : (m_terrain == 1 ? 1 : 0), PC ? m_group : 0, NT, WS, NS);
+  const LdsPlan P = make_plan(B, J, S, D, F, E, use_patch ? 2 : (m_terrain == 1 ? 1 : 0), PC ? m_group : 0, NT, WS, NS, JL);
   float* Lpos = lds + P.pos;
   float* Lvel = lds + P.vel;
   float* Liw = lds + P.iw;
@@ -783,10 +818,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   unsigned* Lcell_m = Lcell_e + cell_e_cap;
   unsigned* Lrow_e = Lcell_m + cell_m_cap;
   unsigned* Lrow_m = Lrow_e + row_e_cap;
-  // Candidate pairs of the capsule-capsule search, in the space the observations are staged in at the end.  The
-  // average of the copies reads its unused entries there, with weight 0: a packed pair, read as a float, is
-  // finite (the env in its top twelve bits would have to reach 2040 to make the exponent of an infinity).
-  static_assert(((kThreadsWide - 1) << 20 | 0xfffff) < 0x7f800000, "a packed pair is no finite float");
+  // Candidate pairs of the capsule-capsule search, in the space the observations are staged in at the end.
   unsigned* Lpair = reinterpret_cast<unsigned*>(lds + P.obs);
   const int pair_cap = (11 + 3 * D + F) * E;
   float* Ltq = lds + P.tq;                           // joint torques, [J][3][E]
@@ -832,7 +864,6 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     root_wx = st[0] + a.origins[3 * ag]; root_wy = st[(size_t)B * N] + a.origins[3 * ag + 1];
   }
   float x[3] = {0, 0, 0}, q[4] = {1, 0, 0, 0}, v[3] = {0, 0, 0}, w[3] = {0, 0, 0};
-  int my_slot0 = 0, my_nslots = 0, my_njs = 0;
   const int b = idx;
   if (is_body) {
     const float* st = a.state + (size_t)b * N + agent;
@@ -841,8 +872,6 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     q[0] = st[3 * fs]; q[1] = st[4 * fs]; q[2] = st[5 * fs]; q[3] = st[6 * fs];
     v[0] = st[7 * fs]; v[1] = st[8 * fs]; v[2] = st[9 * fs];
     w[0] = st[10 * fs]; w[1] = st[11 * fs]; w[2] = st[12 * fs];
-    const BodyTab& bt = M.bodies[b];
-    my_slot0 = bt.slot0; my_nslots = bt.n_slots; my_njs = bt.n_joint_sides;
   }
   if (copy_field && pe < E) {
     // four samples at a time (a row of the copy is seven of them; rows start at any sample), all of a
@@ -903,7 +932,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     if (a.task.enabled && a.count_step && env_t_ok) { a.push[3 * env_t] = fx; a.push[3 * env_t + 1] = fy; a.push[3 * env_t + 2] = 0.0f; }
   }
   for (int i = tid; i < M.table_words; i += kThreads) reinterpret_cast<int*>(lds + P.tjs)[i] = M.table_image[i];
-  for (int i = tid; i < 6 * E; i += kThreads) lds[P.zero + i] = 0.0f;
+  if constexpr (PC == 0)
+    for (int i = tid; i < 6 * E; i += kThreads) lds[P.zero + i] = 0.0f;
   if (tid < 8) Lcount[tid] = 0;
   if constexpr (WS != 0) {
     for (int i = tid; i < J * 6 * E; i += kThreads) {
@@ -950,11 +980,12 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   TMARK(0);
   // wavefronts [0, joint_threads/64) hold the joint-side threads; contact k of a workgroup goes
   // to thread kThreads-1-k as long as that thread is not in a joint wavefront (n_reg contacts)
-  const int joint_threads = ((2 * J * E + 63) / 64) * 64;
+  const int joint_threads = ((JL * J * E + 63) / 64) * 64;
   const int n_reg = kThreads - joint_threads;
   const bool joint_wave = __builtin_amdgcn_readfirstlane(tid) < joint_threads;
-  // joint-side role: lanes 2p and 2p+1 are the parent and the child side of pair p = (joint, env)
-  const int js_side = tid & 1, js_e = (tid >> 1) % E, js_j = (tid >> 1) / E;
+  // joint-side role: JL neighbouring lanes for pair p = (joint, env); the lowest bit says whether a lane is on the
+  // parent's or the child's side, with four lanes the next one whether it has the positional or the angular rows
+  const int js_side = JL > 1 ? tid & 1 : 0, js_kind = JL == 4 ? (tid >> 1) & 1 : 0, js_e = (tid / JL) % E, js_j = (tid / JL) / E;
   const bool js_on = js_j < J && blockIdx.x * E + js_e < N;
 
   // the heightfield with the env's copy of it
@@ -1565,19 +1596,21 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       }
     }
     TMARK(16);
-    // The per-body average is split over several threads when the workgroup has room: thread
-    // (e, p * B + b) takes part p of the six velocity components of body b.  A wavefront issues one
-    // instruction every five to six cycles however many others share its SIMD, so short threads beat
-    // a long one, as long as no SIMD gets more than a few of them.  The number of parts is the
-    // largest that always fits (kMaxBodies bodies); the general form has two or one.
+    // The sums of a body are split over several threads when the workgroup has room: thread (e, b * kParts + p)
+    // takes part p of the six velocity components of body b.  Short threads beat a long one, and the parts of a
+    // body lie next to each other: their rows do too, so that neighbouring lanes read different banks, and a
+    // wavefront holds few bodies, so that few have to go by the one with the most joints or contacts.  The number
+    // of parts is the largest that always fits (kMaxBodies bodies); the general form has two or one.
     constexpr int kParts = EC == 0 ? 2 : (6 * kMaxBodies * EC <= NT ? 6 : (3 * kMaxBodies * EC <= NT ? 3 : 2));
     constexpr int kPartC = 6 / kParts;   // components of a part
     const bool g_split = (EC > 0 && kParts * kMaxBodies * EC <= NT) || kParts * B * E <= kThreads;
-    int g_part = 0;
-#pragma unroll
-    for (int k = 1; k < kParts; ++k) g_part += (g_split && idx >= k * B) ? 1 : 0;
-    const int g_b = idx - g_part * B;
-    const bool g_on = env_ok && g_b < B;
+    // (threads behind the last body's last part, where the wavefront has work at all, do what its threads do, to the
+    // last bit: E divides 64 in the compiled forms, so that part lies in the same wavefront)
+    constexpr bool g_all = EC > 0 && NS == 0;
+    const int g_items = (g_split ? kParts : 1) * B, g_item = g_all && idx >= g_items ? g_items - 1 : idx;
+    const int g_b = g_split ? g_item / kParts : g_item, g_part = g_split ? g_item - g_b * kParts : 0;
+    const bool g_on = g_all || (env_ok && g_b < B);
+    const bool g_wave = !g_all || __builtin_amdgcn_readfirstlane(idx) < g_items;
     const int g_ref = g_b * E + e;
     // capsule-capsule contacts of body g_b: where their (weighted) copies will be (up to kPairList
     // of them; a body with more walks the queue in every sweep), and the sum of their weights
@@ -1627,10 +1660,11 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     //         everybody; without, the lanes that need it add up the body's three slots themselves, which
     //         saves a phase and its barrier.
     if constexpr (PC != 0) {
-      if (is_body) {
-        float nbf = (float)my_njs;
-        for (int k = 0; k < my_nslots; ++k) nbf += Lrec[((my_slot0 + k) * kRecWords + 10) * E + e];
-        Lnb[b * E + e] = nbf + gp_wsum;   // (a body thread is the first averaging thread of its own body)
+      if (g_on && g_part == 0) {
+        const int* tb = Ltjs + g_b * (kMaxBodyJoints + 3);
+        float nbf = (float)tb[0];
+        for (int k = 0; k < tb[2]; ++k) nbf += Lrec[((tb[1] + k) * kRecWords + 10) * E + e];
+        Lnb[g_ref] = nbf + gp_wsum;
       }
     }
     auto weight_sum = [&](int bb, int ee) -> float {
@@ -1671,11 +1705,13 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         }
       }
       __syncthreads();
+      // (the candidates of the search were here; the sums below are behind another barrier)
+      for (int i = tid; i < 6 * E; i += kThreads) lds[P.zero + i] = 0.0f;
     }
 
     TMARK(4);
     // ---- D: row constants
-    const int n_active = Lcount[0];
+    const int n_active = __builtin_amdgcn_readfirstlane(Lcount[0]);
     // The joint rows and the contact rows are built inside the wavefront-uniform branches that use
     // them, so that the two sets of registers are never alive together.  Every lane of the
     // wavefronts concerned builds rows, the idle ones from a clamped index: a value assigned on
@@ -1715,18 +1751,25 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       const float sgl = ghost ? 0.0f : sg;
       for (int c = 0; c < 3; ++c) jr.sr[c] = sgl * r[c];
       jr.sg = sgl;
-      jr.sv = sg * no * imo;
+      jr.sv = sg * imo;
       const float inv_h = __builtin_amdgcn_rcpf(h), bh = p_beta_j * inv_h;
+      float y[3][3], yn[3][3], zn[3][3];   // responses of the rows, and times the body's share
       for (int k = 0; k < 3; ++k) {
-        float cr[3], y[3];
+        float cr[3];
         cross_unit(r, k, cr);
-        sym_vec(iwo, cr, y);
-        const float kp = no * (imo + dot(cr, y));
+        sym_vec(iwo, cr, y[k]);
+        for (int c = 0; c < 3; ++c) yn[k][c] = no * y[k][c];
+        const float kp = fma_(no, imo, cross_unit_dot(r, k, yn[k]));
         const float keff = kp + lane_swap1(kp);
         jr.pme[k] = keff > 0.0f ? -__builtin_amdgcn_rcpf(keff) : 0.0f;
         jr.pnb[k] = jr.pme[k] * (bh * C[k]);
         jr.pD[k] = keff; jr.pb[k] = bh * C[k];
-        for (int c = 0; c < 3; ++c) jr.Y[k][c] = sg * no * y[c];
+        for (int c = 0; c < 3; ++c) jr.Y[k][c] = sg * y[k][c];
+        if constexpr (NS == 0)
+          for (int c = 0; c < k; ++c) {
+            const float kc = cross_unit_dot(r, k, yn[c]);
+            jr.pp[k + c - 1] = jr.pme[k] * (kc + lane_swap1(kc));
+          }
       }
       // joint angles from both orientations; axes live in the parent frame
       float qx[4], qa[4], qb[4], Ra[9], phi[3];
@@ -1758,9 +1801,104 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         jr.aD[k] = keff; jr.ab[k] = bias;
         jr.lam[k] = 0.0f;
         jr.nl[k] = jt.mode[k] == 0 ? -INFINITY : 0.0f;
-        for (int c = 0; c < 3; ++c) { jr.sax[k][c] = sgl * ak[c]; jr.Z[k][c] = sg * no * z[c]; }
+        for (int c = 0; c < 3; ++c) { jr.sax[k][c] = sgl * ak[c]; jr.Z[k][c] = sg * z[c]; }
+        if constexpr (NS == 0) {
+          for (int c = 0; c < 3; ++c) zn[k][c] = no * z[c];
+          for (int c = 0; c < 3; ++c) {
+            const float kc = cross_unit_dot(r, c, zn[k]);
+            jr.ap[k][c] = jr.ame[k] * (kc + lane_swap1(kc));
+          }
+          for (int c = 0; c < k; ++c) {
+            const float kc = dot(ak, zn[c]);
+            jr.aa[k + c - 1] = jr.ame[k] * (kc + lane_swap1(kc));
+          }
+        }
       }
      }
+    };
+    // The same with both sides in one lane: the same operations on the same numbers, without lane swaps.
+    auto build_joint = [&](JointRows& R, int js_j, int e) {
+      const JointTab& jt = Ltjoint[js_j < J ? js_j : J - 1];
+      float xo[2][3], qo[2][4], iwo[2][6], no[2], imo[2], t0[2][3], r[2][3], C[3];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int ob = s ? jt.child : jt.parent;           // -1: the static world
+        const bool ghost = ob < 0;
+        const int bo = ghost ? 0 : ob;
+        for (int c = 0; c < 3; ++c) xo[s][c] = Lpos[(bo * 7 + c) * E + e];
+        for (int c = 0; c < 4; ++c) qo[s][c] = Lpos[(bo * 7 + 3 + c) * E + e];
+        for (int c = 0; c < 6; ++c) iwo[s][c] = Liw[(bo * kVS + c) * E + e];
+        no[s] = weight_sum(bo, e); imo[s] = Ltbody[4 * bo + 3];
+        if (ghost) {
+          for (int c = 0; c < 3; ++c) xo[s][c] = 0.0f;
+          qo[s][0] = 1.0f; qo[s][1] = qo[s][2] = qo[s][3] = 0.0f;
+          for (int c = 0; c < 6; ++c) iwo[s][c] = 0.0f;
+          no[s] = 0.0f; imo[s] = 0.0f;
+        }
+      }
+      float Ra[9], Rb[9];
+      quat_to_mat(qo[0], Ra);
+      quat_to_mat(qo[1], Rb);
+      mat_vec(Ra, jt.la, t0[0]);
+      mat_vec(Rb, jt.lb, t0[1]);
+      for (int c = 0; c < 3; ++c) {
+        C[c] = (xo[1][c] - xo[0][c]) + (t0[1][c] - t0[0][c]);   // child anchor minus parent anchor
+        r[0][c] = fma_(0.5f, C[c], t0[0][c]); r[1][c] = fma_(-0.5f, C[c], t0[1][c]);   // impulses act at the midpoint
+      }
+      for (int c = 0; c < 3; ++c) { R.sr[0][c] = -r[0][c]; R.sr[1][c] = r[1][c]; }
+      R.sv[0] = -imo[0]; R.sv[1] = imo[1];
+      const float inv_h = __builtin_amdgcn_rcpf(h), bh = p_beta_j * inv_h;
+      float yn[2][3][3], zn[2][3][3];
+      for (int k = 0; k < 3; ++k) {
+        float kp[2], y[2][3];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          float cr[3];
+          cross_unit(r[s], k, cr);
+          sym_vec(iwo[s], cr, y[s]);
+          for (int c = 0; c < 3; ++c) { yn[s][k][c] = no[s] * y[s][c]; R.Y[s][k][c] = s ? y[s][c] : -y[s][c]; }
+          kp[s] = fma_(no[s], imo[s], cross_unit_dot(r[s], k, yn[s][k]));
+        }
+        const float keff = kp[0] + kp[1];
+        R.pme[k] = keff > 0.0f ? -__builtin_amdgcn_rcpf(keff) : 0.0f;
+        R.pnb[k] = R.pme[k] * (bh * C[k]);
+        for (int c = 0; c < k; ++c)
+          R.pp[k + c - 1] = R.pme[k] * (cross_unit_dot(r[0], k, yn[0][c]) + cross_unit_dot(r[1], k, yn[1][c]));
+      }
+      float phi[3];
+      rel_rotvec(qo[0], qo[1], phi);
+      R.onesided = 0;
+      R.upper = 0;
+      for (int k = 0; k < 3; ++k) {
+        float ak[3], z[2][3], kp[2];
+        mat_vec(Ra, jt.axes[k], ak);
+        const float th = dot(jt.axes[k], phi);
+        float sgn = 1.0f, bias;
+        if (jt.mode[k] == 0) {
+          bias = bh * th;
+        } else {
+          float glo = th - jt.lo[k], ghi = jt.hi[k] - th, g;
+          if (glo < ghi) { g = glo; } else { g = ghi; sgn = -1.0f; R.upper |= 1 << k; }
+          bias = g >= 0.0f ? g * inv_h : bh * g;
+          R.onesided |= 1 << k;
+        }
+        for (int c = 0; c < 3; ++c) ak[c] *= sgn;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          sym_vec(iwo[s], ak, z[s]);
+          kp[s] = no[s] * dot(ak, z[s]);
+          for (int c = 0; c < 3; ++c) { zn[s][k][c] = no[s] * z[s][c]; R.Z[s][k][c] = s ? z[s][c] : -z[s][c]; R.sax[s][k][c] = s ? ak[c] : -ak[c]; }
+        }
+        const float keff = kp[0] + kp[1];
+        R.ame[k] = keff > 0.0f ? -__builtin_amdgcn_rcpf(keff) : 0.0f;
+        R.anb[k] = R.ame[k] * bias;
+        R.lam[k] = 0.0f;
+        R.nl[k] = jt.mode[k] == 0 ? -INFINITY : 0.0f;
+        for (int c = 0; c < 3; ++c)
+          R.ap[k][c] = R.ame[k] * (cross_unit_dot(r[0], c, zn[0][k]) + cross_unit_dot(r[1], c, zn[1][k]));
+        for (int c = 0; c < k; ++c)
+          R.aa[k + c - 1] = R.ame[k] * (dot(ak, zn[0][c]) + dot(ak, zn[1][c]));
+      }
     };
     // contact k of the workgroup's list goes to thread kThreads-1-k (the joint threads sit at
     // the low end); contacts beyond one per thread start from zero impulse in LDS
@@ -1783,6 +1921,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     const int pk_up = (kThreads - joint_threads) >> 1;
     const int pk = tid >= joint_threads ? (tid - joint_threads) >> 1 : pk_up + ((joint_threads - 1 - tid) >> 1);
     const bool has_pair = PC != 0 && pk < n_pc;
+    // (in the compiled forms there is room above the joint wavefronts for all that a workgroup can hold)
+    constexpr bool kPairsInJoints = PC != 0 && (EC == 0 || (NT - ((JL * kMaxJoints * EC + 63) / 64) * 64) / 2 < kPairCap);
     auto build_pair = [&]() {
       if constexpr (PC != 0) {
         if (n_pc > 0) build_pair_side(pr, tid & 1, Lpq, Lpos, Liw, Lnb, Lorg, Ltbody, pk < n_pc ? pk : n_pc - 1, E, h, p_beta_c, p_vdepen);
@@ -1797,93 +1937,95 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     };
 
     TMARK(5);
-    // The copies a body averages: NJ joint sides and its three contact slots.  Entries that are not in use
-    // point at finite numbers (P.zero) and have weight 0 (the copies share their space with the terrain search,
-    // so only those that a block writes in every sweep are read).
-    float g_inb = 0.0f;
-    int gat_off[NJ], gat_slot[3];
-    float gat_w[NJ + 3];
-    {
+    // What a body adds up: the changes of NJ joint sides and of its contact slots.  Entries that are not in use
+    // point at zeros (P.zero; the changes share their space with the terrain search, so only those that a block
+    // writes in every sweep are read).  The slots that hold a contact come first.
+    // (Newton's method with a wavefront per env has lists of its own)
+    const bool env_per_wave = NS != 0 && 2 * J + S <= 64;
+    int gat_off[NJ], gat_slot[3], g_njs = 0, g_nc = 0;
+#pragma unroll
+    for (int k = 0; k < NJ; ++k) gat_off[k] = P.zero;
+    gat_slot[0] = gat_slot[1] = gat_slot[2] = P.zero;
+    if (!env_per_wave) {
       const int* tb = Ltjs + (g_on ? g_b : 0) * (kMaxBodyJoints + 3);
-      const int g_njs = tb[0], g_slot0 = tb[1], g_nslots = tb[2];
-      const float g_nbf = g_on && NS == 0 ? weight_sum(g_b, e) : 0.0f;
-      g_inb = g_nbf > 0.0f ? 1.0f / g_nbf : 0.0f;
+      g_njs = g_on ? tb[0] : 0;
+      const int g_slot0 = tb[1], g_nslots = tb[2], zero = P.zero + e;
 #pragma unroll
       for (int k = 0; k < NJ; ++k) {
-        const bool used = g_on && k < g_njs;
+        const bool used = k < g_njs;
         int js = used ? tb[3 + k] : 0;
-        gat_off[k] = (used ? P.outj + ((js >> 1) * kJS + (js & 1) * 6) * E : P.zero) + e;
-        gat_w[k] = used ? 1.0f : 0.0f;
+        gat_off[k] = used ? P.outj + ((js >> 1) * kJS + (js & 1) * kSide) * E + e : zero;
       }
+      bool on[3];
+      int at[3];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        const bool used = g_on && k < g_nslots;
-        float wk = used ? Lrec[((g_slot0 + k) * kRecWords + 10) * E + e] : 0.0f;
-        if constexpr (NS != 0) wk = wk > 0.0f ? 1.0f : 0.0f;
-        gat_w[NJ + k] = wk;
-        gat_slot[k] = (wk != 0.0f ? P.outc + (g_slot0 + k) * kCS * E : P.zero) + e;
+        const int sl = g_slot0 + (k < g_nslots ? k : 0);
+        on[k] = g_on && k < g_nslots && Lrec[(sl * kRecWords + 10) * E + e] != 0.0f;
+        at[k] = P.outc + sl * kCS * E + e;
       }
+      gat_slot[0] = on[0] ? at[0] : (on[1] ? at[1] : (on[2] ? at[2] : zero));
+      gat_slot[1] = on[0] && on[1] ? at[1] : ((on[0] || on[1]) && on[2] ? at[2] : zero);
+      gat_slot[2] = on[0] && on[1] && on[2] ? at[2] : zero;
+      g_nc = (int)on[0] + (int)on[1] + (int)on[2];
     }
-    // no body of this wavefront has more than two joint sides: its averages read two joint copies
-    // instead of NJ (the same in all lanes, so the choice is a scalar branch)
-    bool g_few = g_variants && NJ > 2;
-#pragma unroll
-    for (int k = 2; k < NJ; ++k) g_few = g_few && __ballot(gat_w[k] != 0.0f) == 0ull;
-    // no slot of a body of this wavefront holds a contact in this substep: no slot copies are read
-    const bool g_noc = g_variants && __ballot(gat_w[NJ] != 0.0f || gat_w[NJ + 1] != 0.0f || gat_w[NJ + 2] != 0.0f) == 0ull;
+    // The sums of a wavefront read no more entries than its bodies have (the same in all lanes, so the choice is a
+    // scalar branch): two joint entries instead of NJ, no, one or three slots.  An entry is a read from LDS, of
+    // which a wavefront issues one in about eight cycles.
+    const bool g_few = NJ > 2 && __ballot(g_njs > 2) == 0ull;
+    const bool g_noc = __ballot(g_nc > 0) == 0ull, g_onec = __ballot(g_nc > 1) == 0ull, g_twoc = __ballot(g_nc > 2) == 0ull;
     // ---- S: sweeps
+    // What bounds a sweep is the length of one wavefront's chain, twice: rows, then sums, a barrier behind each.  On
+    // this chip an instruction that needs the result of the one before it takes 8 cycles, an independent one 5, a
+    // taken branch 22, a branch around a masked region 27, a read from LDS 70 plus 8 for every further one, and a
+    // lane swap costs another 16 to 30 while a second wavefront of the SIMD computes.  Hence: impulses from a
+    // triangular system instead of a trip through the velocities for every row (48 to 17 instructions waiting for
+    // each other), changes of velocity instead of copies (one addition per entry instead of two operations), no
+    // more entries read than the wavefront's bodies have, loops without branches or masks, four lanes per joint
+    // where the SIMDs have room.  Cycles per sweep, before and now: 64 humanoids (2 envs per workgroup) 869 to 747,
+    // 1024 on the plane (4) 964 to 770, 1500 (8) 1105 to 1000, 4096 (16) 1305 to 1200 and on the plane 1260 to 1150,
+    // 4096 that collide in groups of 4 2260 to 1770.
     // Wavefronts that hold joint threads run only the joint rows, the others only the contact
     // rows (a wave-uniform branch, so neither path carries the other's registers); both paths
     // execute the same two barriers per sweep.
-    // components [c0, c0 + NC) of the average of body g_b (0..2 linear, 3..5 angular velocity)
-    auto gather_part = [&](auto nc_tag, int c0) {
-      constexpr int NC = decltype(nc_tag)::value;
-      if (g_on && g_inb > 0.0f) {
-        // every load is unconditional: unused entries read P.zero and enter the sum with weight 0; all
-        // reads are issued before the first use so their LDS latency is paid once
-        // The average is taken over the copies' differences from the snapshot, (sum of w_k (copy_k -
-        // v0)) / W added to v0: the differences are small next to the velocity itself, so the sum
-        // rounds at their magnitude and the velocity is rounded once per sweep, where a weighted
-        // sum of the copies themselves would round it once per copy.
+    // components [c0, c0 + NC) of the new velocity of body g_b (0..2 linear, 3..5 angular), from KJ joint entries
+    // and HC slots' entries
+    auto gather_part = [&](auto nc_tag, int c0, auto kj_tag, auto hc_tag) {
+      constexpr int NC = decltype(nc_tag)::value, KJ = decltype(kj_tag)::value, HC = decltype(hc_tag)::value;
+      if (g_on) {
+        // The weighted average of the copies of a body, one per block and each scaled by W / w, is its velocity
+        // plus the plain sum of what the blocks' impulses change in it.
+        // Every load is unconditional: unused entries read P.zero.  All reads are issued before the first use so
+        // their LDS latency is paid once; sums of sums, so that few additions wait for each other (in one order for
+        // every KJ and HC: what is left out is zero).
+        // (two components: a linear and an angular one, so that the parts' rows lie one apart)
+        constexpr int kApart = NC == 2 ? 3 : 1;
         const int ho = c0 * E;
-        float v0[NC], acc[NC];
+        float v0[NC], acc[NC], val[KJ + HC][NC];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) v0[c] = Lvel[(g_b * kVS + c) * E + e + ho];
-        // the first KJ joint copies and the three slots' copies
-        auto sum_copies = [&](auto kj_tag, auto hc_tag) {
-          constexpr int KJ = decltype(kj_tag)::value, HC = decltype(hc_tag)::value;
-          float val[KJ + 3][NC];
+        for (int c = 0; c < NC; ++c) v0[c] = Lvel[(g_b * kVS + c * kApart) * E + e + ho];
 #pragma unroll
-          for (int k = 0; k < KJ; ++k)
+        for (int k = 0; k < KJ; ++k)
 #pragma unroll
-            for (int c = 0; c < NC; ++c) val[k][c] = lds[gat_off[k] + ho + c * E];
-          if constexpr (HC != 0) {
+          for (int c = 0; c < NC; ++c) val[k][c] = lds[gat_off[k] + ho + c * kApart * E];
 #pragma unroll
-            for (int k = 0; k < 3; ++k)
+        for (int k = 0; k < HC; ++k)
 #pragma unroll
-              for (int c = 0; c < NC; ++c) val[KJ + k][c] = lds[gat_slot[k] + ho + c * E];
-          }
-          __builtin_amdgcn_sched_group_barrier(0x100, NC == 3 ? (KJ + 1 + 3 * HC) * 2 : KJ + 1 + 3 * HC, 0);  // the DS reads first
+          for (int c = 0; c < NC; ++c) val[KJ + k][c] = lds[gat_slot[k] + ho + c * kApart * E];
+        __builtin_amdgcn_sched_group_barrier(0x100, NC == 3 ? (KJ + 1 + HC) * 2 : KJ + 1 + HC, 0);  // the DS reads first
 #pragma unroll
-          for (int c = 0; c < NC; ++c) acc[c] = 0.0f;
+        for (int c = 0; c < NC; ++c) {
+          float js[KJ];
 #pragma unroll
-          for (int k = 0; k < KJ; ++k)
+          for (int k = 0; k < KJ; ++k) js[k] = val[k][c];
 #pragma unroll
-            for (int c = 0; c < NC; ++c) acc[c] = fma_(gat_w[k], val[k][c] - v0[c], acc[c]);
-          if constexpr (HC != 0) {
+          for (int step = 1; step < KJ; step *= 2)
 #pragma unroll
-            for (int k = 0; k < 3; ++k)
-#pragma unroll
-              for (int c = 0; c < NC; ++c) acc[c] = fma_(gat_w[NJ + k], val[KJ + k][c] - v0[c], acc[c]);
-          }
-        };
-        constexpr int kFew = NJ > 2 ? 2 : NJ;
-        if constexpr (g_variants) {
-          if (g_few && g_noc) sum_copies(std::integral_constant<int, kFew>{}, std::integral_constant<int, 0>{});
-          else if (g_few) sum_copies(std::integral_constant<int, kFew>{}, std::integral_constant<int, 1>{});
-          else sum_copies(std::integral_constant<int, NJ>{}, std::integral_constant<int, 1>{});
-        } else {
-          sum_copies(std::integral_constant<int, NJ>{}, std::integral_constant<int, 1>{});
+            for (int k = 0; k + step < KJ; k += 2 * step) js[k] += js[k + step];
+          acc[c] = js[0];
+          if constexpr (HC == 1) acc[c] += val[KJ][c];
+          if constexpr (HC == 2) acc[c] += val[KJ][c] + val[KJ + 1][c];
+          if constexpr (HC == 3) acc[c] += (val[KJ][c] + val[KJ + 1][c]) + val[KJ + 2][c];
         }
         if constexpr (PC != 0) {
           if (n_pc > 0) {
@@ -1892,21 +2034,19 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
               for (int k = 0; k < n_pc; ++k) {
                 const int refs = __float_as_int(Lpq[k * kPairWords + 1]);
                 if ((refs & 0xffff) == g_ref)
-                  for (int c = 0; c < NC; ++c) acc[c] += Lpo[k * 12 + c0 + c];
+                  for (int c = 0; c < NC; ++c) acc[c] += Lpo[k * 12 + c0 + c * kApart];
                 if (((refs >> 16) & 0xffff) == g_ref)
-                  for (int c = 0; c < NC; ++c) acc[c] += Lpo[k * 12 + 6 + c0 + c];
+                  for (int c = 0; c < NC; ++c) acc[c] += Lpo[k * 12 + 6 + c0 + c * kApart];
               }
-              for (int c = 0; c < NC; ++c) acc[c] = fma_(-gp_wsum, v0[c], acc[c]);   // (their copies come multiplied by the weights)
             } else {
-              // the (weighted) copies of the listed contacts (the list holds the used entries first);
-              // unused entries point at zeros
+              // the entries of the listed contacts (the list holds the used ones first; the others point at zeros)
               auto sum_pairs = [&](auto kp_tag) {
                 constexpr int KP = decltype(kp_tag)::value;
                 float pv[KP][NC];
 #pragma unroll
                 for (int j = 0; j < KP; ++j)
 #pragma unroll
-                  for (int c = 0; c < NC; ++c) pv[j][c] = Lpo[gp_off[j] + c0 + c];
+                  for (int c = 0; c < NC; ++c) pv[j][c] = Lpo[gp_off[j] + c0 + c * kApart];
 #pragma unroll
                 for (int j = 0; j < KP; ++j)
 #pragma unroll
@@ -1918,39 +2058,61 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
               } else {
                 sum_pairs(std::integral_constant<int, kPairList>{});
               }
-              // (the listed copies come multiplied by their weights: the snapshot's share goes off in one piece)
-#pragma unroll
-              for (int c = 0; c < NC; ++c) acc[c] = fma_(-gp_wsum, v0[c], acc[c]);
             }
           }
         }
-        for (int c = 0; c < NC; ++c) Lvel[(g_b * kVS + c) * E + e + ho] = fma_(acc[c], g_inb, v0[c]);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) Lvel[(g_b * kVS + c * kApart) * E + e + ho] = v0[c] + acc[c];
       }
     };
     // one sweep of this thread's side of a capsule-capsule contact, if it has one
     // (a capsule-capsule contact starts every substep without impulses: in the warm start's
-    // sweep -1 its copies are the bodies' velocities as they are)
+    // sweep -1 it changes nothing)
     auto pair_sweep = [&](bool relax) {
       if constexpr (PC != 0) {
         if (has_pair) {
-          float vo[3], wo[3];
-          for (int c = 0; c < 3; ++c) { vo[c] = Lvel[pr.off + c * E]; wo[c] = Lvel[pr.off + (3 + c) * E]; }
-          if (relax) relax_pair_side(pr, p_mu, vo, wo);
+          float vo[3] = {0.0f, 0.0f, 0.0f}, wo[3] = {0.0f, 0.0f, 0.0f};
+          if (relax) {
+            for (int c = 0; c < 3; ++c) { vo[c] = Lvel[pr.off + c * E]; wo[c] = Lvel[pr.off + (3 + c) * E]; }
+            relax_pair_side(pr, p_mu, vo, wo);
+          }
           const int po = (2 * pk + (tid & 1)) * 6;
-          for (int c = 0; c < 3; ++c) { Lpo[po + c] = pr.wk * vo[c]; Lpo[po + 3 + c] = pr.wk * wo[c]; }
+          for (int c = 0; c < 3; ++c) { Lpo[po + c] = vo[c]; Lpo[po + 3 + c] = wo[c]; }
         }
       }
     };
-    auto gather = [&]() {
-      gather_part(std::integral_constant<int, kPartC>{}, kPartC * g_part);
+    auto gather = [&](auto kj_tag, auto hc_tag) {
+      gather_part(std::integral_constant<int, kPartC>{}, (kPartC == 2 ? 1 : kPartC) * g_part, kj_tag, hc_tag);
       if constexpr (kParts == 2) {
-        if (!g_split) gather_part(std::integral_constant<int, kPartC>{}, kPartC);   // one thread per body
+        if (!g_split) gather_part(std::integral_constant<int, kPartC>{}, kPartC, kj_tag, hc_tag);   // one thread per body
       }
     };
+    // All sweeps of a wavefront: rows(it) relaxes what its lanes hold and leaves the changes in LDS, then the sums.
+    // Which form of the sums the wavefront needs is the same in all sweeps, so the choice lies outside the loop
+    // (a branch that is taken costs 22 cycles or more, about as much as four additions).
+    auto sweeps = [&](auto rows) {
+      using std::integral_constant;
+      constexpr int kFew = NJ > 2 ? 2 : NJ;
+      auto loop = [&](auto kj_tag, auto hc_tag) {
+        for (int it = WS ? -1 : 0; it < a.iterations; ++it) {
+          rows(it);
+          __syncthreads();
+          if constexpr (decltype(kj_tag)::value > 0) gather(kj_tag, hc_tag);
+          __syncthreads();
+        }
+      };
+      auto by_slots = [&](auto kj_tag) {
+        if (g_noc) loop(kj_tag, integral_constant<int, 0>{});
+        else if (g_onec) loop(kj_tag, integral_constant<int, 1>{});
+        else if (g_twoc) loop(kj_tag, integral_constant<int, 2>{});
+        else loop(kj_tag, integral_constant<int, 3>{});
+      };
+      if (!g_wave) loop(integral_constant<int, 0>{}, integral_constant<int, 0>{});
+      else if (g_few) by_slots(integral_constant<int, kFew>{});
+      else by_slots(integral_constant<int, NJ>{});
+    };
     // Warm start: sweep -1 relaxes nothing; every block applies the impulses it starts from (the
-    // kept ones times the share) to its copies, and the average of the copies hands every body
-    // the plain sum of them, as a sweep does with the increments.
-    const bool env_per_wave = NS != 0 && 2 * J + S <= 64;
+    // kept ones times the share), as a sweep does with the increments.
     if (NS != 0 && env_per_wave) {
       // ---- S (Newton), where the rows of an env fit one wavefront: the solve of the block below with a
       // wavefront for every env.  Lane l < 2 J is side l & 1 of joint l >> 1, the lanes above hold the
@@ -2017,7 +2179,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         }
         const bool active = jrole || has, counts = has || (jrole && w_side == 0);   // (a joint's rows are counted once)
         const int nr = jrole ? 6 : 3, vo = (ob < 0 ? 0 : ob) * kVS * E + we;
-        float* out = jrole ? Loutj + (w_j * kJS + w_side * 6) * E + we : Loutc + w_s * kCS * E + we;
+        float* out = jrole ? Loutj + (w_j * kJS + w_side * kSide) * E + we : Loutc + w_s * kCS * E + we;
         // gathering lanes: three per body, two velocity components each
         const int g_b = lane / 3, g_c = 2 * (lane - 3 * g_b);
         const bool g_on = g_b < B;
@@ -2028,7 +2190,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
 #pragma unroll
           for (int k = 0; k < NJ; ++k) {
             const int js = k < n_js ? tb[3 + k] : 0;
-            g_src[k] = (g_on && k < n_js ? P.outj + ((js >> 1) * kJS + (js & 1) * 6) * E : P.zero) + g_c * E + we;
+            g_src[k] = (g_on && k < n_js ? P.outj + ((js >> 1) * kJS + (js & 1) * kSide) * E : P.zero) + g_c * E + we;
           }
 #pragma unroll
           for (int k = 0; k < 3; ++k) {
@@ -2267,8 +2429,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
             for (int k = 0; k < 3; ++k)
               for (int c = 0; c < 3; ++c) dw[c] += K[5 + 3 * k + c] * xv[k] + K[23 + 3 * k + c] * xv[3 + k];
             for (int c = 0; c < 3; ++c) {
-              Loutj[(js_j * kJS + js_side * 6 + c) * E + js_e] = K[3] * xv[c];
-              Loutj[(js_j * kJS + js_side * 6 + 3 + c) * E + js_e] = dw[c];
+              Loutj[(js_j * kJS + js_side * kSide + c) * E + js_e] = K[3] * xv[c];
+              Loutj[(js_j * kJS + js_side * kSide + 3 + c) * E + js_e] = dw[c];
             }
           }
         } else if (has_contact) {
@@ -2301,7 +2463,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         for (int c = 0; c < kPartC; ++c) {
           float acc = 0.0f;
 #pragma unroll
-          for (int k = 0; k < NJ + 3; ++k) acc += gat_w[k] * val[k][c];
+          for (int k = 0; k < NJ + 3; ++k) acc += val[k][c];
           dst[(g_b * kVS + c) * E + e + ho] = base[c] + acc;
         }
       };
@@ -2491,84 +2653,213 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       }
     } else
     if (joint_wave) {
-      build_joint_side(js_j, js_e, js_side);
-      build_pair();
+      JointRows jw;
+      if constexpr (JL == 1) build_joint(jw, js_j, js_e);
+      else build_joint_side(js_j, js_e, js_side);
+      if constexpr (kPairsInJoints) build_pair();
       if (PC == 0 && m_terrain == 0) __syncthreads();   // (the velocities, which the other wavefronts integrate meanwhile)
       TMARK(17);
+      // (lanes behind the last joint do what its lanes do, to the last bit)
+      const int jj = js_j < J ? js_j : J - 1;
       float acc[3] = {0.0f, 0.0f, 0.0f};   // impulses of the positional rows so far (kept for the next substep)
       if constexpr (WS != 0) {
-        const int jj = js_j < J ? js_j : J - 1;
         for (int k = 0; k < 3; ++k) acc[k] = p_warm * Lwj[(jj * 6 + k) * E + js_e];
         for (int k = 0; k < 3; ++k) {
-          const float kept = Lwj[(jj * 6 + 3 + k) * E + js_e];
-          float l0 = p_warm * kept;
-          if (jr.onesided & (1 << k)) {
+          const float kept_l = Lwj[(jj * 6 + 3 + k) * E + js_e];
+          const int onesided = JL == 1 ? jw.onesided : jr.onesided, upper = JL == 1 ? jw.upper : jr.upper;
+          float l0 = p_warm * kept_l;
+          if (onesided & (1 << k)) {
             // kept for the other limit: it would push the wrong way
-            const bool was_upper = __float_as_int(kept) < 0, is_upper = (jr.upper >> k) & 1;
+            const bool was_upper = __float_as_int(kept_l) < 0, is_upper = (upper >> k) & 1;
             l0 = was_upper == is_upper ? fabsf(l0) : 0.0f;
           }
-          jr.lam[k] = l0;
-          if (jr.onesided & (1 << k)) jr.nl[k] = -l0;
+          (JL == 1 ? jw.lam[k] : jr.lam[k]) = l0;
+          if (onesided & (1 << k)) (JL == 1 ? jw.nl[k] : jr.nl[k]) = -l0;
         }
       }
-      // own body's velocity rows, found once (the world's side of a joint reads body 0's and writes
-      // nothing): looked up inside the loop, the body index costs every sweep an LDS round trip
+      // With four lanes per joint, the constants of the lane's own three rows, under one set of names: a
+      // positional lane's rows act on the angular velocity through the lever arm, an angular lane's through the axis.
+      QuadRows qr;
+      if constexpr (JL == 4) {
+        const bool ang = js_kind != 0;
+        const float lever[3][3] = {{0.0f, jr.sr[2], -jr.sr[1]}, {-jr.sr[2], 0.0f, jr.sr[0]}, {jr.sr[1], -jr.sr[0], 0.0f}};
+        qr.kv = ang ? 0.0f : jr.sg;
+        qr.sv = jr.sv;
+        for (int k = 0; k < 3; ++k) {
+          for (int c = 0; c < 3; ++c) {
+            qr.K[k][c] = ang ? jr.sax[k][c] : lever[k][c];
+            qr.R[k][c] = ang ? jr.Z[k][c] : jr.Y[k][c];
+            qr.ap[k][c] = ang ? jr.ap[k][c] : 0.0f;
+          }
+          qr.me[k] = ang ? jr.ame[k] : jr.pme[k];
+          qr.nb[k] = ang ? jr.anb[k] : jr.pnb[k];
+          qr.t1[k] = ang ? 0.0f : jr.pp[k];
+          qr.t2[k] = ang ? jr.aa[k] : 0.0f;
+          qr.nl[k] = ang ? jr.nl[k] : -INFINITY;
+          if constexpr (WS != 0) qr.lam[k] = ang ? jr.lam[k] : acc[k];
+        }
+      }
+      // own body's velocity rows, found once (the world's side of a joint reads body 0's): looked up
+      // inside the loop, the body index costs every sweep an LDS round trip
       // ahead of the reads that depend on it
-      const int js_ob = js_side ? Ltjoint[js_j < J ? js_j : 0].child : Ltjoint[js_j < J ? js_j : 0].parent;
-      const int js_voff = (js_ob < 0 ? 0 : js_ob) * kVS * E + js_e;
-      for (int it = WS ? -1 : 0; it < a.iterations; ++it) {
-        if (js_on) {
-          const int e = js_e;
-          const int ob = js_ob;
-          float vo[3], wo[3];
-          for (int c = 0; c < 3; ++c) { vo[c] = Lvel[js_voff + c * E]; wo[c] = Lvel[js_voff + (3 + c) * E]; }
-  #pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            float dl;
-            if (WS != 0 && it < 0) {
-              dl = acc[k];
-            } else {
-              const float part = fma_(jr.sg, vo[k], cross_unit_dot(jr.sr, k, wo));
-              const float jv = part + lane_swap1(part);
-              dl = fma_(jv, jr.pme[k], jr.pnb[k]);
-              if constexpr (WS != 0) acc[k] += dl;
+      const int js_ob = js_side ? Ltjoint[jj].child : Ltjoint[jj].parent;
+      const int js_voff = P.vel + ((js_ob < 0 ? 0 : js_ob) * kVS + 3 * js_kind) * E + js_e;
+      const int js_out = P.outj + (jj * kJS + js_side * kSide + 3 * js_kind) * E + js_e;
+      // Six joint wavefronts of a full workgroup share SIMDs with each other and with the contacts (4096 humanoids, cycles
+      // per sweep: 1274 with DPP moves, 1198 through the crossbar); three of a smaller one have theirs to themselves.
+      constexpr bool kSharedSimd = NT > 512;
+      constexpr int kC = JL == 4 ? 3 : (JL == 2 ? 6 : 12);   // velocity components of a lane
+      // (one lane per joint: the child's rows besides; the world's velocity is read from the zeros)
+      const int js_voff0 = JL == 1 && js_ob < 0 ? P.zero + js_e : js_voff;
+      const int js_voff1 = P.vel + Ltjoint[jj].child * kVS * E + js_e;
+      sweeps([&](int it) {
+        const bool start_only = WS != 0 && it < 0;
+        float own[kC], mine[kC];
+#pragma unroll
+        for (int c = 0; c < kC; ++c) own[c] = lds[JL == 1 && c >= 6 ? js_voff1 + (c - 6) * E : js_voff0 + c * E];
+        if constexpr (JL == 1) {
+          float d[3], dl[3];
+          if (start_only) {
+            for (int k = 0; k < 3; ++k) { d[k] = acc[k]; dl[k] = jw.lam[k]; }
+          } else {
+            const float *va = own, *wa = own + 3, *vb = own + 6, *wb = own + 9;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              const int k1 = (k + 1) % 3, k2 = (k + 2) % 3;
+              const float pa = cross_unit_dot(jw.sr[0], k, wa) - va[k], pb = cross_unit_dot(jw.sr[1], k, wb) + vb[k];
+              const float qa = fma_(jw.sax[0][k][k], wa[k], fma_(jw.sax[0][k][k1], wa[k1], jw.sax[0][k][k2] * wa[k2]));
+              const float qb = fma_(jw.sax[1][k][k], wb[k], fma_(jw.sax[1][k][k1], wb[k1], jw.sax[1][k][k2] * wb[k2]));
+              d[k] = fma_(pa + pb, jw.pme[k], jw.pnb[k]);
+              dl[k] = fma_(qa + qb, jw.ame[k], jw.anb[k]);
             }
-            vo[k] = fma_(jr.sv, dl, vo[k]);
-            for (int c = 0; c < 3; ++c) wo[c] = fma_(jr.Y[k][c], dl, wo[c]);
-          }
-  #pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            float dl;
-            if (WS != 0 && it < 0) {
-              dl = jr.lam[k];
-            } else {
-              const float part = dot(jr.sax[k], wo);
-              const float jv = part + lane_swap1(part);
-              // a limit row's impulse stays >= 0: max(lam + dl, 0) - lam = max(dl, -lam)
-              dl = max_of(fma_(jv, jr.ame[k], jr.anb[k]), jr.nl[k]);
-              jr.nl[k] -= dl;
-              if constexpr (WS != 0) jr.lam[k] += dl;
+            d[1] = fma_(jw.pp[0], d[0], d[1]);
+            d[2] = fma_(jw.pp[2], d[1], fma_(jw.pp[1], d[0], d[2]));
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+              for (int k = 0; k < 3; ++k) dl[k] = fma_(jw.ap[k][c], d[c], dl[k]);
+            dl[0] = max_of(dl[0], jw.nl[0]);
+            dl[1] = max_of(fma_(jw.aa[0], dl[0], dl[1]), jw.nl[1]);
+            dl[2] = max_of(fma_(jw.aa[2], dl[1], fma_(jw.aa[1], dl[0], dl[2])), jw.nl[2]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              jw.nl[k] -= dl[k];
+              if constexpr (WS != 0) { acc[k] += d[k]; jw.lam[k] += dl[k]; }
             }
-            for (int c = 0; c < 3; ++c) wo[c] = fma_(jr.Z[k][c], dl, wo[c]);
           }
-          if (ob >= 0)
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
             for (int c = 0; c < 3; ++c) {
-              Loutj[(js_j * kJS + js_side * 6 + c) * E + e] = vo[c];
-              Loutj[(js_j * kJS + js_side * 6 + 3 + c) * E + e] = wo[c];
+              mine[6 * s + c] = jw.sv[s] * d[c];
+              mine[6 * s + 3 + c] = sum3(jw.Y[s][0][c], d[0], jw.Y[s][1][c], d[1], jw.Y[s][2][c], d[2]) +
+                                    sum3(jw.Z[s][0][c], dl[0], jw.Z[s][1][c], dl[1], jw.Z[s][2][c], dl[2]);
             }
+        } else if constexpr (JL == 2) {
+          float d[3], dl[3];   // impulses of the positional and of the angular rows
+          if (start_only) {
+            for (int k = 0; k < 3; ++k) { d[k] = acc[k]; dl[k] = jr.lam[k]; }
+          } else {
+            const float *vo = own, *wo = own + 3;
+            float jv[6];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              const int k1 = (k + 1) % 3, k2 = (k + 2) % 3;
+              jv[k] = fma_(jr.sg, vo[k], cross_unit_dot(jr.sr, k, wo));
+              jv[3 + k] = fma_(jr.sax[k][k], wo[k], fma_(jr.sax[k][k1], wo[k1], jr.sax[k][k2] * wo[k2]));
+            }
+#pragma unroll
+            for (int k = 0; k < 6; ++k) jv[k] += kSharedSimd ? lane_swap1_crossbar(jv[k]) : lane_swap1(jv[k]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) { d[k] = fma_(jv[k], jr.pme[k], jr.pnb[k]); dl[k] = fma_(jv[3 + k], jr.ame[k], jr.anb[k]); }
+            d[1] = fma_(jr.pp[0], d[0], d[1]);
+            d[2] = fma_(jr.pp[2], d[1], fma_(jr.pp[1], d[0], d[2]));
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+              for (int k = 0; k < 3; ++k) dl[k] = fma_(jr.ap[k][c], d[c], dl[k]);
+            // a limit row's impulse stays >= 0: max(lam + dl, 0) - lam = max(dl, -lam)
+            dl[0] = max_of(dl[0], jr.nl[0]);
+            dl[1] = max_of(fma_(jr.aa[0], dl[0], dl[1]), jr.nl[1]);
+            dl[2] = max_of(fma_(jr.aa[2], dl[1], fma_(jr.aa[1], dl[0], dl[2])), jr.nl[2]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              jr.nl[k] -= dl[k];
+              if constexpr (WS != 0) { acc[k] += d[k]; jr.lam[k] += dl[k]; }
+            }
+          }
+          // (the world's side of a joint responds to nothing and nobody reads its entry)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            mine[c] = jr.sv * d[c];
+            mine[3 + c] = sum3(jr.Y[0][c], d[0], jr.Y[1][c], d[1], jr.Y[2][c], d[2]) +
+                          sum3(jr.Z[0][c], dl[0], jr.Z[1][c], dl[1], jr.Z[2][c], dl[2]);
+          }
+        } else {
+          // lanes 0, 1 of the four hold the positional rows and v of either side, lanes 2, 3 the angular rows and w
+          float d[3];
+          if (start_only) {
+            for (int k = 0; k < 3; ++k) d[k] = qr.lam[k];
+          } else {
+            float w[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) w[c] = quad_move<0xEE>(own[c]);   // from lane 2, 3, 2, 3
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              const int k1 = (k + 1) % 3, k2 = (k + 2) % 3;
+              float y;
+              if (k == 0) y = fma_(qr.K[k][0], w[0], fma_(qr.K[k][1], w[1], qr.K[k][2] * w[2]));
+              else y = fma_(qr.K[k][k], w[k], fma_(qr.K[k][k1], w[k1], qr.K[k][k2] * w[k2]));
+              d[k] = fma_(qr.kv, own[k], y);
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) d[k] += lane_swap1(d[k]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) d[k] = fma_(d[k], qr.me[k], qr.nb[k]);
+            d[1] = fma_(qr.t1[0], d[0], d[1]);
+            d[2] = fma_(qr.t1[2], d[1], fma_(qr.t1[1], d[0], d[2]));
+            float dp[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) dp[c] = quad_move<0x44>(d[c]);    // from lane 0, 1, 0, 1
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+              for (int k = 0; k < 3; ++k) d[k] = fma_(qr.ap[k][c], dp[c], d[k]);
+            d[0] = max_of(d[0], qr.nl[0]);
+            d[1] = max_of(fma_(qr.t2[0], d[0], d[1]), qr.nl[1]);
+            d[2] = max_of(fma_(qr.t2[2], d[1], fma_(qr.t2[1], d[0], d[2])), qr.nl[2]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              qr.nl[k] -= d[k];
+              if constexpr (WS != 0) qr.lam[k] += d[k];
+            }
+          }
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const float r = sum3(qr.R[0][c], d[0], qr.R[1][c], d[1], qr.R[2][c], d[2]);
+            const float both = r + quad_move<0x44>(r);
+            mine[c] = js_kind ? both : qr.sv * d[c];
+          }
         }
-        pair_sweep(!(WS != 0 && it < 0));
-        __syncthreads();
-        gather();
-        __syncthreads();
-      }
+#pragma unroll
+        for (int c = 0; c < kC; ++c) lds[js_out + (c < 6 ? c : c - 6 + kSide) * E] = mine[c];
+        if constexpr (kPairsInJoints) pair_sweep(!start_only);
+      });
       if constexpr (WS != 0) {
         // (both lanes of a joint hold the same impulses; the two sit in one wavefront, so the
         // parent side's stores follow both lanes' reads above)
         if (js_on && js_side == 0) {
-          for (int k = 0; k < 3; ++k) Lwj[(js_j * 6 + k) * E + js_e] = acc[k];
-          for (int k = 0; k < 3; ++k)
-            Lwj[(js_j * 6 + 3 + k) * E + js_e] = ((jr.onesided & jr.upper) >> k) & 1 ? -jr.lam[k] : jr.lam[k];
+          if constexpr (JL == 4) {
+            for (int k = 0; k < 3; ++k)
+              Lwj[(js_j * 6 + 3 * js_kind + k) * E + js_e] = js_kind && (((jr.onesided & jr.upper) >> k) & 1) ? -qr.lam[k] : qr.lam[k];
+          } else {
+            const int uppers = JL == 1 ? jw.onesided & jw.upper : jr.onesided & jr.upper;
+            for (int k = 0; k < 3; ++k) Lwj[(js_j * 6 + k) * E + js_e] = acc[k];
+            for (int k = 0; k < 3; ++k) {
+              const float l = JL == 1 ? jw.lam[k] : jr.lam[k];
+              Lwj[(js_j * 6 + 3 + k) * E + js_e] = (uppers >> k) & 1 ? -l : l;
+            }
+          }
         }
       }
     } else {
@@ -2586,37 +2877,41 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       build_contact();
       build_pair();
       if (PC == 0 && m_terrain == 0) __syncthreads();
-      // the starting impulses of the contacts beyond one per thread are set by the thread that
-      // relaxes them in every sweep below (same index mapping), so no other thread's store is read
-      for (int k = n_reg + (kThreads - 1 - tid); k < n_active; k += n_reg)
-        for (int r = 0; r < 3; ++r) overflow_lam(k, r) = WS ? p_warm * overflow_lam(k, r) : 0.0f;
-      for (int it = WS ? -1 : 0; it < a.iterations; ++it) {
-        if (has_contact) {
-          const int ee = cr.slot_e % E, sl = cr.slot_e / E;
-          float vv[3], ww[3];
-          for (int k = 0; k < 3; ++k) { vv[k] = Lvel[(cr.body * kVS + k) * E + ee]; ww[k] = Lvel[(cr.body * kVS + 3 + k) * E + ee]; }
-          if (WS != 0 && it < 0) apply_contact_impulses(cr, vv, ww);
-          else relax_contact(cr, p_mu, vv, ww);
-          for (int k = 0; k < 3; ++k) { Loutc[(sl * kCS + k) * E + ee] = vv[k]; Loutc[(sl * kCS + 3 + k) * E + ee] = ww[k]; }
-        }
-        for (int k = n_reg + (kThreads - 1 - tid); k < n_active; k += n_reg) {
-          // rare: more active contacts in the workgroup than threads; rows rebuilt from the record
-          const int i = Llist[k];
-          const int ee = i % E, sl = i / E, body = Ltslot[2 * sl];
-          ContactRows c2;
-          build_contact_rows(c2, Lrec, Liw, weight_sum(body, ee), sl, ee, E, body, Ltbody[4 * body + 3], h, p_beta_c, p_vdepen);
-          for (int r = 0; r < 3; ++r) c2.lam[r] = overflow_lam(k, r);
-          float vv[3], ww[3];
-          for (int r = 0; r < 3; ++r) { vv[r] = Lvel[(body * kVS + r) * E + ee]; ww[r] = Lvel[(body * kVS + 3 + r) * E + ee]; }
-          if (WS != 0 && it < 0) apply_contact_impulses(c2, vv, ww);
-          else relax_contact(c2, p_mu, vv, ww);
-          for (int r = 0; r < 3; ++r) overflow_lam(k, r) = c2.lam[r];
-          for (int r = 0; r < 3; ++r) { Loutc[(sl * kCS + r) * E + ee] = vv[r]; Loutc[(sl * kCS + 3 + r) * E + ee] = ww[r]; }
-        }
-        pair_sweep(!(WS != 0 && it < 0));
-        __syncthreads();
-        gather();
-        __syncthreads();
+      {
+        // the starting impulses of the contacts beyond one per thread are set by the thread that
+        // relaxes them in every sweep below (same index mapping), so no other thread's store is read
+        for (int k = n_reg + (kThreads - 1 - tid); k < n_active; k += n_reg)
+          for (int r = 0; r < 3; ++r) overflow_lam(k, r) = WS ? p_warm * overflow_lam(k, r) : 0.0f;
+        // (a lane without a contact of its own does what the last contact's lane of its wavefront does, to the last bit)
+        const bool contacts_here = __ballot(has_contact) != 0ull, more_contacts = n_active > n_reg;
+        const int c_e = cr.slot_e % E, c_out = P.outc + (cr.slot_e / E) * kCS * E + c_e, c_voff = P.vel + cr.body * kVS * E + c_e;
+        auto own_contact = [&](int it) {
+            float vv[3], ww[3];
+            for (int k = 0; k < 3; ++k) { vv[k] = lds[c_voff + k * E]; ww[k] = lds[c_voff + (3 + k) * E]; }
+            if (WS != 0 && it < 0) contact_response(cr, cr.lam, vv, ww);
+            else relax_contact(cr, p_mu, vv, ww);
+            for (int k = 0; k < 3; ++k) { lds[c_out + k * E] = vv[k]; lds[c_out + (3 + k) * E] = ww[k]; }
+        };
+        if (more_contacts) sweeps([&](int it) {
+          own_contact(it);
+          for (int k = n_reg + (kThreads - 1 - tid); k < n_active; k += n_reg) {
+            // rare: more active contacts in the workgroup than threads; rows rebuilt from the record
+            const int i = Llist[k];
+            const int ee = i % E, sl = i / E, body = Ltslot[2 * sl];
+            ContactRows c2;
+            build_contact_rows(c2, Lrec, Liw, weight_sum(body, ee), sl, ee, E, body, Ltbody[4 * body + 3], h, p_beta_c, p_vdepen);
+            for (int r = 0; r < 3; ++r) c2.lam[r] = overflow_lam(k, r);
+            float vv[3], ww[3];
+            for (int r = 0; r < 3; ++r) { vv[r] = Lvel[(body * kVS + r) * E + ee]; ww[r] = Lvel[(body * kVS + 3 + r) * E + ee]; }
+            if (WS != 0 && it < 0) contact_response(c2, c2.lam, vv, ww);
+            else relax_contact(c2, p_mu, vv, ww);
+            for (int r = 0; r < 3; ++r) overflow_lam(k, r) = c2.lam[r];
+            for (int r = 0; r < 3; ++r) { Loutc[(sl * kCS + r) * E + ee] = vv[r]; Loutc[(sl * kCS + 3 + r) * E + ee] = ww[r]; }
+          }
+          pair_sweep(!(WS != 0 && it < 0));
+        });
+        else if (contacts_here) sweeps([&](int it) { own_contact(it); pair_sweep(!(WS != 0 && it < 0)); });
+        else sweeps([&](int it) { pair_sweep(!(WS != 0 && it < 0)); });
       }
       if constexpr (WS != 0) {
         if (has_contact) {
