@@ -873,6 +873,22 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     v[0] = st[7 * fs]; v[1] = st[8 * fs]; v[2] = st[9 * fs];
     w[0] = st[10 * fs]; w[1] = st[11 * fs]; w[2] = st[12 * fs];
   }
+  // First words of the small arrays (actions, origins, tables): asked for here, so that their trips to memory run beside
+  // those of the state and of the heightfield instead of one after the other behind them.
+  const int n_act = E * D, n_tab = M.table_words;
+  const float inv_d = __builtin_amdgcn_rcpf((float)(D > 0 ? D : 1));
+  auto action_of = [&](int i) -> float {   // (i < E D < 2^14, D <= 32: the quotient is exact)
+    const int ee = (int)(((float)i + 0.5f) * inv_d), d = i - ee * D, env_i = blockIdx.x * E + ee;
+    return env_i < N && a.actions ? a.actions[(size_t)agent_at(env_i) * D + d] : 0.0f;
+  };
+  auto origin_of = [&](int i) -> float {
+    const int c = i / E, ee = i - c * E, env_i = blockIdx.x * E + ee;
+    return env_i < N ? a.origins[3 * agent_at(env_i) + c] : 0.0f;
+  };
+  float act_0 = 0.0f, org_0 = 0.0f;
+  if (tid < n_act) act_0 = action_of(tid);
+  if (tid < 3 * E) org_0 = origin_of(tid);
+  int tab_0 = M.table_image[tid < n_tab ? tid : 0], tab_1 = M.table_image[tid + kThreads < n_tab ? tid + kThreads : 0];
   if (copy_field && pe < E) {
     // four samples at a time (a row of the copy is seven of them; rows start at any sample), all of a
     // thread's reads in flight together
@@ -902,18 +918,20 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   const float p_mu = M.mu, p_margin = M.margin, p_beta_j = M.beta_j, p_beta_c = M.beta_c;
   const float p_vdepen = M.v_depen, p_clin = M.c_lin, p_cang = M.c_ang, p_wmax = M.w_max;
   const int p_gyro = M.gyro;
-  for (int i = tid; i < E * D; i += kThreads) {
-    int ee = i / D, d = i - ee * D;
-    int env_i = blockIdx.x * E + ee;
-    float uu = 0.0f;
-    if (env_i < N && a.actions) uu = a.actions[(size_t)agent_at(env_i) * D + d];
-    Lu[d * E + ee] = fminf(fmaxf(uu, -1.0f), 1.0f);
-  }
   // small copies of what the per-slot code looks up all the time
-  for (int i = tid; i < 3 * E; i += kThreads) {
-    int c = i / E, ee = i - c * E, env_i = blockIdx.x * E + ee;
-    Lorg[i] = env_i < N ? a.origins[3 * agent_at(env_i) + c] : 0.0f;
-  }
+  asm volatile("" : "+v"(act_0), "+v"(org_0), "+v"(tab_0), "+v"(tab_1));   // (all four on their way before the first store)
+  auto put_action = [&](int i, float u) {
+    const int ee = (int)(((float)i + 0.5f) * inv_d);
+    Lu[(i - ee * D) * E + ee] = fminf(fmaxf(u, -1.0f), 1.0f);
+  };
+  int* const Ltab = reinterpret_cast<int*>(lds + P.tjs);
+  if (tid < n_act) put_action(tid, act_0);
+  if (tid < 3 * E) Lorg[tid] = org_0;
+  if (tid < n_tab) Ltab[tid] = tab_0;
+  if (tid + kThreads < n_tab) Ltab[tid + kThreads] = tab_1;
+  for (int i = tid + kThreads; i < n_act; i += kThreads) put_action(i, action_of(i));
+  for (int i = tid + kThreads; i < 3 * E; i += kThreads) Lorg[i] = origin_of(i);
+  for (int i = tid + 2 * kThreads; i < n_tab; i += kThreads) Ltab[i] = M.table_image[i];
   // external pushes (Section 4.1): is this frame the env's next push?
   if (tid < E) {
     const bool env_t_ok = blockIdx.x * E + tid < N;
@@ -931,7 +949,6 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     Lpush[0 * E + tid] = fx; Lpush[1 * E + tid] = fy; Lpush[2 * E + tid] = 0.0f;
     if (a.task.enabled && a.count_step && env_t_ok) { a.push[3 * env_t] = fx; a.push[3 * env_t + 1] = fy; a.push[3 * env_t + 2] = 0.0f; }
   }
-  for (int i = tid; i < M.table_words; i += kThreads) reinterpret_cast<int*>(lds + P.tjs)[i] = M.table_image[i];
   if constexpr (PC == 0)
     for (int i = tid; i < 6 * E; i += kThreads) lds[P.zero + i] = 0.0f;
   if (tid < 8) Lcount[tid] = 0;
@@ -2969,6 +2986,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   const int agent = agent_at(env);
   __syncthreads();
   TMARK(8);
+  if (tid < E) Llim[tid] = 0;   // joints of the env at their limits
   if (is_body) {
     float* st = a.state + (size_t)b * N + agent;
     const size_t fs = (size_t)B * N;
@@ -3012,6 +3030,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     quat_to_mat(qa, Ra);
     rel_rotvec(qa, qb, phi);
     float dw[3] = {wb[0] - wa[0], wb[1] - wa[1], wb[2] - wa[2]};
+    int at_limit = 0;
     for (int k = 0; k < 3; ++k) {
       if (jt.mode[k] != 1) continue;
       int ai = jt.act[k];
@@ -3022,8 +3041,9 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       Lobs[e * obs_dim + 11 + D + ai] = dot(ak, dw);
       Lobs[e * obs_dim + 11 + 2 * D + ai] = pass ? 0.0f : Lu[ai * E + e];
       float g = fminf(th - jt.lo[k], jt.hi[k] - th);
-      Llim[ai * E + e] = g <= 0.0f ? 1 : 0;
+      at_limit += g <= 0.0f ? 1 : 0;
     }
+    if (at_limit) atomicAdd(&Llim[e], at_limit);
   }
   };
   // ---- root part.  One thread per env for all of it is a chain of some 1500 instructions (three
@@ -3045,24 +3065,28 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     if (ee < 0 || ee >= E || blockIdx.x * E + ee >= N) return -1;
     return pass == 0 || only_reset || Lrst[ee] ? ee : -1;
   };
-  auto yaw_of = [&](int ee, float& rx, float& ry) -> float {
-    rx = Lpos[(m_root * 7 + 0) * E + ee]; ry = Lpos[(m_root * 7 + 1) * E + ee];
+  // cosine and sine of the heading (the yaw of the ZYX Euler angles; looking straight up or down it counts as zero)
+  auto heading_of = [&](int ee, float& c, float& sn) {
     const float qw = Lpos[(m_root * 7 + 3) * E + ee], qx = Lpos[(m_root * 7 + 4) * E + ee];
     const float qy = Lpos[(m_root * 7 + 5) * E + ee], qz = Lpos[(m_root * 7 + 6) * E + ee];
-    return atan2f(2.0f * (qw * qz + qx * qy), 1.0f - 2.0f * (qy * qy + qz * qz));
+    const float x = 1.0f - 2.0f * (qy * qy + qz * qz), y = 2.0f * (qw * qz + qx * qy), n = sqrtf(x * x + y * y);
+    c = n > 0.0f ? x / n : 1.0f; sn = n > 0.0f ? y / n : 0.0f;
   };
   if (const int ee = part_env(0); ee >= 0) {
     // target in the root's frame, speed towards it
     const int env_e = agent_at(blockIdx.x * E + ee);
     const float gx = a.targets[2 * env_e], gy = a.targets[2 * env_e + 1];
-    float rx, ry;
-    const float yaw = yaw_of(ee, rx, ry);
+    const float rx = Lpos[(m_root * 7 + 0) * E + ee], ry = Lpos[(m_root * 7 + 1) * E + ee];
+    float cy, sy;
+    heading_of(ee, cy, sy);
     const float rv0 = Lvel[(m_root * kVS + 0) * E + ee], rv1 = Lvel[(m_root * kVS + 1) * E + ee];
     const float tx = gx - rx, ty = gy - ry;
-    const float psi = atan2f(ty, tx) - yaw;
     const float tn = sqrtf(tx * tx + ty * ty);
-    Lobs[ee * obs_dim + 9] = sinf(psi); Lobs[ee * obs_dim + 10] = cosf(psi);
-    Lsc[0 * E + ee] = tn > 0.0f ? (rv0 * tx + rv1 * ty) / tn : 0.0f;
+    // sine and cosine of the difference of two directions from their components: no angle is formed (the two
+    // arctangents and the sine and cosine of their difference were the longest chain of this phase)
+    const float ux = tn > 0.0f ? tx / tn : 1.0f, uy = tn > 0.0f ? ty / tn : 0.0f;
+    Lobs[ee * obs_dim + 9] = uy * cy - ux * sy; Lobs[ee * obs_dim + 10] = ux * cy + uy * sy;
+    Lsc[0 * E + ee] = tn > 0.0f ? rv0 * ux + rv1 * uy : 0.0f;
     Lsc[1 * E + ee] = tn;
   }
   if (const int ee = part_env(1); ee >= 0) {
@@ -3085,17 +3109,35 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     Lobs[ee * obs_dim + 2] = asinf(fminf(fmaxf(2.0f * (qw * qy - qz * qx), -1.0f), 1.0f));
   }
   if (const int ee = part_env(3); ee >= 0) {
-    // feet on the ground, sums over the actions (eight reads in flight at a time)
-    int n_feet = 0;
-    for (int f = 0; f < F; ++f) {
-      const int fb = (m_feet >> (8 * f)) & 255;
-      const int s0 = Ltjs[fb * (kMaxBodyJoints + 3) + 1], ns = Ltjs[fb * (kMaxBodyJoints + 3) + 2];
-      int flag = 0;
-      for (int k = 0; k < ns; ++k)
-        if (pass == 0 && Lreci[((s0 + k) * kRecWords + 0) * E + ee] && Lrec[((s0 + k) * kRecWords + 3) * E + ee] <= 0.005f) flag = 1;
-      Lobs[ee * obs_dim + 11 + 3 * D + f] = (float)flag;
-      n_feet += flag;
+    // feet on the ground: the records of all their slots are read together (slot after slot, with a branch around
+    // each, this part was what everybody waited for: 4600 cycles of two ants' 6300 between state and reward)
+    int active[kMaxFeet][3], slots[kMaxFeet];
+    float gap[kMaxFeet][3];
+#pragma unroll
+    for (int f = 0; f < kMaxFeet; ++f) {
+      const int fb = (m_feet >> (8 * f)) & 255;   // (body 0 for feet that there are not)
+      const int s0 = Ltjs[fb * (kMaxBodyJoints + 3) + 1];
+      slots[f] = Ltjs[fb * (kMaxBodyJoints + 3) + 2];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const int sl = s0 + (k < slots[f] ? k : 0);
+        active[f][k] = Lreci[(sl * kRecWords + 0) * E + ee];
+        gap[f][k] = Lrec[(sl * kRecWords + 3) * E + ee];
+      }
     }
+    int n_feet = 0;
+#pragma unroll
+    for (int f = 0; f < kMaxFeet; ++f) {
+      bool down = false;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) down = down || (pass == 0 && k < slots[f] && active[f][k] != 0 && gap[f][k] <= 0.005f);
+      if (f < F) Lobs[ee * obs_dim + 11 + 3 * D + f] = down ? 1.0f : 0.0f;
+      n_feet += f < F && down ? 1 : 0;
+    }
+    Lsc[4 * E + ee] = (float)n_feet;
+  }
+  if (const int ee = part_env(5); ee >= 0) {
+    // sums over the actions (eight reads in flight at a time)
     float l1 = 0.0f, l2 = 0.0f;
     for (int d0 = 0; d0 < D; d0 += 8) {
       float uu[8];
@@ -3105,7 +3147,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       for (int k = 0; k < 8; ++k)
         if (d0 + k < D) { l1 += fabsf(uu[k]); l2 += uu[k] * uu[k]; }
     }
-    Lsc[2 * E + ee] = l1; Lsc[3 * E + ee] = l2; Lsc[4 * E + ee] = (float)n_feet;
+    Lsc[2 * E + ee] = l1; Lsc[3 * E + ee] = l2;
   }
   if (m_height_map) {
     if (const int ee = part_env(4); ee >= 0) {
@@ -3115,10 +3157,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         const float mf = M.body_mass_frac[bb];
         cx += mf * Lpos[(bb * 7 + 0) * E + ee]; cy += mf * Lpos[(bb * 7 + 1) * E + ee]; cz += mf * Lpos[(bb * 7 + 2) * E + ee];
       }
-      float rx, ry;
-      const float yaw = yaw_of(ee, rx, ry);
       Lhm[0 * E + ee] = cx + Lorg[ee]; Lhm[1 * E + ee] = cy + Lorg[E + ee]; Lhm[2 * E + ee] = cz + Lorg[2 * E + ee];
-      Lhm[3 * E + ee] = cosf(yaw); Lhm[4 * E + ee] = sinf(yaw);
+      heading_of(ee, Lhm[3 * E + ee], Lhm[4 * E + ee]);
     }
   }
   };
@@ -3140,14 +3180,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     const float speed = Lsc[0 * E + ee], tn = Lsc[1 * E + ee], l1 = Lsc[2 * E + ee], l2 = Lsc[3 * E + ee];
     const float n_feet = Lsc[4 * E + ee];
     const float qx = Lpos[(rb * 7 + 4) * E + ee], qy = Lpos[(rb * 7 + 5) * E + ee];
-    int n_lim = 0;
-    for (int d0 = 0; d0 < D; d0 += 8) {
-      int lv[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) lv[k] = Llim[(d0 + k < D ? d0 + k : D - 1) * E + ee];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) n_lim += d0 + k < D ? lv[k] : 0;
-    }
+    const int n_lim = Llim[ee];
     float r_head = cps > 0.8f ? 1.0f : cps / 0.8f;
     float cvert = 1.0f - 2.0f * (qx * qx + qy * qy);
     float r_stand = cvert > 0.93f ? 1.0f : 0.0f;
@@ -3187,6 +3220,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   auto reset_envs = [&](const StepArgs& a, const Model& M) {
 #pragma clang fp contract(fast)
     const bool fresh = env_ok && Lrst[e];
+    if (tid < E) Llim[tid] = 0;
     auto seed_of = [&](int ag) -> uint64_t {
       return only_reset ? a.reset_seed : a.task.seed + (uint64_t)(a.task_i[4 * ag + 3] + 1) * kEpisodeStride;
     };
@@ -3259,9 +3293,10 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     const int env0 = blockIdx.x * E;
     const int n_here = min(E, N - env0);
     float* const obs_dst = a.obs_out ? a.obs_out : a.obs;   // one copy: the caller's array when there is one
+    const float inv_dim = __builtin_amdgcn_rcpf((float)obs_dim);
     for (int i = tid; i < n_here * obs_dim; i += kThreads) {
       const float o = Lobs[i];
-      const int ee = i / obs_dim, k = i - ee * obs_dim;
+      const int ee = (int)(((float)i + 0.5f) * inv_dim), k = i - ee * obs_dim;   // (i < 2^16, at most 512 envs: exact)
       obs_dst[(size_t)agent_at(env0 + ee) * obs_row + k] = o;
     }
     if (m_height_map) {
