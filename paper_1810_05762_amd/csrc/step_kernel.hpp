@@ -1917,6 +1917,82 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           R.aa[k + c - 1] = R.ame[k] * (dot(ak, zn[0][c]) + dot(ak, zn[1][c]));
       }
     };
+    // The same for one kind of row of one side (four lanes per joint): positional and angular lanes run through the
+    // same instructions, the three directions u_k (lever arm x world axis, or joint axis) and what goes with them
+    // chosen per lane, so that a lane builds three rows instead of six and has nothing to pick apart afterwards (us a
+    // step: 64 planned humanoids 216.8 to 212.6 for three, 1024 ants 50.4 to 49.5, 1024 humanoids 52.0 to 51.5).
+    auto build_quad = [&](QuadRows& R, int jj, int e, int side, bool ang, int& onesided, int& upper) {
+      const JointTab& jt = Ltjoint[jj];
+      const int ob = side ? jt.child : jt.parent;        // own body; -1: the static world
+      const bool ghost = ob < 0;
+      const int bo = ghost ? 0 : ob;
+      const float sg = side ? 1.0f : -1.0f, sgl = ghost ? 0.0f : sg;
+      float xo[3], qo[4], iwo[6];
+      for (int c = 0; c < 3; ++c) xo[c] = Lpos[(bo * 7 + c) * E + e];
+      for (int c = 0; c < 4; ++c) qo[c] = Lpos[(bo * 7 + 3 + c) * E + e];
+      for (int c = 0; c < 6; ++c) iwo[c] = Liw[(bo * kVS + c) * E + e];
+      float no = weight_sum(bo, e), imo = Ltbody[4 * bo + 3];
+      if (ghost) {
+        for (int c = 0; c < 3; ++c) xo[c] = 0.0f;
+        qo[0] = 1.0f; qo[1] = qo[2] = qo[3] = 0.0f;
+        for (int c = 0; c < 6; ++c) iwo[c] = 0.0f;
+        no = 0.0f; imo = 0.0f;
+      }
+      float Ro[9], Ra[9], lo[3], t0[3], C[3], r[3], qx[4], qa[4], qb[4], phi[3];
+      quat_to_mat(qo, Ro);
+      for (int c = 0; c < 3; ++c) lo[c] = side ? jt.lb[c] : jt.la[c];
+      mat_vec(Ro, lo, t0);
+      for (int c = 0; c < 3; ++c) {
+        C[c] = sg * ((xo[c] - lane_swap1(xo[c])) + (t0[c] - lane_swap1(t0[c])));   // child anchor minus parent anchor
+        r[c] = fma_(-0.5f * sg, C[c], t0[c]);            // impulses act at the midpoint
+      }
+      for (int c = 0; c < 4; ++c) qx[c] = lane_swap1(qo[c]);
+      for (int c = 0; c < 4; ++c) { qa[c] = side ? qx[c] : qo[c]; qb[c] = side ? qo[c] : qx[c]; }
+      for (int c = 0; c < 9; ++c) { const float rx = lane_swap1(Ro[c]); Ra[c] = side ? rx : Ro[c]; }   // the parent's
+      rel_rotvec(qa, qb, phi);
+      const float inv_h = __builtin_amdgcn_rcpf(h), bh = p_beta_j * inv_h;
+      R.kv = ang ? 0.0f : sgl;
+      R.sv = sg * imo;
+      onesided = 0;
+      upper = 0;
+      float yn[3][3];
+      for (int k = 0; k < 3; ++k) {
+        float ak[3], u[3], y[3];
+        mat_vec(Ra, jt.axes[k], ak);
+        const float th = dot(jt.axes[k], phi);
+        float sgn = 1.0f, bias;
+        if (jt.mode[k] == 0) {
+          bias = bh * th;
+        } else {
+          float glo = th - jt.lo[k], ghi = jt.hi[k] - th, g;
+          if (glo < ghi) { g = glo; } else { g = ghi; sgn = -1.0f; upper |= 1 << k; }
+          bias = g >= 0.0f ? g * inv_h : bh * g;
+          onesided |= 1 << k;
+        }
+        cross_unit(r, k, u);
+        for (int c = 0; c < 3; ++c) u[c] = ang ? ak[c] * sgn : u[c];
+        sym_vec(iwo, u, y);
+        for (int c = 0; c < 3; ++c) { yn[k][c] = no * y[c]; R.K[k][c] = sgl * u[c]; R.R[k][c] = sg * y[c]; }
+        // (each kind's products in the order the other forms have)
+        const float kp_pos = fma_(no, imo, cross_unit_dot(r, k, yn[k])), kp_ang = no * dot(u, y), kp = ang ? kp_ang : kp_pos;
+        const float keff = kp + lane_swap1(kp);
+        R.me[k] = keff > 0.0f ? -__builtin_amdgcn_rcpf(keff) : 0.0f;
+        R.nb[k] = R.me[k] * (ang ? bias : bh * C[k]);
+        R.nl[k] = ang && jt.mode[k] != 0 ? 0.0f : -INFINITY;
+        R.lam[k] = 0.0f;
+        for (int c = 0; c < k; ++c) {
+          const float kc_pos = cross_unit_dot(r, k, yn[c]), kc_ang = dot(u, yn[c]), kc = ang ? kc_ang : kc_pos;
+          const float v = R.me[k] * (kc + lane_swap1(kc));
+          R.t1[k + c - 1] = ang ? 0.0f : v;
+          R.t2[k + c - 1] = ang ? v : 0.0f;
+        }
+        const float me_ang = ang ? R.me[k] : 0.0f;
+        for (int c = 0; c < 3; ++c) {
+          const float kc = cross_unit_dot(r, c, yn[k]);
+          R.ap[k][c] = me_ang * (kc + lane_swap1(kc));
+        }
+      }
+    };
     // contact k of the workgroup's list goes to thread kThreads-1-k (the joint threads sit at
     // the low end); contacts beyond one per thread start from zero impulse in LDS
     auto build_contact = [&]() {
@@ -2670,50 +2746,42 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       }
     } else
     if (joint_wave) {
+      // (lanes behind the last joint do what its lanes do, to the last bit)
+      const int jj = js_j < J ? js_j : J - 1;
       JointRows jw;
+      QuadRows qr;
+      int q_onesided = 0, q_upper = 0;
       if constexpr (JL == 1) build_joint(jw, js_j, js_e);
+      else if constexpr (JL == 4) build_quad(qr, jj, js_e, js_side, js_kind != 0, q_onesided, q_upper);
       else build_joint_side(js_j, js_e, js_side);
       if constexpr (kPairsInJoints) build_pair();
       if (PC == 0 && m_terrain == 0) __syncthreads();   // (the velocities, which the other wavefronts integrate meanwhile)
       TMARK(17);
-      // (lanes behind the last joint do what its lanes do, to the last bit)
-      const int jj = js_j < J ? js_j : J - 1;
       float acc[3] = {0.0f, 0.0f, 0.0f};   // impulses of the positional rows so far (kept for the next substep)
-      if constexpr (WS != 0) {
+      if constexpr (WS != 0 && JL == 4) {
+        for (int k = 0; k < 3; ++k) {
+          const float kept = Lwj[(jj * 6 + 3 * js_kind + k) * E + js_e];
+          float l0 = p_warm * kept;
+          if (js_kind && (q_onesided & (1 << k))) {
+            // kept for the other limit: it would push the wrong way
+            const bool was_upper = __float_as_int(kept) < 0, is_upper = (q_upper >> k) & 1;
+            l0 = was_upper == is_upper ? fabsf(l0) : 0.0f;
+            qr.nl[k] = -l0;
+          }
+          qr.lam[k] = l0;
+        }
+      } else if constexpr (WS != 0) {
         for (int k = 0; k < 3; ++k) acc[k] = p_warm * Lwj[(jj * 6 + k) * E + js_e];
         for (int k = 0; k < 3; ++k) {
-          const float kept_l = Lwj[(jj * 6 + 3 + k) * E + js_e];
+          const float kept = Lwj[(jj * 6 + 3 + k) * E + js_e];
           const int onesided = JL == 1 ? jw.onesided : jr.onesided, upper = JL == 1 ? jw.upper : jr.upper;
-          float l0 = p_warm * kept_l;
+          float l0 = p_warm * kept;
           if (onesided & (1 << k)) {
-            // kept for the other limit: it would push the wrong way
-            const bool was_upper = __float_as_int(kept_l) < 0, is_upper = (upper >> k) & 1;
+            const bool was_upper = __float_as_int(kept) < 0, is_upper = (upper >> k) & 1;
             l0 = was_upper == is_upper ? fabsf(l0) : 0.0f;
           }
           (JL == 1 ? jw.lam[k] : jr.lam[k]) = l0;
           if (onesided & (1 << k)) (JL == 1 ? jw.nl[k] : jr.nl[k]) = -l0;
-        }
-      }
-      // With four lanes per joint, the constants of the lane's own three rows, under one set of names: a
-      // positional lane's rows act on the angular velocity through the lever arm, an angular lane's through the axis.
-      QuadRows qr;
-      if constexpr (JL == 4) {
-        const bool ang = js_kind != 0;
-        const float lever[3][3] = {{0.0f, jr.sr[2], -jr.sr[1]}, {-jr.sr[2], 0.0f, jr.sr[0]}, {jr.sr[1], -jr.sr[0], 0.0f}};
-        qr.kv = ang ? 0.0f : jr.sg;
-        qr.sv = jr.sv;
-        for (int k = 0; k < 3; ++k) {
-          for (int c = 0; c < 3; ++c) {
-            qr.K[k][c] = ang ? jr.sax[k][c] : lever[k][c];
-            qr.R[k][c] = ang ? jr.Z[k][c] : jr.Y[k][c];
-            qr.ap[k][c] = ang ? jr.ap[k][c] : 0.0f;
-          }
-          qr.me[k] = ang ? jr.ame[k] : jr.pme[k];
-          qr.nb[k] = ang ? jr.anb[k] : jr.pnb[k];
-          qr.t1[k] = ang ? 0.0f : jr.pp[k];
-          qr.t2[k] = ang ? jr.aa[k] : 0.0f;
-          qr.nl[k] = ang ? jr.nl[k] : -INFINITY;
-          if constexpr (WS != 0) qr.lam[k] = ang ? jr.lam[k] : acc[k];
         }
       }
       // own body's velocity rows, found once (the world's side of a joint reads body 0's): looked up
@@ -2868,7 +2936,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         if (js_on && js_side == 0) {
           if constexpr (JL == 4) {
             for (int k = 0; k < 3; ++k)
-              Lwj[(js_j * 6 + 3 * js_kind + k) * E + js_e] = js_kind && (((jr.onesided & jr.upper) >> k) & 1) ? -qr.lam[k] : qr.lam[k];
+              Lwj[(js_j * 6 + 3 * js_kind + k) * E + js_e] = js_kind && (((q_onesided & q_upper) >> k) & 1) ? -qr.lam[k] : qr.lam[k];
           } else {
             const int uppers = JL == 1 ? jw.onesided & jw.upper : jr.onesided & jr.upper;
             for (int k = 0; k < 3; ++k) Lwj[(js_j * 6 + k) * E + js_e] = acc[k];
