@@ -37,7 +37,8 @@
 //      the margin to 1 at half the margin) and acts inside block c with inverse
 //      mass scaled by W / w_c; then every body takes the weighted average of the
 //      copies, which is the plain sum of what the blocks' impulses change in its
-//      velocity, in static order (no atomics)
+//      velocity (those changes are what the blocks leave in LDS), in static order
+//      (no atomics)
 //   E  damping, angular-velocity cap, position integration
 #pragma once
 #include <hip/hip_runtime.h>
@@ -87,7 +88,7 @@ struct StepArgs {
   const int32_t* place_env;  // [N] agent standing at every place of the launch, or null: agent = place
 };
 
-// Rows (E consecutive floats) per item of the velocity, inverse-inertia and copy arrays.  Odd
+// Rows (E consecutive floats) per item of the velocity, inverse-inertia and change arrays.  Odd
 // counts, so that neighbouring items start in different LDS banks when E is 16.
 // The two sides of a joint lie an odd number of rows apart as well: neighbouring lanes store to both at once.
 constexpr int kVS = 7, kCS = 7, kJS = 13, kSide = 7;
@@ -119,25 +120,25 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.nb = o; o += pairs ? B * E : 0;
   p.tq = o; o += J * 3 * E;
   p.push = o; o += 3 * E;
-  o += o & 1;  // the search results kept in the copy arrays are 64-bit words
-  // The sweep copies.  The terrain search, which is over before the first sweep, keeps its results there:
-  // a 64-bit minimum per slot and half the segment of every body (together never more than the copies,
+  o += o & 1;  // the search results kept in the change arrays are 64-bit words
+  // The sweeps' changes of velocity.  The terrain search, which is over before the first sweep, keeps its results there:
+  // a 64-bit minimum per slot and half the segment of every body (together never more than the changes,
   // since every body has a slot), and behind them the lists of rows and cells, for which 32 words per env are
   // enough.  So does the search for capsule-capsule contacts its spheres (one 16-byte word per body, an
   // odd number of them per env).  A robot with few joints has less room than that behind its results: up to
-  // 16 envs the copies' space is then made larger, which LDS always has room for.  With more of them (which only
+  // 16 envs the changes' space is then made larger, which LDS always has room for.  With more of them (which only
   // a caller asks for) nothing is reserved that the ground does not need, and the lists take what is left at
   // the end: full lists only cost time (the direct search), and no form is refused for them.
   const bool many = E > 16;
-  const int copies = (J * kJS + S * kCS) * E, search = many && !field ? 0 : (2 * S + 3 * B) * E;
+  const int changes = (J * kJS + S * kCS) * E, search = many && !field ? 0 : (2 * S + 3 * B) * E;
   const int spheres = pairs ? 4 * (B | 1) * E + 3 : 0;
   p.outj = o;
   p.outc = o + J * kJS * E;
   p.half = o + 2 * S * E;
   p.cand = o + search;
-  p.cand_cap = copies - search > 32 * E ? copies - search : (many ? copies - search : 32 * E);
-  o += copies > search + p.cand_cap ? copies : search + p.cand_cap;
-  o += many && spheres > copies ? spheres - copies : 0;
+  p.cand_cap = changes - search > 32 * E ? changes - search : (many ? changes - search : 32 * E);
+  o += changes > search + p.cand_cap ? changes : search + p.cand_cap;
+  o += many && spheres > changes ? spheres - changes : 0;
   p.rec = o; o += S * kRecWords * E;
   p.list = o; o += S * E;
   p.surv = o; o += S * E;   // slots near the heightfield: end spheres from the front, mid-segments from the back
@@ -160,7 +161,7 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.tin = o; o += 6 * B;
   p.tjoint = o; o += J * (int)(sizeof(JointTab) / 4);
   p.pq = o; o += pairs ? kPairCap * kPairWords : 0;   // sorted queue of the substep's contacts
-  p.po = o; o += pairs ? (kPairCap + 1) * 12 : 0;     // weighted velocity copies of their two bodies; the last entry stays zero
+  p.po = o; o += pairs ? (kPairCap + 1) * 12 : 0;     // changes of their two bodies' velocities; the last entry stays zero
   p.pnear = o; o += pairs ? E * (pairs - 1) / 2 : 0;  // agent pairs whose bounding spheres overlap: at most all of them
   p.pbs = o; o += pairs ? E : 0;                      // bounding radius of every agent about its root
   p.pcount = o; o += pairs ? 4 : 0;
@@ -594,7 +595,7 @@ __device__ __forceinline__ void relax_pair_side(PairSide& c, float mu, float v[3
 
 // EC > 0: envs per workgroup fixed at compile time (LDS offsets become immediates);
 // EC == 0: taken from the launch arguments.  NJ: compile-time bound on the joints one body
-// belongs to (the per-body average reads NJ joint copies without branching).
+// belongs to (the per-body average reads NJ joint entries without branching).
 #pragma clang fp contract(fast)
 // counter-based uniform draw: one 64-bit mixing finaliser per (seed, env, index)
 __device__ inline float reset_uniform(uint64_t seed, uint64_t env, uint64_t idx) {
@@ -810,7 +811,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   float* Llam = lds + P.lam;                         // impulses of the contacts beyond one per thread
   // fine search: per slot (index s * E + env) the minimum of (squared distance, feature id) packed in 64 bits,
   // half of every body's segment, and four lists (rows of cells and single cells, each for the end
-  // spheres and for the mid-segments); all of it lives in the space of the copies the sweeps use
+  // spheres and for the mid-segments); all of it lives in the space of the changes the sweeps use
   unsigned long long* Lbest64 = reinterpret_cast<unsigned long long*>(lds + P.outj);
   float* Lhalf = lds + P.half;                       // [B][3][E]: from the centre to the segment's second end
   unsigned* Lcell_e = reinterpret_cast<unsigned*>(lds + P.cand);
@@ -836,7 +837,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   float* Ltin = lds + P.tin;                          // body table: inertia(3), inverse inertia(3)
   const JointTab* Ltjoint = reinterpret_cast<const JointTab*>(lds + P.tjoint);  // joint table
   float* Lpq = lds + P.pq;                            // capsule-capsule contacts, kPairWords each, sorted by key
-  float* Lpo = lds + P.po;                            // their copies times the block weight: A (v, w), B (v, w)
+  float* Lpo = lds + P.po;                            // what they change: A (v, w), B (v, w)
   int* Lmeet = reinterpret_cast<int*>(lds + P.pnear);
   int* Lbs = reinterpret_cast<int*>(lds + P.pbs);     // bounding radii as float bits (ordered like ints)
   int* Lpcount = reinterpret_cast<int*>(lds + P.pcount);  // contacts found, near agent pairs
@@ -1393,7 +1394,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
         // Bounding spheres of the bodies for stage 1: centre relative to the group's first origin, radius
         // (enlarged by what the centre's two roundings can be off), one 16-byte word each, env after env
         // with an odd stride, so that a candidate costs two reads from LDS instead of sixteen and neighbouring
-        // lanes fall on different banks.  They lie where the terrain search was and the sweep copies will be.
+        // lanes fall on different banks.  They lie where the terrain search was and the sweeps' changes will be.
         float4* const Lsph = reinterpret_cast<float4*>(lds + ((P.outj + 3) & ~3));
         const int sph_e = B | 1;
         for (int i = tid; i < B * E; i += kThreads) {
@@ -1429,7 +1430,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
             if (near) Lmeet[pos] = pr;
           }
         }
-        float* Ltmp = Lpo;   // unsorted queue; the copies are not in use yet
+        float* Ltmp = Lpo;   // unsorted queue; the changes are not in use yet
         // Every hit also leaves (gap, key) as one 64-bit word whose unsigned order is that of the
         // pair: when a workgroup finds more than it can hold, the kPairCap contacts with the smallest
         // gap stay (ties: smaller key), whichever wavefront found what first.  Where they live:
@@ -1629,7 +1630,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     const bool g_on = g_all || (env_ok && g_b < B);
     const bool g_wave = !g_all || __builtin_amdgcn_readfirstlane(idx) < g_items;
     const int g_ref = g_b * E + e;
-    // capsule-capsule contacts of body g_b: where their (weighted) copies will be (up to kPairList
+    // capsule-capsule contacts of body g_b: where their changes will be (up to kPairList
     // of them; a body with more walks the queue in every sweep), and the sum of their weights
     constexpr int kPairList = 6;   // (the list in LDS and the sorting network below are made for six)
     int gp_off[kPairList];
@@ -3120,7 +3121,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   // are not enough wavefronts the first one takes what is left.  What the reward needs of them is left
   // in LDS (the inverse inertias are no longer read).
   float* Lsc = Liw;       // [5][E]: speed towards the target, distance to it, sums of |u| and u^2, feet on the ground
-  float* Lhm = Loutj;     // [5][E]: centre of mass (world), cosine and sine of the yaw (the sweep copies are free by now)
+  float* Lhm = Loutj;     // [5][E]: centre of mass (world), cosine and sine of the yaw (the sweeps' changes are free by now)
   const bool m_height_map = obs_row > obs_dim;
   auto pack_root = [&](auto pass_c) {
 #pragma clang fp contract(fast)
@@ -3284,7 +3285,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
   return reset_now;
   };
   // The marked envs start from the reset recipe (after a barrier behind Lrst; nothing of the sweeps'
-  // copies is needed any more).
+  // changes is needed any more).
   auto reset_envs = [&](const StepArgs& a, const Model& M) {
 #pragma clang fp contract(fast)
     const bool fresh = env_ok && Lrst[e];
