@@ -297,7 +297,7 @@ static int build_model(const sim_desc_t* d, int num_envs, Model* m) {
 static int pairs_of(const Model& m) { return (m.n_pairs > 0 || m.group > 1) ? (m.group > 1 ? m.group : 1) : 0; }
 // Threads per workgroup of the step launch: the wide workgroup pays off for full workgroups of 16
 // envs (more lanes for the contact search on the heightfield, a finer split of the velocity
-// average everywhere); small batches and the collision and warm-start variants (which need the
+// sums everywhere); small batches and the collision and warm-start variants (which need the
 // registers) keep the narrow one.
 static int threads_for(const Model& m, int E) {
   return (E == 16 && m.max_joint_sides <= 4 && !pairs_of(m) && !(m.warm > 0.0f) && m.solver == 0) ? kThreadsWide : kThreads;
@@ -326,8 +326,8 @@ static const void* step_variant(const Model& m, int E) {
 // Envs per workgroup.  A step is a chain of dependent instructions and barriers whose length hardly
 // depends on how many envs share the workgroup, and one workgroup fills a compute unit; so: one round
 // of workgroups whenever the batch allows it (rounded up: 1500 humanoids on the heightfield take
-// 90 us as 188 workgroups of 8 and 152 us as 375 of 4), in a compiled form (as 300 of 5, which is
-// both two rounds and the general form, they take 194 us).
+// 87 us as 188 workgroups of 8 and 139 us as 375 of 4), in a compiled form (as 300 of 5, which is
+// both two rounds and the general form, they take 179 us).
 static int default_envs_per_block(const Model& m, int N) {
   // bodies need a thread each, joints two (one per side) plus a wavefront left for contacts
   int lim = kThreads / m.B;
@@ -340,15 +340,16 @@ static int default_envs_per_block(const Model& m, int N) {
   const int G = m.group > 1 ? m.group : 1;   // a workgroup holds whole interaction groups
   const bool pairs = pairs_of(m) != 0, newton = m.solver == 1;
   int want = (N + 255) / 256;
-  // A workgroup's envs share its phases (16 to 512 humanoids on the heightfield: 71 to 73 us as workgroups of 2, 76
-  // to 78 us of 4, 74 to 82 us of 1), and fewer workgroups make a slow one among them less likely: two up to 128
-  // envs, four beyond.  (The line was drawn where four cost nothing; up to 512 envs two are 5 us quicker now.)
+  // A workgroup's envs share its phases (16 to 512 humanoids on the heightfield: 66 to 67 us as workgroups of 2, 69
+  // to 72 us of 4, 67 to 69 us of 1), and fewer workgroups make a slow one among them less likely: two up to 128
+  // envs, four beyond.  (Between 129 and 512 envs neither is better for all: humanoids gain 1 to 5 us from two, ants on
+  // the heightfield lose 4: 75.2 us against 71.4.)
   const int least = N > 128 ? 4 : 2;
   if (want < least) want = least;
   // With capsule-capsule collisions a workgroup's envs share a queue of kPairCap contacts, and what
   // does not fit is left out of the step.  There the envs that fill 256 workgroups (rounded down) are
   // the most that share one, unless their own pairs cannot fill it: contacts come before time (300
-  // humanoids: 187 us as workgroups of 1, 102 us of 2; 1500: 211 us of 4, 128 us of 8).
+  // humanoids: 172 us as workgroups of 1, 94 us of 2; 1500: 198 us of 4, 118 us of 8).
   int most = 16;
   if (pairs) {
     most = N / 256 > 1 ? N / 256 : 1;

@@ -7,8 +7,8 @@ namespace sim355 {
 
 // Envs per workgroup that have a form of their own (index arithmetic and LDS offsets fixed at
 // compile time); any other number runs the general form, which takes it from the launch arguments
-// and is a quarter to a third slower (300 self-colliding humanoids with the warm start: 149 us as
-// workgroups of 3, 119 us of 4, 111 us of 2).  The Newton families end at 8 (a contact thread per slot).
+// and is a quarter to a third slower (300 self-colliding humanoids with the warm start: 137 us as
+// workgroups of 3, 104 us of 4, 100 us of 2).  The Newton families end at 8 (a contact thread per slot).
 // One env per workgroup is the library's own choice only with collisions (room in the contact queue)
 // and where two do not fit; elsewhere a caller asks for it.  All forms of a family give the same bits
 // (robots that the whole workgroup solves with Newton's method aside), so size and speed alone decide.
