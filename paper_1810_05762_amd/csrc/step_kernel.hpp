@@ -1722,9 +1722,10 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
           o[6] = __float_as_int(Lpq[tid * kPairWords + 5]); o[7] = __float_as_int(Lpq[tid * kPairWords + 4]);
         }
       }
-      __syncthreads();
-      // (the candidates of the search were here; the sums below are behind another barrier)
+      // The candidates of the search were here (last read before the barrier ahead of the sorted queue).  In front of
+      // the barrier, as the first sweep already reads these rows: the world's velocity, where one lane relaxes a joint.
       for (int i = tid; i < 6 * E; i += kThreads) lds[P.zero + i] = 0.0f;
+      __syncthreads();
     }
 
     TMARK(4);

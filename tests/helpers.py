@@ -40,6 +40,23 @@ def single_scene(robot, terrain=None, params=None, num_envs=1):
     return sc
 
 
+def folded_chains(robot, num_envs, steep=1.1, tight=1.35, n_tight=3):
+    """[N][B][13]: chains (scenes.make_chain along x) folded into zigzags at rest, link after link up and down at `steep`
+    radians, the last `n_tight` at `tight` (second neighbours there touch: 0.15 cos(tight) sin(tight) x 2 apart)."""
+    st = scenes.rest_state(robot, num_envs)
+    top = robot.rest_pos[0] - np.array([robot.half_len[0], 0.0, 0.0])
+    for e in range(num_envs):
+        at = np.array(top)
+        for b in range(robot.n_bodies):
+            phi = (tight if b >= robot.n_bodies - n_tight else steep) + 0.003 * (e % 7)
+            phi = phi if b % 2 else -phi                      # about y: negative angles point up
+            arm = robot.half_len[b] * np.array([np.cos(phi), 0.0, -np.sin(phi)])
+            st[e, b, 0:3] = at + arm
+            st[e, b, 3:7] = (np.cos(0.5 * phi), 0.0, np.sin(0.5 * phi), 0.0)
+            at = at + 2.0 * arm
+    return st
+
+
 TOL_1, TOL_10 = 1e-4, 1e-3     # the task's state tolerances after 1 and after 10 env-steps
 
 

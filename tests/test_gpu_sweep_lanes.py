@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 import scenes
-from helpers import TOL_1, rel_err4
+from helpers import TOL_1, folded_chains, rel_err4
 
 pytestmark = pytest.mark.gpu
 
@@ -40,5 +40,36 @@ def test_joint_lanes_at_the_edges_of_wavefronts(links, anchored, extra):
     ref.step(act[8], dt, sub, its)
     # one step in single precision: the bound of the other one-step comparisons with the oracle
     assert rel_err4(outs[0][1].astype(np.float64), ref.get_state()).max() <= TOL_1
+    for o in outs[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(o, outs[0]))
+
+
+@pytest.mark.parametrize("links", [12, 14])
+@pytest.mark.parametrize("warm", [0.0, 0.8])
+def test_one_lane_per_joint_reads_the_velocity_of_the_world_as_zero(links, warm):
+    """Chains that hang from the world and are folded up: the candidate pairs of the search lie where the first sweep
+    reads the world's velocity, and with 12 and 14 joints of 16 envs some wavefronts of joints clear none of it."""
+    import paper_1810_05762_amd as P
+    n = 32
+    rob = scenes.make_chain(n_links=links, seg_len=0.15, direction=(1.0, 0.0, 0.0), top=(0.0, 0.0, 0.4))
+    sc = scenes.make_scene(rob, scenes.make_plane(), n, params=scenes.SimParams(self_collide=1, warm_start=warm))
+    start = folded_chains(rob, n).astype(np.float32)
+    act = scenes.actions_for_step(5, 0, n, rob.n_dofs)
+    dt, sub, its = float(np.float32(1.0 / 60.0)), 4, 16
+    outs = []
+    for epb in (2, 8, 16):
+        sim = P.Sim(sc)
+        sim.set_envs_per_block(epb)
+        sim.record_contacts(True)
+        sim.set_state(start)
+        sim.step(act, dt, sub, its)
+        pairs, dropped = sim.get_pair_contacts()
+        assert len(pairs) >= n and dropped == 0
+        outs.append([sim.get_state().cpu().numpy()] + [x.cpu().numpy() for x in sim.get_obs()])
+        sim.check(); sim.close()
+    ref = oracle.OracleSim(sc, threads=4)
+    ref.set_state(start.astype(np.float64))
+    ref.step(act, dt, sub, its)
+    assert rel_err4(outs[0][0].astype(np.float64), ref.get_state()).max() <= TOL_1
     for o in outs[1:]:
         assert all(np.array_equal(a, b) for a, b in zip(o, outs[0]))
