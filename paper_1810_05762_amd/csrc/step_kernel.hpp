@@ -3140,7 +3140,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     const float qw = Lpos[(m_root * 7 + 3) * E + ee], qx = Lpos[(m_root * 7 + 4) * E + ee];
     const float qy = Lpos[(m_root * 7 + 5) * E + ee], qz = Lpos[(m_root * 7 + 6) * E + ee];
     const float x = 1.0f - 2.0f * (qy * qy + qz * qz), y = 2.0f * (qw * qz + qx * qy), n = sqrtf(x * x + y * y);
-    c = n > 0.0f ? x / n : 1.0f; sn = n > 0.0f ? y / n : 0.0f;
+    c = n == 0.0f ? 1.0f : x / n; sn = n == 0.0f ? 0.0f : y / n;   // (NaN stays NaN, as a pose that is none must show)
   };
   if (const int ee = part_env(0); ee >= 0) {
     // target in the root's frame, speed towards it
@@ -3154,7 +3154,7 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     const float tn = sqrtf(tx * tx + ty * ty);
     // sine and cosine of the difference of two directions from their components: no angle is formed (the two
     // arctangents and the sine and cosine of their difference were the longest chain of this phase)
-    const float ux = tn > 0.0f ? tx / tn : 1.0f, uy = tn > 0.0f ? ty / tn : 0.0f;
+    const float ux = tn == 0.0f ? 1.0f : tx / tn, uy = tn == 0.0f ? 0.0f : ty / tn;
     Lobs[ee * obs_dim + 9] = uy * cy - ux * sy; Lobs[ee * obs_dim + 10] = ux * cy + uy * sy;
     Lsc[0 * E + ee] = tn > 0.0f ? rv0 * ux + rv1 * uy : 0.0f;
     Lsc[1 * E + ee] = tn;

@@ -261,3 +261,29 @@ def test_sim_from_the_built_in_description_equals_the_sim_from_the_input_recipe(
     torch.cuda.synchronize()
     P.sim_destroy(h)
     ref.close()
+
+
+@pytest.mark.parametrize("at", [0, 3], ids=["position", "orientation"])
+def test_nan_in_the_pose_of_a_root_reaches_its_reward_and_heading_and_nobody_else(at):
+    """A state that is no number any more must not look like a good step to a caller who watches the rewards."""
+    import paper_1810_05762_amd as P
+    n, bad = 6, 3
+    rob = scenes.make_ant()
+    sc = scenes.make_scene(rob, scenes.make_plane(), n)
+    good = P.Sim(sc)
+    good.reset(5)
+    start = good.get_state()
+    good.set_state(start)
+    sim = P.Sim(sc)
+    start[bad, rob.root_body, at] = float("nan")
+    sim.set_state(start)
+    rest = np.arange(n) != bad
+    for s in range(3):
+        if s > 0:                                 # (first the observation of the state as it was set)
+            act = scenes.actions_for_step(5, s, n, rob.n_dofs)
+            good.step(act, 1 / 60, 2, 8)
+            sim.step(act, 1 / 60, 2, 8)
+        a, b = ([t.cpu().numpy() for t in x.get_obs()] for x in (good, sim))
+        assert np.isnan(b[0][bad, 9:11]).all() and np.isnan(b[1][bad]), (s, b[0][bad, 9:11], b[1][bad])
+        assert all(np.array_equal(x[rest], y[rest]) for x, y in zip(a, b)) and np.isfinite(a[0]).all()
+    good.close(); sim.close()
