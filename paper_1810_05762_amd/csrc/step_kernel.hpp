@@ -3135,12 +3135,23 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     if (ee < 0 || ee >= E || blockIdx.x * E + ee >= N) return -1;
     return pass == 0 || only_reset || Lrst[ee] ? ee : -1;
   };
+  // Cosine and sine of the direction of (x, y), as the arctangent has it: the null vector points along x, an infinite
+  // component outweighs a finite one, NaN stays NaN (a pose that is none must show).  The larger component is scaled
+  // into [0.5, 1) by its exponent first, so that no square overflows or vanishes.
+  auto direction_of = [&](float x, float y, float& c, float& sn) {
+    if (isinf(x) || isinf(y)) {
+      x = isinf(x) ? copysignf(1.0f, x) : 0.0f * x; y = isinf(y) ? copysignf(1.0f, y) : 0.0f * y;
+    }
+    const int up = -__builtin_amdgcn_frexp_expf(fmaxf(fabsf(x), fabsf(y)));
+    x = __builtin_amdgcn_ldexpf(x, up); y = __builtin_amdgcn_ldexpf(y, up);
+    const float n = sqrtf(x * x + y * y);
+    c = n == 0.0f ? 1.0f : x / n; sn = n == 0.0f ? 0.0f : y / n;
+  };
   // cosine and sine of the heading (the yaw of the ZYX Euler angles; looking straight up or down it counts as zero)
   auto heading_of = [&](int ee, float& c, float& sn) {
     const float qw = Lpos[(m_root * 7 + 3) * E + ee], qx = Lpos[(m_root * 7 + 4) * E + ee];
     const float qy = Lpos[(m_root * 7 + 5) * E + ee], qz = Lpos[(m_root * 7 + 6) * E + ee];
-    const float x = 1.0f - 2.0f * (qy * qy + qz * qz), y = 2.0f * (qw * qz + qx * qy), n = sqrtf(x * x + y * y);
-    c = n == 0.0f ? 1.0f : x / n; sn = n == 0.0f ? 0.0f : y / n;   // (NaN stays NaN, as a pose that is none must show)
+    direction_of(1.0f - 2.0f * (qy * qy + qz * qz), 2.0f * (qw * qz + qx * qy), c, sn);
   };
   if (const int ee = part_env(0); ee >= 0) {
     // target in the root's frame, speed towards it
@@ -3154,9 +3165,10 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     const float tn = sqrtf(tx * tx + ty * ty);
     // sine and cosine of the difference of two directions from their components: no angle is formed (the two
     // arctangents and the sine and cosine of their difference were the longest chain of this phase)
-    const float ux = tn == 0.0f ? 1.0f : tx / tn, uy = tn == 0.0f ? 0.0f : ty / tn;
+    float ux, uy;
+    direction_of(tx, ty, ux, uy);
     Lobs[ee * obs_dim + 9] = uy * cy - ux * sy; Lobs[ee * obs_dim + 10] = ux * cy + uy * sy;
-    Lsc[0 * E + ee] = tn > 0.0f ? rv0 * ux + rv1 * uy : 0.0f;
+    Lsc[0 * E + ee] = tn > 0.0f ? (rv0 * tx + rv1 * ty) / tn : 0.0f;
     Lsc[1 * E + ee] = tn;
   }
   if (const int ee = part_env(1); ee >= 0) {

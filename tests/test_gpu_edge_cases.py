@@ -287,3 +287,29 @@ def test_nan_in_the_pose_of_a_root_reaches_its_reward_and_heading_and_nobody_els
         assert np.isnan(b[0][bad, 9:11]).all() and np.isnan(b[1][bad]), (s, b[0][bad, 9:11], b[1][bad])
         assert all(np.array_equal(x[rest], y[rest]) for x, y in zip(a, b)) and np.isfinite(a[0]).all()
     good.close(); sim.close()
+
+
+def test_direction_of_a_target_at_any_distance():
+    """The direction is that of the arctangent of the two components, also where their squares overflow or vanish, where
+    one is infinite and where the root stands on its target."""
+    import paper_1810_05762_amd as P
+    inf = float("inf")
+    ts = [(0.0, 0.0), (3.0, -4.0), (1e-30, -2e-30), (-1e-44, 0.0), (0.0, 2e-25), (1e20, 1e20), (-3e38, 1e38), (5.0, -2e30), (-1e19, 2e-3),
+          (inf, 5.0), (-inf, 1e38), (0.0, -inf), (inf, inf), (-inf, inf)]
+    n = len(ts)
+    sc = scenes.make_scene(scenes.make_single(radius=0.1, pos=(0.0, 0.0, 1.0)), scenes.make_plane(), n)
+    st = scenes.rest_state(sc.robot, n)
+    q = np.random.default_rng(3).normal(size=(n, 4))
+    st[:, 0, 3:7] = q / np.linalg.norm(q, axis=1, keepdims=True)
+    st = st.astype(np.float32)
+    assert not st[:, 0, 0:2].any()
+    t = np.array(ts, np.float32)
+    sim = P.Sim(sc)
+    sim.set_targets(t)
+    sim.set_state(st)
+    obs = sim.get_obs()[0].cpu().numpy().astype(np.float64)
+    w, x, y, z = st[:, 0, 3:7].astype(np.float64).T
+    psi = np.arctan2(t[:, 1].astype(np.float64), t[:, 0].astype(np.float64)) - np.arctan2(2 * (w * z + x * y), 1 - 2 * (y * y + z * z))
+    # (the bound of the heading terms in the comparison of angles from identical states)
+    assert np.abs(obs[:, 9] - np.sin(psi)).max() <= 5e-6 and np.abs(obs[:, 10] - np.cos(psi)).max() <= 5e-6, obs[:, 9:11] - np.stack((np.sin(psi), np.cos(psi)), 1)
+    sim.close()
