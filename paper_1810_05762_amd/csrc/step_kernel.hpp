@@ -2965,12 +2965,16 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       build_pair();
       if (PC == 0 && m_terrain == 0) __syncthreads();
       {
-        // the starting impulses of the contacts beyond one per thread are set by the thread that
-        // relaxes them in every sweep below (same index mapping), so no other thread's store is read
-        for (int k = n_reg + (kThreads - 1 - tid); k < n_active; k += n_reg)
-          for (int r = 0; r < 3; ++r) overflow_lam(k, r) = WS ? p_warm * overflow_lam(k, r) : 0.0f;
         // (a lane without a contact of its own does what the last contact's lane of its wavefront does, to the last bit)
-        const bool contacts_here = __ballot(has_contact) != 0ull, more_contacts = n_active > n_reg;
+        // (up to four envs have a contact thread for every slot a robot can have)
+        constexpr bool kMoreContacts = EC == 0 || kMaxSlots * EC > NT - ((JL * kMaxJoints * EC + 63) / 64) * 64;
+        const bool contacts_here = __ballot(has_contact) != 0ull, more_contacts = kMoreContacts && n_active > n_reg;
+        if constexpr (kMoreContacts) {
+          // the starting impulses of the contacts beyond one per thread are set by the thread that
+          // relaxes them in every sweep below (same index mapping), so no other thread's store is read
+          for (int k = n_reg + (kThreads - 1 - tid); k < n_active; k += n_reg)
+            for (int r = 0; r < 3; ++r) overflow_lam(k, r) = WS ? p_warm * overflow_lam(k, r) : 0.0f;
+        }
         const int c_e = cr.slot_e % E, c_out = P.outc + (cr.slot_e / E) * kCS * E + c_e, c_voff = P.vel + cr.body * kVS * E + c_e;
         auto own_contact = [&](int it) {
             float vv[3], ww[3];
