@@ -2792,9 +2792,11 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
       const int js_ob = js_side ? Ltjoint[jj].child : Ltjoint[jj].parent;
       const int js_voff = P.vel + ((js_ob < 0 ? 0 : js_ob) * kVS + 3 * js_kind) * E + js_e;
       const int js_out = P.outj + (jj * kJS + js_side * kSide + 3 * js_kind) * E + js_e;
-      // Six joint wavefronts of a full workgroup share SIMDs with each other and with the contacts (4096 humanoids, cycles
-      // per sweep: 1274 with DPP moves, 1198 through the crossbar); three of a smaller one have theirs to themselves.
-      constexpr bool kSharedSimd = NT > 512;
+      // Where a robot can have more joint wavefronts than there are SIMDs, they share SIMDs with each other and with the
+      // contacts (16 envs with two lanes per joint: a humanoid has six; 4096 of them, cycles per sweep with DPP moves and
+      // through the crossbar: 1274 and 1198, with the warm start, in 512 threads, 1330 and 1225); three of a smaller
+      // workgroup have theirs to themselves.
+      constexpr bool kSharedSimd = JL * kMaxJoints * EC > 4 * 64;
       constexpr int kC = JL == 4 ? 3 : (JL == 2 ? 6 : 12);   // velocity components of a lane
       // (one lane per joint: the child's rows besides; the world's velocity is read from the zeros)
       const int js_voff0 = JL == 1 && js_ob < 0 ? P.zero + js_e : js_voff;
