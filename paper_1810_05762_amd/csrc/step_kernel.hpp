@@ -148,7 +148,7 @@ __host__ __device__ inline LdsPlan make_plan(int B, int J, int S, int D, int F, 
   p.u = o; o += (D > 0 ? D : 1) * E;
   p.obs = o; o += (11 + 3 * D + F) * E;
   p.zero = p.obs;   // (the first six rows are zeros while the sweeps run)
-  p.lim = o; o += (D > 0 ? D : 1) * E;
+  p.lim = o; o += (D > 0 ? D : 1) * E;   // (one count per env is in use; the room decides which numbers of envs fit, and stays)
   if (with_patch) o = (o + 3) & ~3;   // (written four samples at a time)
   p.patch = o; o += with_patch ? E * kPatch * kPatch : 0;
   p.mip = o; o += with_patch ? E * kPatchBlocks * kPatchBlocks : 0;
@@ -3122,8 +3122,8 @@ __global__ __launch_bounds__(NT) void step_kernel(StepArgs a) {
     if (at_limit) atomicAdd(&Llim[e], at_limit);
   }
   };
-  // ---- root part.  One thread per env for all of it is a chain of some 1500 instructions (three
-  // arctangents, an arcsine, sine and cosine, and reads from global memory) that every other wavefront
+  // ---- root part.  One thread per env for all of it is a chain of many hundred instructions (two unit
+  // directions, an arctangent, an arcsine, and reads from global memory) that every other wavefront
   // waits for, so its independent parts go to a wavefront each, above the joint threads; where there
   // are not enough wavefronts the first one takes what is left.  What the reward needs of them is left
   // in LDS (the inverse inertias are no longer read).

@@ -18,9 +18,10 @@ constexpr bool step_compiled_envs(int E, bool newton) {
 
 // Lanes that relax one joint in the form for E envs per workgroup.  More lanes make a wavefront's chain shorter and
 // give the SIMDs more wavefronts that hold each other up.  Cycles per sweep: up to 4 envs four lanes (64 humanoids
-// 747, with two 789; 1024 765 and 834) fill three wavefronts at most; 8 envs two lanes (1500 humanoids 1003, with one
-// 1186; that collide in groups of 8 1267 and 1440); collisions of 16 envs in 512 threads one (groups of 4: 1765, with
-// two 2015); of up to 4 envs two, as four win nothing beside the pairs' own lanes (groups of 4: 1077 and 1093).
+// 747, with two 789; 1024 765 and 834), which fill no more wavefronts than there are SIMDs (three with humanoids);
+// 8 envs two lanes (1500 humanoids 1003, with one 1186; that collide in groups of 8 1267 and 1440); collisions of 16
+// envs in 512 threads one (groups of 4: 1765, with two 2015); of up to 4 envs two, as four win nothing beside the
+// pairs' own lanes (groups of 4: 1077 and 1093).
 constexpr int joint_lanes(int E, bool few, bool pairs, bool newton) {
   if (!few || newton) return 2;
   if (pairs) return E == 16 ? 1 : 2;
