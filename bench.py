@@ -325,7 +325,7 @@ def main():
         "roofline": {"bound": "alu", "kernel": "step_kernel", "achieved": achieved_tflops, "peak": peak_tflops,
                      "unit": "TFLOP/s", "frac": achieved_tflops / peak_tflops, "traffic": traffic,
                      "flops_per_env_step": fl, "kernel_ms": kern_ms,
-                     "valu_issue_frac": (valu_insts * 64 / (kern_ms * 1e-3) / (256 * 4 * 16 * 2.4e9)) if valu_insts else None},
+                     "valu_issue_vs_nominal": (valu_insts * 64 / (kern_ms * 1e-3) / (256 * 4 * 16 * 2.4e9)) if valu_insts else None},
         # HBM is not what bounds this kernel (body state stays in LDS through all substeps and
         # sweeps); the byte accountings are printed for the record.  A and B are bytes the kernel has
         # to move, as fractions of 8 TB/s; C is what an engine with one kernel per sweep would stream
